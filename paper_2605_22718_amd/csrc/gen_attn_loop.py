@@ -1,11 +1,13 @@
 #!/usr/bin/env python3
-"""Writes wk_attn_loop_gfx950.inc: the steady-state loop of k_attn_bf16 (8 waves x 32 queries, 64-key tiles) as
-one hand-scheduled inline-assembly body for gfx950.
+"""Writes wk_attn_loop_gfx950.inc and wk_attn_pair_loop_gfx950.inc: the steady-state loops of k_attn_bf16 (8 waves,
+32 queries each, 64-key tiles) as hand-scheduled inline-assembly bodies for gfx950.
 
-    python gen_attn_loop.py [output file]      (default: wk_attn_loop_gfx950.inc beside this script)
+    python gen_attn_loop.py [directory]      (default: beside this script)
 
-The loop does exactly what four consecutive `step`s of the C++ kernel do -- the same ring protocol, the same
-arithmetic in the same order, bit-identical results -- but with the schedule fixed by hand:
+The loop does exactly what one trip of `step`s round the ring does in the C++ kernel -- four steps of one tile, or
+two steps of a pair of tiles (kg = 2: wave group 0 takes the even tiles, group 1 the odd ones, through a group offset in
+its LDS read addresses) -- the same ring protocol, the same arithmetic in the same order, bit-identical results, but with
+the schedule fixed by hand:
 
   * K fragments are requested two pairs of reads ahead of the matrix instructions that consume them, V^T
     fragments six matrix instructions ahead; every wait on the LDS counter is partial (LDS reads return in
@@ -33,7 +35,8 @@ Register map (VGPR), fixed through operand constraints in the kernel source:
   KAD v[224:231]  LDS address of K operand read st
   VAD v[232:235]  LDS address of V^T operand read blk (V ring base included)
   KSRC v[236:237] VSRC v[238:239]   per-lane source offsets of this wave's tile loads
-  M v240  L v241  MT v243   running max (log2 units), row sum, scaled max of the next tile
+  M v240  L v[241:242]  MT v243   running max (log2 units), row sums of the even and the odd tiles (kg = 2: of this
+              wave group's tiles, and nothing), scaled max of the next tile
   T   v[244:246]  temporaries
 SGPR:
   s[36:37] K rows of this head, s[38:39] V rows, s40 byte offset of the K tile requested next, s41 same for V,
@@ -74,7 +77,8 @@ def VAD(b):
 
 
 KSRC, VSRC = (236, 237), (238, 239)
-M, L, MT = 240, 241, 243
+M, MT = 240, 243
+L = (241, 242)
 T0, T1, T2 = 244, 245, 246
 ONES = "0x3f803f80"    # two bf16 ones
 
@@ -109,9 +113,9 @@ class Emitter:
             self.lds = self.lds[k + 1:]
 
 
-def head(E, pos):
-    """The first three pairs of K fragment reads of a step (tile j+1, ring slot pos+1)."""
-    koff = ((pos + 1) & 3) * TILE
+def head(E, pos, kg):
+    """The first three pairs of K fragment reads of a step (the wave's next tile, kg ring slots on)."""
+    koff = ((pos + kg) & 3) * TILE
     kreads = {}
     for st in range(3):
         for b in range(2):
@@ -121,14 +125,14 @@ def head(E, pos):
     return kreads
 
 
-def step(E, pos, kreads=None):
-    cur = S[pos & 1]            # S^T of the tile consumed in this step (ring slot pos)
-    nxt = S[(pos + 1) & 1]      # S^T of the next tile, formed in this step
-    koff = ((pos + 1) & 3) * TILE
+def step(E, pos, kg, kreads=None):
+    cur = S[(pos // kg) & 1]          # S^T of the tile consumed in this step (ring slot pos)
+    nxt = S[(pos // kg + 1) & 1]      # S^T of the wave's next tile, formed in this step
+    koff = ((pos + kg) & 3) * TILE
     voff = pos * TILE
 
     if kreads is None:
-        kreads = head(E, pos)
+        kreads = head(E, pos, kg)
         for txt in E.deferred:   # the value products kept back by the previous step
             E.emit(txt)
         E.deferred = []
@@ -139,17 +143,26 @@ def step(E, pos, kreads=None):
             rid = E.lds_read(f"ds_read_b128 {rng(KF(buf), 4)}, v{KAD(st)} offset:{koff + b * 8192}")
             kreads[(st, b)] = (buf, rid)
 
-    # this wave's share of K tile j+4 (into the K slot whose tile went into S^T one step ago) and of V tile j+3
-    for i in range(2):
-        E.emit(f"s_add_u32 m0, s42, {pos * TILE + i * 1024}")
-        E.emit(f"v_add_u32_e32 v{T0}, s40, v{KSRC[i]}")
-        E.emit(f"global_load_lds_dwordx4 v{T0}, s[36:37]")
-    for i in range(2):
-        E.emit(f"s_add_u32 m0, s42, {VRING + ((pos + 3) & 3) * TILE + i * 1024}")
-        E.emit(f"v_add_u32_e32 v{T0}, s41, v{VSRC[i]}")
-        E.emit(f"global_load_lds_dwordx4 v{T0}, s[38:39]")
-    E.emit(f"s_add_u32 s40, s40, {TILE}")
-    E.emit(f"s_add_u32 s41, s41, {TILE}")
+    # this wave's share of the K tiles requested in this step (into the slots whose tiles went into S^T one step ago)
+    # and of the V tiles (into the slots behind the ones read in this step)
+    def load_k():
+        for t in range(kg):
+            for i in range(2):
+                E.emit(f"s_add_u32 m0, s42, {(pos + t) * TILE + i * 1024}")
+                E.emit(f"v_add_u32_e32 v{T0}, s40, v{KSRC[i]}")
+                E.emit(f"global_load_lds_dwordx4 v{T0}, s[36:37]")
+            E.emit(f"s_add_u32 s40, s40, {TILE}")
+
+    def load_v():
+        for t in range(kg):
+            for i in range(2):
+                E.emit(f"s_add_u32 m0, s42, {VRING + ((pos + 3 - (kg - 1) + t) & 3) * TILE + i * 1024}")
+                E.emit(f"v_add_u32_e32 v{T0}, s41, v{VSRC[i]}")
+                E.emit(f"global_load_lds_dwordx4 v{T0}, s[38:39]")
+            E.emit(f"s_add_u32 s41, s41, {TILE}")
+
+    load_k()
+    load_v()
 
     # lazy rescale: only when some row's maximum grew by more than 2^8
     lab = f"L_norescale_{pos}_%="
@@ -163,7 +176,8 @@ def step(E, pos, kreads=None):
     E.emit(f"v_exp_f32_e32 v{T1}, v{T1}")
     E.emit(f"v_mov_b32_e32 v{M}, v{T0}")
     E.emit("s_nop 1")
-    E.emit(f"v_mul_f32_e32 v{L}, v{L}, v{T1}")
+    for t in range(3 - kg):
+        E.emit(f"v_mul_f32_e32 v{L[t]}, v{L[t]}, v{T1}")
     for r in range(64):
         E.emit(f"v_mul_f32_e32 v{r}, v{T1}, v{r}")
     E.emit(f"{lab}:")
@@ -184,7 +198,7 @@ def step(E, pos, kreads=None):
             k = i - 2
             ops += [f"v_cvt_pk_bf16_f32 v{P(0) + k}, v{cur + 2 * k}, v{cur + 2 * k + 1}"]
         if 3 <= i < 19:
-            ops += [f"v_dot2c_f32_bf16_e32 v{L}, {ONES}, v{P(0) + i - 3}"]
+            ops += [f"v_dot2c_f32_bf16_e32 v{L[0 if kg == 2 else pos & 1]}, {ONES}, v{P(0) + i - 3}"]
         stream.append(ops)
 
     vreads = {}
@@ -245,32 +259,33 @@ def step(E, pos, kreads=None):
     for op in mx[mi:]:
         E.emit(op)
     assert not E.lds
-    E.emit("s_waitcnt vmcnt(8)")   # all but the tile loads of this step and the one before have landed
+    # kg = 1: all but the tile loads of this step and the one before have landed; kg = 2: all have
+    E.emit(f"s_waitcnt vmcnt({8 if kg == 1 else 0})")
     E.emit("s_barrier")
 
 
-def generate():
-    # what position 3 keeps back is the same text in every iteration: find it with a dry run
+def generate(kg):
+    # what the last step of a trip keeps back is the same text in every iteration: find it with a dry run
     dry = Emitter()
-    for pos in range(4):
-        step(dry, pos)
+    for pos in range(0, 4, kg):
+        step(dry, pos, kg)
     carried = list(dry.deferred)
 
     E = Emitter()
     E.emit("s_mov_b32 s45, m0")   # m0 is the compiler's to manage: hand it back as it was
     # entry: the first reads of position 0 with nothing kept back (the C++ step before finished its tile)
-    kr = head(E, 0)
+    kr = head(E, 0, kg)
     E.emit("s_branch L_body_%=")
     state = (list(E.lds), E.next_id)
     E.emit("L_group_%=:")
     E.lds, E.next_id = [], 0
-    assert head(E, 0) == kr and (list(E.lds), E.next_id) == state
+    assert head(E, 0, kg) == kr and (list(E.lds), E.next_id) == state
     for txt in carried:
         E.emit(txt)
     E.emit("L_body_%=:")
-    step(E, 0, kreads=kr)
-    for pos in range(1, 4):
-        step(E, pos)
+    step(E, 0, kg, kreads=kr)
+    for pos in range(kg, 4, kg):
+        step(E, pos, kg)
     assert E.deferred == carried
     E.emit("s_sub_u32 s44, s44, 1")
     E.emit("s_cmp_lg_u32 s44, 0")
@@ -283,15 +298,17 @@ def generate():
     return E.lines
 
 
-def render():
+def render(kg=1):
     out = ["// Written by gen_attn_loop.py: the hand-scheduled steady-state loop of k_attn_bf16 (see that script).\n"]
-    out += ['"' + ln + '\\n\\t"\n' for ln in generate()]
+    out += ['"' + ln + '\\n\\t"\n' for ln in generate(kg)]
     return "".join(out)
 
 
+FILES = {1: "wk_attn_loop_gfx950.inc", 2: "wk_attn_pair_loop_gfx950.inc"}
+
 if __name__ == "__main__":
-    here = os.path.dirname(os.path.abspath(__file__))
-    path = sys.argv[1] if len(sys.argv) > 1 else os.path.join(here, "wk_attn_loop_gfx950.inc")
-    with open(path, "w") as f:
-        f.write(render())
-    print(path)
+    here = sys.argv[1] if len(sys.argv) > 1 else os.path.dirname(os.path.abspath(__file__))
+    for kg, name in FILES.items():
+        with open(os.path.join(here, name), "w") as f:
+            f.write(render(kg))
+        print(os.path.join(here, name))

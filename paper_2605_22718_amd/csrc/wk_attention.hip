@@ -13,6 +13,7 @@
 // and the rescale factor of O^T is again a per-lane scalar.  The S^T accumulator registers are,
 // after exp2 and rounding, exactly the B operand of the second product: which key an MFMA
 // "k slot" means is a free choice, as long as the V^T operand uses the same choice.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -313,8 +314,14 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, SubTabl
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16: v_mfma_f32_32x32x16_bf16, 8 waves x 32 queries per workgroup (4 waves x 32 for small grids),
-// 64-key tiles.
+// bf16: v_mfma_f32_32x32x16_bf16, 8 waves of 32 queries per workgroup, 64-key tiles.
+//
+// KG == 1: 256 queries, every wave multiplies every tile.  KG == 2 (grids that would leave compute units idle): 128
+// queries; waves 0..3 take the even tiles and waves 4..7 the odd ones for the same queries, and their (O, max, sum) meet
+// in LDS at the end.  That keeps two waves on every SIMD, so that one covers the other's waits: 12 heads x 2,640 queries x
+// 10,560 keys take 162 us, against 178 us with workgroups of four waves (one per SIMD) and 229 us with KG == 1
+// (132 workgroups for 256 compute units).  Splitting each tile's keys between the two wave groups instead, with one
+// tile per step, halves the work between barriers: 177 us.
 //
 // K and V tiles go from global memory straight into a 4-deep LDS ring (global_load_lds, no
 // register staging), K tiles four and V tiles three ahead of the step that loads them, which
@@ -330,6 +337,7 @@ constexpr int kTileBytes = kKeys * 256; // one K or V tile
 constexpr int kStages = 4;
 constexpr int kVRing = kStages * kTileBytes;          // K ring at 0, V ring behind it
 constexpr int kSmemBytes = 2 * kStages * kTileBytes;  // 128 KB
+constexpr int kSmemBytesPair = kSmemBytes + 512;      // KG == 2: and the first tile's row maxima of 128 queries
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
@@ -373,12 +381,13 @@ __device__ inline const char *uniform_ptr(const char *p) {
     return reinterpret_cast<const char *>(((uint64_t)hi << 32) | lo);
 }
 
-template <int WAVES, bool MULTI, bool IN_PLACE>
-__global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTable sub) {
-    static_assert(WAVES == 8 || WAVES == 4, "8 or 4 waves of 32 queries");
-    constexpr int NB = 16 / WAVES;     // 1 KB blocks of a tile that a wave loads
-    // s_waitcnt vmcnt(4 * NB), everything else unconstrained: all but the last four tile shares have landed
-    constexpr int kWaitTwoSteps = NB == 2 ? 0x0F78 : 0x4F70;
+template <int KG, bool MULTI, bool IN_PLACE>
+__global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) {
+    static_assert(KG == 1 || KG == 2, "one tile, or a pair of tiles, per step");
+    constexpr int QW = 8 / KG;         // waves across the queries
+    constexpr int NB = 2;              // 1 KB blocks of a tile that a wave loads
+    constexpr int kWaitTwoSteps = 0x0F78;   // s_waitcnt vmcnt(8) alone: all but the last four tile shares have landed
+    constexpr int kWaitAll = 0x0F70;        // vmcnt(0)
     static_assert(!(MULTI && IN_PLACE), "a table of launches over one window array only");
     extern __shared__ __attribute__((aligned(256))) char smem[];
     int c, h, qt, sp;
@@ -434,7 +443,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
     const int n_kv = IN_PLACE ? seg_tiles * 64 : win.n_kv;   // IN_PLACE: only its tile count is used
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
-    const int q = qt * (WAVES * 32) + wave * 32 + col;
+    const int qw = KG == 1 ? wave : wave & 3, kg = KG == 1 ? 0 : wave >> 2;   // 32 queries of the workgroup's, tile of every pair (KG == 2)
+    const int q = qt * (QW * 32) + qw * 32 + col;
     const bool q_ok = q < a.N_q;
     const int q_ld = q_ok ? q : a.N_q - 1;
     const char *Qrow = a.Q + ((size_t)h * a.q_rows + a.q_off + q_ld) * 256;
@@ -476,7 +486,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
     const unsigned lds0 = (unsigned)(size_t)WK_LDS(smem);
     unsigned k_rd[8];
 #pragma unroll
-    for (int st = 0; st < 8; ++st) k_rd[st] = lds0 + col * 256 + (((2 * st + g) ^ (col & 15)) << 4);
+    for (int st = 0; st < 8; ++st) k_rd[st] = lds0 + kg * kTileBytes + col * 256 + (((2 * st + g) ^ (col & 15)) << 4);
     // V tile: row-major, chunk c of key k at slot c ^ ((k & 3) << 2).  The transpose read hands lane
     // i of a 16-lane group element (i & 3) of source lane 4*j + (i >> 2), j = 0..3.  Source lane p of
     // group u points at key 16*ks + 8*tt + 4*g + (p >> 2), features 32*blk + 16*(u&1) + 4*(p&3) .. +3,
@@ -488,7 +498,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
         const int u = lane >> 4, p = lane & 15;
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk)
-            v_rd[blk] = lds0 + kVRing + (4 * g + (p >> 2)) * 256 +
+            v_rd[blk] = lds0 + kVRing + kg * kTileBytes + (4 * g + (p >> 2)) * 256 +
                         ((4 * (blk ^ (p >> 2)) + 2 * (u & 1) + ((p & 3) >> 1)) << 4) + 8 * (p & 1);
     }
     // tile loads: wave w fills 1 KB blocks NB*w .. NB*w + NB-1 of the K tile and of the V tile; lane l
@@ -518,7 +528,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
     // All of this is wave-uniform scalar state.
     struct TileRef { const char *base; int row, len; };
     const char *cur_k = nullptr, *cur_v = nullptr;
-    int cur_len = 0, cur_row = 0, cur_seg = 0;
+    int cur_len = 0, cur_row = 0, cur_seg = 0, cur_left = seg_tiles;
     TileRef v_line[2] = {{nullptr, 0, 0}, {nullptr, 0, 0}};
     unsigned valid_line = 0;   // four entries of 8 bits, newest lowest: valid keys of a tile, capped at 64 (scalar registers are scarce here)
     if constexpr (IN_PLACE) {
@@ -548,7 +558,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
         issue_at(cur_k, cur_row, cur_len, k_src, dst);
         v_line[1] = v_line[0];
         v_line[0] = TileRef{cur_v, cur_row, cur_len};
-        valid_line = (valid_line << 8) | (unsigned)min(cur_len - cur_row, kKeys);   // 64: a full tile
+        unsigned valid = (unsigned)min(cur_len - cur_row, kKeys);   // 64: a full tile
+        // 0: past the list's last tile, where an odd count of tiles leaves the second wave group without one
+        if constexpr (KG == 2) valid = cur_left-- > 0 ? valid : 0u;
+        valid_line = (valid_line << 8) | valid;
         if (cur_row + kKeys < cur_len) {
             cur_row += kKeys;
         } else if (cur_seg + 1 < n_seg) {
@@ -578,11 +591,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
             }
         }
     };
-    auto issue_v = [&](int rel, int slot) {
+    auto issue_v = [&](int rel, int slot, const TileRef &ref) {   // ref: where the tile is (IN_PLACE)
         const unsigned t_off = (unsigned)(t0 + rel) * (kKeys * 256u);
         char *dst = dma_dst + slot * kTileBytes + kVRing;
         if constexpr (IN_PLACE) {
-            issue_at(v_line[1].base, v_line[1].row, v_line[1].len, v_src, dst);
+            issue_at(ref.base, ref.row, ref.len, v_src, dst);
             return;
         }
         if ((t0 + rel + 1) * kKeys <= n_kv) {
@@ -603,7 +616,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
     for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;   // m_run in scaled (log2) units
+    float m_run = -INFINITY;        // in scaled (log2) units
+    float l_run[2] = {0.f, 0.f};    // row sums over the even and the odd tiles (KG == 2: this wave group's, and nothing)
     const float c_log2 = a.scale_log2;
 
     auto compute_s = [&](int byte_off, f32x16 (&s)[2]) __attribute__((always_inline)) {
@@ -611,7 +625,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[b][r] = 0.f;
-        // the two 32-key blocks are independent accumulation chains: alternate them
+        // the 32-key blocks are independent accumulation chains: alternate them
 #pragma unroll
         for (int st = 0; st < 8; ++st)
 #pragma unroll
@@ -623,7 +637,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
     // IN_PLACE: the tile whose S^T has just been formed had its K tile requested three requests ago; keys
     // past its segment's end get -inf (weight exactly 0).
     auto mask_segment_tail = [&](f32x16 (&s)[2]) __attribute__((always_inline)) {
-        const int valid = (int)(valid_line >> 24);
+        const int valid = (int)((valid_line >> (24 - 8 * kg)) & 255u);
         if (valid < kKeys) {
 #pragma unroll
             for (int b = 0; b < 2; ++b)
@@ -650,7 +664,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
             const float m_new = fmaxf(m_run, m_tile);
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
-            l_run *= alpha;
+            l_run[0] *= alpha;
+            if constexpr (KG == 1) l_run[1] *= alpha;
 #pragma unroll
             for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -658,8 +673,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
         }
     };
     // p = exp2(s*c - m) rounded to bf16; registers 8*t2 .. 8*t2+7 of block b -> k step 2*b + t2.
-    // The row sum uses the rounded probabilities, the ones the P V product sees.
-    auto probabilities = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4]) __attribute__((always_inline)) {
+    // The row sum uses the rounded probabilities, the ones the P V product sees.  Even and odd tiles are summed apart,
+    // as the two wave groups of KG == 2 do, so that the log-sum-exp does not depend on the layout of the launch.
+    auto probabilities = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4], float &l_sum) __attribute__((always_inline)) {
         const float neg_m = -m_run;
         const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
@@ -673,7 +689,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
                     const bf16x2 pk = __builtin_convertvector(f32x2{p0, p1}, bf16x2);
                     pb[2 * b + t2][e] = pk[0];
                     pb[2 * b + t2][e + 1] = pk[1];
-                    l_run = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, l_run, false);
+                    l_sum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, l_sum, false);
                 }
     };
     auto accumulate_pv = [&](int byte_off, const bf16x8 (&pb)[4]) __attribute__((always_inline)) {
@@ -689,33 +705,62 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
             }
     };
 
-    // The ring slot of tile j is j & 3.  Whole groups of four steps come first (the steady state), then the
-    // n_steps & 3 left-over steps, then the last tile at whatever ring position that leaves it.
-    const int n_steps = t1 - t0 - 1;
-    // Step j multiplies K tile j+1 (S^T one step early) and V tile j, so K runs one tile ahead of V:
-    // step j loads K tile j+4 into the slot of K tile j (read in step j-1) and V tile j+3 into the slot
-    // of V tile j-1.  Both then have three steps to land before the step that needs them.
+    // The ring slot of tile j is j & 3.  Whole trips round the ring come first (the steady state), then the left-over
+    // steps, then the last tile (pair) at whatever ring position that leaves it.
+    // KG == 1: step j multiplies K tile j+1 (S^T one step early) and V tile j, so K runs one tile ahead of V:
+    // it loads K tile j+4 into the slot of K tile j (read in step j-1) and V tile j+3 into the slot of V tile j-1.
+    // Both then have three steps to land before the step that needs them.
+    // KG == 2: step j multiplies K tiles 2j+2, 2j+3 and V tiles 2j, 2j+1 (wave group kg one of each) and loads K tiles
+    // 2j+4, 2j+5 and V tiles 2j+2, 2j+3 into the slots read in step j-1: one step to land.
+    const int n_steps = KG == 1 ? t1 - t0 - 1 : (t1 - t0 + 1) / 2 - 1;
+    auto issue_step = [&](int j, const int POS) __attribute__((always_inline)) {   // POS: ring slot of the step's first V tile
+        if constexpr (KG == 1) {
+            issue_k(j + 4, POS);
+            issue_v(j + 3, (POS + 3) & 3, v_line[1]);
+        } else {
+            issue_v(2 * j + 2, (POS + 2) & 3, v_line[1]);
+            issue_v(2 * j + 3, (POS + 3) & 3, v_line[0]);
+            issue_k(2 * j + 4, POS);
+            issue_k(2 * j + 5, POS + 1);
+        }
+    };
+    auto ring_pos = [](int j) { return KG == 1 ? j & 3 : (2 * j) & 3; };
+    auto end_step = [&]() __attribute__((always_inline)) {
+        // KG == 1: all but the loads of this step and the one before have landed
+        __builtin_amdgcn_s_waitcnt(KG == 1 ? kWaitTwoSteps : kWaitAll);
+        __syncthreads();
+    };
     issue_k(0, 0);
     issue_k(1, 1);
-    issue_v(0, 0);
-    issue_k(2, 2);
-    issue_v(1, 1);
-    issue_k(3, 3);
-    issue_v(2, 2);
-    __builtin_amdgcn_s_waitcnt(kWaitTwoSteps);   // K tiles 0, 1 and V tile 0 of this wave have landed
+    issue_v(0, 0, v_line[1]);
+    if constexpr (KG == 1) {
+        issue_k(2, 2);
+        issue_v(1, 1, v_line[1]);
+        issue_k(3, 3);
+        issue_v(2, 2, v_line[1]);
+    } else {
+        issue_v(1, 1, v_line[0]);
+        issue_k(2, 2);
+        issue_k(3, 3);
+    }
+    // KG == 1: K tiles 0, 1 and V tile 0 of this wave have landed; KG == 2: K tiles 0 and 1 (and V tile 0 or the like)
+    __builtin_amdgcn_s_waitcnt(kWaitTwoSteps);
     __syncthreads();
-    if (qt * (WAVES * 32) + wave * 32 >= a.N_q) {
+    if (qt * (QW * 32) + qw * 32 >= a.N_q) {
         // A wave whose 32 queries all lie past N_q (last query tile of a head): it keeps loading its
         // share of every tile and meets every barrier, but leaves the matrix and vector pipes of its
         // SIMD to the wave that has work.
+        if constexpr (KG == 2) __builtin_amdgcn_s_waitcnt(kWaitAll);
         __syncthreads();   // the others' first S^T has been formed from K tile 0
         for (int j = 0; j < n_steps; ++j) {
-            issue_k(j + 4, j & 3);
-            issue_v(j + 3, (j + 3) & 3);
-            __builtin_amdgcn_s_waitcnt(kWaitTwoSteps);
+            issue_step(j, ring_pos(j));
+            end_step();
+        }
+        __builtin_amdgcn_s_waitcnt(kWaitAll);
+        if constexpr (KG == 2) {   // the two barriers around the meeting of the wave groups
+            __syncthreads();
             __syncthreads();
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);
         return;
     }
     f32x16 s_a[2], s_b[2];   // S^T of tiles at even / odd ring positions
@@ -723,93 +768,148 @@ __global__ __launch_bounds__(WAVES * 64, 2) void k_attn_bf16(AttnArgs a, SubTabl
     compute_s(0, s_a);
     if constexpr (IN_PLACE) mask_segment_tail(s_a);
     mt = tile_max(s_a);
-    __syncthreads();   // K tile 0 has been read by every wave: step 0 may load K tile 4 into its slot
+    float *const m_first = reinterpret_cast<float *>(smem + kSmemBytes) + qw * 32 + col;
+    if constexpr (KG == 2) {
+        if (kg == 0) *m_first = mt;
+        __builtin_amdgcn_s_waitcnt(kWaitAll);   // everything requested so far is read in step 0
+    }
+    __syncthreads();   // the first K tile (pair) has been read by every wave: step 0 may load into its slot
 
-    // one pipeline step: tile j (ring position POS) is consumed, S^T of tile j+1 produced
-    auto step = [&](int j, const int POS, f32x16 (&s_cur)[2], f32x16 (&s_next)[2]) __attribute__((always_inline)) {
-        issue_k(j + 4, POS);
-        issue_v(j + 3, (POS + 3) & 3);
+    // both wave groups start from the maximum of the first tile, as a wave that walks every tile does
+    if constexpr (KG == 2) m_run = *m_first;
+
+    // one pipeline step: this wave's tile at ring position POS (+ kg) is consumed, S^T of its next tile produced
+    auto step = [&](int j, const int POS, f32x16 (&s_cur)[2], f32x16 (&s_next)[2], float &l_sum)
+        __attribute__((always_inline)) {
+        issue_step(j, POS);
         maybe_rescale(mt);
-        compute_s(((POS + 1) & 3) * kTileBytes, s_next);
+        compute_s(((POS + KG) & 3) * kTileBytes, s_next);
         bf16x8 pb[4];
-        probabilities(s_cur, pb);
+        probabilities(s_cur, pb, l_sum);
         // (the rare branch sits between the two matrix products, so that the row max below can still be
         // interleaved with the second one)
         if constexpr (IN_PLACE) mask_segment_tail(s_next);
         accumulate_pv(POS * kTileBytes, pb);
         mt = tile_max(s_next);
-        __builtin_amdgcn_s_waitcnt(kWaitTwoSteps);   // all but the loads of this step and the one before have landed
-        __syncthreads();
+        end_step();
     };
     int j = 0;
-    if constexpr (WAVES == 8 && !IN_PLACE) {
-        // Steady state: whole groups of four steps whose look-ahead loads all lie inside the window run in the
-        // hand-scheduled loop of wk_attn_loop_gfx950.inc (written by gen_attn_loop.py, which documents its schedule
-        // and register map).  It is the four `step`s below instruction for instruction in what it computes -- same
-        // ring protocol, same arithmetic in the same order, bit-identical results -- so the steps behind it
-        // stay in C++: the last whole groups, whose loads are clamped to the window, the left-over steps and the
-        // last, possibly partial tile.  Its operands are pinned to the registers its text names.
-        int G = (n_kv / kKeys - 4 - t0 - j) / 4;
-        const int G_steps = (n_steps - j) / 4;
+    if constexpr (!IN_PLACE) {
+        // Steady state: whole trips round the ring whose look-ahead loads all lie inside the window run in a
+        // hand-scheduled loop (written by gen_attn_loop.py, which documents its schedule and register map).  It is
+        // the four (KG == 2: two) `step`s below instruction for instruction in what it computes -- same ring protocol,
+        // same arithmetic in the same order, bit-identical results -- so the steps behind it stay in C++: the last whole
+        // trips, whose loads are clamped to the window, the left-over steps and the last, possibly partial tile.  Its
+        // operands are pinned to the registers its text names.
+        int G = (n_kv / kKeys - 4 - t0) / 4;
+        const int G_steps = n_steps / (4 / KG);
         G = G < G_steps ? G : G_steps;
         if (G > 0) {
-            const unsigned koff = (unsigned)(t0 + j + 4) * (kKeys * 256u), voff = (unsigned)(t0 + j + 3) * (kKeys * 256u);
+            const unsigned koff = (unsigned)(t0 + 4) * (kKeys * 256u), voff = (unsigned)(t0 + 4 - KG) * (kKeys * 256u);
             const unsigned dst = (unsigned)(size_t)WK_LDS(dma_dst);
             int g_left = G;
             const bf16x8 q0 = qb[0], q1 = qb[1], q2 = qb[2], q3 = qb[3], q4 = qb[4], q5 = qb[5], q6 = qb[6], q7 = qb[7];
             f32x16 o0 = o[0], o1 = o[1], o2 = o[2], o3 = o[3], sa0 = s_a[0], sa1 = s_a[1];
             const unsigned ks0 = k_src[0], ks1 = k_src[NB - 1], vs0 = v_src[0], vs1 = v_src[NB - 1];
-            asm volatile(
+#define WK_ATTN_LOOP_OPERANDS \
+                : "+{v[0:15]}"(o0), "+{v[16:31]}"(o1), "+{v[32:47]}"(o2), "+{v[48:63]}"(o3), "+{v[64:79]}"(sa0), \
+                  "+{v[80:95]}"(sa1), "+{v240}"(m_run), "+{v241}"(l_run[0]), "+{v242}"(l_run[1]), "+{v243}"(mt), "+{s44}"(g_left) \
+                : "{v[128:131]}"(q0), "{v[132:135]}"(q1), "{v[136:139]}"(q2), "{v[140:143]}"(q3), "{v[144:147]}"(q4), \
+                  "{v[148:151]}"(q5), "{v[152:155]}"(q6), "{v[156:159]}"(q7), "{v224}"(k_rd[0]), "{v225}"(k_rd[1]), \
+                  "{v226}"(k_rd[2]), "{v227}"(k_rd[3]), "{v228}"(k_rd[4]), "{v229}"(k_rd[5]), "{v230}"(k_rd[6]), "{v231}"(k_rd[7]), \
+                  "{v232}"(v_rd[0]), "{v233}"(v_rd[1]), "{v234}"(v_rd[2]), "{v235}"(v_rd[3]), "{v236}"(ks0), "{v237}"(ks1), \
+                  "{v238}"(vs0), "{v239}"(vs1), "{s[36:37]}"(Kh), "{s[38:39]}"(Vh), "{s40}"(koff), "{s41}"(voff), \
+                  "{s42}"(dst), "{s43}"(c_log2) \
+                : WK_ATTN_LOOP_CLOBBERS, "s45", "vcc", "memory"
+            if constexpr (KG == 1) {
+                asm volatile(
 #include "wk_attn_loop_gfx950.inc"
-                : "+{v[0:15]}"(o0), "+{v[16:31]}"(o1), "+{v[32:47]}"(o2), "+{v[48:63]}"(o3), "+{v[64:79]}"(sa0),
-                  "+{v[80:95]}"(sa1), "+{v240}"(m_run), "+{v241}"(l_run), "+{v243}"(mt), "+{s44}"(g_left)
-                : "{v[128:131]}"(q0), "{v[132:135]}"(q1), "{v[136:139]}"(q2), "{v[140:143]}"(q3), "{v[144:147]}"(q4),
-                  "{v[148:151]}"(q5), "{v[152:155]}"(q6), "{v[156:159]}"(q7), "{v224}"(k_rd[0]), "{v225}"(k_rd[1]),
-                  "{v226}"(k_rd[2]), "{v227}"(k_rd[3]), "{v228}"(k_rd[4]), "{v229}"(k_rd[5]), "{v230}"(k_rd[6]), "{v231}"(k_rd[7]),
-                  "{v232}"(v_rd[0]), "{v233}"(v_rd[1]), "{v234}"(v_rd[2]), "{v235}"(v_rd[3]), "{v236}"(ks0), "{v237}"(ks1),
-                  "{v238}"(vs0), "{v239}"(vs1), "{s[36:37]}"(Kh), "{s[38:39]}"(Vh), "{s40}"(koff), "{s41}"(voff),
-                  "{s42}"(dst), "{s43}"(c_log2)
-                : WK_ATTN_LOOP_CLOBBERS, "s45", "vcc", "memory");
+                    WK_ATTN_LOOP_OPERANDS);
+            } else {
+                asm volatile(
+#include "wk_attn_pair_loop_gfx950.inc"
+                    WK_ATTN_LOOP_OPERANDS);
+            }
             o[0] = o0; o[1] = o1; o[2] = o2; o[3] = o3; s_a[0] = sa0; s_a[1] = sa1;
-            j += 4 * G;
+            j = G * (4 / KG);
         }
     }
-    for (; j + 4 <= n_steps; j += 4) {
-        step(j, 0, s_a, s_b);
-        step(j + 1, 1, s_b, s_a);
-        step(j + 2, 2, s_a, s_b);
-        step(j + 3, 3, s_b, s_a);
+    if constexpr (KG == 1) {
+        for (; j + 4 <= n_steps; j += 4) {
+            step(j, 0, s_a, s_b, l_run[0]);
+            step(j + 1, 1, s_b, s_a, l_run[1]);
+            step(j + 2, 2, s_a, s_b, l_run[0]);
+            step(j + 3, 3, s_b, s_a, l_run[1]);
+        }
+    } else {
+        for (; j + 2 <= n_steps; j += 2) {
+            step(j, 0, s_a, s_b, l_run[0]);
+            step(j + 1, 2, s_b, s_a, l_run[0]);
+        }
     }
     // last tile (ring position POS): the only one that can be partial.  Mask the keys past the window and
     // redo its max.
-    auto last_tile = [&](const int POS, f32x16 (&s_cur)[2]) __attribute__((always_inline)) {
-        const int kt = (t1 - 1) * kKeys;
-        if (!IN_PLACE && kt + kKeys > n_kv) {
+    auto last_tile = [&](const int POS, f32x16 (&s_cur)[2], float &l_sum) __attribute__((always_inline)) {
+        const int kt = KG == 1 ? (t1 - 1) * kKeys : (t0 + 2 * n_steps + kg) * kKeys;
+        const int kt_end = min(n_kv, t1 * kKeys);   // (the second group's tile of an odd count lies behind it entirely)
+        if (!IN_PLACE && kt + kKeys > kt_end) {
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int key = kt + 32 * b + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (key >= n_kv) s_cur[b][r] = -INFINITY;
+                    if (key >= kt_end) s_cur[b][r] = -INFINITY;
                 }
             mt = tile_max(s_cur);
         }
         maybe_rescale(mt);
         bf16x8 pb[4];
-        probabilities(s_cur, pb);
+        probabilities(s_cur, pb, l_sum);
         accumulate_pv(POS * kTileBytes, pb);
     };
-    // the n_steps & 3 left-over steps and the last tile: one copy of the code, ring position at run time,
-    // S^T handed back to s_a after each step
+    // the left-over steps and the last tile: one copy of the code, ring position at run time,
+    // S^T handed back to s_a (and the sum of the next tile's parity to l_run[0]) after each step
     for (; j < n_steps; ++j) {
-        step(j, j & 3, s_a, s_b);
+        step(j, ring_pos(j), s_a, s_b, l_run[0]);
 #pragma unroll
         for (int b = 0; b < 2; ++b) s_a[b] = s_b[b];
+        if constexpr (KG == 1) {
+            const float t = l_run[0];
+            l_run[0] = l_run[1];
+            l_run[1] = t;
+        }
     }
-    last_tile(n_steps & 3, s_a);
+    last_tile(ring_pos(n_steps), s_a, l_run[0]);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // drain the clamped look-ahead loads before the LDS is released
 
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    if constexpr (KG == 2) {
+        // The wave groups meet: waves 4..7 leave (O^T, max, sum) of their keys in the ring, waves 0..3 add it to theirs.
+        // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.
+        float *meet = reinterpret_cast<float *>(smem) + qw * (66 * 64) + lane;
+        __syncthreads();   // every wave has read its last tile and its look-ahead loads have landed
+        if (kg == 1) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) meet[(16 * b + r) * 64] = o[b][r];
+            meet[64 * 64] = m_run;
+            meet[65 * 64] = l_run[0];
+        }
+        __syncthreads();
+        if (kg == 1) return;
+        const float m_other = meet[64 * 64];
+        const float m_new = fmaxf(m_run, m_other);
+        const float w0 = __builtin_amdgcn_exp2f(m_run - m_new), w1 = __builtin_amdgcn_exp2f(m_other - m_new);
+        m_run = m_new;
+        l_run[0] *= w0;
+        l_run[1] = w1 * meet[65 * 64];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
+    }
+    const float l_lane = l_run[0] + l_run[1];
+    const float l_tot = l_lane + __shfl_xor(l_lane, 32);
     if (q_ok && !partial_out) {
         const size_t qrow = out_row();
         char *Orow = a.O + qrow * 256;
@@ -872,9 +972,9 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
     bf16x8 qb[8];
 #pragma unroll
     for (int st = 0; st < 8; ++st) qb[st] = *reinterpret_cast<const bf16x8 *>(Qrow + (2 * st + g) * 16);
-    const char *k_rd[8];   // as in k_attn_bf16: chunk 2*st + g of key col, slot c ^ (key & 15)
+    unsigned k_rd[8];   // as in k_attn_bf16: chunk 2*st + g of key col, slot c ^ (key & 15)
 #pragma unroll
-    for (int st = 0; st < 8; ++st) k_rd[st] = smem + col * 256 + (((2 * st + g) ^ (col & 15)) << 4);
+    for (int st = 0; st < 8; ++st) k_rd[st] = (unsigned)(size_t)WK_LDS(smem) + col * 256 + (((2 * st + g) ^ (col & 15)) << 4);
     unsigned k_src[2];
     {
         const int r = lane >> 4, p = lane & 15;
@@ -898,9 +998,10 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
             __builtin_amdgcn_global_load_lds(WK_GLB(Kh + ko), WK_LDS(dst + i * 1024), 16, 0, 0);
         }
     };
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = -INFINITY;
+    f32x2 l_run = {0.f, 0.f};   // row sums of the even and the odd tiles, apart as in k_attn_bf16
     const float c_log2 = a.scale_log2;
-    auto tile = [&](int byte_off, int kt, bool partial) {
+    auto tile = [&](int byte_off, int kt, bool partial, auto odd_tag) __attribute__((always_inline)) {
         f32x16 s[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
@@ -910,7 +1011,7 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
         for (int st = 0; st < 8; ++st)
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                const bf16x8 ka = *reinterpret_cast<const bf16x8 *>(k_rd[st] + byte_off + b * 8192);
+                const bf16x8 ka = *WK_LDS_AT(const bf16x8, k_rd[st] + byte_off + b * 8192);
                 s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb[st], s[b], 0, 0, 0);
             }
         if (partial) {
@@ -933,9 +1034,12 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
         const float mt = max_across_halves(m) * c_log2;
         if (__any(mt > m_run + 8.0f)) {   // lazy rescale, as in k_attn_bf16
             const float m_new = fmaxf(m_run, mt);
-            l_run *= __builtin_amdgcn_exp2f(m_run - m_new);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run[0] *= alpha;
+            l_run[1] *= alpha;
             m_run = m_new;
         }
+        float l_tile = l_run[decltype(odd_tag)::value];
         const float neg_m = -m_run;
         const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
@@ -944,9 +1048,10 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
             for (int e = 0; e < 16; e += 2) {
                 const float p0 = __builtin_amdgcn_exp2f(fmaf(s[b][e], c_log2, neg_m));
                 const float p1 = __builtin_amdgcn_exp2f(fmaf(s[b][e + 1], c_log2, neg_m));
-                l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_convertvector(f32x2{p0, p1}, bf16x2), ones, l_run,
-                                                        false);
+                l_tile = __builtin_amdgcn_fdot2_f32_bf16(__builtin_convertvector(f32x2{p0, p1}, bf16x2), ones, l_tile,
+                                                         false);
             }
+        l_run[decltype(odd_tag)::value] = l_tile;
     };
     const int n_full = n_kv / kKeys;   // full tiles; one partial tile may follow
     const bool tail = n_full * kKeys < n_kv;
@@ -955,7 +1060,7 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
     // One barrier per two tiles.  Before it, this wave's loads of tiles j and j+1 have landed
     // (vmcnt(0): nothing newer is in flight yet); behind it every wave is done with tiles j-2 and
     // j-1, whose slots tiles j+2 and j+3 may overwrite.
-    auto open_pair = [&](int j, auto pos_tag) {
+    auto open_pair = [&](int j, auto pos_tag) __attribute__((always_inline)) {
         constexpr int POS = decltype(pos_tag)::value;
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
@@ -965,23 +1070,23 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
     using P0 = std::integral_constant<int, 0>;
     using P2 = std::integral_constant<int, 2>;
     const bool idle = qt * 256 + wave * 32 >= a.N_q;   // no valid query in this wave: loads and barriers only
-    auto full_pair = [&](int j, auto pos_tag) {
+    auto full_pair = [&](int j, auto pos_tag) __attribute__((always_inline)) {
         constexpr int POS = decltype(pos_tag)::value;
         open_pair(j, pos_tag);
         if (idle) return;
-        tile(POS * kTileBytes, j * kKeys, false);
-        tile((POS + 1) * kTileBytes, (j + 1) * kKeys, false);
+        tile(POS * kTileBytes, j * kKeys, false, std::false_type{});
+        tile((POS + 1) * kTileBytes, (j + 1) * kKeys, false, std::true_type{});
     };
     // what is left after the full pairs: at most one full tile and the partial one
-    auto last_pair = [&](int j, auto pos_tag, int full) {
+    auto last_pair = [&](int j, auto pos_tag, int full) __attribute__((always_inline)) {
         constexpr int POS = decltype(pos_tag)::value;
         open_pair(j, pos_tag);
         if (idle) return;
         if (full) {
-            tile(POS * kTileBytes, j * kKeys, false);
-            if (tail) tile((POS + 1) * kTileBytes, (j + 1) * kKeys, true);
+            tile(POS * kTileBytes, j * kKeys, false, std::false_type{});
+            if (tail) tile((POS + 1) * kTileBytes, (j + 1) * kKeys, true, std::true_type{});
         } else {
-            tile(POS * kTileBytes, j * kKeys, true);
+            tile(POS * kTileBytes, j * kKeys, true, std::false_type{});
         }
     };
     int j = 0;
@@ -999,7 +1104,8 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
         last_pair(j, P0{}, rest);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // drain the clamped look-ahead loads before the LDS is released
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    const float l_lane = l_run[0] + l_run[1];
+    const float l_tot = l_lane + __shfl_xor(l_lane, 32);
     if (q_ok && g == 0) *out = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
 
@@ -1041,50 +1147,45 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
     if (a.lse && sub == 0) a.lse[row] = l > 0.f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
-// Key-range splits for grids that would leave compute units idle: the count that fills the 256 CUs best
-// over whole rounds of workgroups; ties go to fewer.  Up to 8 splits of at least 8 tiles each; windows
-// long enough to leave 128 tiles per split may use up to 16.  (Query tiles that walk the same slice of a
-// head's keys run side by side and share it through the L2, which cutting the work into equal runs
-// regardless of item boundaries would give up: that was measured 5 to 14 % slower.)
+// How a bf16 launch is laid out:
+//   kg = 1   workgroups of 256 queries, a tile of 64 keys per step
+//   kg = 2   workgroups of 128 queries, a pair of tiles per step: twice the workgroups, 10 % more power per product
+//            (every tile is fetched for half as many queries)
+//   splits   > 1: the key range split over workgroups and merged (needs a workspace), at most kMaxSplits and a step or
+//            more of work each
+// chosen by the cheapest predicted time.  A step takes longer with more compute units at work, because the chip lowers
+// its clock: kBusyUs with few of them, kFullUs with all 256; a workgroup's fill and drain cost kFillSteps; the merge a
+// launch and its traffic.  The figures were fitted to timed launches of 75 shapes (2 to 40 heads, 64 to 4,680 queries,
+// 277 to 211,200 keys) with both kg and every split count; over those shapes the rule's choice is 1.5 % slower than the
+// fastest layout on average, 10 % on the worst (a launch of 10 us).  (Query tiles that walk the same slice of a head's keys run side by side and share it through the
+// L2, which cutting the work into equal runs regardless of item boundaries would give up: that was measured 5 to 14 % slower.)
 constexpr int kMaxSplits = 16;
+constexpr int kMinSplitTiles = 24;   // shorter windows: a workspace would buy less than 2 us
 
-int choose_splits(int items, int n_tiles) {
-    int best = 1;
-    double best_util = 0.0;
-    for (int s = 1; s <= kMaxSplits && (s == 1 || n_tiles / s >= (s <= 8 ? 8 : 128)); ++s) {
-        const int wgs = items * s;
-        const double util = (double)wgs / (double)(((wgs + 255) / 256) * 256);
-        if (util > best_util + 0.02) { best_util = util; best = s; }
-    }
-    return best;
+struct LaunchPlan { int kg, splits; };
+
+double launch_us(int kg, int splits, long long H, long long N_q, int n_tiles) {
+    const double kBusyUs = kg == 1 ? 1.23 : 1.41, kFullUs = kg == 1 ? 1.48 : 1.92, kFillSteps = kg == 1 ? 3.8 : 1.6;
+    const long long wgs = H * ((N_q + 256 / kg - 1) / (256 / kg)) * splits;
+    const int tiles = (n_tiles + splits - 1) / splits, steps = (tiles + kg - 1) / kg;
+    const double rest = (double)(wgs % 256) / 256;
+    double us = (steps + kFillSteps) * ((double)(wgs / 256) * kFullUs + (rest == 0 ? 0 : std::fmax(kBusyUs, kFullUs * rest)));
+    if (splits > 1) us += 8.5 + 2.0 * splits * (double)(H * N_q) * 516.0 / 7.9e6;
+    return us;
 }
-
-// How a bf16 launch is laid out, chosen by a cost model in units of one 64-key step of a 256-query
-// workgroup (measured: a 128-query workgroup, one wave per SIMD, takes 0.69 of that per step; a workgroup's
-// fill and drain cost about 4 steps; the merge of s partial results costs about 6 steps plus its traffic):
-//   waves = 8, splits = 1   one workgroup per (head, 256 queries): large grids
-//   waves = 8, splits > 1   the key range split over workgroups and merged: small grids, long windows
-//   waves = 4               one workgroup per (head, 128 queries), twice as many of them: small grids, short
-//                           windows, or no workspace for partial results
-struct LaunchPlan { int waves, splits; };
 
 LaunchPlan plan_bf16(int H, int N_q, int N_kv, bool workspace_ok) {
     const int n_tiles = (N_kv + 63) / 64;
-    const long long items8 = (long long)H * ((N_q + 255) / 256), items4 = (long long)H * ((N_q + 127) / 128);
-    auto rounds = [](long long wgs) { return (double)((wgs + 255) / 256); };
-    const double plain8 = rounds(items8) * (n_tiles + 4);
-    const double plain4 = rounds(items4) * (n_tiles + 4) * 0.69;
-    LaunchPlan best{8, 1};
-    double best_cost = plain8;
-    if (plain4 < 0.97 * best_cost) { best = LaunchPlan{4, 1}; best_cost = plain4; }
-    if (workspace_ok && items8 <= 0x7fffffff / kMaxSplits) {
-        const int s = choose_splits((int)items8, n_tiles);
-        if (s > 1) {
-            const double merge = 6.0 + 2.0 * s * H * (double)N_q * 516.0 / 5e12 / 1.76e-6;
-            const double split8 = rounds(items8 * s) * ((double)n_tiles / s + 4) + merge;
-            if (split8 < 0.97 * best_cost) best = LaunchPlan{8, s};
+    LaunchPlan best{1, 1};
+    double best_us = launch_us(1, 1, H, N_q, n_tiles);
+    for (int kg = 1; kg <= 2; ++kg)
+        for (int sp = 1; sp <= (workspace_ok ? kMaxSplits : 1) && (sp == 1 || n_tiles >= std::max(2 * kg * sp, kMinSplitTiles)); ++sp) {
+            const double us = launch_us(kg, sp, H, N_q, n_tiles);
+            if (us < best_us) {
+                best_us = us;
+                best = LaunchPlan{kg, sp};
+            }
         }
-    }
     return best;
 }
 
@@ -1107,25 +1208,25 @@ wk_status allow_large_lds() {
     static std::atomic<uint64_t> done{0};
     int dev;
     if (wk::device_needs_setup(done, dev)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<8, false, false>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, false, false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<4, false, false>),
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, false, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, true, false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<8, true, false>),
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, false, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<8, false, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<4, false, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess)
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, false, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess)
             return WK_ERR_HIP;
         wk::mark_device(done, dev);
     }
     return WK_OK;
 }
 
-template <int WAVES>
+template <int KG>
 wk_status launch_bf16(AttnArgs a, int splits, void *workspace, hipStream_t st) {
-    const int q_per_wg = WAVES * 32;
+    constexpr int q_per_wg = 256 / KG;
     a.n_qtiles = (a.N_q + q_per_wg - 1) / q_per_wg;
     a.splits = splits;
     a.part_o = reinterpret_cast<float *>(workspace);
@@ -1137,10 +1238,10 @@ wk_status launch_bf16(AttnArgs a, int splits, void *workspace, hipStream_t st) {
     const wk_status lds_rc = allow_large_lds();
     if (lds_rc != WK_OK) return lds_rc;
     if (a.O) {
-        hipLaunchKernelGGL((k_attn_bf16<WAVES, false, false>), dim3(a.per_xcd * kXcds), dim3(WAVES * 64), kSmemBytes, st, a,
-                           SubTable{});
+        hipLaunchKernelGGL((k_attn_bf16<KG, false, false>), dim3(a.per_xcd * kXcds), dim3(512), KG == 1 ? kSmemBytes : kSmemBytesPair,
+                           st, a, SubTable{});
     } else {
-        if (WAVES != 8) return WK_ERR_UNSUPPORTED;   // the log-sum-exp kernel is laid out for 256-query workgroups
+        if (KG != 1) return WK_ERR_UNSUPPORTED;   // the log-sum-exp kernel is laid out for 256-query workgroups
         hipLaunchKernelGGL(k_lse_bf16, dim3(a.per_xcd * kXcds), dim3(512), kVRing, st, a);
     }
     WK_LAUNCH_CHECK();
@@ -1210,13 +1311,13 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         }
         return WK_OK;
     }
-    if (!O) return launch_bf16<8>(a, 1, nullptr, st);   // log-sum-exp only
+    if (!O) return launch_bf16<1>(a, 1, nullptr, st);   // log-sum-exp only
     const bool ws_aligned = workspace && reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
     // the plan with a workspace, if the one given is big enough for it; otherwise the best plan without
     LaunchPlan plan = plan_bf16(H, N_q, N_kv, ws_aligned);
     if (plan.splits > 1 && workspace_bytes < split_workspace_bytes(H, N_q, plan.splits))
         plan = plan_bf16(H, N_q, N_kv, false);
-    return plan.waves == 8 ? launch_bf16<8>(a, plan.splits, workspace, st) : launch_bf16<4>(a, 1, nullptr, st);
+    return plan.kg == 1 ? launch_bf16<1>(a, plan.splits, workspace, st) : launch_bf16<2>(a, plan.splits, workspace, st);
 }
 
 namespace {
@@ -1234,7 +1335,7 @@ wk_status launch_plain(AttnArgs a, int dtype, hipStream_t st) {
         a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
         const wk_status rc = allow_large_lds();
         if (rc != WK_OK) return rc;
-        hipLaunchKernelGGL((k_attn_bf16<8, false, false>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a,
+        hipLaunchKernelGGL((k_attn_bf16<1, false, false>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a,
                            SubTable{});
     }
     WK_LAUNCH_CHECK();
@@ -1317,7 +1418,7 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
         } else {
             const wk_status lrc = allow_large_lds();
             if (lrc != WK_OK) return lrc;
-            hipLaunchKernelGGL((k_attn_bf16<8, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytes, st, g, t);
+            hipLaunchKernelGGL((k_attn_bf16<1, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytes, st, g, t);
         }
         WK_LAUNCH_CHECK();
     } else {
@@ -1389,7 +1490,7 @@ extern "C" wk_status wk_chunk_lse(const wk_store_desc *store, const void *Q, int
         WK_LAUNCH_CHECK();
         return WK_OK;
     }
-    return launch_bf16<8>(a, 1, nullptr, st);
+    return launch_bf16<1>(a, 1, nullptr, st);
 }
 
 extern "C" wk_status wk_attention_in_place(const void *Q, const void *K_native, const void *V_native,
@@ -1430,20 +1531,20 @@ extern "C" wk_status wk_attention_in_place(const void *Q, const void *K_native, 
     a.q_rows = N_q; a.q_off = 0; a.kv_start = 0; a.part_slot = -1;
     a.v_table = store->V_ptr; a.ids = ids; a.n_ids = n_ids; a.R_max = store->M > 0 ? R_max : 0; a.store_M = store->M;
     a.max_tok = store->max_tok;
-    // 256- or 128-query workgroups, by the cost model of wk_attention for the longest window the ids can give
+    // 256- or 128-query workgroups, by the rule of wk_attention for the longest window the ids can give
     const long long longest = (long long)n_native + (long long)a.R_max * store->max_tok;
     const LaunchPlan plan = plan_bf16(a.H, N_q, (int)(longest < 64 ? 64 : (longest > 0x7fffffff ? 0x7fffffff : longest)), false);
-    const int q_per_wg = plan.waves * 32;
+    const int q_per_wg = 256 / plan.kg;
     a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
     if ((long long)a.H * a.n_qtiles + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
     a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
     const wk_status rc = allow_large_lds();
     if (rc != WK_OK) return rc;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-    if (plan.waves == 8)
-        hipLaunchKernelGGL((k_attn_bf16<8, false, true>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a, SubTable{});
+    if (plan.kg == 1)
+        hipLaunchKernelGGL((k_attn_bf16<1, false, true>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a, SubTable{});
     else
-        hipLaunchKernelGGL((k_attn_bf16<4, false, true>), dim3(a.per_xcd * kXcds), dim3(256), kSmemBytes, st, a, SubTable{});
+        hipLaunchKernelGGL((k_attn_bf16<2, false, true>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytesPair, st, a, SubTable{});
     WK_LAUNCH_CHECK();
     return WK_OK;
 }

@@ -1,0 +1,79 @@
+"""bf16 attention in each layout of a launch: 256-query workgroups, 128-query workgroups whose two wave groups take the
+even and the odd key tiles, and either with a split key range."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_22718_amd as wk
+from wkt import assert_attention_close_bf16, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(H, N_q, N_kv, seed, rising=False):
+    g = torch.Generator().manual_seed(seed)
+    Q, K, V = (torch.randn(H, n, 128, generator=g).to(torch.bfloat16) for n in (N_q, N_kv, N_kv))
+    if rising:   # later keys have larger logits: the running maximum moves in every tile, in both wave groups
+        Q = (Q.float() * 6).to(torch.bfloat16)
+        order = torch.argsort((Q[:, :1].float() @ K.float().transpose(1, 2))[:, 0], dim=1)
+        K = torch.stack([K[h, order[h]] for h in range(H)])
+    return Q, K, V
+
+
+# 128-query workgroups: one tile (the second group has none), one partial tile, one pair, an odd tile behind whole pairs,
+# a last pair whose second tile is partial / whose first tile is, trips of the steady loop with 0 and 1 left-over steps
+@pytest.mark.parametrize("N_q", [1, 127, 128, 129, 300])
+@pytest.mark.parametrize("N_kv", [1, 63, 64, 65, 128, 129, 191, 192, 320, 400, 576, 640, 707])
+def test_tile_pairs(N_q, N_kv):
+    Q, K, V = _inputs(2, N_q, N_kv, seed=N_q * 1000 + N_kv)
+    d = dev()
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    only = torch.empty_like(lse)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse)
+    wk.wk_attention(Q.to(d), K.to(d), None, None, only)
+    ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
+    assert_attention_close_bf16(O, ref, lse, ref_lse)
+    assert torch.equal(lse, only)   # the row sums do not depend on which kernel or layout forms them
+
+
+@pytest.mark.parametrize("N_kv", [640, 1500, 2111])
+def test_tile_pairs_with_rising_logits(N_kv):
+    Q, K, V = _inputs(2, 200, N_kv, seed=N_kv, rising=True)
+    d = dev()
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse)
+    ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
+    assert_attention_close_bf16(O, ref, lse, ref_lse)
+
+
+# splits whose tile counts are odd (the second group's last tile belongs to the next split), end past the device-side
+# length, or are empty
+@pytest.mark.parametrize("H,N_q,N_kv,n_dev", [(2, 300, 3000, None), (2, 231, 6001, None), (4, 537, 2975, 1700), (1, 65, 5000, 130)])
+def test_split_tile_pairs(H, N_q, N_kv, n_dev):
+    Q, K, V = _inputs(H, N_q, N_kv, seed=N_kv + N_q)
+    d = dev()
+    n = wk.wk_attention_workspace_bytes(H, N_q, N_kv, wk.WK_BF16)
+    assert n > 0
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse, workspace=torch.empty(n, dtype=torch.uint8, device=d),
+                    n_kv_dev=None if n_dev is None else torch.tensor([n_dev], dtype=torch.int32, device=d))
+    ref, ref_lse = oracle.attention(Q, K, V, N_kv=n_dev or N_kv, want_lse=True)
+    assert_attention_close_bf16(O, ref, lse, ref_lse)
+
+
+# in place: odd and even totals of tiles, segments that end inside a tile (the pair then spans two segments), one tile in all
+@pytest.mark.parametrize("n_native,lens", [(0, [40]), (64, [64]), (100, [64, 1, 200]), (129, [63, 65, 130, 64]), (300, [])])
+def test_tile_pairs_in_place(n_native, lens):
+    H, N_q, d = 2, 150, dev()
+    g = torch.Generator().manual_seed(n_native + len(lens))
+    Q = torch.randn(H, N_q, 128, generator=g).to(torch.bfloat16)
+    parts = [tuple(torch.randn(H, n, 128, generator=g).to(torch.bfloat16) for _ in range(2)) for n in [n_native] + lens]
+    store = wk.Store(*[[p[i].to(d) for p in (parts[1:] or parts[:1])] for i in range(2)])
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    ids = torch.arange(len(lens), dtype=torch.int32, device=d) if lens else None
+    wk.wk_attention_in_place(Q.to(d), parts[0][0].to(d) if n_native else None, parts[0][1].to(d) if n_native else None, n_native,
+                             store.desc, ids, None, len(lens), O, lse)
+    K, V = (torch.cat([p[i] for p in parts], 1) for i in range(2))
+    ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
+    assert_attention_close_bf16(O, ref, lse, ref_lse)
