@@ -264,7 +264,7 @@ def step(E, pos, kg, kreads=None):
     E.emit("s_barrier")
 
 
-def generate(kg):
+def generate(kg=1):
     # what the last step of a trip keeps back is the same text in every iteration: find it with a dry run
     dry = Emitter()
     for pos in range(0, 4, kg):
