@@ -1,0 +1,31 @@
+"""wk_score_chunks where its launch changes: one workgroup more per 64 candidates, other workgroups above 128 and 1,024."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_22718_amd as wk
+from wkt import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M", [63, 64, 65, 127, 128, 129, 1023, 1024, 1025, 4095])
+@pytest.mark.parametrize("norm_mode", [wk.WK_NORM_MAX, wk.WK_NORM_MINMAX, wk.WK_NORM_MEAN])
+def test_exact_ties_across_workgroups(M, norm_mode):
+    # poses on a coarse grid: many candidates at exactly the same distance, in different workgroups; lower id first
+    rng = np.random.default_rng(M)
+    poses = rng.integers(-1, 2, (M, 5)).astype(np.float32)
+    cur = np.array([1, 0, -1, 0.5, 0.25], np.float32)
+    R, d = M, dev()
+    ids = torch.full((R,), -7, dtype=torch.int32, device=d)
+    dist = torch.full((R,), -7.0, dtype=torch.float64, device=d)
+    nf = torch.full((1,), -7, dtype=torch.int32, device=d)
+    wk.wk_score_chunks(torch.from_numpy(poses).to(d), M, cur, norm_mode, R, ids, dist, nf)
+    ids, dist = ids.cpu().numpy(), dist.cpu().numpy()
+    _, _, o_all = oracle.score_chunks(poses, cur, R, norm_mode)
+    assert int(nf.item()) == M
+    np.testing.assert_array_equal(np.sort(ids), np.arange(M))
+    np.testing.assert_allclose(dist, o_all[ids], rtol=0, atol=1e-7)   # as the bar of the other retrieval tests
+    assert np.all(np.diff(dist) >= 0)
+    assert np.all(np.diff(ids)[np.diff(dist) == 0] > 0)
