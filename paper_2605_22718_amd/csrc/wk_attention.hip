@@ -1164,12 +1164,17 @@ constexpr int kMinSplitTiles = 24;   // shorter windows: a workspace would buy l
 
 struct LaunchPlan { int kg, splits; };
 
-double launch_us(int kg, int splits, long long H, long long N_q, int n_tiles) {
+// wgs workgroups of `steps` steps each (on average)
+double grid_us(int kg, long long wgs, double steps) {
     const double kBusyUs = kg == 1 ? 1.23 : 1.41, kFullUs = kg == 1 ? 1.48 : 1.92, kFillSteps = kg == 1 ? 3.8 : 1.6;
+    const double rest = (double)(wgs % 256) / 256;
+    return (steps + kFillSteps) * ((double)(wgs / 256) * kFullUs + (rest == 0 ? 0 : std::fmax(kBusyUs, kFullUs * rest)));
+}
+
+double launch_us(int kg, int splits, long long H, long long N_q, int n_tiles) {
     const long long wgs = H * ((N_q + 256 / kg - 1) / (256 / kg)) * splits;
     const int tiles = (n_tiles + splits - 1) / splits, steps = (tiles + kg - 1) / kg;
-    const double rest = (double)(wgs % 256) / 256;
-    double us = (steps + kFillSteps) * ((double)(wgs / 256) * kFullUs + (rest == 0 ? 0 : std::fmax(kBusyUs, kFullUs * rest)));
+    double us = grid_us(kg, wgs, steps);
     if (splits > 1) us += 8.5 + 2.0 * splits * (double)(H * N_q) * 516.0 / 7.9e6;
     return us;
 }
@@ -1186,6 +1191,30 @@ LaunchPlan plan_bf16(int H, int N_q, int N_kv, bool workspace_ok) {
                 best = LaunchPlan{kg, sp};
             }
         }
+    return best;
+}
+
+// The workgroup size of a table of launches, by the same model: the grid's time if every workgroup had the average
+// number of steps, or the longest workgroup's alone.  12 heads x 3 frames of 880 queries on 10,560 keys are 276
+// workgroups of 256 queries, which leave a second round of 20: 220 us; as 504 of 128 queries 171 us.
+int table_kg(const SubTable &t, long long H) {
+    int best = 1;
+    double best_us = 0;
+    for (int kg = 1; kg <= 2; ++kg) {
+        long long wgs = 0, steps = 0, longest = 0;
+        for (int e = 0; e < t.n; ++e) {
+            const long long n = H * ((t.s[e].N_q + 256 / kg - 1) / (256 / kg)), tiles = (t.s[e].N_kv + 63) / 64;
+            const long long len = (tiles + kg - 1) / kg;
+            wgs += n;
+            steps += n * len;
+            longest = std::max(longest, len);
+        }
+        const double us = std::fmax(grid_us(kg, wgs, (double)steps / (double)wgs), grid_us(kg, std::min(wgs, 256ll), (double)longest));
+        if (kg == 1 || us < best_us) {
+            best = kg;
+            best_us = us;
+        }
+    }
     return best;
 }
 
@@ -1214,6 +1243,8 @@ wk_status allow_large_lds() {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, true, false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, true, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, false, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, false, true>),
@@ -1398,17 +1429,18 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
     if (frames + 1 <= kMaxSub) {
         // all ranges in one grid: entry 0 = the rows behind the chunk for every query (the long
         // items first), entries 1.. = the prefix up to frame f for that frame's queries
-        const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : 256;
         SubTable t;
         t.n = frames + 1;
-        t.s[0] = SubLaunch{0, N_q, (N_q + q_per_wg - 1) / q_per_wg, start, N_kv - start, start, 1};
-        t.per_head = t.s[0].n_qtiles;
-        for (int f = 0; f < frames; ++f) {
-            t.s[f + 1] = SubLaunch{f * frame_T, frame_T, (frame_T + q_per_wg - 1) / q_per_wg, 0,
-                                   denoise_row0 + (f + 1) * frame_T, 0, 0};
-            t.per_head += t.s[f + 1].n_qtiles;
-        }
+        t.s[0] = SubLaunch{0, N_q, 0, start, N_kv - start, start, 1};
+        for (int f = 0; f < frames; ++f) t.s[f + 1] = SubLaunch{f * frame_T, frame_T, 0, 0, denoise_row0 + (f + 1) * frame_T, 0, 0};
         for (int e = t.n; e < kMaxSub; ++e) t.s[e] = SubLaunch{0, 0, 0, 0, 0, 0, 0};
+        const int kg = dtype == WK_F32 ? 1 : table_kg(t, H);
+        const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : 256 / kg;
+        t.per_head = 0;
+        for (int e = 0; e < t.n; ++e) {
+            t.s[e].n_qtiles = (t.s[e].N_q + q_per_wg - 1) / q_per_wg;
+            t.per_head += t.s[e].n_qtiles;
+        }
         AttnArgs g = a;
         if ((long long)H * t.per_head + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
         g.per_xcd = (H * t.per_head + kXcds - 1) / kXcds;
@@ -1418,7 +1450,10 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
         } else {
             const wk_status lrc = allow_large_lds();
             if (lrc != WK_OK) return lrc;
-            hipLaunchKernelGGL((k_attn_bf16<1, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytes, st, g, t);
+            if (kg == 1)
+                hipLaunchKernelGGL((k_attn_bf16<1, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytes, st, g, t);
+            else
+                hipLaunchKernelGGL((k_attn_bf16<2, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytesPair, st, g, t);
         }
         WK_LAUNCH_CHECK();
     } else {

@@ -77,3 +77,16 @@ def test_tile_pairs_in_place(n_native, lens):
     K, V = (torch.cat([p[i] for p in parts], 1) for i in range(2))
     ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
     assert_attention_close_bf16(O, ref, lse, ref_lse)
+
+
+# the frame mask's table of launches in 128-query workgroups (small grids): frames that end
+# inside a query tile, a key range behind the chunk that is empty, one key, and an odd count of tiles
+@pytest.mark.parametrize("H,T,row0,n_after", [(2, 250, 0, 0), (2, 129, 64, 1), (3, 249, 130, 191)])
+def test_frame_mask_layouts(H, T, row0, n_after):
+    N_q, d = 3 * T, dev()
+    Q, K, V = _inputs(H, N_q, row0 + N_q + n_after, seed=T + H)
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    ws = torch.empty(wk.wk_attention_block_causal_workspace_bytes(H, N_q), dtype=torch.uint8, device=d)
+    wk.wk_attention_block_causal(Q.to(d), K.to(d), V.to(d), O, row0, T, ws, lse=lse)
+    ref, ref_lse = oracle.attention_block_causal(Q, K, V, row0, T, want_lse=True)
+    assert_attention_close_bf16(O, ref, lse, ref_lse)
