@@ -302,23 +302,30 @@ __global__ __launch_bounds__(256) void k_score_factored(const char *__restrict__
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 // ---- Eq. 5 as the similarity GEMM on the matrix cores (WK_SCORE_GEMM) ------------------------
 //
 // C[i][j] = sum over the group's heads and the 128 features of (anchor key i) . (candidate key j),
 // then partial[j] = sum_i C[i][j] / |k_i|.  A workgroup of 8 waves owns a 256 (anchors) x 256
-// (candidates) block of C: wave (wa, wc) holds 128 x 64 of it in eight 32x32 accumulators, so a
-// 16-feature step costs 4 + 2 operand reads from LDS for 8 MFMAs.  The contraction runs over
-// heads x 128 features in steps of 64 features; both operand tiles of a step (256 rows x 128 bytes
-// each) go from global memory straight into one of two LDS stages (global_load_lds), the next step's
-// loads being in flight while the current one is multiplied.  Rows are 128 bytes, their eight
-// 16-byte chunks stored at chunk ^ ((row >> 1) & 7), which makes the 16 lanes of an operand read
-// hit 16 different bank groups.  The block of C never leaves registers: it is folded with the
-// column weights 1/|k_i| and summed over the anchors in the epilogue.
+// (candidates) block of C: wave (wa, wc) holds 128 x 64 of it in 8 x 4 accumulators of 16 x 16, so a
+// 32-feature step costs 8 + 4 operand reads from LDS for 32 products.  The contraction runs over
+// heads x 128 features in steps of 32 features; both operand tiles of a step (256 rows x 64 bytes
+// each) go from global memory straight into one of four LDS stages (global_load_lds), three steps
+// ahead.  Two rows share a 128-byte line, whose eight 16-byte chunks are stored at chunk ^ ((line >> 1) & 3):
+// the 16 lanes of an operand read then hit 16 different bank groups.  The block of C never leaves registers: it
+// is folded with the column weights 1/|k_i| and summed over the anchors in the epilogue.
+//
+// What bounds it is power: matrix pipe busy 53 % of the cycles at 1.87 GHz; with the tile loads always from the same
+// (cached) place 20 % fewer cycles, at 1.59 GHz, and 5 % less time.  The 16x16x32 products need less power than
+// 32x32x16 ones (4 % faster here), a wave no longer waits for its own operand reads and the workgroups
+// of an XCD share tiles (below): 64-feature steps of 32x32x16 products in two stages, in plain grid order, took 880 us
+// for 16 chunks of 40 heads x 1,560 tokens, this 758 us (1.05 PFLOP/s).
+constexpr int kXcds = 8;
 constexpr int kGemmTile = 256;        // anchors and candidates per workgroup block
 constexpr int kGemmMaxSplits = 32;    // partial sums per candidate: (anchor blocks) x (head ranges), one workgroup each
-constexpr int kGemmStage = 2 * kGemmTile * 128;   // bytes: anchor tile + candidate tile of one 64-feature step
-constexpr int kGemmLds = 2 * kGemmStage + kGemmTile * 4 + 2 * kGemmTile * 4;
+constexpr int kGemmStages = 4;
+constexpr int kGemmStage = 2 * kGemmTile * 64;    // bytes: anchor tile + candidate tile of one 32-feature step
+constexpr int kGemmLds = kGemmStages * kGemmStage + kGemmTile * 4 + 2 * kGemmTile * 4;
 
 #define WK_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 #define WK_GLB_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
@@ -329,59 +336,77 @@ constexpr int kGemmLds = 2 * kGemmStage + kGemmTile * 4 + 2 * kGemmTile * 4;
 // they fill the chip when one chunk alone gives too few blocks.)
 __global__ __launch_bounds__(512, 2) void k_score_gemm(const char *__restrict__ K, const char *__restrict__ A,
                                                        CompressDims p, const double *__restrict__ nsq_a,
-                                                       int asplits, int hsplits, float *__restrict__ partial) {
+                                                       int asplits, int hsplits, int n_ranges, int per_xcd,
+                                                       float *__restrict__ partial) {
     extern __shared__ __attribute__((aligned(256))) char smem[];
-    float *w_lds = reinterpret_cast<float *>(smem + 2 * kGemmStage);   // [256] column weights of the anchor block
+    float *w_lds = reinterpret_cast<float *>(smem + kGemmStages * kGemmStage);   // [256] column weights of the anchor block
     float *red = w_lds + kGemmTile;                                    // [2][256] partial sums of the two anchor halves
+    // Workgroups reach the 8 XCDs round-robin; XCD x takes the contiguous range of work items [x*per_xcd, (x+1)*per_xcd),
+    // ordered list, head range, group of 4 anchor blocks, candidate tile, anchor block: the 32 workgroups of an XCD
+    // then walk about 4 + 8 operand tiles at a time instead of nearly all of them.
     const int splits = asplits * hsplits;
-    const int g = blockIdx.y / splits, sp = blockIdx.y % splits, b = blockIdx.z;
-    const int sa = sp % asplits, sh = sp / asplits;
-    const int j0 = blockIdx.x * kGemmTile;
+    const int cand_tiles = (p.n_cand + kGemmTile - 1) / kGemmTile;
+    const int w = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+    const int per_range = asplits * cand_tiles, range = w / per_range;   // range = list * hsplits + sh
+    if (range >= n_ranges) return;
+    const int list = range / hsplits, sh = range % hsplits;
+    const int g = list % p.G, b = list / p.G;
+    int rest = w % per_range;
+    const int a0 = rest / (4 * cand_tiles) * 4, a_n = min(4, asplits - a0);
+    rest -= a0 * cand_tiles;
+    const int sa = a0 + rest % a_n, sp = sh * asplits + sa;
+    const int j0 = rest / a_n * kGemmTile;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 31, gh = lane >> 5;
+    const int col = lane & 15, quad = lane >> 4;
     const int wa = wave & 1, wc = wave >> 1;
     const double *na = nsq_a + ((size_t)b * p.G + g) * p.T;
     const int n_ablocks = (p.T + kGemmTile - 1) / kGemmTile;
     const int h_per = (p.hg + hsplits - 1) / hsplits;
     const int h_lo = sh * h_per, h_hi = min(p.hg, h_lo + h_per);
-    const int n_steps = max(h_hi - h_lo, 0) * 2;   // 64-feature steps of the contraction
+    const int n_steps = max(h_hi - h_lo, 0) * 4;   // 32-feature steps of the contraction
 
-    // operand reads: chunk 2*st + gh of row (128*wa + 32*mb + col) resp. (64*wc + 32*nb + col)
-    const char *a_rd[4], *b_rd[4];
+    // operand reads: chunk quad of row (128*wa + 16*mb + col) resp. (64*wc + 16*nb + col), address + 1024 per 16 rows
+    const int rd = (col >> 1) * 128 + (((col & 1) * 4 + (quad ^ ((col >> 2) & 3))) << 4);
+    const char *const a_rd = smem + 8192 * wa + rd, *const b_rd = smem + kGemmTile * 64 + 4096 * wc + rd;
+    // tile loads: wave w fills 1 KB blocks (16 rows) 2*w and 2*w + 1 of both tiles, a lane one 16-byte slot of each
+    const int ld_row = 32 * wave + 2 * (lane >> 3) + ((lane >> 2) & 1);   // and 16 further down
+    const unsigned ld_chunk = (unsigned)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+    unsigned cand_off[2];
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-        const int slot = ((2 * st + gh) ^ ((col >> 1) & 7)) << 4;
-        a_rd[st] = smem + (128 * wa + col) * 128 + slot;
-        b_rd[st] = smem + kGemmTile * 128 + (64 * wc + col) * 128 + slot;
-    }
-    // tile loads: thread t fills 16-byte slot (t & 7) of rows 64*i + (t >> 3), i = 0..3, of both tiles
-    const int ld_row = tid >> 3;
-    const unsigned ld_chunk = (unsigned)(((tid & 7) ^ ((tid >> 4) & 7)) << 4);
-    unsigned cand_off[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)   // rows past the last candidate are clamped; their sums are never written
-        cand_off[i] = (unsigned)(p.first_cand + min(j0 + 64 * i + ld_row, p.n_cand - 1)) * 256u + ld_chunk;
-    char *const dma_dst = smem + wave * 1024;
+    for (int i = 0; i < 2; ++i)   // rows past the last candidate are clamped; their sums are never written
+        cand_off[i] = (unsigned)(p.first_cand + min(j0 + 16 * i + ld_row, p.n_cand - 1)) * 256u + ld_chunk;
+    const unsigned lds0 = (unsigned)(size_t)WK_LDS_PTR(smem);
 
-    float psum[2] = {0.f, 0.f};
+    float psum[4] = {0.f, 0.f, 0.f, 0.f};
     for (int ab = sa; ab < n_ablocks; ab += asplits) {
-        unsigned anc_off[4];
+        unsigned anc_off[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)   // anchors past T are clamped and get weight 0
-            anc_off[i] = (unsigned)min(ab * kGemmTile + 64 * i + ld_row, p.T - 1) * 256u + ld_chunk;
-        auto issue = [&](int step, int stage) {
-            const int hh = h_lo + (step >> 1);
-            const int h = p.G == 1 ? hh : g;
-            const char *Ah = A + ((size_t)b * p.H + h) * p.a_rows * 256 + (step & 1) * 128;
-            const char *Kh = K + ((size_t)b * p.H + h) * p.n_tok * 256 + (step & 1) * 128;
-            char *dst = dma_dst + stage * kGemmStage;
+        for (int i = 0; i < 2; ++i)   // anchors past T are clamped and get weight 0
+            anc_off[i] = (unsigned)min(ab * kGemmTile + 16 * i + ld_row, p.T - 1) * 256u + ld_chunk;
+        // tiles are requested in order: where the next step's begin, and its stage
+        const char *next_a = A + ((size_t)b * p.H + (p.G == 1 ? h_lo : g)) * p.a_rows * 256;
+        const char *next_k = K + ((size_t)b * p.H + (p.G == 1 ? h_lo : g)) * p.n_tok * 256;
+        unsigned next_dst = lds0 + wave * 2048;
+        int next_step = 0;
+        // i-th of the four loads of a step and wave (in assembly: 32-bit offsets to a scalar base, nothing else to compute)
+        auto load = [&](int i) __attribute__((always_inline)) {
+            const unsigned dst = next_dst + (i >> 1) * (kGemmTile * 64) + (i & 1) * 1024;
+            const unsigned off = i < 2 ? anc_off[i & 1] : cand_off[i & 1];
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(dst), "v"(off), "s"(i < 2 ? next_a : next_k) : "memory");   // nothing else here uses m0
+        };
+        auto advance = [&]() __attribute__((always_inline)) {   // 64 bytes on in every row, after four steps to the next head
+            ++next_step;
+            const bool head = (next_step & 3) == 0;
+            next_a += head ? (ptrdiff_t)p.a_rows * 256 - 192 : 64;
+            next_k += head ? (ptrdiff_t)p.n_tok * 256 - 192 : 64;
+            next_dst += head ? -3 * kGemmStage : kGemmStage;
+        };
+        auto issue = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_global_load_lds(WK_GLB_PTR(Ah + anc_off[i]), WK_LDS_PTR(dst + i * 8192), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds(WK_GLB_PTR(Kh + cand_off[i]), WK_LDS_PTR(dst + kGemmTile * 128 + i * 8192),
-                                                 16, 0, 0);
-            }
+            for (int i = 0; i < 4; ++i) load(i);
+            advance();
         };
         __syncthreads();   // the previous block's weights and stages are no longer read
         if (tid < kGemmTile) {
@@ -393,13 +418,11 @@ __global__ __launch_bounds__(512, 2) void k_score_gemm(const char *__restrict__ 
             }
             w_lds[tid] = rn;
         }
-        f32x16 acc[4][2];
+        f32x4 acc[8][4];
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.f;
+            for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
         // 32-row groups of this wave's 128 anchors that hold at least one anchor below T: all 4 except in
         // the last anchor block, where the groups of pure padding are skipped (their weights are 0 anyway)
         const int rows_left = p.T - (ab * kGemmTile + 128 * wa);
@@ -408,33 +431,83 @@ __global__ __launch_bounds__(512, 2) void k_score_gemm(const char *__restrict__ 
         // is multiplied
         const int cols_left = p.n_cand - (j0 + 64 * wc);
         const int nb_valid = cols_left >= 64 ? 2 : (cols_left <= 0 ? 0 : (cols_left + 31) / 32);
+        // MV, NV: 32-row groups and 32-candidate groups of this wave that are multiplied.  A step is two halves of
+        // MV x 2*NV products (the wave's first MV blocks of 16 anchors, then the others).  A half's operands are read
+        // while the half before is multiplied, and the second half runs behind the next step's barrier: a wave never
+        // waits for reads it has just issued.
         auto contract = [&](auto mv_tag, auto nv_tag) {
-            constexpr int MV = decltype(mv_tag)::value, NV = decltype(nv_tag)::value;
-            for (int step = 0; step < n_steps; ++step) {
-                __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the step's tiles has landed
-                __syncthreads();                      // everyone's has, and the other stage is free again
-                if (step + 1 < n_steps) issue(step + 1, (step + 1) & 1);
-                const int off = (step & 1) * kGemmStage;
-                if constexpr (MV > 0) {
+            constexpr int MV = decltype(mv_tag)::value, NB = 2 * decltype(nv_tag)::value, N = MV * NB;
+            bf16x8 fa[2][MV > 0 ? MV : 1], fb[2][NB > 0 ? NB : 1];
+            auto read_a = [&](int off, int half, int i) __attribute__((always_inline)) {
+                fa[half][i] = *reinterpret_cast<const bf16x8 *>(a_rd + off + (half * MV + i) * 1024);
+            };
+            auto read_b = [&](int off, int buf, int i) __attribute__((always_inline)) {
+                fb[buf][i] = *reinterpret_cast<const bf16x8 *>(b_rd + off + i * 1024);
+            };
+            auto multiply = [&](int half, int buf, auto &&between) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int st = 0; st < 4; ++st) {
-                        bf16x8 fa[MV], fb[NV];
-#pragma unroll
-                        for (int mb = 0; mb < MV; ++mb)
-                            fa[mb] = *reinterpret_cast<const bf16x8 *>(a_rd[st] + off + mb * 4096);
-#pragma unroll
-                        for (int nb = 0; nb < NV; ++nb)
-                            fb[nb] = *reinterpret_cast<const bf16x8 *>(b_rd[st] + off + nb * 4096);
-#pragma unroll
-                        for (int mb = 0; mb < MV; ++mb)
-#pragma unroll
-                            for (int nb = 0; nb < NV; ++nb)
-                                acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mb], fb[nb], acc[mb][nb], 0, 0, 0);
-                    }
+                for (int i = 0; i < N; ++i) {
+                    between(i);
+                    const int mb = i / NB, nb = (mb & 1) ? NB - 1 - i % NB : i % NB;   // one operand stays from product to product
+                    acc[half * MV + mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][mb], fb[buf][nb], acc[half * MV + mb][nb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+            };
+            auto one_step = [&](int step, auto parity_tag) __attribute__((always_inline)) {
+                constexpr int P = decltype(parity_tag)::value;
+                // this wave's part of the step's tiles has landed (the two steps behind it may be under way), its reads
+                // of the last step have returned
+                if (step + 2 < n_steps) __builtin_amdgcn_s_waitcnt(0x0078);
+                else __builtin_amdgcn_s_waitcnt(0x0070);
+                // everyone's, and the stage of the last step is free again (a bare barrier: __syncthreads would wait for
+                // the loads under way too)
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                const bool more = step + 3 < n_steps;
+                const int off = (step % kGemmStages) * kGemmStage;
+                if constexpr (MV > 0) {
+                    auto read_first = [&](int i) __attribute__((always_inline)) {   // the operands of the first half
+                        if (i < NB) read_b(off, P, i);
+                        else if (i < NB + MV) read_a(off, 0, i - NB);
+                    };
+                    if (step == 0) {
+#pragma unroll
+                        for (int i = 0; i < NB + MV; ++i) read_first(i);
+                        if (more) issue();
+                    } else {
+                        multiply(1, P ^ 1, [&](int i) __attribute__((always_inline)) {
+                            constexpr int per = (NB + MV + N - 1) / N;   // reads before each product
+#pragma unroll
+                            for (int r = 0; r < per; ++r) read_first(i * per + r);
+                            // the loads between the first products behind the barrier, so that these run meanwhile
+                            if (more) {
+#pragma unroll
+                                for (int l = 0; l < 4; ++l)
+                                    if (i == min(2 * l + 1, N - 1)) load(l);
+                                if (i == N - 1) advance();
+                            }
+                        });
+                    }
+                    multiply(0, P, [&](int i) __attribute__((always_inline)) {
+                        if (i < MV) read_a(off, 1, i);
+                    });
+                } else if (more) {
+                    issue();
+                }
+            };
+            for (int step = 0; step < n_steps; step += 2) {
+                one_step(step, std::integral_constant<int, 0>{});
+                one_step(step + 1, std::integral_constant<int, 1>{});
             }
+            if constexpr (MV > 0)
+                if (n_steps > 0) multiply(1, 1, [](int) {});
         };
-        if (n_steps > 0) issue(0, 0);
+        if (n_steps > 0) {
+            issue();
+            issue();
+            issue();
+        }
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
         using I2 = std::integral_constant<int, 2>;
@@ -451,22 +524,26 @@ __global__ __launch_bounds__(512, 2) void k_score_gemm(const char *__restrict__ 
         case 2: contract(I1{}, I1{}); break;
         default: contract(I0{}, I0{}); break;
         }
-        // fold the block in: accumulator register r of block mb is anchor 128*wa + 32*mb + 8*(r/4) + 4*gh + r%4
+        // fold the block in: accumulator register r of block mb is anchor 128*wa + 16*mb + 4*quad + r
         // (an empty head range has passed no barrier since the weights were written, and has nothing to add)
         if (n_steps > 0)
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int mb = 0; mb < 8; ++mb) {
+            const float4 w = *reinterpret_cast<const float4 *>(w_lds + 128 * wa + 16 * mb + 4 * quad);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float w = w_lds[128 * wa + 32 * mb + 8 * (r >> 2) + 4 * gh + (r & 3)];
-                psum[0] = fmaf(acc[mb][0][r], w, psum[0]);
-                psum[1] = fmaf(acc[mb][1][r], w, psum[1]);
+            for (int nb = 0; nb < 4; ++nb) {
+                psum[nb] = fmaf(acc[mb][nb][0], w.x, psum[nb]);
+                psum[nb] = fmaf(acc[mb][nb][1], w.y, psum[nb]);
+                psum[nb] = fmaf(acc[mb][nb][2], w.z, psum[nb]);
+                psum[nb] = fmaf(acc[mb][nb][3], w.w, psum[nb]);
             }
+        }
     }
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const float v = psum[nb] + __shfl_xor(psum[nb], 32);
-        if (gh == 0) red[wa * kGemmTile + 64 * wc + 32 * nb + col] = v;
+    for (int nb = 0; nb < 4; ++nb) {
+        float v = psum[nb] + __shfl_xor(psum[nb], 16);
+        v += __shfl_xor(v, 32);
+        if (quad == 0) red[wa * kGemmTile + 64 * wc + 16 * nb + col] = v;
     }
     __syncthreads();
     if (tid < kGemmTile && j0 + tid < p.n_cand)
@@ -664,6 +741,29 @@ FusePlan fuse_plan(const wk_compress_desc *d, const CompressDims &p) {
     return f;
 }
 
+// Workgroups of k_score_gemm: one per candidate block, anchor block (beyond 8 anchor blocks a workgroup walks several)
+// and head range.  One workgroup fits a compute unit, so the grid runs in rounds of 256; the number of head ranges is
+// the one with the cheapest rounds, a workgroup costing kGemmFill heads' worth beside its heads.  Whole calls with 1, 2,
+// 3 and 4 head ranges, 40 heads x 1,560 tokens: one chunk (91 blocks) 156, 110, 135, 116 us; three chunks 314, 255,
+// 251, 245 us; four 343, 307, 322, 311 us.
+constexpr double kGemmFill = 1.5;
+struct GemmPlan { int asplits, hsplits; };
+
+GemmPlan gemm_plan(const CompressDims &p, int batch) {
+    const int n_ablocks = (p.T + kGemmTile - 1) / kGemmTile;
+    GemmPlan g{n_ablocks < 8 ? n_ablocks : 8, 1};
+    const long long wgs = (long long)((p.n_cand + kGemmTile - 1) / kGemmTile) * g.asplits * p.G * batch;
+    double best = 0;
+    for (int h = 1; h <= p.hg && h * g.asplits <= kGemmMaxSplits; ++h) {
+        const double cost = (double)((wgs * h + 255) / 256) * ((p.hg + h - 1) / h + kGemmFill);
+        if (h == 1 || cost < best) {
+            best = cost;
+            g.hsplits = h;
+        }
+    }
+    return g;
+}
+
 bool make_dims(const wk_compress_desc *d, CompressDims &p, WsLayout &ws) {
     if (!d || d->H < 1 || d->T < 1 || d->F < 1 || d->batch < 1) return false;
     int32_t n_out = 0, n_keep = 0;
@@ -783,17 +883,9 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
                     hipLaunchKernelGGL((k_rows_normsq<DT, 1>), g2, dim3(256), 0, st, Kc, p, p.n_tok, p.first_cand,
                                        p.n_cand, nsq_cand);
                 WK_LAUNCH_CHECK();
-                // one workgroup per (candidate block, anchor block); beyond 8 anchor blocks a workgroup
-                // walks several
                 const int cand_tiles = (p.n_cand + kGemmTile - 1) / kGemmTile;
-                const int n_ablocks = (p.T + kGemmTile - 1) / kGemmTile;
-                const int asplits = n_ablocks < 8 ? n_ablocks : 8;
-                // head ranges: as many as keep the grid within one round of 256 workgroups
-                const long long blocks = (long long)cand_tiles * p.G * asplits * d->batch;
-                int hsplits = (int)(256 / (blocks > 0 ? blocks : 1));
-                hsplits = hsplits < 1 ? 1 : hsplits;
-                hsplits = hsplits > p.hg ? p.hg : hsplits;
-                hsplits = hsplits > kGemmMaxSplits / asplits ? kGemmMaxSplits / asplits : hsplits;
+                const GemmPlan plan = gemm_plan(p, d->batch);
+                const int asplits = plan.asplits, hsplits = plan.hsplits;
                 const int splits = asplits * hsplits;
                 float *partial = reinterpret_cast<float *>(wsp + ws.gemm_partial);
                 static std::atomic<uint64_t> lds_limit_set{0};   // more than the default 64 KB of dynamic LDS
@@ -804,8 +896,11 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
                         return WK_ERR_HIP;
                     wk::mark_device(lds_limit_set, dev);
                 }
-                hipLaunchKernelGGL(k_score_gemm, dim3(cand_tiles, p.G * splits, d->batch), dim3(512), kGemmLds, st, Kc,
-                                   A, p, nsq, asplits, hsplits, partial);
+                const long long ranges = (long long)d->batch * p.G * hsplits, items = ranges * asplits * cand_tiles;
+                if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+                const int per_xcd = (int)((items + kXcds - 1) / kXcds);
+                hipLaunchKernelGGL(k_score_gemm, dim3(per_xcd * kXcds), dim3(512), kGemmLds, st, Kc, A, p, nsq, asplits, hsplits,
+                                   (int)ranges, per_xcd, partial);
                 WK_LAUNCH_CHECK();
                 hipLaunchKernelGGL(k_score_gemm_finish, dim3((p.n_cand + 255) / 256, d->batch * p.G), dim3(256), 0, st,
                                    partial, p, splits, nsq_cand, scores);

@@ -149,6 +149,16 @@ def test_gemm_scoring_small_chunks(head_mode, H, T, F):
         _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], head_mode, rho, kind)
 
 
+# 256 x 256 blocks: one row or candidate beyond a block, every count of 32-row groups in an edge block, anchor blocks past a
+# group of four, more than eight of them (a workgroup walks two), an odd number of heads in unequal ranges
+@pytest.mark.parametrize("H,T,F", [(1, 257, 2), (3, 352, 2), (2, 450, 3), (7, 224, 3), (1, 1100, 2), (1, 2081, 2)])
+def test_gemm_scoring_block_edges(H, T, F):
+    cfg = ws.get_config(1).with_(H=H, T=T, F=F)
+    K, V, _ = ws.make_chunk(cfg, 6)
+    gi, gK, gV, gs, _ = _gpu_compress(cfg, K, V, None, rho=0.5, ratio_kind=wk.WK_RATIO_NONANCHOR, score_algo=wk.WK_SCORE_GEMM)
+    _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], wk.WK_HEADS_SHARED, 0.5, wk.WK_RATIO_NONANCHOR)
+
+
 def test_gemm_scoring_external_anchor_batch_and_fp32_refusal():
     cfg = ws.get_config(0).with_(H=2, T=70, dtype=ws.configs.DT_BF16)
     chunks = [ws.make_chunk(cfg, c) for c in range(2)]
