@@ -24,6 +24,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
 
@@ -166,25 +167,45 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32: v_mfma_f32_32x32x2_f32, 4 waves x 32 queries per workgroup, 32-key tiles.
+// fp32: v_mfma_f32_32x32x2_f32, 128 queries per workgroup, 32-key tiles in pairs.
+//
+// Bound by the matrix pipe: 128 products of 64 cycles per tile and wave, all else must run beside them.  Eight waves, two
+// per SIMD: waves 0..3 take the even tiles, waves 4..7 the odd ones for the same queries, and their (O, max, sum) meet in
+// LDS at the end.  The next pair of tiles goes from global memory straight into the other half of the LDS while a pair is
+// multiplied.  A pair takes 7.9 us on an otherwise idle chip, where the products alone would take 6.8 us at 2.4 GHz.
+// 4 heads x 880 queries x 2,640 keys: 58 us in 9 key ranges; 40 x 1,560 x 4,680: 1,410 us (106 TFLOP/s in 2.03 rounds of
+// workgroups).  (Four waves of one workgroup per compute unit, one per SIMD because of 268 registers, with the tiles staged
+// through registers between two barriers, took 87 us, in 14 key ranges, and 2,180 us.)
+//
+// Tiles are row-major, 32 chunks of 16 bytes per row, chunk c of K row k at slot c ^ (k & 15), of V row k at
+// slot c ^ (8 * (k >> 2 & 1)): the 16 lanes of a K read then hit 16 different bank groups, the two key rows of a V read
+// different halves of the banks.
 // ------------------------------------------------------------------------------------------
-constexpr int kF32Waves = 4;
+constexpr int kF32Waves = 4;                           // across the queries
+constexpr int kF32Threads = 2 * kF32Waves * 64;
 constexpr int kF32Keys = 32;
-constexpr int kF32KPitch = WK_D + 4;  // floats; 16 lanes x 16 B then cover all 64 banks
-constexpr int kF32VPitch = WK_D + 8;  // rows 4 apart land 32 banks apart
+constexpr int kF32Tile = kF32Keys * 512;               // bytes of one K or V tile
+constexpr int kF32Stage = 4 * kF32Tile;                // [tile of the pair][K, V]
+constexpr int kF32Lds = 2 * kF32Stage;
+
+#define WK_LDS(p) ((__attribute__((address_space(3))) void *)(p))
+// typed LDS pointer from a 32-bit LDS byte address
+#define WK_LDS_AT(T, addr) ((__attribute__((address_space(3))) T *)(size_t)(addr))
+#define WK_GLB(p) ((const __attribute__((address_space(1))) void *)(p))
 
 template <bool MULTI>
-__global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, SubTable sub) {
-    __shared__ float Ks[kF32Keys * kF32KPitch];
-    __shared__ float Vs[kF32Keys * kF32VPitch];
+__global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTable sub) {
+    extern __shared__ __attribute__((aligned(256))) char smem[];
     int c, h, qt, sp;
     if (!select_work<MULTI>(a, sub, 512, c, h, qt, sp)) return;
     const Window win = window_of(a, c);
     const int n_kv = win.n_kv;
     float *const lse = win.lse;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qw = wave & 3, kg = wave >> 2;   // 32 queries of the workgroup's, tile of every pair
     const int col = lane & 31, g = lane >> 5;
-    const int q = qt * (kF32Waves * 32) + wave * 32 + col;
+    const int q = qt * (kF32Waves * 32) + qw * 32 + col;
     const bool q_ok = q < a.N_q;
     const int q_ld = q_ok ? q : a.N_q - 1;
     const size_t qrow = (size_t)h * a.q_rows + a.q_off + q_ld;   // row of this lane's query in Q / O / lse
@@ -224,69 +245,141 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, SubTabl
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    const float *Kh = reinterpret_cast<const float *>(win.K) + (size_t)h * win.stride * WK_D;
-    const float *Vh = reinterpret_cast<const float *>(a.V) + (size_t)h * win.stride * WK_D;
-
-    for (int kt = kt0; kt < kt1; kt += kF32Keys) {
-        __syncthreads();  // previous tile fully consumed
+    const char *Kh = win.K + (size_t)h * win.stride * 512;
+    const char *Vh = a.V + (size_t)h * win.stride * 512;
+    const unsigned lds0 = (unsigned)(size_t)WK_LDS(smem) + kg * (2 * kF32Tile);
+    // A operand reads: chunk 2*c + g of K row col; feature 32*b + col of V row 8*(r/4) + 4*g + r%4
+    unsigned k_rd[8], v_rd[4];   // chunks 2*c + g and 2*(c + 8) + g differ in bit 4 alone
 #pragma unroll
-        for (int i = 0; i < (kF32Keys * WK_D / 4) / (kF32Waves * 64); ++i) {
-            const int x = tid + i * (kF32Waves * 64);
-            const int row = x / (WK_D / 4), c4 = x % (WK_D / 4);
-            float4 kv = float4{0, 0, 0, 0}, vv = float4{0, 0, 0, 0};
-            if (kt + row < kt1) {
-                kv = *reinterpret_cast<const float4 *>(Kh + (size_t)(kt + row) * WK_D + 4 * c4);
-                if (with_o) vv = *reinterpret_cast<const float4 *>(Vh + (size_t)(kt + row) * WK_D + 4 * c4);
-            }
-            *reinterpret_cast<float4 *>(&Ks[row * kF32KPitch + 4 * c4]) = kv;
-            *reinterpret_cast<float4 *>(&Vs[row * kF32VPitch + 4 * c4]) = vv;
+    for (int c = 0; c < 8; ++c) k_rd[c] = lds0 + col * 512 + (((2 * c + g) ^ (col & 15)) << 4);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v_rd[b] = lds0 + kF32Tile + 4 * g * 512 + (((8 * b + (col >> 2)) ^ (8 * g)) << 4) + (col & 3) * 4;
+    // tile loads: wave qw of a group fills rows 8*qw .. 8*qw+7 of its tile, two rows per load; rows past the range clamp to
+    // its last one (those keys are masked)
+    const int ld_row = 8 * qw + (lane >> 5), ld_slot = lane & 31;
+    auto issue = [&](int pair) {
+        char *dst = smem + (pair & 1) * kF32Stage + kg * (2 * kF32Tile) + qw * 4096;
+        const int kt = kt0 + (2 * pair + kg) * kF32Keys;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int R = ld_row + 2 * i;
+            const size_t row = (size_t)min(kt + R, kt1 - 1) * 512;
+            __builtin_amdgcn_global_load_lds(WK_GLB(Kh + row + ((ld_slot ^ (R & 15)) << 4)), WK_LDS(dst + i * 1024), 16, 0, 0);
+            if (with_o)
+                __builtin_amdgcn_global_load_lds(WK_GLB(Vh + row + ((ld_slot ^ (8 * (R >> 2 & 1))) << 4)), WK_LDS(dst + kF32Tile + i * 1024),
+                                                 16, 0, 0);
         }
-        __syncthreads();
-
+    };
+    const bool idle = qt * (kF32Waves * 32) + qw * 32 >= a.N_q;   // no valid query in this wave: loads and barriers only
+    const int n_pairs = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + 1) / 2;
+    issue(0);
+    // the two waves of a SIMD belong to different groups: the first one ahead, so that one does its softmax arithmetic
+    // while the other multiplies
+    if (kg == 0) __builtin_amdgcn_s_setprio(1);
+    for (int j = 0; j < n_pairs; ++j) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the pair has landed
+        __syncthreads();                      // everyone's has, and the pair before is fully consumed
+        if (j + 1 < n_pairs) issue(j + 1);
+        const int kt = kt0 + (2 * j + kg) * kF32Keys, stage = (j & 1) * kF32Stage;
+        if (kt >= kt1 || idle) continue;      // an odd count of tiles leaves the second group without one
+        // operands are read two groups of four products ahead, and the order is kept: left to itself the compiler reads each
+        // one right before its product and waits for it
+        typedef __attribute__((address_space(3))) const char lds_char;
+        lds_char *k_at[8], *v_at[4];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) k_at[c] = WK_LDS_AT(const char, k_rd[c] + stage);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) v_at[b] = WK_LDS_AT(const char, v_rd[b] + stage);
+        f32x4 ka[3];
+        float va[3][4];
+        auto read_k = [&](int c) __attribute__((always_inline)) {
+            ka[c % 3] = *reinterpret_cast<__attribute__((address_space(3))) const f32x4 *>(k_at[c & 7] + (c >> 3) * 256);
+        };
+        auto read_v = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                va[r % 3][b] = *reinterpret_cast<__attribute__((address_space(3))) const float *>(v_at[b] + (8 * (r >> 2) + (r & 3)) * 512);
+        };
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        read_k(0);
+        read_k(1);
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-            const float4 ka = *reinterpret_cast<const float4 *>(&Ks[col * kF32KPitch + 8 * c + 4 * g]);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka.x, qr[c].x, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka.y, qr[c].y, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka.z, qr[c].z, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka.w, qr[c].w, s, 0, 0, 0);
+            if (c + 2 < 16) read_k(c + 2);
+            else if (with_o) read_v(c - 14);
+            __builtin_amdgcn_sched_barrier(0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][0], qr[c].x, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][1], qr[c].y, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][2], qr[c].z, s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][3], qr[c].w, s, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
         // accumulator register r of this lane is key kt + 8*(r/4) + 4*g + r%4
         float m_tile = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = kt + 8 * (r >> 2) + 4 * g + (r & 3);
-            s[r] = key < kt1 ? s[r] * a.scale_log2 : -INFINITY;
-            m_tile = fmaxf(m_tile, s[r]);
+        for (int r = 0; r < 16; ++r) s[r] *= a.scale_log2;
+        if (kt + kF32Keys > kt1) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (kt + 8 * (r >> 2) + 4 * g + (r & 3) >= kt1) s[r] = -INFINITY;
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) m_tile = fmaxf(m_tile, s[r]);
         m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 32));
         const float m_new = fmaxf(m_run, m_tile);  // finite: every tile holds at least one valid key
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        if (__any(m_new > m_run)) {                // otherwise the factor is 1
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+            m_run = m_new;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
+        }
         float l_tile = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             s[r] = __builtin_amdgcn_exp2f(s[r] - m_new);
             l_tile += s[r];
         }
-        l_run = l_run * alpha + l_tile;
+        l_run += l_tile;
+        // O^T += V^T P^T: k slot g of step r means key 8*(r/4) + 4*g + r%4
+        if (with_o)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (r + 2 < 16) read_v(r + 2);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[r % 3][b], s[r], o[b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    }
+    // The wave groups meet: waves 4..7 leave (O^T, max, sum) of their keys in LDS, waves 0..3 add them to theirs.
+    // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.
+    {
+        float *meet = reinterpret_cast<float *>(smem) + qw * (66 * 64) + lane;
+        __syncthreads();   // every wave is done with its last tile
+        if (kg == 1) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) meet[(16 * b + r) * 64] = o[b][r];
+            meet[64 * 64] = m_run;
+            meet[65 * 64] = l_run;
+        }
+        __syncthreads();
+        if (kg == 1 || idle) return;
+        const float m_other = meet[64 * 64];   // -inf if the second group had no tile
+        const float m_new = fmaxf(m_run, m_other);
+        const float w0 = __builtin_amdgcn_exp2f(m_run - m_new), w1 = __builtin_amdgcn_exp2f(m_other - m_new);
         m_run = m_new;
+        l_run = fmaf(w1, meet[65 * 64], w0 * l_run);
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
-        // O^T += V^T P^T: k slot g of step r means key 8*(r/4) + 4*g + r%4
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int krow = 8 * (r >> 2) + 4 * g + (r & 3);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const float va = Vs[krow * kF32VPitch + 32 * b + col];
-                o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, s[r], o[b], 0, 0, 0);
-            }
-        }
+            for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
     }
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (q_ok && partial_out) {   // (O, max, sum) of this key range, merged by k_attn_merge
@@ -362,11 +455,6 @@ __device__ inline float max_across_halves(float x) {
     "v200", "v201", "v202", "v203", "v204", "v205", "v206", "v207", "v208", "v209", "v210", "v211", \
     "v212", "v213", "v214", "v215", "v216", "v217", "v218", "v219", "v220", "v221", "v222", "v223", \
     "v244", "v245", "v246"
-
-#define WK_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-// typed LDS pointer from a 32-bit LDS byte address
-#define WK_LDS_AT(T, addr) ((__attribute__((address_space(3))) T *)(size_t)(addr))
-#define WK_GLB(p) ((const __attribute__((address_space(1))) void *)(p))
 
 // IN_PLACE: the window is a list of segments (the native rows, then each retrieved chunk where the store
 // keeps it) instead of one array.  Tiles never straddle segments: a segment's last tile may be partial and
@@ -1109,6 +1197,8 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
     if (q_ok && g == 0) *out = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
 
+// Bound by its reads of the partial results (516 bytes per row and split), with the loads of four splits in flight: 6 us
+// for 9 splits of 3,520 rows, where one split at a time took 9 us.
 // Merge of the key-range splits: O = sum_s 2^(m_s - m) O_s / sum_s 2^(m_s - m) l_s, m = max_s m_s.
 // 16 lanes per query row, 8 features each; fixed summation order.
 template <int DT>
@@ -1117,19 +1207,38 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
     const int sub = threadIdx.x % 16;
     const size_t rows = (size_t)a.H * a.q_rows;
     if (row >= rows) return;
+    // four splits' loads are in flight at a time (a split past the last one repeats it with weight 0, as an empty split
+    // has: its sums were written as zeros)
+    constexpr int kBatch = 4;
+    const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + row;
     float m = -INFINITY;
-    for (int s = 0; s < a.splits; ++s) m = fmaxf(m, a.part_ml[((size_t)s * rows + row) * 2]);
+    for (int s0 = 0; s0 < a.splits; s0 += kBatch) {
+        float ms[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) ms[u] = ml[min(s0 + u, a.splits - 1) * rows].x;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) m = fmaxf(m, ms[u]);
+    }
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     float l = 0.f;
-    for (int s = 0; s < a.splits; ++s) {
-        const float ms = a.part_ml[((size_t)s * rows + row) * 2];
-        if (ms == -INFINITY) continue;   // empty split
-        const float w = __builtin_amdgcn_exp2f(ms - m);
-        l = fmaf(w, a.part_ml[((size_t)s * rows + row) * 2 + 1], l);
-        const float4 *po = reinterpret_cast<const float4 *>(a.part_o + ((size_t)s * rows + row) * WK_D) + 2 * sub;
-        const float4 x = po[0], y = po[1];
-        acc[0] = fmaf(w, x.x, acc[0]); acc[1] = fmaf(w, x.y, acc[1]); acc[2] = fmaf(w, x.z, acc[2]); acc[3] = fmaf(w, x.w, acc[3]);
-        acc[4] = fmaf(w, y.x, acc[4]); acc[5] = fmaf(w, y.y, acc[5]); acc[6] = fmaf(w, y.z, acc[6]); acc[7] = fmaf(w, y.w, acc[7]);
+    for (int s0 = 0; s0 < a.splits; s0 += kBatch) {
+        float2 t[kBatch];
+        float4 x[kBatch], y[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const size_t at = min(s0 + u, a.splits - 1) * rows;
+            t[u] = ml[at];
+            const float4 *po = reinterpret_cast<const float4 *>(a.part_o + (at + row) * WK_D) + 2 * sub;
+            x[u] = po[0];
+            y[u] = po[1];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const float w = s0 + u < a.splits && t[u].x > -INFINITY ? __builtin_amdgcn_exp2f(t[u].x - m) : 0.f;
+            l = fmaf(w, t[u].y, l);
+            acc[0] = fmaf(w, x[u].x, acc[0]); acc[1] = fmaf(w, x[u].y, acc[1]); acc[2] = fmaf(w, x[u].z, acc[2]); acc[3] = fmaf(w, x[u].w, acc[3]);
+            acc[4] = fmaf(w, y[u].x, acc[4]); acc[5] = fmaf(w, y[u].y, acc[5]); acc[6] = fmaf(w, y[u].z, acc[6]); acc[7] = fmaf(w, y[u].w, acc[7]);
+        }
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if constexpr (DT == WK_BF16) {
@@ -1218,12 +1327,22 @@ int table_kg(const SubTable &t, long long H) {
     return best;
 }
 
-// fp32 kernel: four of its workgroups fit a compute unit, so up to 1024 are resident; the smallest split
-// count that reaches that, at most 16 and leaving at least 4 tiles of 32 keys per split.
-int choose_splits_f32(long long items, int n_tiles) {
-    int s = 1;
-    while (s < kMaxSplits && items * s < 1024 && n_tiles / (s + 1) >= 4) ++s;
-    return s;
+// fp32: one workgroup fits a compute unit.  The split count with the cheapest rounds of 256 workgroups, a pair of tiles
+// costing 7.9 us, a workgroup's fill and drain 5 us, the merge a launch and its traffic; at least 2 pairs per split.
+int choose_splits_f32(long long H, long long N_q, int n_tiles) {
+    const long long items = H * ((N_q + kF32Waves * 32 - 1) / (kF32Waves * 32));
+    int best = 1;
+    double best_us = 0;
+    for (int s = 1; s <= kMaxSplits && (s == 1 || n_tiles >= 4 * s); ++s) {
+        const int pairs = ((n_tiles + s - 1) / s + 1) / 2;
+        double us = (double)((items * s + 255) / 256) * (7.9 * pairs + 5);
+        if (s > 1) us += 5 + s * (double)(H * N_q) * 520.0 / 4e6;
+        if (s == 1 || us < best_us) {
+            best = s;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 size_t split_workspace_bytes(int H, int N_q, int splits) {
@@ -1231,7 +1350,7 @@ size_t split_workspace_bytes(int H, int N_q, int splits) {
     return wk::align_up(rows * WK_D * sizeof(float), 256) + wk::align_up(rows * 2 * sizeof(float), 256);
 }
 
-// k_attn_bf16 uses more than the default 64 KB of dynamic LDS: raise its limit once per device and
+// k_attn_bf16 and k_attn_f32 use more than the default 64 KB of dynamic LDS: raise its limit once per device and
 // process (not a stream operation, so a first call under graph capture is fine too).
 wk_status allow_large_lds() {
     static std::atomic<uint64_t> done{0};
@@ -1248,7 +1367,11 @@ wk_status allow_large_lds() {
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, false, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, false, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess)
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_f32<false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kF32Lds) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_f32<true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kF32Lds) != hipSuccess)
             return WK_ERR_HIP;
         wk::mark_device(done, dev);
     }
@@ -1320,10 +1443,12 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
     a.v_table = nullptr; a.ids = nullptr; a.n_ids = nullptr; a.R_max = 0; a.store_M = 0; a.max_tok = 0;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
     if (dtype == WK_F32) {
+        const wk_status lds_rc = allow_large_lds();
+        if (lds_rc != WK_OK) return lds_rc;
         const int q_per_wg = kF32Waves * 32;
         a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
         const long long items1 = (long long)H * a.n_qtiles;
-        a.splits = O ? choose_splits_f32(items1, (N_kv + kF32Keys - 1) / kF32Keys) : 1;
+        a.splits = O ? choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys) : 1;
         if (a.splits > 1 && (!workspace || workspace_bytes < split_workspace_bytes(H, N_q, a.splits) ||
                              reinterpret_cast<uintptr_t>(workspace) % 256 != 0))
             a.splits = 1;
@@ -1333,7 +1458,7 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         const long long items = items1 * a.splits;
         if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
         a.per_xcd = (int)((items + kXcds - 1) / kXcds);
-        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Waves * 64), 0, st, a, SubTable{});
+        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
         WK_LAUNCH_CHECK();
         if (a.splits > 1) {
             const size_t rows = (size_t)H * N_q;
@@ -1357,15 +1482,15 @@ namespace {
 // key-range splits, no merge.
 wk_status launch_plain(AttnArgs a, int dtype, hipStream_t st) {
     a.splits = 1;
+    const wk_status rc = allow_large_lds();
+    if (rc != WK_OK) return rc;
     if (dtype == WK_F32) {
         a.n_qtiles = (a.N_q + kF32Waves * 32 - 1) / (kF32Waves * 32);
         a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
-        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Waves * 64), 0, st, a, SubTable{});
+        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
     } else {
         a.n_qtiles = (a.N_q + 255) / 256;
         a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
-        const wk_status rc = allow_large_lds();
-        if (rc != WK_OK) return rc;
         hipLaunchKernelGGL((k_attn_bf16<1, false, false>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a,
                            SubTable{});
     }
@@ -1445,11 +1570,11 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
         if ((long long)H * t.per_head + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
         g.per_xcd = (H * t.per_head + kXcds - 1) / kXcds;
         g.n_qtiles = 0;
+        const wk_status lrc = allow_large_lds();
+        if (lrc != WK_OK) return lrc;
         if (dtype == WK_F32) {
-            hipLaunchKernelGGL(k_attn_f32<true>, dim3(g.per_xcd * kXcds), dim3(kF32Waves * 64), 0, st, g, t);
+            hipLaunchKernelGGL(k_attn_f32<true>, dim3(g.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, g, t);
         } else {
-            const wk_status lrc = allow_large_lds();
-            if (lrc != WK_OK) return lrc;
             if (kg == 1)
                 hipLaunchKernelGGL((k_attn_bf16<1, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytes, st, g, t);
             else
@@ -1519,9 +1644,11 @@ extern "C" wk_status wk_chunk_lse(const wk_store_desc *store, const void *Q, int
     const long long items = (long long)store->M * store->H * ((N_q + q_per_wg - 1) / q_per_wg);
     if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
     if (store->dtype == WK_F32) {
+        const wk_status rc = allow_large_lds();
+        if (rc != WK_OK) return rc;
         a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
         a.per_xcd = (int)((items + kXcds - 1) / kXcds);
-        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Waves * 64), 0, st, a, SubTable{});
+        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
         WK_LAUNCH_CHECK();
         return WK_OK;
     }
@@ -1588,8 +1715,7 @@ extern "C" size_t wk_attention_workspace_bytes(int32_t H, int32_t N_q, int32_t N
     if (H < 1 || N_q < 1 || N_kv < 1 || (dtype != WK_BF16 && dtype != WK_F32)) return 0;
     if ((long long)H * ((N_q + 31) / 32) > 0x7fffffffLL / kMaxSplits) return 0;
     if (dtype == WK_F32) {
-        const int s = choose_splits_f32((long long)H * ((N_q + kF32Waves * 32 - 1) / (kF32Waves * 32)),
-                                        (N_kv + kF32Keys - 1) / kF32Keys);
+        const int s = choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys);
         return s > 1 ? split_workspace_bytes(H, N_q, s) : 0;
     }
     const LaunchPlan plan = plan_bf16(H, N_q, N_kv, true);

@@ -6,9 +6,13 @@ import torch
 
 import oracle
 import paper_2605_22718_amd as wk
-from wkt import assert_attention_close_bf16, dev
+from wkt import ATT_MAX_ABS_F32, assert_attention_close_bf16, attention_errors, dev
 
 pytestmark = pytest.mark.gpu
+
+
+def _assert_close_f32(O, lse, ref, ref_lse, tol=ATT_MAX_ABS_F32):
+    assert attention_errors(O, ref)[0] <= tol and np.abs(lse.cpu().numpy() - ref_lse).max() <= 1e-4
 
 
 def _inputs(H, N_q, N_kv, seed, rising=False):
@@ -60,6 +64,37 @@ def test_split_tile_pairs(H, N_q, N_kv, n_dev):
                     n_kv_dev=None if n_dev is None else torch.tensor([n_dev], dtype=torch.int32, device=d))
     ref, ref_lse = oracle.attention(Q, K, V, N_kv=n_dev or N_kv, want_lse=True)
     assert_attention_close_bf16(O, ref, lse, ref_lse)
+
+
+# fp32, pairs of 32-key tiles: one tile (the second wave group has none), one key, a partial first and second tile of a
+# pair, odd and even counts; queries that leave waves of a workgroup without one
+@pytest.mark.parametrize("N_q", [1, 32, 33, 128, 161])
+@pytest.mark.parametrize("N_kv", [1, 31, 32, 33, 64, 65, 95, 97, 128, 161])
+def test_tile_pairs_f32(N_q, N_kv):
+    Q, K, V = (x.float() for x in _inputs(2, N_q, N_kv, seed=N_q * 1000 + N_kv))
+    d = dev()
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    only = torch.empty_like(lse)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse)
+    wk.wk_attention(Q.to(d), K.to(d), None, None, only)
+    ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
+    _assert_close_f32(O, lse, ref, ref_lse)
+    assert torch.equal(lse, only)
+
+
+# 2e-4: logits six times as large, see the large-logit case of test_gpu_attention.py
+@pytest.mark.parametrize("rising,tol", [(False, ATT_MAX_ABS_F32), (True, 2e-4)])
+@pytest.mark.parametrize("H,N_q,N_kv,n_dev", [(2, 300, 1500, None), (1, 65, 3001, 517), (3, 129, 2000, 40)])
+def test_split_tile_pairs_f32(H, N_q, N_kv, n_dev, rising, tol):
+    Q, K, V = (x.float() for x in _inputs(H, N_q, N_kv, seed=N_kv + N_q, rising=rising))
+    d = dev()
+    n = wk.wk_attention_workspace_bytes(H, N_q, N_kv, wk.WK_F32)
+    assert n > 0
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse, workspace=torch.empty(n, dtype=torch.uint8, device=d),
+                    n_kv_dev=None if n_dev is None else torch.tensor([n_dev], dtype=torch.int32, device=d))
+    ref, ref_lse = oracle.attention(Q, K, V, N_kv=n_dev or N_kv, want_lse=True)
+    _assert_close_f32(O, lse, ref, ref_lse, tol)
 
 
 # in place: odd and even totals of tiles, segments that end inside a tile (the pair then spans two segments), one tile in all
