@@ -85,7 +85,9 @@ __global__ __launch_bounds__(256) void k_rows_normsq(const char *__restrict__ sr
 // busy); partial sums meet in a fixed order in k_anchor_mean_finish, so the result is deterministic.
 constexpr int kMeanSplits = 16;
 
-template <int DT>
+// OWN_NORM: a token's vector is one head's row (per-head lists), whose norm the row itself gives: no pass for the norms
+// before this one (24 heads x 1,013 tokens: 3.8 us).
+template <int DT, bool OWN_NORM>
 __global__ __launch_bounds__(256) void k_anchor_mean_partial(const char *__restrict__ A, CompressDims p,
                                                              const double *__restrict__ nsq,
                                                              double *__restrict__ partial) {
@@ -99,13 +101,29 @@ __global__ __launch_bounds__(256) void k_anchor_mean_partial(const char *__restr
     const int per = (p.T + kMeanSplits - 1) / kMeanSplits;
     const int i_end = min(p.T, (sp + 1) * per);
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = sp * per + slot; i < i_end; i += kRowsPerBlock) {
-        float v[8];
-        load_row8<DT>(base + (size_t)i * row_bytes, sub, v);
-        const double n2 = nq[i];
-        const double rn = n2 < 1e-60 ? 0.0 : 1.0 / sqrt(n2);  // zero-norm key: its cosines are 0
+    constexpr int kRows = 4;   // rows (and norms) requested before the first is used
+    for (int i0 = sp * per + slot; i0 < i_end; i0 += kRows * kRowsPerBlock) {
+        float v[kRows][8];
+        double n2[kRows];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += (double)v[e] * rn;
+        for (int u = 0; u < kRows; ++u) {
+            const int i = min(i0 + u * kRowsPerBlock, i_end - 1);
+            load_row8<DT>(base + (size_t)i * row_bytes, sub, v[u]);
+            if constexpr (!OWN_NORM) n2[u] = nq[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            if constexpr (OWN_NORM) {
+                float s = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s = fmaf(v[u][e], v[u][e], s);
+                n2[u] = wk::row_group_sum((double)s);
+            }
+            // zero-norm key: its cosines are 0 (as are those of the repeated last row)
+            const double rn = n2[u] < 1e-60 || i0 + u * kRowsPerBlock >= i_end ? 0.0 : 1.0 / sqrt(n2[u]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += (double)v[u][e] * rn;
+        }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[slot][sub * 8 + e] = acc[e];
@@ -571,6 +589,10 @@ __device__ inline uint64_t order_key(double s) {
     return (u >> 63) ? ~u : (u | 0x8000000000000000ull);  // unsigned order == numeric order
 }
 
+__device__ inline double key_score(uint64_t key) {   // the score of an order key
+    return __longlong_as_double((long long)(key >> 63 ? key & 0x7fffffffffffffffull : ~key));
+}
+
 constexpr int kSelThreads = 1024;
 
 // exclusive scan of one int per thread over the block; total = sum over the block
@@ -596,7 +618,7 @@ __device__ inline int block_excl_scan(int v, int *wsum /*[kSelThreads/64]*/, int
     return off + x - v;
 }
 
-// One block per list.  Radix-select (up to 8 passes of 8 bits, from the top, over order-preserving
+// Lists longer than kSelHeld (k_select_held, below, takes the others).  One block per list.  Radix-select (up to 8 passes of 8 bits, from the top, over order-preserving
 // 64-bit keys) finds the n_keep-th smallest score tau; then tokens with score < tau, plus the first
 // few (by index) with score == tau, are written in ascending index order via block scans.  The passes
 // stop as soon as every key that shares tau's leading digits is kept anyway (for fp64 scores usually
@@ -690,6 +712,163 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const double *__restrict
         if (keep && pos < p.n_keep) out[p.first_cand + pos] = p.first_cand + j;
         eq_base += eq_tot;
         out_base += keep_tot;
+    }
+}
+
+// Lists of up to kSelHeld keys: a thread holds four of them in registers (j = thread, thread + 1024, ...).  One block per
+// list, bound by its chain of barriers, so there are few: the keys still in question are dealt to 1024 buckets over their
+// range -- by the scores themselves first, which are spread evenly where their bit patterns are not -- and all but those
+// of the bucket that holds the n_keep-th are settled at once.  When a wave's worth is left (for scores of real chunks after
+// one round) they are ranked by comparing each with each.  Kept tokens leave as one bit per candidate, whose prefix
+// counts give the places.  A list of 3,120 candidates: 9.5 us, with the byte-wise passes and ordered block scans of k_select
+// 12.6 us; 24 lists of 2,026: 8.3 and 9.8 us.  (Counting, for every key, the keys before it -- 64 keys per
+// workgroup, comparing all pairs -- takes 12 and 22 us: 64-bit comparisons are slow.)
+constexpr int kSelHeld = 4 * kSelThreads;
+
+__global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__restrict__ scores, CompressDims p,
+                                                             int32_t *__restrict__ kept_idx) {
+    constexpr int kWaves = kSelThreads / 64, kEach = kSelHeld / kSelThreads, kList = 64;
+    __shared__ int hist[kSelThreads];
+    __shared__ uint64_t w_lo[kWaves], w_hi[kWaves], list_key[kList], words[kSelHeld / 64];
+    __shared__ int list_j[kList], wsum[kWaves];
+    __shared__ int s_bucket, s_below, s_count, s_listed;
+    const int list = blockIdx.x, n = p.n_cand, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const double *s = scores + (size_t)list * n;
+    int32_t *out = kept_idx + (size_t)list * p.n_out;
+    for (int i = tid; i < p.first_cand; i += kSelThreads) out[i] = i;  // anchor tokens, kept in full
+    if (p.n_keep == 0) return;
+    double v[kEach];
+    uint64_t key[kEach];
+    bool open[kEach], kept[kEach];   // still in question; settled as kept
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) {
+        const int j = tid + u * kSelThreads;
+        v[u] = s[min(j, n - 1)];
+        key[u] = order_key(v[u]);
+        open[u] = j < n;
+        kept[u] = false;
+    }
+    int k = p.n_keep, left = n;   // of the keys in question, the k lowest are kept
+    for (int round = 0; left > k; ++round) {
+        uint64_t lo = ~0ull, hi = 0;
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            if (open[u]) {
+                lo = key[u] < lo ? key[u] : lo;
+                hi = key[u] > hi ? key[u] : hi;
+            }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            const uint64_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+            lo = a < lo ? a : lo;
+            hi = b > hi ? b : hi;
+        }
+        hist[tid] = 0;
+        if (lane == 0) {
+            w_lo[wave] = lo;
+            w_hi[wave] = hi;
+        }
+        if (tid == 0) s_listed = 0;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            lo = w_lo[w] < lo ? w_lo[w] : lo;
+            hi = w_hi[w] > hi ? w_hi[w] : hi;
+        }
+        if (lo == hi) {   // equal scores: the lowest indices are kept
+            int base = 0;
+#pragma unroll
+            for (int u = 0; u < kEach; ++u) {
+                int total;
+                const int rank = base + block_excl_scan(open[u] ? 1 : 0, wsum, total);
+                if (open[u] && rank < k) kept[u] = true;
+                open[u] = false;
+                base += total;
+            }
+            k = 0;
+            break;
+        }
+        // bucket of a key: monotone in the key, 0 .. 1023
+        const double v_lo = key_score(lo), range = key_score(hi) - v_lo;
+        const bool by_score = round == 0 && range < INFINITY && range > 1e-290;   // (no NaN: comparisons with it fail)
+        const double per = by_score ? 1023.0 / range : 0.0;
+        const int shift = max(0, 54 - __clzll(hi - lo));
+        int bucket[kEach];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            bucket[u] = by_score ? min((int)((v[u] - v_lo) * per), kSelThreads - 1) : (int)((key[u] - lo) >> shift);
+            if (open[u]) atomicAdd(&hist[bucket[u]], 1);
+        }
+        __syncthreads();
+        const int count = hist[tid];
+        int incl = count;   // inclusive prefix sums of the buckets, first one >= k
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) incl += w < wave ? wsum[w] : 0;
+        if (incl >= k && incl - count < k) {   // exactly one bucket satisfies this
+            s_bucket = tid;
+            s_below = incl - count;
+            s_count = count;
+        }
+        __syncthreads();
+        k -= s_below;
+        left = s_count;
+        const int at = s_bucket;
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            if (open[u] && bucket[u] != at) {
+                kept[u] = bucket[u] < at;
+                open[u] = false;
+            }
+        if (left <= kList && left > k) {
+            int slot[kEach];
+#pragma unroll
+            for (int u = 0; u < kEach; ++u)
+                if (open[u]) {
+                    slot[u] = atomicAdd(&s_listed, 1);
+                    list_key[slot[u]] = key[u];
+                    list_j[slot[u]] = tid + u * kSelThreads;
+                }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kEach; ++u)
+                if (open[u]) {
+                    int rank = 0;
+                    for (int i = 0; i < left; ++i)
+                        rank += list_key[i] < key[u] || (list_key[i] == key[u] && list_j[i] < tid + u * kSelThreads);
+                    kept[u] = rank < k;
+                    open[u] = false;
+                }
+            k = 0;
+            break;
+        }
+        __syncthreads();   // the shared results have been read
+    }
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) {
+        kept[u] |= open[u];   // what is left when all of it is kept
+        const uint64_t bits = __ballot(kept[u]);
+        if (lane == 0) words[wave + u * kWaves] = bits;
+    }
+    __syncthreads();
+    // kept tokens before each 64 candidates: a lane per word
+    int incl = __popcll(words[lane]);
+    const int ones = incl;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+    }
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) {
+        const int w = wave + u * kWaves, pos = __shfl(incl - ones, w) + __popcll(words[w] & ((1ull << lane) - 1));
+        if (kept[u]) out[p.first_cand + pos] = p.first_cand + tid + u * kSelThreads;
     }
 }
 
@@ -866,7 +1045,8 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
         const bool split = p.hg >= 4;
         const int rows_pb = split ? kRowsPerBlock / 4 : kRowsPerBlock;
         const FusePlan fuse = fuse_plan(d, p);
-        if (!fuse.use) {   // squared norms of the anchor tokens, a pass of their own
+        const bool own_norm = p.hg == 1 && d->score_algo == WK_SCORE_FACTORED;
+        if (!fuse.use && !own_norm) {   // squared norms of the anchor tokens, a pass of their own
             dim3 g1((p.T + rows_pb - 1) / rows_pb, p.G, d->batch);
             if (split) hipLaunchKernelGGL((k_rows_normsq<DT, 4>), g1, dim3(256), 0, st, A, p, p.a_rows, 0, p.T, nsq);
             else hipLaunchKernelGGL((k_rows_normsq<DT, 1>), g1, dim3(256), 0, st, A, p, p.a_rows, 0, p.T, nsq);
@@ -918,8 +1098,9 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
                 WK_LAUNCH_CHECK();
             } else {
                 double *mean_partial = reinterpret_cast<double *>(wsp + ws.mean_partial);
-                hipLaunchKernelGGL(k_anchor_mean_partial<DT>, dim3(p.H, kMeanSplits, d->batch), dim3(256), 0, st, A, p,
-                                   nsq, mean_partial);
+                const dim3 gm(p.H, kMeanSplits, d->batch);
+                if (own_norm) hipLaunchKernelGGL((k_anchor_mean_partial<DT, true>), gm, dim3(256), 0, st, A, p, nsq, mean_partial);
+                else hipLaunchKernelGGL((k_anchor_mean_partial<DT, false>), gm, dim3(256), 0, st, A, p, nsq, mean_partial);
                 WK_LAUNCH_CHECK();
                 hipLaunchKernelGGL(k_anchor_mean_finish, dim3(p.H, d->batch), dim3(WK_D), 0, st, mean_partial, p, mean);
                 WK_LAUNCH_CHECK();
@@ -930,7 +1111,10 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
             WK_LAUNCH_CHECK();
         }
     }
-    hipLaunchKernelGGL(k_select, dim3(d->batch * p.G), dim3(kSelThreads), 0, st, scores, p, kept);
+    if (p.n_cand > 0 && p.n_cand <= kSelHeld)
+        hipLaunchKernelGGL(k_select_held, dim3(d->batch * p.G), dim3(kSelThreads), 0, st, scores, p, kept);
+    else
+        hipLaunchKernelGGL(k_select, dim3(d->batch * p.G), dim3(kSelThreads), 0, st, scores, p, kept);
     WK_LAUNCH_CHECK();
     dim3 g5((p.n_out + kRowsPerBlock - 1) / kRowsPerBlock, p.H, d->batch);
     hipLaunchKernelGGL(k_compact<DT>, g5, dim3(256), 0, st, Kc, reinterpret_cast<const char *>(V), p, kept,

@@ -149,6 +149,42 @@ def test_gemm_scoring_small_chunks(head_mode, H, T, F):
         _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], head_mode, rho, kind)
 
 
+# list lengths at the edges of a wave, of a round of threads and of the kernel that holds a list in registers
+@pytest.mark.parametrize("T,F", [(1, 2), (63, 2), (65, 2), (1025, 2), (2048, 3), (2049, 3)])
+def test_selection_list_lengths(T, F):
+    cfg = ws.get_config(1).with_(H=1, T=T, F=F)
+    K, V, _ = ws.make_chunk(cfg, 8)
+    for rho in (0.0, 0.3, 0.5, 1.0):
+        gi, gK, gV, gs, _ = _gpu_compress(cfg, K, V, None, rho=rho, ratio_kind=wk.WK_RATIO_NONANCHOR)
+        _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], wk.WK_HEADS_SHARED, float(np.float32(rho)), wk.WK_RATIO_NONANCHOR)
+
+
+# equal scores by the hundred on either side of the cut, all scores equal, all zero, and scores of very different size
+@pytest.mark.parametrize("kind", ["two", "one", "zero", "scales"])
+def test_selection_of_crowded_scores(kind):
+    cfg = ws.get_config(1).with_(H=2, T=300, F=3)
+    K, V, _ = ws.make_chunk(cfg, 9)
+    T = cfg.T
+    if kind == "two":
+        K[:, T + 100:T + 330] = K[:, T + 7:T + 8]
+        K[:, T + 330:] = K[:, T + 8:T + 9]
+    elif kind == "one":
+        K[:, T:] = K[:, T + 7:T + 8]
+    elif kind == "zero":
+        K[:, T:] = 0
+    else:   # a candidate orthogonal to the mean but for one feature of decreasing size: scores over twenty orders of magnitude
+        K[:] = 0
+        K[:, :T, 0] = 1
+        K[:, T:, 1] = 1
+        K[:, T:, 0] = (2.0 ** -(torch.arange(2 * T) % 67).float()).to(K.dtype)
+    for rho in (0.1, 0.5, 0.9):
+        gi, gK, gV, gs, n_out = _gpu_compress(cfg, K, V, None, rho=rho, ratio_kind=wk.WK_RATIO_NONANCHOR)
+        order = np.lexsort((np.arange(2 * T), gs[0, 0]))[:n_out - T]
+        np.testing.assert_array_equal(gi[0, 0], np.concatenate([np.arange(T), T + np.sort(order)]))
+        if kind != "scales":   # (the oracle's scores differ in the last digits, which decide between neighbours there)
+            _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], wk.WK_HEADS_SHARED, float(np.float32(rho)), wk.WK_RATIO_NONANCHOR)
+
+
 # 256 x 256 blocks: one row or candidate beyond a block, every count of 32-row groups in an edge block, anchor blocks past a
 # group of four, more than eight of them (a workgroup walks two), an odd number of heads in unequal ranges
 @pytest.mark.parametrize("H,T,F", [(1, 257, 2), (3, 352, 2), (2, 450, 3), (7, 224, 3), (1, 1100, 2), (1, 2081, 2)])
