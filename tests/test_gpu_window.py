@@ -195,3 +195,28 @@ def test_slot_refresh_at_the_lingbot_window_size():
             r0 = cfg.n_native + s * n_out
             assert torch.equal(bits(Kw[:, r0:r0 + n_out]), bits(Ks[c])) and torch.equal(bits(Vw[:, r0:r0 + n_out]), bits(Vs[c])), s
         assert torch.equal(bits(Kw[:, :cfg.n_native]), bits(Kn)) and torch.equal(bits(Vw[:, :cfg.n_native]), bits(Vn))
+
+
+# a copy that ends inside a block, by grids that keep eight, four, two and one block per workgroup under way
+@pytest.mark.parametrize("max_wg", [1, 7, 40, 100, 0])
+@pytest.mark.parametrize("dtype,pinned", [(torch.bfloat16, True), (torch.bfloat16, False), (torch.float32, False)])
+def test_slot_refresh_grids(dtype, pinned, max_wg):
+    d, H, slot_tokens, M, R, n_native = dev(), 5, 1001, 5, 3, 70
+    place = (lambda t: t.pin_memory()) if pinned else (lambda t: t.to(d))
+    Ks = [place(_pattern(H, slot_tokens, 128, c, 0, dtype)) for c in range(M)]
+    Vs = [place(_pattern(H, slot_tokens, 128, c + 50, 0, dtype)) for c in range(M)]
+    store = wk.Store(Ks, Vs, d)
+    cap = n_native + R * slot_tokens + 9
+    Kw, Vw = (torch.full((H, cap, 128), x, dtype=dtype, device=d) for x in (251.0, 253.0))
+    slot_ids = torch.full((R,), -1, dtype=torch.int32, device=d)
+    n_win, n_f = (torch.zeros(1, dtype=torch.int32, device=d) for _ in range(2))
+    wsb = torch.empty(wk.wk_window_update_workspace_bytes(R), dtype=torch.uint8, device=d)
+    for wanted, fetched in (([3, 0, 4], 3), ([4, 1, 3], 1), ([1, 2, 0], 2)):
+        wk.wk_window_update(store.desc, torch.tensor(wanted, dtype=torch.int32, device=d), None, R, slot_tokens, slot_ids, n_native, Kw, Vw,
+                            cap, n_win, n_f, wsb, max_wg)
+        assert int(n_f.item()) == fetched
+        slots = slot_ids.cpu().tolist()
+        assert sorted(slots) == sorted(wanted)
+        for win, chunks, fill in ((Kw.cpu(), Ks, 251.0), (Vw.cpu(), Vs, 253.0)):
+            assert torch.equal(win[:, n_native:n_native + R * slot_tokens], torch.cat([chunks[c].cpu() for c in slots], 1))
+            assert (win[:, :n_native] == fill).all() and (win[:, n_native + R * slot_tokens:] == fill).all()
