@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kQThreads) void k_query_mass_partial(const float *_
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < kQThreads / 64; ++w) s += acc[w][c];
-        partial[(size_t)blockIdx.x * M + c] = s;
+        partial[(size_t)c * gridDim.x + blockIdx.x] = s;   // (k_query_topk reads a chunk's sums side by side)
     }
 }
 
@@ -234,10 +234,18 @@ __global__ __launch_bounds__(kThreads) void k_query_topk(const double *__restric
         if (mass_out) mass_out[r] = -INFINITY;
     }
     if (M == 0) return;
-    // one wave per chunk: lanes sum interleaved blocks, then a fixed-shape tree over the lanes
+    // one wave per chunk: lanes sum interleaved blocks, then a fixed-shape tree over the lanes.  Up to 16 blocks per lane
+    // (1024 in all), requested eight at a time: 120 chunks of 732 blocks 16 us, 36 us one by one and M doubles apart.
     for (int c = tid >> 6; c < M; c += kThreads / 64) {
+        const double *mine = partial + (size_t)c * n_blocks;
         double s = 0.0;
-        for (int b = tid & 63; b < n_blocks; b += 64) s += partial[(size_t)b * M + c];
+        for (int b = tid & 63; b < n_blocks; b += 8 * 64) {
+            double t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = b + u * 64 < n_blocks ? mine[b + u * 64] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += t[u];
+        }
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
         s /= (double)n_rows;
