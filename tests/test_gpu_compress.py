@@ -185,6 +185,21 @@ def test_selection_of_crowded_scores(kind):
             _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], wk.WK_HEADS_SHARED, float(np.float32(rho)), wk.WK_RATIO_NONANCHOR)
 
 
+def test_compaction_past_the_caches():
+    """A batch larger than the Infinity Cache: its rows are copied past the caches, bit for bit, by the indices returned."""
+    H, T, F, batch, d = 40, 1560, 3, 11, dev()
+    desc = wk.make_compress_desc(H, T, F, wk.WK_BF16, 0.5, batch=batch, ratio_kind=wk.WK_RATIO_NONANCHOR)
+    n_out, _ = wk.wk_keep_count(desc.rho, desc.ratio_kind, desc.anchor_mode, F, T)
+    g = torch.Generator(device=d).manual_seed(3)
+    K, V = (torch.randn((batch, H, F * T, 128), generator=g, device=d, dtype=torch.bfloat16) for _ in range(2))
+    Ko, Vo = (torch.empty((batch, H, n_out, 128), dtype=torch.bfloat16, device=d) for _ in range(2))
+    idx = torch.empty((batch, 1, n_out), dtype=torch.int32, device=d)
+    wk.wk_compress_chunk(desc, K, V, None, idx, Ko, Vo, torch.empty(wk.wk_compress_workspace_bytes(desc), dtype=torch.uint8, device=d))
+    for b in range(batch):
+        rows = idx[b, 0].long()
+        assert torch.equal(Ko[b], K[b][:, rows]) and torch.equal(Vo[b], V[b][:, rows])
+
+
 # 256 x 256 blocks: one row or candidate beyond a block, every count of 32-row groups in an edge block, anchor blocks past a
 # group of four, more than eight of them (a workgroup walks two), an odd number of heads in unequal ranges
 @pytest.mark.parametrize("H,T,F", [(1, 257, 2), (3, 352, 2), (2, 450, 3), (7, 224, 3), (1, 1100, 2), (1, 2081, 2)])
