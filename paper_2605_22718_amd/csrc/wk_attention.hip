@@ -1207,8 +1207,8 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
     const int sub = threadIdx.x % 16;
     const size_t rows = (size_t)a.H * a.q_rows;
     if (row >= rows) return;
-    // four splits' loads are in flight at a time (a split past the last one repeats it with weight 0, as an empty split
-    // has: its sums were written as zeros)
+    // four splits' loads are in flight at a time (a split past the last one repeats its loads and is left out of the sums, as
+    // is a split with no weight at all: an infinity or NaN times a weight of zero would not be zero)
     constexpr int kBatch = 4;
     const float2 *ml = reinterpret_cast<const float2 *>(a.part_ml) + row;
     float m = -INFINITY;
@@ -1234,7 +1234,8 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const float w = s0 + u < a.splits && t[u].x > -INFINITY ? __builtin_amdgcn_exp2f(t[u].x - m) : 0.f;
+            if (s0 + u >= a.splits || t[u].x == -INFINITY) continue;
+            const float w = __builtin_amdgcn_exp2f(t[u].x - m);
             l = fmaf(w, t[u].y, l);
             acc[0] = fmaf(w, x[u].x, acc[0]); acc[1] = fmaf(w, x[u].y, acc[1]); acc[2] = fmaf(w, x[u].z, acc[2]); acc[3] = fmaf(w, x[u].w, acc[3]);
             acc[4] = fmaf(w, y[u].x, acc[4]); acc[5] = fmaf(w, y[u].y, acc[5]); acc[6] = fmaf(w, y[u].z, acc[6]); acc[7] = fmaf(w, y[u].w, acc[7]);
