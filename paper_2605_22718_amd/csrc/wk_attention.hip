@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
 #pragma unroll
     for (int b = 0; b < 4; ++b) v_rd[b] = lds0 + kF32Tile + 4 * g * 512 + (((8 * b + (col >> 2)) ^ (8 * g)) << 4) + (col & 3) * 4;
     // tile loads: wave qw of a group fills rows 8*qw .. 8*qw+7 of its tile, two rows per load; rows past the range clamp to
-    // its last one (those keys are masked)
+    // its last one (those keys are masked, their V rows cleared once they have landed)
     const int ld_row = 8 * qw + (lane >> 5), ld_slot = lane & 31;
     auto issue = [&](int pair) {
         char *dst = smem + (pair & 1) * kF32Stage + kg * (2 * kF32Tile) + qw * 4096;
@@ -277,10 +277,16 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
     // while the other multiplies
     if (kg == 0) __builtin_amdgcn_s_setprio(1);
     for (int j = 0; j < n_pairs; ++j) {
+        const int kt = kt0 + (2 * j + kg) * kF32Keys, stage = (j & 1) * kF32Stage;
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the pair has landed
+        if (with_o && kt + kF32Keys > kt1) {  // V rows past the range become zeros: the last row there may be infinite
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (kt + ld_row + 2 * i >= kt1)
+                    *reinterpret_cast<float4 *>(smem + stage + kg * (2 * kF32Tile) + qw * 4096 + kF32Tile + i * 1024 + lane * 16) = float4{0, 0, 0, 0};
+        }
         __syncthreads();                      // everyone's has, and the pair before is fully consumed
         if (j + 1 < n_pairs) issue(j + 1);
-        const int kt = kt0 + (2 * j + kg) * kF32Keys, stage = (j & 1) * kF32Stage;
         if (kt >= kt1 || idle) continue;      // an odd count of tiles leaves the second group without one
         // operands are read two groups of four products ahead, and the order is kept: left to itself the compiler reads each
         // one right before its product and waits for it

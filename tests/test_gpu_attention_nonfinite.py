@@ -61,3 +61,9 @@ def test_key_ranges_without_weight(H, N_q, N_kv, dtype):
     K[:, 100:, 0] = float("-inf")
     O, lse = _run(Q, K, V, split=True)
     _check(O, lse, Q, K[:, :100].contiguous(), V[:, :100].contiguous())
+
+
+# the rows that fill the last fp32 tile of a window
+@pytest.mark.parametrize("N_kv", [1, 31, 33, 95, 161])
+def test_infinite_value_in_the_last_row_f32(N_kv):
+    _check_infinite_value(*_inputs(2, 70, N_kv, torch.float32, N_kv), N_kv - 1, split=False)
