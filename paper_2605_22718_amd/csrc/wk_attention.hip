@@ -622,7 +622,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
     // All of this is wave-uniform scalar state.
     struct TileRef { const char *base; int row, len; };
     const char *cur_k = nullptr, *cur_v = nullptr;
-    int cur_len = 0, cur_row = 0, cur_seg = 0, cur_left = seg_tiles;
+    int cur_len = 0, cur_row = 0, cur_seg = 0;
     TileRef v_line[2] = {{nullptr, 0, 0}, {nullptr, 0, 0}};
     unsigned valid_line = 0;   // four entries of 8 bits, newest lowest: valid keys of a tile, capped at 64 (scalar registers are scarce here)
     if constexpr (IN_PLACE) {
@@ -652,10 +652,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
         issue_at(cur_k, cur_row, cur_len, k_src, dst);
         v_line[1] = v_line[0];
         v_line[0] = TileRef{cur_v, cur_row, cur_len};
-        unsigned valid = (unsigned)min(cur_len - cur_row, kKeys);   // 64: a full tile
-        // 0: past the list's last tile, where an odd count of tiles leaves the second wave group without one
-        if constexpr (KG == 2) valid = cur_left-- > 0 ? valid : 0u;
-        valid_line = (valid_line << 8) | valid;
+        valid_line = (valid_line << 8) | (unsigned)min(cur_len - cur_row, kKeys);   // 64: a full tile
         if (cur_row + kKeys < cur_len) {
             cur_row += kKeys;
         } else if (cur_seg + 1 < n_seg) {
@@ -945,14 +942,13 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
     // redo its max.
     auto last_tile = [&](const int POS, f32x16 (&s_cur)[2], float &l_sum) __attribute__((always_inline)) {
         const int kt = KG == 1 ? (t1 - 1) * kKeys : (t0 + 2 * n_steps + kg) * kKeys;
-        const int kt_end = min(n_kv, t1 * kKeys);   // (the second group's tile of an odd count lies behind it entirely)
-        if (!IN_PLACE && kt + kKeys > kt_end) {
+        if (!IN_PLACE && kt + kKeys > n_kv) {
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int key = kt + 32 * b + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (key >= kt_end) s_cur[b][r] = -INFINITY;
+                    if (key >= n_kv) s_cur[b][r] = -INFINITY;
                 }
             mt = tile_max(s_cur);
         }
@@ -973,7 +969,9 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
             l_run[1] = t;
         }
     }
-    last_tile(ring_pos(n_steps), s_a, l_run[0]);
+    // (an odd count of tiles leaves the second wave group without one: what lies behind the range -- the next range's rows, or
+    // the last row again -- has no part in this one)
+    if (KG == 1 || kg == 0 || (t1 - t0) % 2 == 0) last_tile(ring_pos(n_steps), s_a, l_run[0]);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // drain the clamped look-ahead loads before the LDS is released
 
     if constexpr (KG == 2) {

@@ -67,3 +67,24 @@ def test_key_ranges_without_weight(H, N_q, N_kv, dtype):
 @pytest.mark.parametrize("N_kv", [1, 31, 33, 95, 161])
 def test_infinite_value_in_the_last_row_f32(N_kv):
     _check_infinite_value(*_inputs(2, 70, N_kv, torch.float32, N_kv), N_kv - 1, split=False)
+
+
+# an odd count of whole tiles leaves the second wave group of a 128-query workgroup without one; in a split window the rows
+# behind its range are the next range's, whose values have their weight there alone
+@pytest.mark.parametrize("split,N_q,N_kv", [(False, 300, 64 * 21), (False, 300, 64 * 9), (True, 300, 64 * 47), (True, 64, 64 * 83)])
+def test_infinite_value_beside_an_odd_count_of_tiles(split, N_q, N_kv):
+    _check_infinite_value(*_inputs(2, N_q, N_kv, torch.bfloat16, N_kv), N_kv - 1, split=split)
+
+
+def test_infinite_value_beside_an_odd_count_of_tiles_in_place():
+    Q, K, V = _inputs(2, 200, 64 * 11, torch.bfloat16, 5)
+    V[:, -1, FEATURE] = float("inf")
+    d, cut = dev(), 64 * 6
+    store = wk.Store([K[:, cut:].contiguous().to(d)], [V[:, cut:].contiguous().to(d)])
+    O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
+    wk.wk_attention_in_place(Q.to(d), K[:, :cut].contiguous().to(d), V[:, :cut].contiguous().to(d), cut, store.desc,
+                             torch.zeros(1, dtype=torch.int32, device=d), None, 1, O, lse)
+    O, lse = O.cpu(), lse.cpu()
+    assert (O[..., FEATURE] == float("inf")).all()
+    O[..., FEATURE], V[..., FEATURE] = 0, 0
+    _check(O, lse, Q, K, V)
