@@ -14,6 +14,7 @@
 // after exp2 and rounding, exactly the B operand of the second product: which key an MFMA
 // "k slot" means is a free choice, as long as the V^T operand uses the same choice.
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -243,7 +244,9 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
     for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    // (finite: scores of -inf then have weight 0 also in tiles that hold nothing else, whichever wave group or key range
+    // begins with one)
+    float m_run = -FLT_MAX, l_run = 0.f;
 
     const char *Kh = win.K + (size_t)h * win.stride * 512;
     const char *Vh = a.V + (size_t)h * win.stride * 512;
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
 #pragma unroll
         for (int r = 0; r < 16; ++r) m_tile = fmaxf(m_tile, s[r]);
         m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 32));
-        const float m_new = fmaxf(m_run, m_tile);  // finite: every tile holds at least one valid key
+        const float m_new = fmaxf(m_run, m_tile);
         if (__any(m_new > m_run)) {                // otherwise the factor is 1
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             l_run *= alpha;
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
         }
         __syncthreads();
         if (kg == 1 || idle) return;
-        const float m_other = meet[64 * 64];   // -inf if the second group had no tile
+        const float m_other = meet[64 * 64];   // -FLT_MAX, with sums of 0, if the second group had no tile
         const float m_new = fmaxf(m_run, m_other);
         const float w0 = __builtin_amdgcn_exp2f(m_run - m_new), w1 = __builtin_amdgcn_exp2f(m_other - m_new);
         m_run = m_new;
@@ -707,7 +710,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
     for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
-    float m_run = -INFINITY;        // in scaled (log2) units
+    float m_run = -FLT_MAX;         // in scaled (log2) units; finite for the sake of scores of -inf, as in k_attn_f32
     float l_run[2] = {0.f, 0.f};    // row sums over the even and the odd tiles (KG == 2: this wave group's, and nothing)
     const float c_log2 = a.scale_log2;
 
@@ -867,7 +870,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
     __syncthreads();   // the first K tile (pair) has been read by every wave: step 0 may load into its slot
 
     // both wave groups start from the maximum of the first tile, as a wave that walks every tile does
-    if constexpr (KG == 2) m_run = *m_first;
+    if constexpr (KG == 2) m_run = fmaxf(*m_first, -FLT_MAX);
 
     // one pipeline step: this wave's tile at ring position POS (+ kg) is consumed, S^T of its next tile produced
     auto step = [&](int j, const int POS, f32x16 (&s_cur)[2], f32x16 (&s_next)[2], float &l_sum)

@@ -88,3 +88,17 @@ def test_infinite_value_beside_an_odd_count_of_tiles_in_place():
     assert (O[..., FEATURE] == float("inf")).all()
     O[..., FEATURE], V[..., FEATURE] = 0, 0
     _check(O, lse, Q, K, V)
+
+
+# whole tiles without weight, wherever a wave group or a key range begins with one: every other tile of 32 or 64 keys, and
+# all but the last
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("H,N_q,N_kv,split", [(2, 200, 160, False), (2, 300, 700, False), (2, 300, 3000, True), (1, 64, 4000, True)])
+@pytest.mark.parametrize("tile,skip", [(32, 1), (64, 1), (64, 0)])
+def test_tiles_without_weight(H, N_q, N_kv, split, tile, skip, dtype):
+    Q, K, V = _inputs(H, N_q, N_kv, dtype, N_kv + tile)
+    Q[..., 0] = 1
+    dead = (torch.arange(N_kv) // tile) % 2 == skip
+    K[:, dead, 0] = float("-inf")
+    O, lse = _run(Q, K, V, split)
+    _check(O, lse, Q, K[:, ~dead].contiguous(), V[:, ~dead].contiguous())
