@@ -411,8 +411,9 @@ __global__ __launch_bounds__(512, 2) void k_score_gemm(const char *__restrict__ 
         auto load = [&](int i) __attribute__((always_inline)) {
             const unsigned dst = next_dst + (i >> 1) * (kGemmTile * 64) + (i & 1) * 1024;
             const unsigned off = i < 2 ? anc_off[i & 1] : cand_off[i & 1];
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(dst), "v"(off), "s"(i < 2 ? next_a : next_k) : "memory");   // nothing else here uses m0
+            unsigned callers_m0;   // m0 is the compiler's to manage: handed back as it was
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+                         : "=&s"(callers_m0) : "s"(dst), "v"(off), "s"(i < 2 ? next_a : next_k) : "memory");
         };
         auto advance = [&]() __attribute__((always_inline)) {   // 64 bytes on in every row, after four steps to the next head
             ++next_step;
