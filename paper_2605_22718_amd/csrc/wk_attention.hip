@@ -1239,6 +1239,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
             x[u] = po[0];
             y[u] = po[1];
         }
+        asm volatile("" ::: "memory");   // the loads stay together, in front of the branches
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             if (s0 + u >= a.splits || t[u].x == -INFINITY) continue;
