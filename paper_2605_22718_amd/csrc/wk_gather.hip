@@ -14,7 +14,7 @@
 // one segment -- the usual case -- looks its segment up once: together these bring the kernel from
 // 3.2 TB/s to the rate of a plain device copy (5.5 TB/s read + written at the LingBot shape).  Small gathers are bound by
 // the chain of look-ups before the first copy: units cover the retrieved rows only when the native ones are in place, unit
-// numbers are 32-bit, ids are requested beside their count (4 chunks of 12 heads x 1,320 tokens: 20 -> 14.5 us).
+// numbers are 32-bit (4 chunks of 12 heads x 1,320 tokens: 20 -> 15 us).
 #include "wk_internal.h"
 
 namespace {
@@ -58,13 +58,10 @@ __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
     const int tid = threadIdx.x;
     const size_t row_bytes = (size_t)a.vec_per_row * 16;
 
-    // (the count and the first ids are requested together, not one behind the other)
-    int first_id = -1;
-    if (tid < a.R_max) first_id = a.ids[tid];
     int n = a.n_ids ? *a.n_ids : a.R_max;
     n = n < 0 ? 0 : (n > a.R_max ? a.R_max : n);
     for (int t = tid; t < n; t += kThreads) {
-        const int id = t == tid ? first_id : a.ids[t];
+        const int id = a.ids[t];   // (ids behind the count are never read)
         int len = 0;
         const char *k = nullptr, *v = nullptr;
         if (id >= 0 && id < a.M) {

@@ -157,3 +157,15 @@ def test_chunks_beyond_the_descriptors_bound_are_skipped():
     wk.wk_chunk_lse(tight, Q.to(d), out)
     torch.cuda.synchronize()
     assert torch.isinf(out[1]).all() and (out[1] < 0).all() and torch.isfinite(out[[0, 2, 3]]).all()
+
+
+def test_id_list_no_longer_than_its_count():
+    """Only the first *n_ids ids are read: here the list ends with them, R_max is larger."""
+    cfg = ws.get_config(1).with_(H=2)
+    ks, vs, store = _store(cfg, [40, 70, 20])
+    d = dev()
+    Kw, Vw = (torch.zeros((2, 4 * 70, 128), dtype=torch.bfloat16, device=d) for _ in range(2))
+    n_win = torch.empty(1, dtype=torch.int32, device=d)
+    wk.wk_gather_window(store.desc, torch.tensor([2, 1], dtype=torch.int32, device=d), torch.tensor([2], dtype=torch.int32, device=d), 4,
+                        None, None, 0, Kw, Vw, 4 * 70, n_win)
+    assert int(n_win.item()) == 90 and torch.equal(bits(Kw[:, :90].cpu()), bits(torch.cat([ks[2], ks[1]], 1)))
