@@ -48,6 +48,9 @@ struct GatherArgs {
 
 // dynamic LDS: per segment s (0 = native rows, 1.. = retrieved chunks in the order of ids) the
 // base address of its K block and V block, its length and the first window row after it
+// U: the type of unit numbers, 32 bits except for a capped grid over 2^31 units or more (heads without end and next to no
+// rows; the windows of anything else would not fit the device).  A 64-bit division takes longer than a unit's look-ups.
+template <typename U>
 __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int cap = a.R_max + 1;
@@ -99,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
     // checked on the host)
     const int row_shift = a.vec_per_row == 16 ? 4 : 5;
     const unsigned total_vec = (unsigned)total_rows << row_shift, first_vec = (unsigned)a.first_row << row_shift;
-    const unsigned units = (unsigned)a.units_per_head * (unsigned)a.H * 2u;   // fits: checked on the host
+    const U units = (U)a.units_per_head * (U)a.H * 2u;
     // smallest s in [lo, hi] with row < seg_end[s]
     auto segment_of = [&](int row, int lo, int hi) {
         while (lo < hi) {
@@ -109,8 +112,8 @@ __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
         return lo;
     };
 
-    for (unsigned u = blockIdx.x; u < units; u += gridDim.x) {
-        const unsigned hz = u / (unsigned)a.units_per_head, unit = u - hz * (unsigned)a.units_per_head;
+    for (U u = blockIdx.x; u < units; u += gridDim.x) {
+        const unsigned hz = (unsigned)(u / (U)a.units_per_head), unit = (unsigned)(u - (U)hz * (U)a.units_per_head);
         const unsigned v0 = first_vec + unit * kVecPerBlock;
         if (v0 >= total_vec) continue;
         const int h = (int)(hz % (unsigned)a.H);
@@ -181,11 +184,14 @@ wk_status wk::gather_launch(const wk_store_desc *store, const int32_t *ids, cons
     long long per_head = (cap_vec + kVecPerBlock - 1) / kVecPerBlock;
     if (per_head == 0) per_head = 1;  // nothing to copy: one workgroup still reports the (zero) length
     a.units_per_head = (int)per_head;
-    long long grid = per_head * store->H * 2;
+    const long long units = per_head * store->H * 2;
+    const long long grid = max_workgroups > 0 && units > max_workgroups ? max_workgroups : units;
     if (grid > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
-    if (max_workgroups > 0 && grid > max_workgroups) grid = max_workgroups;
     const size_t lds_bytes = (size_t)(R_max + 1) * (2 * sizeof(char *) + 2 * sizeof(int));
-    hipLaunchKernelGGL(k_gather, dim3((unsigned)grid), dim3(kThreads), lds_bytes, stream, a);
+    if (units <= 0x7fffffffLL)   // (a unit number plus a grid stays below 2^32)
+        hipLaunchKernelGGL(k_gather<uint32_t>, dim3((unsigned)grid), dim3(kThreads), lds_bytes, stream, a);
+    else
+        hipLaunchKernelGGL(k_gather<uint64_t>, dim3((unsigned)grid), dim3(kThreads), lds_bytes, stream, a);
     WK_LAUNCH_CHECK();
     return WK_OK;
 }

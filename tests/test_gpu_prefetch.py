@@ -162,3 +162,24 @@ def test_eviction_to_host_store_on_the_copy_stream():
     assert torch.equal(bits(Kh), bits(oK)) and torch.equal(bits(Vh), bits(oV))
     mx, mean = attention_errors(O, oracle.attention(Q.cpu(), Kn.cpu(), Vn.cpu()))
     assert mx <= ATT_MAX_ABS_BF16 and mean <= ATT_MEAN_ABS_BF16
+
+
+def test_capped_gather_over_more_units_than_a_grid_can_have():
+    """2^31 work units (2^30 heads, no row retrieved): refused as a grid of one workgroup each, walked by a capped one."""
+    d = dev()
+    row = torch.zeros((1, 1, 128), dtype=torch.bfloat16, device=d)
+    store = wk.Store([row], [row])
+    desc = type(store.desc).from_buffer_copy(store.desc)
+    desc.H = 1 << 30
+    ids, n_win = torch.tensor([-1], dtype=torch.int32, device=d), torch.full((1,), 7, dtype=torch.int32, device=d)
+    p = wk.wk_prefetch_create(1)
+    try:
+        with pytest.raises(wk.WkError) as e:
+            wk.wk_prefetch_gather(p, 0, desc, ids, None, 1, None, None, 0, row, row, 1, n_win, 0)
+        assert e.value.status == wk.WK_ERR_UNSUPPORTED
+        wk.wk_prefetch_gather(p, 0, desc, ids, None, 1, None, None, 0, row, row, 1, n_win, 2048)
+        wk.wk_prefetch_acquire(p, 0)
+        torch.cuda.synchronize()
+    finally:
+        wk.wk_prefetch_destroy(p)
+    assert int(n_win.item()) == 0 and not row.any()
