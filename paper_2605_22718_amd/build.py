@@ -40,10 +40,15 @@ def _compile(src: str) -> str:
     return obj
 
 
+def dependencies():
+    """Every file whose change makes the built library stale: sources, their headers and the generated loops they include."""
+    return [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".h", ".inc"))] + \
+        [os.path.join(ROOT, "include", "wk.h")]
+
+
 def build(force: bool = True) -> str:
     srcs = sources()
-    deps = srcs + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
-    deps.append(os.path.join(ROOT, "include", "wk.h"))
+    deps = dependencies()
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
         return LIB
     os.makedirs(OBJ, exist_ok=True)

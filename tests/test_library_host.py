@@ -25,6 +25,14 @@ def test_library_exports_every_declared_symbol():
         assert getattr(L, name) is not None
 
 
+def test_build_knows_every_included_file():
+    from paper_2605_22718_amd import build
+    deps = {os.path.basename(f) for f in build.dependencies()}
+    for src in build.sources():
+        included = re.findall(r'^\s*#include "([^"]+)"', open(src).read(), re.M)
+        assert included and {os.path.basename(src), *map(os.path.basename, included)} <= deps
+
+
 def test_status_strings():
     seen = {wk.status_string(s) for s in range(7)}
     assert len(seen) == 7 and "ok" in seen
