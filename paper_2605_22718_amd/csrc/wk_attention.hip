@@ -478,12 +478,13 @@ __device__ inline const char *uniform_ptr(const char *p) {
     return reinterpret_cast<const char *>(((uint64_t)hi << 32) | lo);
 }
 
-template <int KG, bool MULTI, bool IN_PLACE>
-__global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) {
-    static_assert(KG == 1 || KG == 2, "one tile, or a pair of tiles, per step");
-    constexpr int QW = 8 / KG;         // waves across the queries
-    constexpr int NB = 2;              // 1 KB blocks of a tile that a wave loads
-    constexpr int kWaitTwoSteps = 0x0F78;   // s_waitcnt vmcnt(8) alone: all but the last four tile shares have landed
+// QW: waves across the queries; KG: wave groups, which take alternate tiles
+template <int QW, int KG, bool MULTI, bool IN_PLACE>
+__global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTable sub) {
+    static_assert((QW == 8 && KG == 1) || (QW == 4 && (KG == 1 || KG == 2)), "one tile, or a pair of tiles, per step");
+    constexpr int NB = 16 / (QW * KG); // 1 KB blocks of a tile that a wave loads
+    // s_waitcnt vmcnt(4 * NB) alone: all but the last four tile shares have landed
+    constexpr int kWaitTwoSteps = NB == 2 ? 0x0F78 : 0x4F70;
     constexpr int kWaitAll = 0x0F70;        // vmcnt(0)
     static_assert(!(MULTI && IN_PLACE), "a table of launches over one window array only");
     extern __shared__ __attribute__((aligned(256))) char smem[];
@@ -888,7 +889,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16(AttnArgs a, SubTable sub) 
         end_step();
     };
     int j = 0;
-    if constexpr (!IN_PLACE) {
+    if constexpr (!IN_PLACE && QW * KG == 8) {
         // Steady state: whole trips round the ring whose look-ahead loads all lie inside the window run in a
         // hand-scheduled loop (written by gen_attn_loop.py, which documents its schedule and register map).  It is
         // the four (KG == 2: two) `step`s below instruction for instruction in what it computes -- same ring protocol,
@@ -1266,70 +1267,92 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
 }
 
 // How a bf16 launch is laid out:
-//   kg = 1   workgroups of 256 queries, a tile of 64 keys per step
-//   kg = 2   workgroups of 128 queries, a pair of tiles per step: twice the workgroups, 10 % more power per product
-//            (every tile is fetched for half as many queries)
-//   splits   > 1: the key range split over workgroups and merged (needs a workspace), at most kMaxSplits and a step or
-//            more of work each
+//   k256      workgroups of 256 queries, a tile of 64 keys per step
+//   k128Pair  workgroups of 128 queries, a pair of tiles per step: twice the workgroups, 10 % more power per product
+//             (every tile is fetched for half as many queries)
+//   k128      workgroups of 128 queries in four waves, a tile per step: no pair to wait for, no wave groups to meet
+//   splits    > 1: the key range split over workgroups and merged (needs a workspace), at most kMaxSplits and a step or
+//             more of work each
 // chosen by the cheapest predicted time.  A step takes longer with more compute units at work, because the chip lowers
-// its clock: kBusyUs with few of them, kFullUs with all 256; a workgroup's fill and drain cost kFillSteps; the merge a
-// launch and its traffic.  The figures were fitted to timed launches of 75 shapes (2 to 40 heads, 64 to 4,680 queries,
-// 277 to 211,200 keys) with both kg and every split count; over those shapes the rule's choice is 1.5 % slower than the
-// fastest layout on average, 10 % on the worst (a launch of 10 us).  (Query tiles that walk the same slice of a head's keys run side by side and share it through the
-// L2, which cutting the work into equal runs regardless of item boundaries would give up: that was measured 5 to 14 % slower.)
+// its clock: busy_us with few of them, full_us with all 256; a workgroup's fill and drain cost fill_steps; a launch has
+// launch_us of its own, whatever its size (a pair's meeting among it); the merge a launch and its traffic.  The figures were
+// fitted to timed launches of 497 shapes (2 to 40 heads, 64 to 4,680 queries, 64 to 211,200 keys, with and without a
+// workspace) in all layouts and split counts: over those the rule's choice is 0.3 % slower than the fastest on average, 11 % at
+// most, and never more than 2 % slower than the choice between k256 with splits and k128 that went before k128Pair.
+// k128 is the best for up to 5 tiles and for 7 and 9 (an odd count leaves one wave group of a pair idle for a step): 12 heads x 512
+// queries x 64 keys 6.9 us, in pairs 8.9 us, x 448 13.0 and 13.7 us; x 768 17.4 and 17.0 us.
+// Predictions within 0.3 % count as equal and the fewer splits are taken: 12 heads x 2,640 queries x 211,200 keys take 3.0 ms
+// with 11, 13 and 15 splits alike.
+// (Query tiles that walk the same slice of a head's keys run side by side and share it through the L2, which cutting the
+// work into equal runs regardless of item boundaries would give up: that was measured 5 to 14 % slower.)
+enum Layout { k256, k128Pair, k128, kLayouts };
 constexpr int kMaxSplits = 16;
 constexpr int kMinSplitTiles = 24;   // shorter windows: a workspace would buy less than 2 us
 
-struct LaunchPlan { int kg, splits; };
-
-// wgs workgroups of `steps` steps each (on average)
-double grid_us(int kg, long long wgs, double steps) {
-    const double kBusyUs = kg == 1 ? 1.23 : 1.41, kFullUs = kg == 1 ? 1.48 : 1.92, kFillSteps = kg == 1 ? 3.8 : 1.6;
-    const double rest = (double)(wgs % 256) / 256;
-    return (steps + kFillSteps) * ((double)(wgs / 256) * kFullUs + (rest == 0 ? 0 : std::fmax(kBusyUs, kFullUs * rest)));
+size_t split_workspace_bytes(int H, int N_q, int splits) {
+    const size_t rows = (size_t)splits * H * N_q;
+    return wk::align_up(rows * WK_D * sizeof(float), 256) + wk::align_up(rows * 2 * sizeof(float), 256);
 }
 
-double launch_us(int kg, int splits, long long H, long long N_q, int n_tiles) {
-    const long long wgs = H * ((N_q + 256 / kg - 1) / (256 / kg)) * splits;
-    const int tiles = (n_tiles + splits - 1) / splits, steps = (tiles + kg - 1) / kg;
-    double us = grid_us(kg, wgs, steps);
-    if (splits > 1) us += 8.5 + 2.0 * splits * (double)(H * N_q) * 516.0 / 7.9e6;
+struct LayoutModel { int qw, kg; double busy_us, full_us, fill_steps, launch_us; };
+constexpr LayoutModel kModel[kLayouts] = {{8, 1, 1.25, 1.26, 1.9, 5.6}, {4, 2, 1.48, 1.67, 1.0, 6.2}, {4, 1, 0.98, 1.08, 5.0, 1.1}};
+
+struct LaunchPlan { Layout layout; int splits; };
+
+constexpr int queries_per_wg(Layout l) { return 32 * kModel[l].qw; }
+
+// wgs workgroups of `steps` steps each (on average)
+double grid_us(const LayoutModel &m, long long wgs, double steps) {
+    const double rest = (double)(wgs % 256) / 256;
+    return m.launch_us + (steps + m.fill_steps) * ((double)(wgs / 256) * m.full_us + (rest == 0 ? 0 : std::fmax(m.busy_us, m.full_us * rest)));
+}
+
+double launch_us(Layout l, int splits, long long H, long long N_q, int n_tiles) {
+    const LayoutModel &m = kModel[l];
+    const long long wgs = H * ((N_q + queries_per_wg(l) - 1) / queries_per_wg(l)) * splits;
+    const int tiles = (n_tiles + splits - 1) / splits, steps = (tiles + m.kg - 1) / m.kg;
+    double us = grid_us(m, wgs, steps);
+    if (splits > 1) us += 2.4 + 2.0 * splits * (double)(H * N_q) * 516.0 / 4.6e6;
     return us;
 }
 
-LaunchPlan plan_bf16(int H, int N_q, int N_kv, bool workspace_ok) {
+// the best plan whose partial results fit workspace_bytes
+LaunchPlan plan_bf16(int H, int N_q, int N_kv, size_t workspace_bytes) {
     const int n_tiles = (N_kv + 63) / 64;
-    LaunchPlan best{1, 1};
-    double best_us = launch_us(1, 1, H, N_q, n_tiles);
-    for (int kg = 1; kg <= 2; ++kg)
-        for (int sp = 1; sp <= (workspace_ok ? kMaxSplits : 1) && (sp == 1 || n_tiles >= std::max(2 * kg * sp, kMinSplitTiles)); ++sp) {
-            const double us = launch_us(kg, sp, H, N_q, n_tiles);
-            if (us < best_us) {
+    LaunchPlan best{k256, 1};
+    double best_us = launch_us(k256, 1, H, N_q, n_tiles);
+    for (const Layout l : {k256, k128Pair, k128}) {
+        for (int sp = 1; sp <= (l == k128 ? 1 : kMaxSplits); ++sp) {
+            if (sp > 1 && (n_tiles < std::max(2 * kModel[l].kg * sp, kMinSplitTiles) || split_workspace_bytes(H, N_q, sp) > workspace_bytes)) break;
+            const double us = launch_us(l, sp, H, N_q, n_tiles);
+            if (us < 0.997 * best_us) {
                 best_us = us;
-                best = LaunchPlan{kg, sp};
+                best = LaunchPlan{l, sp};
             }
         }
+    }
     return best;
 }
 
 // The workgroup size of a table of launches, by the same model: the grid's time if every workgroup had the average
 // number of steps, or the longest workgroup's alone.  12 heads x 3 frames of 880 queries on 10,560 keys are 276
 // workgroups of 256 queries, which leave a second round of 20: 220 us; as 504 of 128 queries 171 us.
-int table_kg(const SubTable &t, long long H) {
-    int best = 1;
+Layout table_layout(const SubTable &t, long long H) {
+    Layout best = k256;
     double best_us = 0;
-    for (int kg = 1; kg <= 2; ++kg) {
+    for (const Layout l : {k256, k128Pair}) {
+        const LayoutModel &m = kModel[l];
         long long wgs = 0, steps = 0, longest = 0;
         for (int e = 0; e < t.n; ++e) {
-            const long long n = H * ((t.s[e].N_q + 256 / kg - 1) / (256 / kg)), tiles = (t.s[e].N_kv + 63) / 64;
-            const long long len = (tiles + kg - 1) / kg;
+            const long long n = H * ((t.s[e].N_q + queries_per_wg(l) - 1) / queries_per_wg(l)), tiles = (t.s[e].N_kv + 63) / 64;
+            const long long len = (tiles + m.kg - 1) / m.kg;
             wgs += n;
             steps += n * len;
             longest = std::max(longest, len);
         }
-        const double us = std::fmax(grid_us(kg, wgs, (double)steps / (double)wgs), grid_us(kg, std::min(wgs, 256ll), (double)longest));
-        if (kg == 1 || us < best_us) {
-            best = kg;
+        const double us = std::fmax(grid_us(m, wgs, (double)steps / (double)wgs), grid_us(m, std::min(wgs, 256ll), (double)longest));
+        if (l == k256 || us < best_us) {
+            best = l;
             best_us = us;
         }
     }
@@ -1354,44 +1377,41 @@ int choose_splits_f32(long long H, long long N_q, int n_tiles) {
     return best;
 }
 
-size_t split_workspace_bytes(int H, int N_q, int splits) {
-    const size_t rows = (size_t)splits * H * N_q;
-    return wk::align_up(rows * WK_D * sizeof(float), 256) + wk::align_up(rows * 2 * sizeof(float), 256);
-}
-
 // k_attn_bf16 and k_attn_f32 use more than the default 64 KB of dynamic LDS: raise its limit once per device and
 // process (not a stream operation, so a first call under graph capture is fine too).
 wk_status allow_large_lds() {
     static std::atomic<uint64_t> done{0};
     int dev;
     if (wk::device_needs_setup(done, dev)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, false, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, false, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, true, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, true, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<1, false, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_bf16<2, false, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kSmemBytesPair) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_f32<false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kF32Lds) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attn_f32<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kF32Lds) != hipSuccess)
-            return WK_ERR_HIP;
+        struct { const void *kernel; int bytes; } const kernels[] = {
+            {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, false, false>), kSmemBytes},
+            {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, true, false>), kSmemBytes},
+            {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, false, true>), kSmemBytes},
+            {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, false, false>), kSmemBytesPair},
+            {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, true, false>), kSmemBytesPair},
+            {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, false, true>), kSmemBytesPair},
+            {reinterpret_cast<const void *>(&k_attn_bf16<4, 1, false, false>), kSmemBytes},
+            {reinterpret_cast<const void *>(&k_attn_bf16<4, 1, false, true>), kSmemBytes},
+            {reinterpret_cast<const void *>(&k_attn_f32<false>), kF32Lds},
+            {reinterpret_cast<const void *>(&k_attn_f32<true>), kF32Lds},
+        };
+        for (const auto &k : kernels)
+            if (hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes) != hipSuccess) return WK_ERR_HIP;
         wk::mark_device(done, dev);
     }
     return WK_OK;
 }
 
-template <int KG>
-wk_status launch_bf16(AttnArgs a, int splits, void *workspace, hipStream_t st) {
-    constexpr int q_per_wg = 256 / KG;
+template <int QW, int KG, bool MULTI, bool IN_PLACE>
+void launch_layout(const AttnArgs &a, const SubTable &t, hipStream_t st) {
+    hipLaunchKernelGGL((k_attn_bf16<QW, KG, MULTI, IN_PLACE>), dim3(a.per_xcd * kXcds), dim3(QW * KG * 64),
+                       KG == 1 ? kSmemBytes : kSmemBytesPair, st, a, t);
+}
+
+wk_status launch_bf16(AttnArgs a, LaunchPlan plan, void *workspace, hipStream_t st) {
+    const int q_per_wg = queries_per_wg(plan.layout);
     a.n_qtiles = (a.N_q + q_per_wg - 1) / q_per_wg;
-    a.splits = splits;
+    a.splits = plan.splits;
     a.part_o = reinterpret_cast<float *>(workspace);
     a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
                                           wk::align_up((size_t)a.splits * a.H * a.N_q * WK_D * sizeof(float), 256));
@@ -1400,12 +1420,15 @@ wk_status launch_bf16(AttnArgs a, int splits, void *workspace, hipStream_t st) {
     a.per_xcd = (int)((items + kXcds - 1) / kXcds);
     const wk_status lds_rc = allow_large_lds();
     if (lds_rc != WK_OK) return lds_rc;
-    if (a.O) {
-        hipLaunchKernelGGL((k_attn_bf16<KG, false, false>), dim3(a.per_xcd * kXcds), dim3(512), KG == 1 ? kSmemBytes : kSmemBytesPair,
-                           st, a, SubTable{});
-    } else {
-        if (KG != 1) return WK_ERR_UNSUPPORTED;   // the log-sum-exp kernel is laid out for 256-query workgroups
+    if (!a.O) {
+        if (plan.layout != k256) return WK_ERR_UNSUPPORTED;   // the log-sum-exp kernel is laid out for 256-query workgroups
         hipLaunchKernelGGL(k_lse_bf16, dim3(a.per_xcd * kXcds), dim3(512), kVRing, st, a);
+    } else if (plan.layout == k256) {
+        launch_layout<8, 1, false, false>(a, SubTable{}, st);
+    } else if (plan.layout == k128Pair) {
+        launch_layout<4, 2, false, false>(a, SubTable{}, st);
+    } else {
+        launch_layout<4, 1, false, false>(a, SubTable{}, st);
     }
     WK_LAUNCH_CHECK();
     if (a.splits > 1) {
@@ -1476,13 +1499,9 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         }
         return WK_OK;
     }
-    if (!O) return launch_bf16<1>(a, 1, nullptr, st);   // log-sum-exp only
+    if (!O) return launch_bf16(a, LaunchPlan{k256, 1}, nullptr, st);   // log-sum-exp only
     const bool ws_aligned = workspace && reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
-    // the plan with a workspace, if the one given is big enough for it; otherwise the best plan without
-    LaunchPlan plan = plan_bf16(H, N_q, N_kv, ws_aligned);
-    if (plan.splits > 1 && workspace_bytes < split_workspace_bytes(H, N_q, plan.splits))
-        plan = plan_bf16(H, N_q, N_kv, false);
-    return plan.kg == 1 ? launch_bf16<1>(a, plan.splits, workspace, st) : launch_bf16<2>(a, plan.splits, workspace, st);
+    return launch_bf16(a, plan_bf16(H, N_q, N_kv, ws_aligned ? workspace_bytes : 0), workspace, st);
 }
 
 namespace {
@@ -1500,8 +1519,7 @@ wk_status launch_plain(AttnArgs a, int dtype, hipStream_t st) {
     } else {
         a.n_qtiles = (a.N_q + 255) / 256;
         a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
-        hipLaunchKernelGGL((k_attn_bf16<1, false, false>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a,
-                           SubTable{});
+        launch_layout<8, 1, false, false>(a, SubTable{}, st);
     }
     WK_LAUNCH_CHECK();
     return WK_OK;
@@ -1568,8 +1586,8 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
         t.s[0] = SubLaunch{0, N_q, 0, start, N_kv - start, start, 1};
         for (int f = 0; f < frames; ++f) t.s[f + 1] = SubLaunch{f * frame_T, frame_T, 0, 0, denoise_row0 + (f + 1) * frame_T, 0, 0};
         for (int e = t.n; e < kMaxSub; ++e) t.s[e] = SubLaunch{0, 0, 0, 0, 0, 0, 0};
-        const int kg = dtype == WK_F32 ? 1 : table_kg(t, H);
-        const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : 256 / kg;
+        const Layout layout = dtype == WK_F32 ? k256 : table_layout(t, H);   // (fp32 has one of its own)
+        const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : queries_per_wg(layout);
         t.per_head = 0;
         for (int e = 0; e < t.n; ++e) {
             t.s[e].n_qtiles = (t.s[e].N_q + q_per_wg - 1) / q_per_wg;
@@ -1584,10 +1602,8 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
         if (dtype == WK_F32) {
             hipLaunchKernelGGL(k_attn_f32<true>, dim3(g.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, g, t);
         } else {
-            if (kg == 1)
-                hipLaunchKernelGGL((k_attn_bf16<1, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytes, st, g, t);
-            else
-                hipLaunchKernelGGL((k_attn_bf16<2, true, false>), dim3(g.per_xcd * kXcds), dim3(512), kSmemBytesPair, st, g, t);
+            if (layout == k256) launch_layout<8, 1, true, false>(g, t, st);
+            else launch_layout<4, 2, true, false>(g, t, st);
         }
         WK_LAUNCH_CHECK();
     } else {
@@ -1661,7 +1677,7 @@ extern "C" wk_status wk_chunk_lse(const wk_store_desc *store, const void *Q, int
         WK_LAUNCH_CHECK();
         return WK_OK;
     }
-    return launch_bf16<1>(a, 1, nullptr, st);
+    return launch_bf16(a, LaunchPlan{k256, 1}, nullptr, st);
 }
 
 extern "C" wk_status wk_attention_in_place(const void *Q, const void *K_native, const void *V_native,
@@ -1704,18 +1720,17 @@ extern "C" wk_status wk_attention_in_place(const void *Q, const void *K_native, 
     a.max_tok = store->max_tok;
     // 256- or 128-query workgroups, by the rule of wk_attention for the longest window the ids can give
     const long long longest = (long long)n_native + (long long)a.R_max * store->max_tok;
-    const LaunchPlan plan = plan_bf16(a.H, N_q, (int)(longest < 64 ? 64 : (longest > 0x7fffffff ? 0x7fffffff : longest)), false);
-    const int q_per_wg = 256 / plan.kg;
+    const LaunchPlan plan = plan_bf16(a.H, N_q, (int)(longest < 64 ? 64 : (longest > 0x7fffffff ? 0x7fffffff : longest)), 0);
+    const int q_per_wg = queries_per_wg(plan.layout);
     a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
     if ((long long)a.H * a.n_qtiles + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
     a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
     const wk_status rc = allow_large_lds();
     if (rc != WK_OK) return rc;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-    if (plan.kg == 1)
-        hipLaunchKernelGGL((k_attn_bf16<1, false, true>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytes, st, a, SubTable{});
-    else
-        hipLaunchKernelGGL((k_attn_bf16<2, false, true>), dim3(a.per_xcd * kXcds), dim3(512), kSmemBytesPair, st, a, SubTable{});
+    if (plan.layout == k256) launch_layout<8, 1, false, true>(a, SubTable{}, st);
+    else if (plan.layout == k128Pair) launch_layout<4, 2, false, true>(a, SubTable{}, st);
+    else launch_layout<4, 1, false, true>(a, SubTable{}, st);
     WK_LAUNCH_CHECK();
     return WK_OK;
 }
@@ -1727,7 +1742,7 @@ extern "C" size_t wk_attention_workspace_bytes(int32_t H, int32_t N_q, int32_t N
         const int s = choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys);
         return s > 1 ? split_workspace_bytes(H, N_q, s) : 0;
     }
-    const LaunchPlan plan = plan_bf16(H, N_q, N_kv, true);
+    const LaunchPlan plan = plan_bf16(H, N_q, N_kv, SIZE_MAX);
     return plan.splits > 1 ? split_workspace_bytes(H, N_q, plan.splits) : 0;
 }
 
