@@ -234,10 +234,17 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
         return;
     }
 
+    // One tile in all leaves the second wave group nothing to do: no operands, no loads, no meeting (8 heads x 300 queries x 32
+    // keys 10.4 us, with them 13.0 us).  idle: no valid query in this wave, or no tile for it: its loads and barriers only.
+    const bool alone = kt1 - kt0 <= kF32Keys;
+    const bool idle = qt * (kF32Waves * 32) + qw * 32 >= a.N_q || (alone && kg == 1);
+
     // B operand of S^T = K Q^T: k slot (g, step 4c+e) means feature 8c + 4g + e
     float4 qr[16];
+    if (!idle) {
 #pragma unroll
-    for (int c = 0; c < 16; ++c) qr[c] = *reinterpret_cast<const float4 *>(Qrow + 8 * c + 4 * g);
+        for (int c = 0; c < 16; ++c) qr[c] = *reinterpret_cast<const float4 *>(Qrow + 8 * c + 4 * g);
+    }
 
     f32x16 o[4];
 #pragma unroll
@@ -273,16 +280,15 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
                                                  16, 0, 0);
         }
     };
-    const bool idle = qt * (kF32Waves * 32) + qw * 32 >= a.N_q;   // no valid query in this wave: loads and barriers only
     const int n_pairs = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + 1) / 2;
-    issue(0);
+    if (!alone || kg == 0) issue(0);
     // the two waves of a SIMD belong to different groups: the first one ahead, so that one does its softmax arithmetic
     // while the other multiplies
     if (kg == 0) __builtin_amdgcn_s_setprio(1);
     for (int j = 0; j < n_pairs; ++j) {
         const int kt = kt0 + (2 * j + kg) * kF32Keys, stage = (j & 1) * kF32Stage;
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the pair has landed
-        if (with_o && kt + kF32Keys > kt1) {  // V rows past the range become zeros: the last row there may be infinite
+        if (with_o && kt < kt1 && kt + kF32Keys > kt1) {  // V rows past the range become zeros: the last row there may be infinite
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (kt + ld_row + 2 * i >= kt1)
@@ -367,14 +373,17 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
     }
     // The wave groups meet: waves 4..7 leave (O^T, max, sum) of their keys in LDS, waves 0..3 add them to theirs.
     // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.
-    {
+    if (alone) {
+        if (idle) return;
+    } else {
         float *meet = reinterpret_cast<float *>(smem) + qw * (66 * 64) + lane;
         __syncthreads();   // every wave is done with its last tile
         if (kg == 1) {
+            if (with_o)
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+                for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) meet[(16 * b + r) * 64] = o[b][r];
+                    for (int r = 0; r < 16; ++r) meet[(16 * b + r) * 64] = o[b][r];
             meet[64 * 64] = m_run;
             meet[65 * 64] = l_run;
         }
@@ -385,10 +394,11 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
         const float w0 = __builtin_amdgcn_exp2f(m_run - m_new), w1 = __builtin_amdgcn_exp2f(m_other - m_new);
         m_run = m_new;
         l_run = fmaf(w1, meet[65 * 64], w0 * l_run);
+        if (with_o)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+            for (int b = 0; b < 4; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
+                for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
     }
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (q_ok && partial_out) {   // (O, max, sum) of this key range, merged by k_attn_merge
