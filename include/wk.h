@@ -237,8 +237,9 @@ wk_status wk_gather_window(const wk_store_desc *store, const int32_t *ids, const
  *   workspace  device, 256-byte aligned, or NULL.  When one workgroup per head and query tile would leave
  *              compute units idle (few heads, short query chunk, long window) the key range is split
  *              over several workgroups whose partial results are merged by a second kernel; that
- *              needs wk_attention_workspace_bytes(...) bytes.  Without (enough) workspace the call
- *              runs unsplit: same result up to fp32 rounding order, lower occupancy.
+ *              needs wk_attention_workspace_bytes(...) bytes.  With less the call takes the best split whose
+ *              partial results fit, without any it runs unsplit: same result up to fp32 rounding order (bf16:
+ *              and up to which running maximum a probability is rounded against), lower occupancy.
  * Errors: INVALID_ARG, UNSUPPORTED (d != 128; bf16 with N_kv > 2^24 - 512 rows), SHAPE (N_kv < 1 or
  *         N_kv > kv_row_stride). */
 wk_status wk_attention(const void *Q, const void *K_win, const void *V_win, void *O, float *lse,

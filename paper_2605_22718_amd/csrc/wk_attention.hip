@@ -1370,15 +1370,17 @@ Layout table_layout(const SubTable &t, long long H) {
 }
 
 // fp32: one workgroup fits a compute unit.  The split count with the cheapest rounds of 256 workgroups, a pair of tiles
-// costing 7.9 us, a workgroup's fill and drain 5 us, the merge a launch and its traffic; at least 2 pairs per split.
-int choose_splits_f32(long long H, long long N_q, int n_tiles) {
-    const long long items = H * ((N_q + kF32Waves * 32 - 1) / (kF32Waves * 32));
+// costing 7.9 us, a workgroup's fill and drain 5 us, the merge a launch and its traffic; at least 2 pairs per split, and
+// partial results that fit workspace_bytes.
+int choose_splits_f32(int H, int N_q, int n_tiles, size_t workspace_bytes) {
+    const long long items = (long long)H * ((N_q + kF32Waves * 32 - 1) / (kF32Waves * 32));
     int best = 1;
     double best_us = 0;
-    for (int s = 1; s <= kMaxSplits && (s == 1 || n_tiles >= 4 * s); ++s) {
+    for (int s = 1; s <= kMaxSplits; ++s) {
+        if (s > 1 && (n_tiles < 4 * s || split_workspace_bytes(H, N_q, s) > workspace_bytes)) break;
         const int pairs = ((n_tiles + s - 1) / s + 1) / 2;
         double us = (double)((items * s + 255) / 256) * (7.9 * pairs + 5);
-        if (s > 1) us += 5 + s * (double)(H * N_q) * 520.0 / 4e6;
+        if (s > 1) us += 5 + s * ((double)H * N_q) * 520.0 / 4e6;
         if (s == 1 || us < best_us) {
             best = s;
             best_us = us;
@@ -1483,6 +1485,7 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
     a.n_chunks = 0;
     a.q_rows = N_q; a.q_off = 0; a.kv_start = 0; a.part_slot = -1;
     a.v_table = nullptr; a.ids = nullptr; a.n_ids = nullptr; a.R_max = 0; a.store_M = 0; a.max_tok = 0;
+    const size_t usable_bytes = workspace && reinterpret_cast<uintptr_t>(workspace) % 256 == 0 ? workspace_bytes : 0;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
     if (dtype == WK_F32) {
         const wk_status lds_rc = allow_large_lds();
@@ -1490,10 +1493,7 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         const int q_per_wg = kF32Waves * 32;
         a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
         const long long items1 = (long long)H * a.n_qtiles;
-        a.splits = O ? choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys) : 1;
-        if (a.splits > 1 && (!workspace || workspace_bytes < split_workspace_bytes(H, N_q, a.splits) ||
-                             reinterpret_cast<uintptr_t>(workspace) % 256 != 0))
-            a.splits = 1;
+        a.splits = O ? choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, usable_bytes) : 1;
         a.part_o = reinterpret_cast<float *>(workspace);
         a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
                                               wk::align_up((size_t)a.splits * H * N_q * WK_D * sizeof(float), 256));
@@ -1510,8 +1510,7 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         return WK_OK;
     }
     if (!O) return launch_bf16(a, LaunchPlan{k256, 1}, nullptr, st);   // log-sum-exp only
-    const bool ws_aligned = workspace && reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
-    return launch_bf16(a, plan_bf16(H, N_q, N_kv, ws_aligned ? workspace_bytes : 0), workspace, st);
+    return launch_bf16(a, plan_bf16(H, N_q, N_kv, usable_bytes), workspace, st);
 }
 
 namespace {
@@ -1749,7 +1748,7 @@ extern "C" size_t wk_attention_workspace_bytes(int32_t H, int32_t N_q, int32_t N
     if (H < 1 || N_q < 1 || N_kv < 1 || (dtype != WK_BF16 && dtype != WK_F32)) return 0;
     if ((long long)H * ((N_q + 31) / 32) > 0x7fffffffLL / kMaxSplits) return 0;
     if (dtype == WK_F32) {
-        const int s = choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys);
+        const int s = choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, SIZE_MAX);
         return s > 1 ? split_workspace_bytes(H, N_q, s) : 0;
     }
     const LaunchPlan plan = plan_bf16(H, N_q, N_kv, SIZE_MAX);

@@ -123,6 +123,24 @@ def test_split_key_range_matches_oracle_and_unsplit(H, Nq, Nkv, n_dev):
     assert (O.float() - O1.float()).abs().max().item() <= 4e-3     # same math, different fp32 summation order
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("H,Nq,Nkv", [(2, 300, 3000), (1, 64, 4000)])
+@pytest.mark.parametrize("part", [0.99, 0.5, 0.1])
+def test_workspace_smaller_than_asked_for(H, Nq, Nkv, dtype, part):
+    """A call that is given less than wk_attention_workspace_bytes splits into as many key ranges as fit, and keeps to it."""
+    Q, K, V = _rand(H, Nq, Nkv, dtype, seed=Nkv)
+    d = dev()
+    asked = wk.wk_attention_workspace_bytes(H, Nq, Nkv, wk.WK_BF16 if dtype == torch.bfloat16 else wk.WK_F32)
+    given = int(asked * part)
+    buf = torch.full((asked,), 0xCD, dtype=torch.uint8, device=d)
+    O, lse = torch.empty_like(Q, device=d), torch.empty((H, Nq), device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse, workspace=buf[:given])
+    _check(Q, K, V, O, lse)
+    assert (buf[given:] == 0xCD).all()
+    two_ranges = 2 * H * Nq * (128 + 2) * 4 + 512   # partial outputs, maxima and sums
+    assert bool((buf[:given] != 0xCD).any()) == (given >= two_ranges)
+
+
 @pytest.mark.parametrize("H,Nq,Nkv,n_dev", [(10, 7500, 1000, None), (5, 15000, 520, 500), (12, 2640, 3000, None),
                                             (9, 7400, 700, 64)])
 def test_more_items_than_compute_units_with_and_without_workspace(H, Nq, Nkv, n_dev):
