@@ -597,7 +597,8 @@ __device__ inline double key_score(uint64_t key) {   // the score of an order ke
 constexpr int kSelThreads = 1024;
 
 // exclusive scan of one int per thread over the block; total = sum over the block
-__device__ inline int block_excl_scan(int v, int *wsum /*[kSelThreads/64]*/, int &total) {
+template <int THREADS>
+__device__ inline int block_excl_scan(int v, int *wsum /*[THREADS/64]*/, int &total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int x = v;
 #pragma unroll
@@ -610,7 +611,7 @@ __device__ inline int block_excl_scan(int v, int *wsum /*[kSelThreads/64]*/, int
     __syncthreads();
     int off = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < kSelThreads / 64; ++i) {
+    for (int i = 0; i < THREADS / 64; ++i) {
         const int t = wsum[i];
         if (i < w) off += t;
         tot += t;
@@ -619,8 +620,8 @@ __device__ inline int block_excl_scan(int v, int *wsum /*[kSelThreads/64]*/, int
     return off + x - v;
 }
 
-// Lists longer than kSelHeld (k_select_held, below, takes the others).  One block per list.  Radix-select (up to 8 passes of 8 bits, from the top, over order-preserving
-// 64-bit keys) finds the n_keep-th smallest score tau; then tokens with score < tau, plus the first
+// Lists longer than kSelHeld (k_select_held, below, takes the others).  One block per list.  Radix-select (up to 8 passes
+// of 8 bits, from the top, over order-preserving 64-bit keys) finds the n_keep-th smallest score tau; then tokens with score < tau, plus the first
 // few (by index) with score == tau, are written in ascending index order via block scans.  The passes
 // stop as soon as every key that shares tau's leading digits is kept anyway (for fp64 scores usually
 // after three or four digits); comparisons then look at those leading digits only.  Lists of up to
@@ -707,43 +708,48 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const double *__restrict
             eq = (key >> low) == (prefix >> low);
         }
         int eq_tot, keep_tot;
-        const int eq_rank = eq_base + block_excl_scan(eq ? 1 : 0, wsum, eq_tot);
+        const int eq_rank = eq_base + block_excl_scan<kSelThreads>(eq ? 1 : 0, wsum, eq_tot);
         const bool keep = less || (eq && eq_rank < k);
-        const int pos = out_base + block_excl_scan(keep ? 1 : 0, wsum, keep_tot);
+        const int pos = out_base + block_excl_scan<kSelThreads>(keep ? 1 : 0, wsum, keep_tot);
         if (keep && pos < p.n_keep) out[p.first_cand + pos] = p.first_cand + j;
         eq_base += eq_tot;
         out_base += keep_tot;
     }
 }
 
-// Lists of up to kSelHeld keys: a thread holds four of them in registers (j = thread, thread + 1024, ...).  One block per
-// list, bound by its chain of barriers, so there are few: the keys still in question are dealt to 1024 buckets over their
+// Lists of up to kSelHeld keys: a thread holds EACH of them in registers (j = thread, thread + THREADS, ...).  One block per
+// list, bound by its chain of barriers, so there are few: the keys still in question are dealt to THREADS buckets over their
 // range -- by the scores themselves first, which are spread evenly where their bit patterns are not -- and all but those
 // of the bucket that holds the n_keep-th are settled at once.  When a wave's worth is left (for scores of real chunks after
 // one round) they are ranked by comparing each with each.  Kept tokens leave as one bit per candidate, whose prefix
 // counts give the places.  A list of 3,120 candidates: 9.5 us, with the byte-wise passes and ordered block scans of k_select
 // 12.6 us; 24 lists of 2,026: 8.3 and 9.8 us.  (Counting, for every key, the keys before it -- 64 keys per
 // workgroup, comparing all pairs -- takes 12 and 22 us: 64-bit comparisons are slow.)
+// The workgroup is the smallest that holds the list: barriers of sixteen waves and the work on keys that are not there
+// made short lists slower than k_select does (whole calls with 1 list of 128, 2 of 400 and 12 of 936 candidates 18.5, 21.9 and 31.6 us;
+// k_select 16.8, 19.4 and 30.2; now 15.6, 18.7 and 30.1).
 constexpr int kSelHeld = 4 * kSelThreads;
 
-__global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__restrict__ scores, CompressDims p,
-                                                             int32_t *__restrict__ kept_idx) {
-    constexpr int kWaves = kSelThreads / 64, kEach = kSelHeld / kSelThreads, kList = 64;
-    __shared__ int hist[kSelThreads];
-    __shared__ uint64_t w_lo[kWaves], w_hi[kWaves], list_key[kList], words[kSelHeld / 64];
+template <int THREADS, int EACH>
+__global__ __launch_bounds__(THREADS) void k_select_held(const double *__restrict__ scores, CompressDims p,
+                                                         int32_t *__restrict__ kept_idx) {
+    constexpr int kWaves = THREADS / 64, kList = 64, kWords = EACH * kWaves;
+    constexpr int kBits = 31 - __builtin_clz(THREADS);   // of a bucket number
+    __shared__ int hist[THREADS];
+    __shared__ uint64_t w_lo[kWaves], w_hi[kWaves], list_key[kList], words[kWords];
     __shared__ int list_j[kList], wsum[kWaves];
     __shared__ int s_bucket, s_below, s_count, s_listed;
     const int list = blockIdx.x, n = p.n_cand, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const double *s = scores + (size_t)list * n;
     int32_t *out = kept_idx + (size_t)list * p.n_out;
-    for (int i = tid; i < p.first_cand; i += kSelThreads) out[i] = i;  // anchor tokens, kept in full
+    for (int i = tid; i < p.first_cand; i += THREADS) out[i] = i;  // anchor tokens, kept in full
     if (p.n_keep == 0) return;
-    double v[kEach];
-    uint64_t key[kEach];
-    bool open[kEach], kept[kEach];   // still in question; settled as kept
+    double v[EACH];
+    uint64_t key[EACH];
+    bool open[EACH], kept[EACH];   // still in question; settled as kept
 #pragma unroll
-    for (int u = 0; u < kEach; ++u) {
-        const int j = tid + u * kSelThreads;
+    for (int u = 0; u < EACH; ++u) {
+        const int j = tid + u * THREADS;
         v[u] = s[min(j, n - 1)];
         key[u] = order_key(v[u]);
         open[u] = j < n;
@@ -753,7 +759,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__res
     for (int round = 0; left > k; ++round) {
         uint64_t lo = ~0ull, hi = 0;
 #pragma unroll
-        for (int u = 0; u < kEach; ++u)
+        for (int u = 0; u < EACH; ++u)
             if (open[u]) {
                 lo = key[u] < lo ? key[u] : lo;
                 hi = key[u] > hi ? key[u] : hi;
@@ -779,9 +785,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__res
         if (lo == hi) {   // equal scores: the lowest indices are kept
             int base = 0;
 #pragma unroll
-            for (int u = 0; u < kEach; ++u) {
+            for (int u = 0; u < EACH; ++u) {
                 int total;
-                const int rank = base + block_excl_scan(open[u] ? 1 : 0, wsum, total);
+                const int rank = base + block_excl_scan<THREADS>(open[u] ? 1 : 0, wsum, total);
                 if (open[u] && rank < k) kept[u] = true;
                 open[u] = false;
                 base += total;
@@ -789,15 +795,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__res
             k = 0;
             break;
         }
-        // bucket of a key: monotone in the key, 0 .. 1023
+        // bucket of a key: monotone in the key, 0 .. THREADS - 1
         const double v_lo = key_score(lo), range = key_score(hi) - v_lo;
         const bool by_score = round == 0 && range < INFINITY && range > 1e-290;   // (no NaN: comparisons with it fail)
-        const double per = by_score ? 1023.0 / range : 0.0;
-        const int shift = max(0, 54 - __clzll(hi - lo));
-        int bucket[kEach];
+        const double per = by_score ? (THREADS - 1) / range : 0.0;
+        const int shift = max(0, 64 - kBits - __clzll(hi - lo));
+        int bucket[EACH];
 #pragma unroll
-        for (int u = 0; u < kEach; ++u) {
-            bucket[u] = by_score ? min((int)((v[u] - v_lo) * per), kSelThreads - 1) : (int)((key[u] - lo) >> shift);
+        for (int u = 0; u < EACH; ++u) {
+            bucket[u] = by_score ? min((int)((v[u] - v_lo) * per), THREADS - 1) : (int)((key[u] - lo) >> shift);
             if (open[u]) atomicAdd(&hist[bucket[u]], 1);
         }
         __syncthreads();
@@ -822,27 +828,27 @@ __global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__res
         left = s_count;
         const int at = s_bucket;
 #pragma unroll
-        for (int u = 0; u < kEach; ++u)
+        for (int u = 0; u < EACH; ++u)
             if (open[u] && bucket[u] != at) {
                 kept[u] = bucket[u] < at;
                 open[u] = false;
             }
         if (left <= kList && left > k) {
-            int slot[kEach];
+            int slot[EACH];
 #pragma unroll
-            for (int u = 0; u < kEach; ++u)
+            for (int u = 0; u < EACH; ++u)
                 if (open[u]) {
                     slot[u] = atomicAdd(&s_listed, 1);
                     list_key[slot[u]] = key[u];
-                    list_j[slot[u]] = tid + u * kSelThreads;
+                    list_j[slot[u]] = tid + u * THREADS;
                 }
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < kEach; ++u)
+            for (int u = 0; u < EACH; ++u)
                 if (open[u]) {
                     int rank = 0;
                     for (int i = 0; i < left; ++i)
-                        rank += list_key[i] < key[u] || (list_key[i] == key[u] && list_j[i] < tid + u * kSelThreads);
+                        rank += list_key[i] < key[u] || (list_key[i] == key[u] && list_j[i] < tid + u * THREADS);
                     kept[u] = rank < k;
                     open[u] = false;
                 }
@@ -852,14 +858,14 @@ __global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__res
         __syncthreads();   // the shared results have been read
     }
 #pragma unroll
-    for (int u = 0; u < kEach; ++u) {
+    for (int u = 0; u < EACH; ++u) {
         kept[u] |= open[u];   // what is left when all of it is kept
         const uint64_t bits = __ballot(kept[u]);
         if (lane == 0) words[wave + u * kWaves] = bits;
     }
     __syncthreads();
     // kept tokens before each 64 candidates: a lane per word
-    int incl = __popcll(words[lane]);
+    int incl = lane < kWords ? __popcll(words[lane]) : 0;
     const int ones = incl;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -867,9 +873,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_held(const double *__res
         if (lane >= o) incl += y;
     }
 #pragma unroll
-    for (int u = 0; u < kEach; ++u) {
+    for (int u = 0; u < EACH; ++u) {
         const int w = wave + u * kWaves, pos = __shfl(incl - ones, w) + __popcll(words[w] & ((1ull << lane) - 1));
-        if (kept[u]) out[p.first_cand + pos] = p.first_cand + tid + u * kSelThreads;
+        if (kept[u]) out[p.first_cand + pos] = p.first_cand + tid + u * THREADS;
     }
 }
 
@@ -1125,10 +1131,13 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
             WK_LAUNCH_CHECK();
         }
     }
-    if (p.n_cand > 0 && p.n_cand <= kSelHeld)
-        hipLaunchKernelGGL(k_select_held, dim3(d->batch * p.G), dim3(kSelThreads), 0, st, scores, p, kept);
-    else
-        hipLaunchKernelGGL(k_select, dim3(d->batch * p.G), dim3(kSelThreads), 0, st, scores, p, kept);
+    auto select = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3(d->batch * p.G), dim3(threads), 0, st, scores, p, kept); };
+    if (p.n_cand == 0 || p.n_cand > kSelHeld) select(k_select, kSelThreads);
+    else if (p.n_cand <= 256) select(k_select_held<256, 1>, 256);
+    else if (p.n_cand <= 512) select(k_select_held<512, 1>, 512);
+    else if (p.n_cand <= 1024) select(k_select_held<1024, 1>, 1024);
+    else if (p.n_cand <= 2048) select(k_select_held<1024, 2>, 1024);
+    else select(k_select_held<1024, 4>, 1024);
     WK_LAUNCH_CHECK();
     dim3 g5((p.n_out + kRowsPerBlock - 1) / kRowsPerBlock, p.H, d->batch);
     const char *Vc = reinterpret_cast<const char *>(V);

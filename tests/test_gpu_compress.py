@@ -149,8 +149,10 @@ def test_gemm_scoring_small_chunks(head_mode, H, T, F):
         _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], head_mode, rho, kind)
 
 
-# list lengths at the edges of a wave, of a round of threads and of the kernel that holds a list in registers
-@pytest.mark.parametrize("T,F", [(1, 2), (63, 2), (65, 2), (1025, 2), (2048, 3), (2049, 3)])
+# list lengths at the edges of a wave, of each workgroup size, of a round of threads and of the kernel that holds a list in
+# registers
+@pytest.mark.parametrize("T,F", [(1, 2), (63, 2), (65, 2), (128, 3), (257, 2), (256, 3), (513, 2), (512, 3), (1025, 2), (1024, 3), (683, 4),
+                                 (2048, 3), (2049, 3)])
 def test_selection_list_lengths(T, F):
     cfg = ws.get_config(1).with_(H=1, T=T, F=F)
     K, V, _ = ws.make_chunk(cfg, 8)
@@ -160,14 +162,14 @@ def test_selection_list_lengths(T, F):
 
 
 # equal scores by the hundred on either side of the cut, all scores equal, all zero, and scores of very different size
+@pytest.mark.parametrize("T", [300, 100, 220, 900, 1900])
 @pytest.mark.parametrize("kind", ["two", "one", "zero", "scales"])
-def test_selection_of_crowded_scores(kind):
-    cfg = ws.get_config(1).with_(H=2, T=300, F=3)
+def test_selection_of_crowded_scores(kind, T):
+    cfg = ws.get_config(1).with_(H=2, T=T, F=3)
     K, V, _ = ws.make_chunk(cfg, 9)
-    T = cfg.T
     if kind == "two":
-        K[:, T + 100:T + 330] = K[:, T + 7:T + 8]
-        K[:, T + 330:] = K[:, T + 8:T + 9]
+        K[:, T + T // 3:T + 11 * T // 10] = K[:, T + 7:T + 8]
+        K[:, T + 11 * T // 10:] = K[:, T + 8:T + 9]
     elif kind == "one":
         K[:, T:] = K[:, T + 7:T + 8]
     elif kind == "zero":
