@@ -358,7 +358,7 @@ wk_status wk_window_plan(const wk_window_desc *w, int64_t chunk_index, wk_window
  *   n_win      device out, int32 = n_native + n * slot_tokens.  May be NULL.
  *   n_fetched  device out, int32 = chunks copied by this call.  May be NULL.
  *   workspace  device, wk_window_update_workspace_bytes(R) bytes, 256-byte aligned
- *   max_workgroups  > 0 caps the copy grid (see wk_prefetch_gather); 0 = one per 32 KB
+ *   max_workgroups  > 0 caps the copy grid (see wk_prefetch_gather); 0 = one per 32 KB, more for small copies
  * Errors: INVALID_ARG, UNSUPPORTED (d != 128, R > 1024), SHAPE (slots exceed win_capacity, or slot_tokens
  *         exceeds the store's max_tok), WORKSPACE. */
 wk_status wk_window_update(const wk_store_desc *store, const int32_t *ids, const int32_t *n_ids, int32_t R,

@@ -481,12 +481,7 @@ __device__ inline float max_across_halves(float x) {
 constexpr int kMaxSegments = 33;   // native rows + up to 32 retrieved chunks
 struct Segment { const char *K; const char *V; int len; int pad; };
 
-__device__ inline const char *uniform_ptr(const char *p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<const char *>(((uint64_t)hi << 32) | lo);
-}
+using wk::uniform_ptr;
 
 // QW: waves across the queries; KG: wave groups, which take alternate tiles
 template <int QW, int KG, bool MULTI, bool IN_PLACE>

@@ -37,6 +37,14 @@ wk_status gather_launch(const wk_store_desc *store, const int32_t *ids, const in
                         const void *K_native, const void *V_native, int32_t n_native, void *K_win, void *V_win,
                         int32_t win_capacity, int32_t *n_win, int32_t max_workgroups, hipStream_t stream);
 
+// a pointer that is the same in every lane, as a scalar
+__device__ inline const char *uniform_ptr(const char *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const char *>(((uint64_t)hi << 32) | lo);
+}
+
 // 16 lanes share one 128-element row; each lane owns elements 8*sub .. 8*sub+7.
 constexpr int kRowLanes = 16;
 

@@ -16,6 +16,8 @@
 // are copied from the store (HBM or pinned host), into the slots of the chunks that left.  One
 // small kernel turns (old slot table, wanted ids) into (new slot table, fetch list); a second
 // copies the fetch list.
+#include <type_traits>
+
 #include "wk_internal.h"
 
 namespace {
@@ -24,6 +26,15 @@ constexpr int kPlanThreads = 1024;
 constexpr int kMaxSlots = 1024;
 constexpr int kThreads = 256;
 constexpr int kBlocksPerWg = 8;
+constexpr int kBlocksInFlight = 256;   // 1 MB
+
+// Workgroups for a list of `blocks` blocks: beyond 128 two blocks for each, beyond 512 more of them and one block in flight for
+// each, at most kBlocksPerWg in turn.  (From pinned memory 300 blocks take 31.8 us with 128 workgroups, 35.3 with 256; 660
+// blocks from HBM 9.0 and 8.3 us.)
+__host__ __device__ inline long long fetch_grid(long long blocks) {
+    const long long few = blocks < 128 ? blocks : (blocks <= 512 ? 128 : 256), many = (blocks + kBlocksPerWg - 1) / kBlocksPerWg;
+    return few > many ? few : many;
+}
 
 typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
 
@@ -125,6 +136,28 @@ __global__ __launch_bounds__(kPlanThreads) void k_slot_plan(const int32_t *__res
     }
 }
 
+// Division by a number the host knows.  32 bits: with m = min(2^32 / d, 2^32 - 1), rounded down, n * m / 2^32 is the quotient
+// or one less.  (In full they would take longer than a block's look-ups.)
+struct Divider {
+    uint64_t d;
+    uint32_t m;
+    __host__ explicit Divider(uint64_t by = 1) : d(by), m(by <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / by)) {}
+    __device__ uint32_t divide(uint32_t n, uint32_t &rest) const {
+        uint32_t q = __umulhi(n, m);
+        rest = n - q * (uint32_t)d;
+        if (rest >= (uint32_t)d) {
+            ++q;
+            rest -= (uint32_t)d;
+        }
+        return q;
+    }
+    __device__ uint64_t divide(uint64_t n, uint64_t &rest) const {
+        const uint64_t q = n / d;
+        rest = n - q * d;
+        return q;
+    }
+};
+
 struct FetchArgs {
     const void *const *K_ptr;
     const void *const *V_ptr;
@@ -135,50 +168,89 @@ struct FetchArgs {
     char *V_win;
     int H, R, slot_tokens, n_native, win_capacity, vec_per_row;
     long long blocks;   // 4 KB blocks that cover one chunk's K, all heads (its V the same)
+    Divider by_blocks, by_units, by_slot_vec;   // by that, by kBlocksPerWg blocks at a time, by the 16-byte vectors of one head
+    bool wide, capped;
 };
 
 // The fetch list's chunks, K and V of each, are laid end to end in blocks of 4 KB (a chunk's heads are contiguous in the
-// store), which the workgroups walk side by side, each with DEPTH of them in flight: about 1 MB in all, or one
-// block per workgroup.  That matters for a store in pinned host memory, which bounds the call there: a burst for all of a chunk
-// at once begins with a storm of address translations.  One chunk of 12 x 1,320 tokens took 187 us with 32 KB in flight in each
-// of 264 workgroups, now 152 us (the copy engine: 151 us).  From HBM it takes 13 us either way, two of 40 x 2,340 43 us.
+// store), which the workgroups walk side by side.
 //
-// I: the type of block and vector numbers (64-bit divisions cost a capped grid more than its loads do).
-template <typename I, int DEPTH>
-__device__ inline void fetch_blocks(const FetchArgs &a, const char *const *src_of, const int *row_of, int n_fetch, unsigned grid) {
-    const I slot_vec = (I)a.slot_tokens * (I)a.vec_per_row, chunk_vec = (I)a.H * slot_vec, blocks = (I)a.blocks;
-    const I total = 2 * blocks * (I)n_fetch;
-    // (a grid capped to a few workgroups walks further with consecutive blocks for each)
-    for (I y0 = blockIdx.x; y0 * (DEPTH == kBlocksPerWg ? DEPTH : 1) < total; y0 += (I)grid * (DEPTH == kBlocksPerWg ? 1 : DEPTH)) {
-        uvec4 buf[DEPTH];
-        I v[DEPTH];
-        int e[DEPTH];   // entry and K / V: 2 * f + (0 or 1)
+// From HBM everything should be in flight at once; from pinned host memory, which bounds the call there, not: a
+// burst for all of a chunk begins with a storm of address translations, and one chunk of 12 x 1,320 tokens takes
+// 187 us with 32 KB in flight in each of 264 workgroups, 154 us (the copy engine: 151 us) with about 1 MB in flight in all.  So
+// each workgroup times its first blocks: if they came within kNearCycles they came from HBM (a load takes 0.3 to 1 us there; 1.1
+// to 2.6 us from the host, and then its turn on the link), and eight times as much is in flight from then on.  From HBM that
+// chunk takes 11.2 us (10.3 us all at once, 12.6 us never more than 1 MB); two of 40 x 2,340 43 us either way.
+// A grid that the caller caps (16 workgroups serve the host link) takes 32 KB per workgroup and trip.
+//
+// The threads of a block share its entry, head and first vector: scalar work; a thread only steps over the heads that
+// begin inside the block.
+constexpr int kNearCycles = 3500;   // about 1.5 us
+
+template <typename I>
+struct Fetch {
+    const FetchArgs &a;
+    I chunk_vec, slot_vec;   // 16-byte vectors of a chunk's K, of one head of it
+
+    // D consecutive runs of kThreads vectors from vector `first` on; entry e = 2 * f + (0: K, 1: V)
+    template <int D>
+    __device__ __forceinline__ void load(uvec4 (&buf)[D], const char *src, I first) const {
 #pragma unroll
-        for (int i = 0; i < DEPTH; ++i) {
-            const I y = DEPTH == kBlocksPerWg ? y0 * DEPTH + i : y0 + i * (I)grid, z = y < total ? y : total - 1;
-            const I q = z / blocks;
-            e[i] = (int)q;
-            v[i] = (z - q * blocks) * kThreads + threadIdx.x;
-            // past the end: the last vector again, and no store
-            const I at = v[i] < chunk_vec ? v[i] : chunk_vec - 1;
-            if (y >= total) v[i] = chunk_vec;
-            buf[i] = __builtin_nontemporal_load(reinterpret_cast<const uvec4 *>(src_of[e[i]]) + at);
-        }
-#pragma unroll
-        for (int i = 0; i < DEPTH; ++i) {
-            const I h = v[i] / slot_vec;
-            uvec4 *win = reinterpret_cast<uvec4 *>(e[i] & 1 ? a.V_win : a.K_win);
-            if (v[i] < chunk_vec)
-                __builtin_nontemporal_store(buf[i], win + ((size_t)h * a.win_capacity + row_of[e[i] >> 1]) * a.vec_per_row + (v[i] - h * slot_vec));
+        for (int i = 0; i < D; ++i) {   // past the end: the last vector again, and no store
+            const I v = first + i * kThreads + threadIdx.x;
+            buf[i] = __builtin_nontemporal_load(reinterpret_cast<const uvec4 *>(src) + (v < chunk_vec ? v : chunk_vec - 1));
         }
     }
-}
+    template <int D>
+    __device__ __forceinline__ void store(const uvec4 (&buf)[D], int e, int row, I first) const {
+        I in_head;
+        const I h = a.by_slot_vec.divide(first, in_head);
+        uvec4 *at = reinterpret_cast<uvec4 *>(e & 1 ? a.V_win : a.K_win) + ((size_t)h * a.win_capacity + row) * a.vec_per_row;
+        if (in_head + D * kThreads <= slot_vec) {   // all in one head, the usual case
+#pragma unroll
+            for (int i = 0; i < D; ++i) __builtin_nontemporal_store(buf[i], at + in_head + i * kThreads + threadIdx.x);
+            return;
+        }
+        in_head += threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            for (; in_head >= slot_vec; in_head -= slot_vec) at += (size_t)a.win_capacity * a.vec_per_row;
+            if (first + i * kThreads + threadIdx.x < chunk_vec) __builtin_nontemporal_store(buf[i], at + in_head);
+            in_head += kThreads;
+        }
+    }
+    // a grid capped to fewer workgroups than that: units of kBlocksPerWg blocks of one entry, all in flight
+    __device__ __forceinline__ void units(int n_fetch) const {
+        const I total = 2 * (I)a.by_units.d * (I)n_fetch;
+        for (I u = blockIdx.x; u < total; u += gridDim.x) {
+            I unit;
+            const int e = (int)a.by_units.divide(u, unit);
+            const int id = a.fetch_id[e >> 1], row = a.n_native + a.fetch_slot[e >> 1] * a.slot_tokens;
+            uvec4 buf[kBlocksPerWg];
+            load(buf, reinterpret_cast<const char *>(e & 1 ? a.V_ptr[id] : a.K_ptr[id]), unit * (kBlocksPerWg * kThreads));
+            store(buf, e, row, unit * (kBlocksPerWg * kThreads));
+        }
+    }
+};
 
 __global__ __launch_bounds__(kThreads) void k_slot_fetch(FetchArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int n_fetch = a.head->n_fetch;
+    if (a.wide) {   // numbers beyond 32 bits
+        const Fetch<uint64_t> fetch{a, (uint64_t)a.H * a.by_slot_vec.d, a.by_slot_vec.d};
+        fetch.units(n_fetch);
+        return;
+    }
+    const Fetch<uint32_t> fetch{a, (uint32_t)a.H * (uint32_t)a.by_slot_vec.d, (uint32_t)a.by_slot_vec.d};
+    if (a.capped) {
+        fetch.units(n_fetch);
+        return;
+    }
+    // as many workgroups as the list needs, of those launched for R entries
+    const uint32_t total = 2 * (uint32_t)a.by_blocks.d * (uint32_t)n_fetch, grid = (uint32_t)fetch_grid(total);
+    if (blockIdx.x >= grid) return;
     const char **src_of = reinterpret_cast<const char **>(lds);   // [2 * n_fetch]: K and V of each entry
     int *row_of = reinterpret_cast<int *>(src_of + 2 * a.R);      // [n_fetch]: first window row of its slot
-    const int n_fetch = a.head->n_fetch;
     for (int f = threadIdx.x; f < n_fetch; f += kThreads) {
         const int id = a.fetch_id[f];
         src_of[2 * f] = reinterpret_cast<const char *>(a.K_ptr[id]);
@@ -186,18 +258,50 @@ __global__ __launch_bounds__(kThreads) void k_slot_fetch(FetchArgs a) {
         row_of[f] = a.n_native + a.fetch_slot[f] * a.slot_tokens;
     }
     __syncthreads();
-    // as many workgroups as the list needs, of those launched for R entries
-    const long long total = 2 * a.blocks * n_fetch, wanted = (total + kBlocksPerWg - 1) / kBlocksPerWg;
-    const unsigned grid = wanted < gridDim.x ? (unsigned)wanted : gridDim.x;
-    if (blockIdx.x >= grid) return;
-    // (the last pass's block numbers run past the total by less than eight grids)
-    if (total + 16ll * grid < (1ll << 31) && a.blocks * kThreads < (1ll << 32)) {
-        if (grid <= 32) fetch_blocks<uint32_t, 8>(a, src_of, row_of, n_fetch, grid);
-        else if (grid <= 64) fetch_blocks<uint32_t, 4>(a, src_of, row_of, n_fetch, grid);
-        else if (grid <= 128) fetch_blocks<uint32_t, 2>(a, src_of, row_of, n_fetch, grid);
-        else fetch_blocks<uint32_t, 1>(a, src_of, row_of, n_fetch, grid);
-    } else {
-        fetch_blocks<uint64_t, 8>(a, src_of, row_of, n_fetch, grid);
+    // D blocks y, y + grid, ...: all requested before the first is stored
+    long long landed = 0;
+    auto blocks = [&](auto depth, uint32_t y, bool timed) __attribute__((always_inline)) {
+        constexpr int D = decltype(depth)::value;
+        uvec4 buf[D][1];
+        uint32_t first[D];
+        int e[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            const uint32_t z = y + i * grid;
+            uint32_t block;
+            e[i] = (int)a.by_blocks.divide(z < total ? z : total - 1, block);
+            first[i] = block * kThreads;
+            fetch.load(buf[i], src_of[e[i]], first[i]);
+            if (z >= total) first[i] = fetch.chunk_vec;
+        }
+        if (timed) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            landed = clock64();
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if (first[i] < fetch.chunk_vec) fetch.store(buf[i], e[i], row_of[e[i] >> 1], first[i]);
+    };
+    uint32_t depth = kBlocksInFlight / grid, y = blockIdx.x;
+    bool timed = true;
+    const long long asked = clock64();
+    while (y < total) {
+        const uint32_t rounds = (total - y + grid - 1) / grid, d = depth < rounds ? depth : rounds;
+        if (d > 4) {
+            blocks(std::integral_constant<int, 8>{}, y, timed);
+            y += 8 * grid;
+        } else if (d > 2) {
+            blocks(std::integral_constant<int, 4>{}, y, timed);
+            y += 4 * grid;
+        } else if (d > 1) {
+            blocks(std::integral_constant<int, 2>{}, y, timed);
+            y += 2 * grid;
+        } else {
+            blocks(std::integral_constant<int, 1>{}, y, timed);
+            y += grid;
+        }
+        if (timed && landed - asked < kNearCycles) depth = 8 * kBlocksInFlight / grid;
+        timed = false;
     }
 }
 
@@ -283,9 +387,16 @@ extern "C" wk_status wk_window_update(const wk_store_desc *store, const int32_t 
     a.V_win = reinterpret_cast<char *>(V_win);
     a.H = store->H; a.R = R; a.slot_tokens = slot_tokens; a.n_native = n_native; a.win_capacity = win_capacity;
     a.vec_per_row = (int)(WK_D * wk::esize(store->dtype) / 16);
-    a.blocks = ((long long)a.H * slot_tokens * a.vec_per_row + kThreads - 1) / kThreads;
-    long long grid = (2 * a.blocks * R + kBlocksPerWg - 1) / kBlocksPerWg;
-    if (max_workgroups > 0 && grid > max_workgroups) grid = max_workgroups;
+    const long long slot_vec = (long long)slot_tokens * a.vec_per_row;
+    a.blocks = (a.H * slot_vec + kThreads - 1) / kThreads;
+    a.by_blocks = Divider(a.blocks);
+    a.by_units = Divider((a.blocks + kBlocksPerWg - 1) / kBlocksPerWg);
+    a.by_slot_vec = Divider(slot_vec);
+    // (block and unit numbers run past their ends by less than eight grids, vector numbers by less than eight blocks)
+    a.wide = 2 * a.blocks * R > (1ll << 26) || a.blocks * kThreads > (1ll << 30);
+    const long long units = 2 * (long long)a.by_units.d * R, wanted = a.wide ? units : fetch_grid(2 * a.blocks * R);
+    a.capped = max_workgroups > 0 && wanted > max_workgroups;
+    long long grid = a.capped ? max_workgroups : wanted;
     if (grid > 0x7fffffffLL) grid = 0x7fffffffLL;
     const size_t lds_bytes = (size_t)R * (2 * sizeof(char *) + sizeof(int));
     hipLaunchKernelGGL(k_slot_fetch, dim3((unsigned)grid), dim3(kThreads), lds_bytes, st, a);

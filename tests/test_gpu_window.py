@@ -197,11 +197,13 @@ def test_slot_refresh_at_the_lingbot_window_size():
         assert torch.equal(bits(Kw[:, :cfg.n_native]), bits(Kn)) and torch.equal(bits(Vw[:, :cfg.n_native]), bits(Vn))
 
 
-# a copy that ends inside a block, by grids that keep eight, four, two and one block per workgroup under way
+# a copy that ends inside a block, by capped grids and by the library's own, with up to eight blocks in flight per workgroup
+# from a store in HBM; heads that begin inside a block, many heads to a block, less than a block
 @pytest.mark.parametrize("max_wg", [1, 7, 40, 100, 0])
+@pytest.mark.parametrize("H,slot_tokens", [(5, 1001), (1, 1), (7, 3), (50, 1), (3, 17), (9, 333), (40, 600)])
 @pytest.mark.parametrize("dtype,pinned", [(torch.bfloat16, True), (torch.bfloat16, False), (torch.float32, False)])
-def test_slot_refresh_grids(dtype, pinned, max_wg):
-    d, H, slot_tokens, M, R, n_native = dev(), 5, 1001, 5, 3, 70
+def test_slot_refresh_grids(dtype, pinned, H, slot_tokens, max_wg):
+    d, M, R, n_native = dev(), 5, 3, 70
     place = (lambda t: t.pin_memory()) if pinned else (lambda t: t.to(d))
     Ks = [place(_pattern(H, slot_tokens, 128, c, 0, dtype)) for c in range(M)]
     Vs = [place(_pattern(H, slot_tokens, 128, c + 50, 0, dtype)) for c in range(M)]
