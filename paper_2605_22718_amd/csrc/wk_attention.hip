@@ -774,7 +774,8 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
     };
     // p = exp2(s*c - m) rounded to bf16; registers 8*t2 .. 8*t2+7 of block b -> k step 2*b + t2.
     // The row sum uses the rounded probabilities, the ones the P V product sees.  Even and odd tiles are summed apart,
-    // as the two wave groups of KG == 2 do, so that the log-sum-exp does not depend on the layout of the launch.
+    // as the two wave groups of KG == 2 do: the log-sum-exp is then the same in every layout of the launch, as long as the key range
+    // is not split and no row's maximum grows by more than 2^8 behind the first tile (the groups' maxima then part).
     auto probabilities = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4], float &l_sum) __attribute__((always_inline)) {
         const float neg_m = -m_run;
         const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -1050,7 +1051,7 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
 // others' exp2; the workgroup's waves meet at a barrier only every second tile.  Same tile layout,
 // loads and arithmetic (bf16-rounded probabilities summed by
 // dot2) as the full kernel: the lse values are bit-identical to those wk_attention returns
-// beside O.
+// beside O, as long as that call neither splits the key range nor lets the maxima of its wave groups part.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) char smem[];
@@ -1365,6 +1366,17 @@ Layout table_layout(const SubTable &t, long long H) {
     return best;
 }
 
+// The visible key ranges of a frame-masked call as launches: entry 0 = the rows behind the chunk for every query (the long items
+// first), entries 1.. = the prefix up to frame f for that frame's queries.
+SubTable frame_table(int N_q, int N_kv, int row0, int frame_T) {
+    SubTable t{};
+    t.n = N_q / frame_T + 1;
+    const int start = row0 + N_q;
+    t.s[0] = SubLaunch{0, N_q, 0, start, N_kv - start, start, 1};
+    for (int f = 0; f + 1 < t.n; ++f) t.s[f + 1] = SubLaunch{f * frame_T, frame_T, 0, 0, row0 + (f + 1) * frame_T, 0, 0};
+    return t;
+}
+
 // fp32: one workgroup fits a compute unit.  The split count with the cheapest rounds of 256 workgroups, a pair of tiles
 // costing 7.9 us, a workgroup's fill and drain 5 us, the merge a launch and its traffic; at least 2 pairs per split, and
 // partial results that fit workspace_bytes.
@@ -1584,13 +1596,7 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
     const int frames = N_q / frame_T;
     const int start = denoise_row0 + N_q;
     if (frames + 1 <= kMaxSub) {
-        // all ranges in one grid: entry 0 = the rows behind the chunk for every query (the long
-        // items first), entries 1.. = the prefix up to frame f for that frame's queries
-        SubTable t;
-        t.n = frames + 1;
-        t.s[0] = SubLaunch{0, N_q, 0, start, N_kv - start, start, 1};
-        for (int f = 0; f < frames; ++f) t.s[f + 1] = SubLaunch{f * frame_T, frame_T, 0, 0, denoise_row0 + (f + 1) * frame_T, 0, 0};
-        for (int e = t.n; e < kMaxSub; ++e) t.s[e] = SubLaunch{0, 0, 0, 0, 0, 0, 0};
+        SubTable t = frame_table(N_q, N_kv, denoise_row0, frame_T);   // all ranges in one grid
         const Layout layout = dtype == WK_F32 ? k256 : table_layout(t, H);   // (fp32 has one of its own)
         const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : queries_per_wg(layout);
         t.per_head = 0;
@@ -1749,6 +1755,15 @@ extern "C" size_t wk_attention_workspace_bytes(int32_t H, int32_t N_q, int32_t N
     }
     const LaunchPlan plan = plan_bf16(H, N_q, N_kv, SIZE_MAX);
     return plan.splits > 1 ? split_workspace_bytes(H, N_q, plan.splits) : 0;
+}
+
+extern "C" int32_t wk_internal_attention_plan(int32_t H, int32_t N_q, int32_t N_kv, size_t workspace_bytes) {
+    const LaunchPlan plan = plan_bf16(H, N_q, N_kv, workspace_bytes);
+    return (int32_t)plan.layout * 100 + plan.splits;
+}
+
+extern "C" int32_t wk_internal_frame_mask_layout(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T) {
+    return N_q / frame_T + 1 <= kMaxSub ? (int32_t)table_layout(frame_table(N_q, N_kv, denoise_row0, frame_T), H) : -1;
 }
 
 extern "C" const char *wk_status_string(wk_status s) {

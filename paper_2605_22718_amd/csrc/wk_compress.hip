@@ -546,7 +546,7 @@ __global__ __launch_bounds__(512, 2) void k_score_gemm(const char *__restrict__ 
         default: contract(I0{}, I0{}); break;
         }
         // fold the block in: accumulator register r of block mb is anchor 128*wa + 16*mb + 4*quad + r
-        // (an empty head range has passed no barrier since the weights were written, and has nothing to add)
+        // (gemm_plan makes no empty head range; one would have passed no barrier since the weights were written)
         if (n_steps > 0)
 #pragma unroll
         for (int mb = 0; mb < 8; ++mb) {
@@ -1240,6 +1240,12 @@ wk_status scratch_of_current_device(char **out) {
 }  // namespace
 
 extern "C" size_t wk_compress_scratch_bytes(void) { return WK_COMPRESS_SCRATCH_BYTES; }
+
+extern "C" int32_t wk_internal_gemm_head_ranges(const wk_compress_desc *desc) {
+    CompressDims p;
+    WsLayout ws;
+    return make_dims(desc, p, ws) ? gemm_plan(p, desc->batch).hsplits : 0;
+}
 
 extern "C" wk_status wk_compress_chunk_noalloc(const wk_compress_desc *desc, const void *K, const void *V,
                                                const void *K_anchor, int32_t *kept_idx, void *K_out,

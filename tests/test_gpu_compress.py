@@ -1,5 +1,7 @@
 """GPU parity of wk_compress_chunk against the oracle (World Compression, Sec. 4.3, Eq. 5).
 Kept-index sets must be bit-exact outside the 1e-6 tie band; compaction is byte-exact."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -187,14 +189,18 @@ def test_selection_of_crowded_scores(kind, T):
             _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], wk.WK_HEADS_SHARED, float(np.float32(rho)), wk.WK_RATIO_NONANCHOR)
 
 
-def test_compaction_past_the_caches():
+# more than 512 MB of K: a batch of whole chunks, and an odd number of kept rows (rho 0.3001) in both types
+@pytest.mark.parametrize("dtype,T,batch,rho", [(torch.bfloat16, 1560, 12, 0.5), (torch.bfloat16, 1559, 12, 0.3001), (torch.float32, 1560, 6, 0.5),
+                                               (torch.float32, 1559, 6, 0.3001)])
+def test_compaction_past_the_caches(dtype, T, batch, rho):
     """A batch larger than the Infinity Cache: its rows are copied past the caches, bit for bit, by the indices returned."""
-    H, T, F, batch, d = 40, 1560, 3, 11, dev()
-    desc = wk.make_compress_desc(H, T, F, wk.WK_BF16, 0.5, batch=batch, ratio_kind=wk.WK_RATIO_NONANCHOR)
+    H, F, d = 40, 3, dev()
+    assert batch * H * F * T * 128 * dtype.itemsize > 512 << 20
+    desc = wk.make_compress_desc(H, T, F, wk.WK_BF16 if dtype == torch.bfloat16 else wk.WK_F32, rho, batch=batch, ratio_kind=wk.WK_RATIO_NONANCHOR)
     n_out, _ = wk.wk_keep_count(desc.rho, desc.ratio_kind, desc.anchor_mode, F, T)
     g = torch.Generator(device=d).manual_seed(3)
-    K, V = (torch.randn((batch, H, F * T, 128), generator=g, device=d, dtype=torch.bfloat16) for _ in range(2))
-    Ko, Vo = (torch.empty((batch, H, n_out, 128), dtype=torch.bfloat16, device=d) for _ in range(2))
+    K, V = (torch.randn((batch, H, F * T, 128), generator=g, device=d, dtype=dtype) for _ in range(2))
+    Ko, Vo = (torch.empty((batch, H, n_out, 128), dtype=dtype, device=d) for _ in range(2))
     idx = torch.empty((batch, 1, n_out), dtype=torch.int32, device=d)
     wk.wk_compress_chunk(desc, K, V, None, idx, Ko, Vo, torch.empty(wk.wk_compress_workspace_bytes(desc), dtype=torch.uint8, device=d))
     for b in range(batch):
@@ -203,13 +209,26 @@ def test_compaction_past_the_caches():
 
 
 # 256 x 256 blocks: one row or candidate beyond a block, every count of 32-row groups in an edge block, anchor blocks past a
-# group of four, more than eight of them (a workgroup walks two), an odd number of heads in unequal ranges
+# group of four, more than eight of them (a workgroup walks two)
 @pytest.mark.parametrize("H,T,F", [(1, 257, 2), (3, 352, 2), (2, 450, 3), (7, 224, 3), (1, 1100, 2), (1, 2081, 2)])
 def test_gemm_scoring_block_edges(H, T, F):
     cfg = ws.get_config(1).with_(H=H, T=T, F=F)
     K, V, _ = ws.make_chunk(cfg, 6)
     gi, gK, gV, gs, _ = _gpu_compress(cfg, K, V, None, rho=0.5, ratio_kind=wk.WK_RATIO_NONANCHOR, score_algo=wk.WK_SCORE_GEMM)
     _compare_chunk(cfg, K, V, None, gi[0], gK[0], gV[0], gs[0], wk.WK_HEADS_SHARED, 0.5, wk.WK_RATIO_NONANCHOR)
+
+
+# several heads per workgroup: a range of one, unequal ranges, all heads in one (the four LDS stages go round five times)
+@pytest.mark.parametrize("H,T,batch,ranges", [(3, 257, 22, 2), (5, 257, 13, 3), (5, 257, 33, 1)])
+def test_gemm_scoring_head_ranges(H, T, batch, ranges):
+    cfg = ws.get_config(1).with_(H=H, T=T, F=2)
+    desc = wk.make_compress_desc(H, T, 2, wk.WK_BF16, 0.5, batch=batch, ratio_kind=wk.WK_RATIO_NONANCHOR, score_algo=wk.WK_SCORE_GEMM)
+    assert wk.lib().wk_internal_gemm_head_ranges(ctypes.byref(desc)) == ranges
+    chunks = [ws.make_chunk(cfg, c) for c in range(batch)]
+    K, V = (torch.stack([c[i] for c in chunks]) for i in range(2))
+    gi, gK, gV, gs, _ = _gpu_compress(cfg, K, V, None, batch=batch, rho=0.5, ratio_kind=wk.WK_RATIO_NONANCHOR, score_algo=wk.WK_SCORE_GEMM)
+    for b in (0, batch // 2, batch - 1):
+        _compare_chunk(cfg, K[b], V[b], None, gi[b], gK[b], gV[b], gs[b], wk.WK_HEADS_SHARED, 0.5, wk.WK_RATIO_NONANCHOR)
 
 
 def test_gemm_scoring_external_anchor_batch_and_fp32_refusal():

@@ -1,4 +1,6 @@
 """Helpers shared by the GPU parity tests (no arithmetic of the method lives here)."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -13,6 +15,25 @@ ATT_MAX_ABS_F32 = 1e-5
 ATT_ROW_REL_L2_BF16 = 6e-3      # per (head, row): |o_gpu - o_ref|_2 / |o_ref|_2
 ATT_MAX_ABS_OVER_RMS_BF16 = 5e-2
 ATT_LSE_ABS_BF16_FULL = 5e-4
+
+
+# layouts of a bf16 attention launch
+K256, K128_PAIR, K128 = 0, 1, 2
+
+
+def attention_plan(H, N_q, N_kv, workspace_bytes=0):
+    """(layout, key ranges) that the library takes for a bf16 call (in-place calls: for the longest window, no workspace)."""
+    import paper_2605_22718_amd as wk
+    f = wk.lib().wk_internal_attention_plan
+    f.argtypes, f.restype = [ctypes.c_int32] * 3 + [ctypes.c_size_t], ctypes.c_int32
+    return divmod(f(H, N_q, N_kv, workspace_bytes), 100)
+
+
+def frame_mask_layout(H, N_q, N_kv, row0, frame_T):
+    import paper_2605_22718_amd as wk
+    f = wk.lib().wk_internal_frame_mask_layout
+    f.argtypes, f.restype = [ctypes.c_int32] * 5, ctypes.c_int32
+    return f(H, N_q, N_kv, row0, frame_T)
 
 
 def dev():
