@@ -1281,13 +1281,14 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
 //             more of work each
 // chosen by the cheapest predicted time.  A step takes longer with more compute units at work, because the chip lowers
 // its clock: busy_us with few of them, full_us with all 256; a workgroup's fill and drain cost fill_steps; a launch has
-// launch_us of its own, whatever its size (a pair's meeting among it); the merge a launch and its traffic.  The figures were
-// fitted to timed launches of 497 shapes (2 to 40 heads, 64 to 4,680 queries, 64 to 211,200 keys, with and without a
-// workspace) in all layouts and split counts: over those the rule's choice is 0.3 % slower than the fastest on average, 11 % at
-// most, and never more than 2 % slower than the choice between k256 with splits and k128 that went before k128Pair.
+// launch_us of its own, whatever its size (a pair's meeting among it); the merge a launch, its traffic and a round trip for
+// every four splits.  The figures were fitted to timed launches of 851 shapes (2 to 40 heads, 64 to 4,680 queries, 64 to
+// 211,200 keys, with and without a workspace, inputs in turn) in all layouts and split counts: over those the rule's choice is
+// 0.4 % slower than the fastest on average, 10 % at most, and never more than 4 % slower than the choice between k256 with splits
+// and k128 that went before k128Pair.
 // k128 is the best for up to 5 tiles and for 7 and 9 (an odd count leaves one wave group of a pair idle for a step): 12 heads x 512
 // queries x 64 keys 6.9 us, in pairs 8.9 us, x 448 13.0 and 13.7 us; x 768 17.4 and 17.0 us.
-// Predictions within 0.3 % count as equal and the fewer splits are taken: 12 heads x 2,640 queries x 211,200 keys take 3.0 ms
+// Predictions of one layout within 0.3 % count as equal and the fewer splits are taken: 12 heads x 2,640 queries x 211,200 keys take 3.0 ms
 // with 11, 13 and 15 splits alike.
 // (Query tiles that walk the same slice of a head's keys run side by side and share it through the L2, which cutting the
 // work into equal runs regardless of item boundaries would give up: that was measured 5 to 14 % slower.)
@@ -1301,7 +1302,7 @@ size_t split_workspace_bytes(int H, int N_q, int splits) {
 }
 
 struct LayoutModel { int qw, kg; double busy_us, full_us, fill_steps, launch_us; };
-constexpr LayoutModel kModel[kLayouts] = {{8, 1, 1.25, 1.26, 1.9, 5.6}, {4, 2, 1.48, 1.67, 1.0, 6.2}, {4, 1, 0.98, 1.08, 5.0, 1.1}};
+constexpr LayoutModel kModel[kLayouts] = {{8, 1, 1.22, 1.35, 1.2, 5.8}, {4, 2, 1.47, 1.67, 1.2, 6.0}, {4, 1, 1.01, 1.04, 5.8, 0.0}};
 
 struct LaunchPlan { Layout layout; int splits; };
 
@@ -1318,7 +1319,7 @@ double launch_us(Layout l, int splits, long long H, long long N_q, int n_tiles) 
     const long long wgs = H * ((N_q + queries_per_wg(l) - 1) / queries_per_wg(l)) * splits;
     const int tiles = (n_tiles + splits - 1) / splits, steps = (tiles + m.kg - 1) / m.kg;
     double us = grid_us(m, wgs, steps);
-    if (splits > 1) us += 2.4 + 2.0 * splits * (double)(H * N_q) * 516.0 / 4.6e6;
+    if (splits > 1) us += 2.0 + 0.86 * ((splits + 3) / 4) + 2.0 * splits * (double)(H * N_q) * 516.0 / 5.1e6;
     return us;
 }
 
@@ -1331,7 +1332,7 @@ LaunchPlan plan_bf16(int H, int N_q, int N_kv, size_t workspace_bytes) {
         for (int sp = 1; sp <= (l == k128 ? 1 : kMaxSplits); ++sp) {
             if (sp > 1 && (n_tiles < std::max(2 * kModel[l].kg * sp, kMinSplitTiles) || split_workspace_bytes(H, N_q, sp) > workspace_bytes)) break;
             const double us = launch_us(l, sp, H, N_q, n_tiles);
-            if (us < 0.997 * best_us) {
+            if (us < (l == best.layout ? 0.997 : 1.0) * best_us) {
                 best_us = us;
                 best = LaunchPlan{l, sp};
             }
@@ -1342,8 +1343,7 @@ LaunchPlan plan_bf16(int H, int N_q, int N_kv, size_t workspace_bytes) {
 
 // The workgroup size of a table of launches, by the same model: the grid's time if every workgroup had the average
 // number of steps, or the longest workgroup's alone.  12 heads x 3 frames of 880 queries on 10,560 keys are 276
-// workgroups of 256 queries, which leave a second round of 20: 220 us; as 504 of 128 queries 171 us.  Predictions within
-// 1 % go to the larger workgroups, which draw less power (8 heads x 2 frames of 1,130 queries x 3,955 keys: 61.7 and 62.7 us).
+// workgroups of 256 queries, which leave a second round of 20: 220 us; as 504 of 128 queries 171 us.
 Layout table_layout(const SubTable &t, long long H) {
     Layout best = k256;
     double best_us = 0;
@@ -1358,7 +1358,7 @@ Layout table_layout(const SubTable &t, long long H) {
             longest = std::max(longest, len);
         }
         const double us = std::fmax(grid_us(m, wgs, (double)steps / (double)wgs), grid_us(m, std::min(wgs, 256ll), (double)longest));
-        if (l == k256 || us < 0.99 * best_us) {
+        if (l == k256 || us < best_us) {
             best = l;
             best_us = us;
         }
