@@ -29,10 +29,10 @@ constexpr int kBlocksPerWg = 8;
 constexpr int kBlocksInFlight = 256;   // 1 MB
 
 // Workgroups for a list of `blocks` blocks: beyond 128 two blocks for each, beyond 512 more of them and one block in flight for
-// each, at most kBlocksPerWg in turn.  (From pinned memory 300 blocks take 31.8 us with 128 workgroups, 35.3 with 256; 660
-// blocks from HBM 9.0 and 8.3 us.)
+// each, at most kBlocksPerWg in turn.  (From pinned memory 300 blocks take 31.8 us with 128 workgroups, 35.3 with 256, and 1,320
+// blocks 104.2 with 192, 105.3 with 256; 660 blocks from HBM 9.0, 8.6 and 8.4 us with 128, 192 and 256.)
 __host__ __device__ inline long long fetch_grid(long long blocks) {
-    const long long few = blocks < 128 ? blocks : (blocks <= 512 ? 128 : 256), many = (blocks + kBlocksPerWg - 1) / kBlocksPerWg;
+    const long long few = blocks < 128 ? blocks : (blocks <= 512 ? 128 : 192), many = (blocks + kBlocksPerWg - 1) / kBlocksPerWg;
     return few > many ? few : many;
 }
 
