@@ -426,12 +426,13 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16: v_mfma_f32_32x32x16_bf16, 8 waves of 32 queries per workgroup, 64-key tiles.
+// bf16: v_mfma_f32_32x32x16_bf16, waves of 32 queries, 64-key tiles.
 //
-// KG == 1: 256 queries, every wave multiplies every tile.  KG == 2 (grids that would leave compute units idle): 128
+// QW == 8: 256 queries in eight waves, every wave multiplies every tile.  QW == 4, KG == 1: 128 queries in four waves, the same
+// steps (compiled; the hand-scheduled loop is for eight waves), for small grids of short windows.  KG == 2 (grids that would leave compute units idle): 128
 // queries; waves 0..3 take the even tiles and waves 4..7 the odd ones for the same queries, and their (O, max, sum) meet
 // in LDS at the end.  That keeps two waves on every SIMD, so that one covers the other's waits: 12 heads x 2,640 queries x
-// 10,560 keys take 162 us, against 178 us with workgroups of four waves (one per SIMD) and 229 us with KG == 1
+// 10,560 keys take 162 us, against 178 us with workgroups of four waves (one per SIMD) and 229 us with QW == 8
 // (132 workgroups for 256 compute units).  Splitting each tile's keys between the two wave groups instead, with one
 // tile per step, halves the work between barriers: 177 us.
 //
