@@ -200,7 +200,7 @@ def test_slot_refresh_at_the_lingbot_window_size():
 # a copy that ends inside a block, by capped grids and by the library's own, with up to eight blocks in flight per workgroup
 # from a store in HBM; heads that begin inside a block, many heads to a block, less than a block
 @pytest.mark.parametrize("max_wg", [1, 7, 40, 100, 0])
-@pytest.mark.parametrize("H,slot_tokens", [(5, 1001), (1, 1), (7, 3), (50, 1), (3, 17), (9, 333), (40, 600)])
+@pytest.mark.parametrize("H,slot_tokens", [(5, 1001), (1, 1), (7, 3), (50, 1), (3, 17), (9, 333), (40, 600), (1200, 3)])
 @pytest.mark.parametrize("dtype,pinned", [(torch.bfloat16, True), (torch.bfloat16, False), (torch.float32, False)])
 def test_slot_refresh_grids(dtype, pinned, H, slot_tokens, max_wg):
     d, M, R, n_native = dev(), 5, 3, 70
