@@ -951,16 +951,16 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
     }
 }
 
-// K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of the rows behind the anchors, copied verbatim.  STREAM: past the caches, for batches that
+// K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of rows first_row and up (behind the anchors), copied verbatim.  STREAM: past the caches, for batches that
 // they cannot hold anyway (kStreamBytes): 64 chunks of 40 heads x 4,680 tokens, whole call 2,159 -> 2,087 us.  Smaller
 // ones find K's rows in the Infinity Cache: four chunks take 298 us, streaming 303; one of 24 x 3,039 28.7 and 30.2.
 constexpr long long kStreamBytes = 512ll << 20;   // of K: twice the Infinity Cache
 
 template <int DT, bool STREAM>
 __global__ __launch_bounds__(256) void k_compact(const char *__restrict__ K, const char *__restrict__ V,
-                                                 CompressDims p, const int32_t *__restrict__ kept_idx,
+                                                 CompressDims p, int first_row, const int32_t *__restrict__ kept_idx,
                                                  char *__restrict__ K_out, char *__restrict__ V_out) {
-    const int r = p.first_cand + blockIdx.x * kRowsPerBlock + threadIdx.x / kRowLanes;
+    const int r = first_row + blockIdx.x * kRowsPerBlock + threadIdx.x / kRowLanes;
     const int sub = threadIdx.x % kRowLanes;
     const int h = blockIdx.y, b = blockIdx.z;
     if (r >= p.n_out) return;
@@ -1217,13 +1217,16 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
             WK_LAUNCH_CHECK();
         }
     }
+    int first_row = p.first_cand;   // of the compaction
     AnchorCopy copy{k_anchors_stored ? nullptr : Kc, Vc, Ko, Vo, d->batch * p.G, (int)(WK_D * wk::esize(DT)), 0, stream};
     auto select = [&](auto kernel, int threads) {
         long long blocks = copy.lists;
         if (p.first_cand > 0) {
             const long long vectors = (long long)p.T * copy.row_bytes / 16;
             copy.units = (unsigned)((vectors + 2 * threads - 1) / (2 * threads));
-            blocks += (long long)d->batch * p.H * (copy.K ? 2 : 1) * copy.units;
+            const long long copies = (long long)d->batch * p.H * (copy.K ? 2 : 1) * copy.units;
+            if ((blocks + copies) * threads <= UINT32_MAX) blocks += copies;   // a launch has fewer than 2^32 threads
+            else first_row = 0;                                                // the compaction copies the anchors too
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, st, scores, p, kept, copy);
     };
@@ -1234,10 +1237,10 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
     else if (p.n_cand <= 2048) select(k_select_held<1024, 2>, 1024);
     else select(k_select_held<1024, 4>, 1024);
     WK_LAUNCH_CHECK();
-    if (p.n_keep == 0) return WK_OK;
-    const dim3 g5((p.n_keep + kRowsPerBlock - 1) / kRowsPerBlock, p.H, d->batch);
-    if (stream) hipLaunchKernelGGL((k_compact<DT, true>), g5, dim3(256), 0, st, Kc, Vc, p, kept, Ko, Vo);
-    else hipLaunchKernelGGL((k_compact<DT, false>), g5, dim3(256), 0, st, Kc, Vc, p, kept, Ko, Vo);
+    if (first_row == p.n_out) return WK_OK;
+    const dim3 g5((p.n_out - first_row + kRowsPerBlock - 1) / kRowsPerBlock, p.H, d->batch);
+    if (stream) hipLaunchKernelGGL((k_compact<DT, true>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, kept, Ko, Vo);
+    else hipLaunchKernelGGL((k_compact<DT, false>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, kept, Ko, Vo);
     WK_LAUNCH_CHECK();
     return WK_OK;
 }

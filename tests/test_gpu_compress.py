@@ -353,3 +353,18 @@ def test_anchors_are_stored_whole(dtype, head_mode, T, F, rho):
     for src, got in zip((K, V), out):
         assert torch.equal(got[:B * H * n_out].view(B, H, n_out, 128), torch.gather(src, 2, rows))
         assert (got[B * H * n_out:] == 7.0).all()
+
+
+# so many small chunks that a copy workgroup for each head's anchors would give the selection's launch 2^32 threads
+@pytest.mark.parametrize("T,batch", [(1, 32768), (2, 32767)])
+def test_two_million_heads_of_anchors(T, batch):
+    d, H = dev(), 64
+    g = torch.Generator(device=d).manual_seed(batch)
+    K, V = (torch.randint(-2 ** 15, 2 ** 15, (batch, H, T, 128), generator=g, device=d, dtype=torch.int16) for _ in range(2))
+    desc = wk.make_compress_desc(H, T, 1, wk.WK_BF16, 0.5, batch=batch, ratio_kind=wk.WK_RATIO_NONANCHOR)
+    idx = torch.full((batch, 1, T), -1, dtype=torch.int32, device=d)
+    out = [torch.full_like(K, 7) for _ in range(2)]
+    ws = torch.empty(wk.wk_compress_workspace_bytes(desc), dtype=torch.uint8, device=d)
+    wk.wk_compress_chunk(desc, K.view(torch.bfloat16), V.view(torch.bfloat16), None, idx, *(x.view(torch.bfloat16) for x in out), ws)
+    assert torch.equal(idx, torch.arange(T, dtype=torch.int32, device=d).expand(batch, 1, T))
+    assert torch.equal(out[0], K) and torch.equal(out[1], V)
