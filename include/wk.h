@@ -113,8 +113,8 @@ size_t wk_compress_workspace_bytes(const wk_compress_desc *desc);
  *   workspace  device, at least wk_compress_workspace_bytes(desc) bytes, 256-byte aligned.
  *              After the call its first batch*G*N_c doubles hold the Eq. 5 scores
  *              ([batch][G][N_c], N_c = candidates per chunk), which callers may read.
- * Errors: INVALID_ARG (null/enum), UNSUPPORTED (d != 128; GEMM scoring with fp32),
- *         RATIO, WORKSPACE. */
+ * Errors: INVALID_ARG (null/enum), UNSUPPORTED (d != 128; GEMM scoring with fp32; so many lists that a launch
+ *         would have 2^32 threads: 2^22 with 1,024 threads a list, fewer candidates more), RATIO, WORKSPACE. */
 wk_status wk_compress_chunk(const wk_compress_desc *desc, const void *K, const void *V,
                             const void *K_anchor, int32_t *kept_idx, void *K_out, void *V_out,
                             int32_t *n_out, void *workspace, size_t workspace_bytes,
@@ -303,7 +303,8 @@ wk_status wk_attention_in_place(const void *Q, const void *K_native, const void 
  *   Q          device, [H][N_q][d], element type store->dtype
  *   scale      logit scale; 0 means 1/sqrt(d)
  *   lse_out    device out, [M][H][N_q] float; -inf where a chunk holds no token
- * Errors: INVALID_ARG, UNSUPPORTED (d != 128, more than 2^31 workgroups, bf16 with max_tok > 2^24 - 512). */
+ * Errors: INVALID_ARG, UNSUPPORTED (d != 128, 2^32 threads and more (at most 512 per chunk, head and 256 queries), bf16 with
+ *         max_tok > 2^24 - 512). */
 wk_status wk_chunk_lse(const wk_store_desc *store, const void *Q, int32_t N_q, float scale,
                        float *lse_out, void *hip_stream);
 

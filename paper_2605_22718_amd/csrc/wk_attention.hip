@@ -1730,13 +1730,14 @@ wk_status launch_bf16(AttnArgs a, LaunchPlan plan, void *workspace, hipStream_t 
     a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
                                           wk::align_up((size_t)a.splits * a.H * a.N_q * WK_D * sizeof(float), 256));
     const long long items = (long long)a.H * a.n_qtiles * a.splits * (a.n_chunks > 0 ? a.n_chunks : 1);
-    if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+    const bool wide = !a.O && lse_wide(a);
+    if (!wk::fits_launch(items + kXcds, wide ? kLseWaves * 64 : kModel[plan.layout].qw * kModel[plan.layout].kg * 64)) return WK_ERR_UNSUPPORTED;
     a.per_xcd = (int)((items + kXcds - 1) / kXcds);
     const wk_status lds_rc = allow_large_lds();
     if (lds_rc != WK_OK) return lds_rc;
     if (!a.O) {
         if (plan.layout != k256) return WK_ERR_UNSUPPORTED;   // the log-sum-exp kernel is laid out for 256-query workgroups
-        if (lse_wide(a)) hipLaunchKernelGGL(k_lse_wide_bf16, dim3(a.per_xcd * kXcds), dim3(kLseWaves * 64), kVRing, st, a);
+        if (wide) hipLaunchKernelGGL(k_lse_wide_bf16, dim3(a.per_xcd * kXcds), dim3(kLseWaves * 64), kVRing, st, a);
         else hipLaunchKernelGGL(k_lse_bf16, dim3(a.per_xcd * kXcds), dim3(512), kVRing, st, a);
     } else if (plan.layout == k256) {
         launch_layout<8, 1, false, false>(a, SubTable{}, st);
@@ -1791,8 +1792,6 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
     const size_t usable_bytes = workspace && reinterpret_cast<uintptr_t>(workspace) % 256 == 0 ? workspace_bytes : 0;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
     if (dtype == WK_F32) {
-        const wk_status lds_rc = allow_large_lds();
-        if (lds_rc != WK_OK) return lds_rc;
         const int q_per_wg = kF32Waves * 32;
         a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
         const long long items1 = (long long)H * a.n_qtiles;
@@ -1801,8 +1800,10 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
                                               wk::align_up((size_t)a.splits * H * N_q * WK_D * sizeof(float), 256));
         const long long items = items1 * a.splits;
-        if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+        if (!wk::fits_launch(items + kXcds, kF32Threads)) return WK_ERR_UNSUPPORTED;
         a.per_xcd = (int)((items + kXcds - 1) / kXcds);
+        const wk_status lds_rc = allow_large_lds();
+        if (lds_rc != WK_OK) return lds_rc;
         hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
         WK_LAUNCH_CHECK();
         if (a.splits > 1) {
@@ -1821,18 +1822,17 @@ namespace {
 // One launch of the attention kernel for the dtype, exactly as the arguments say: no choice of
 // key-range splits, no merge.
 wk_status launch_plain(AttnArgs a, int dtype, hipStream_t st) {
+    const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : 256;
     a.splits = 1;
+    a.n_qtiles = (a.N_q + q_per_wg - 1) / q_per_wg;
+    if (!wk::fits_launch((long long)a.H * a.n_qtiles + kXcds, 512)) return WK_ERR_UNSUPPORTED;
+    a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
     const wk_status rc = allow_large_lds();
     if (rc != WK_OK) return rc;
-    if (dtype == WK_F32) {
-        a.n_qtiles = (a.N_q + kF32Waves * 32 - 1) / (kF32Waves * 32);
-        a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
+    if (dtype == WK_F32)
         hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
-    } else {
-        a.n_qtiles = (a.N_q + 255) / 256;
-        a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
+    else
         launch_layout<8, 1, false, false>(a, SubTable{}, st);
-    }
     WK_LAUNCH_CHECK();
     return WK_OK;
 }
@@ -1901,7 +1901,7 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
             t.per_head += t.s[e].n_qtiles;
         }
         AttnArgs g = a;
-        if ((long long)H * t.per_head + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+        if (!wk::fits_launch((long long)H * t.per_head + kXcds, 512)) return WK_ERR_UNSUPPORTED;
         g.per_xcd = (H * t.per_head + kXcds - 1) / kXcds;
         g.n_qtiles = 0;
         const wk_status lrc = allow_large_lds();
@@ -1979,6 +1979,7 @@ extern "C" wk_status wk_chunk_lse(const wk_store_desc *store, const void *Q, int
     const long long items = (long long)store->M * store->H * ((N_q + q_per_wg - 1) / q_per_wg);
     if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
     if (store->dtype == WK_F32) {
+        if (!wk::fits_launch(items + kXcds, kF32Threads)) return WK_ERR_UNSUPPORTED;
         const wk_status rc = allow_large_lds();
         if (rc != WK_OK) return rc;
         a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
@@ -2033,7 +2034,7 @@ extern "C" wk_status wk_attention_in_place(const void *Q, const void *K_native, 
     const LaunchPlan plan = plan_bf16(a.H, N_q, (int)(longest < 64 ? 64 : (longest > 0x7fffffff ? 0x7fffffff : longest)), 0);
     const int q_per_wg = queries_per_wg(plan.layout);
     a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
-    if ((long long)a.H * a.n_qtiles + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+    if (!wk::fits_launch((long long)a.H * a.n_qtiles + kXcds, kModel[plan.layout].qw * kModel[plan.layout].kg * 64)) return WK_ERR_UNSUPPORTED;
     a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
     const wk_status rc = allow_large_lds();
     if (rc != WK_OK) return rc;

@@ -1088,6 +1088,17 @@ wk_status check_desc(const wk_compress_desc *d) {
     return WK_OK;
 }
 
+int select_threads(const CompressDims &p) { return p.n_cand == 0 || p.n_cand > 512 ? kSelThreads : p.n_cand > 256 ? 512 : 256; }
+
+// the selection's workgroup per list and the similarity GEMM's work items as one launch each
+bool launchable(const wk_compress_desc *d, const CompressDims &p) {
+    const long long lists = (long long)d->batch * p.G;
+    if (!wk::fits_launch(lists, select_threads(p))) return false;
+    if (d->score_algo != WK_SCORE_GEMM || p.n_cand == 0) return true;
+    const GemmPlan plan = gemm_plan(p, d->batch);
+    return wk::fits_launch(lists * plan.hsplits * plan.asplits * ((p.n_cand + kGemmTile - 1) / kGemmTile) + kXcds, 512);
+}
+
 // k_anchor_norm_mean for the plan's rows-per-group count; its LDS (four waves' sums of H x 128 floats) can exceed
 // the default 64 KB of dynamic LDS, so the limit is raised once per device and instantiation.
 template <int DT, int IT>
@@ -1181,8 +1192,7 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
                         return WK_ERR_HIP;
                     wk::mark_device(lds_limit_set, dev);
                 }
-                const long long ranges = (long long)d->batch * p.G * hsplits, items = ranges * asplits * cand_tiles;
-                if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+                const long long ranges = (long long)d->batch * p.G * hsplits, items = ranges * asplits * cand_tiles;   // (launchable has looked)
                 const int per_xcd = (int)((items + kXcds - 1) / kXcds);
                 hipLaunchKernelGGL(k_score_gemm, dim3(per_xcd * kXcds), dim3(512), kGemmLds, st, Kc, A, p, nsq, asplits, hsplits,
                                    (int)ranges, per_xcd, partial);
@@ -1225,17 +1235,18 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
             const long long vectors = (long long)p.T * copy.row_bytes / 16;
             copy.units = (unsigned)((vectors + 2 * threads - 1) / (2 * threads));
             const long long copies = (long long)d->batch * p.H * (copy.K ? 2 : 1) * copy.units;
-            if ((blocks + copies) * threads <= UINT32_MAX) blocks += copies;   // a launch has fewer than 2^32 threads
-            else first_row = 0;                                                // the compaction copies the anchors too
+            if (wk::fits_launch(blocks + copies, threads)) blocks += copies;
+            else first_row = 0;   // the compaction copies the anchors too
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, st, scores, p, kept, copy);
     };
-    if (p.n_cand == 0 || p.n_cand > kSelHeld) select(k_select, kSelThreads);
-    else if (p.n_cand <= 256) select(k_select_held<256, 1>, 256);
-    else if (p.n_cand <= 512) select(k_select_held<512, 1>, 512);
-    else if (p.n_cand <= 1024) select(k_select_held<1024, 1>, 1024);
-    else if (p.n_cand <= 2048) select(k_select_held<1024, 2>, 1024);
-    else select(k_select_held<1024, 4>, 1024);
+    const int threads = select_threads(p);
+    if (p.n_cand == 0 || p.n_cand > kSelHeld) select(k_select, threads);
+    else if (threads == 256) select(k_select_held<256, 1>, threads);
+    else if (threads == 512) select(k_select_held<512, 1>, threads);
+    else if (p.n_cand <= 1024) select(k_select_held<1024, 1>, threads);
+    else if (p.n_cand <= 2048) select(k_select_held<1024, 2>, threads);
+    else select(k_select_held<1024, 4>, threads);
     WK_LAUNCH_CHECK();
     if (first_row == p.n_out) return WK_OK;
     const dim3 g5((p.n_out - first_row + kRowsPerBlock - 1) / kRowsPerBlock, p.H, d->batch);
@@ -1295,6 +1306,7 @@ extern "C" wk_status wk_compress_chunk(const wk_compress_desc *desc, const void 
     if (!make_dims(desc, p, ws)) return WK_ERR_INVALID_ARG;
     if (!workspace || workspace_bytes < ws.total) return WK_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return WK_ERR_WORKSPACE;
+    if (!launchable(desc, p)) return WK_ERR_UNSUPPORTED;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     char *wsp = reinterpret_cast<char *>(workspace);
     if (desc->dtype == WK_BF16)

@@ -25,6 +25,9 @@ namespace wk {
 
 __host__ __device__ inline size_t esize(int dtype) { return dtype == WK_BF16 ? 2 : 4; }
 
+// A launch has fewer than 2^32 threads: the runtime drops the bits above without an error.
+inline bool fits_launch(long long workgroups, int threads) { return workgroups * threads <= UINT32_MAX; }
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Once per device and process: true if `flags` did not yet have the current device's bit (the caller then

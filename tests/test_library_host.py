@@ -225,6 +225,29 @@ def test_argument_validation_of_the_other_calls():
     assert L.wk_host_device_pointer(None, None) == wk.WK_ERR_INVALID_ARG
 
 
+def test_launches_of_two_to_the_32_threads_are_refused():
+    """The runtime takes them and drops the upper bits: part of the work would be left out without an error."""
+    L = wk.lib()
+    one, size = C.c_void_p(256), 1 << 50   # never dereferenced
+    H = 1 << 25
+    for dtype in (wk.WK_BF16, wk.WK_F32):
+        assert L.wk_attention(one, one, one, one, None, H, 1, 64, 128, 64, dtype, 0.0, None, None, 0, None) == wk.WK_ERR_UNSUPPORTED
+        assert L.wk_attention(one, one, None, None, one, H, 1, 64, 128, 64, dtype, 0.0, None, None, 0, None) == wk.WK_ERR_UNSUPPORTED
+        for frames in (2, 8):   # one table of launches, a launch per range
+            assert L.wk_attention_block_causal(one, one, one, one, None, H, frames, 64, 128, 64, dtype, 0.0, None, 0, 1, one, size,
+                                               None) == wk.WK_ERR_UNSUPPORTED
+    for dtype, M, heads, max_tok, N_q in ((wk.WK_BF16, 1 << 20, 8, 64, 300), (wk.WK_BF16, 1 << 20, 8, 1560, 300), (wk.WK_F32, 1 << 20, 8, 64, 1)):
+        store = wk.wk_store_desc(256, 256, 256, M, max_tok, heads, 128, dtype)
+        assert L.wk_chunk_lse(C.byref(store), one, N_q, 0.0, one, None) == wk.WK_ERR_UNSUPPORTED
+    store = wk.wk_store_desc(256, 256, 256, 4, 64, H, 128, wk.WK_BF16)
+    assert L.wk_attention_in_place(one, one, one, 64, 64, C.byref(store), one, None, 2, one, None, 1, 0.0, None) == wk.WK_ERR_UNSUPPORTED
+    for F, T, batch, heads, algo in ((1, 1, 1 << 16, 64, wk.WK_SCORE_FACTORED), (2, 1, 1 << 18, 64, wk.WK_SCORE_FACTORED),
+                                     (2, 400, 1 << 17, 64, wk.WK_SCORE_FACTORED), (2, 1, 1 << 17, 64, wk.WK_SCORE_GEMM)):
+        d = wk.make_compress_desc(heads, T, F, wk.WK_BF16, 0.5, batch=batch, head_mode=wk.WK_HEADS_INDEPENDENT, ratio_kind=wk.WK_RATIO_NONANCHOR,
+                                  score_algo=algo)
+        assert L.wk_compress_chunk(C.byref(d), one, one, None, None, one, one, None, one, size, None) == wk.WK_ERR_UNSUPPORTED
+
+
 def test_window_plan_matches_the_rolling_window_simulation():
     """The planner's row arithmetic, applied to a label array standing for the window rows, must put
     every generated chunk exactly where the oracle's simulation says it lives (Sec. 4.2 regions)."""
