@@ -1722,13 +1722,17 @@ void launch_layout(const AttnArgs &a, const SubTable &t, hipStream_t st) {
                        KG == 1 ? kSmemBytes : kSmemBytesPair, st, a, t);
 }
 
+void partials_in(AttnArgs &a, void *workspace) {   // (O, then maximum and sum) of a.splits key ranges
+    a.part_o = reinterpret_cast<float *>(workspace);
+    a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
+                                          wk::align_up((size_t)a.splits * a.H * a.N_q * WK_D * sizeof(float), 256));
+}
+
 wk_status launch_bf16(AttnArgs a, LaunchPlan plan, void *workspace, hipStream_t st) {
     const int q_per_wg = queries_per_wg(plan.layout);
     a.n_qtiles = (a.N_q + q_per_wg - 1) / q_per_wg;
     a.splits = plan.splits;
-    a.part_o = reinterpret_cast<float *>(workspace);
-    a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
-                                          wk::align_up((size_t)a.splits * a.H * a.N_q * WK_D * sizeof(float), 256));
+    if (a.splits > 1) partials_in(a, workspace);
     const long long items = (long long)a.H * a.n_qtiles * a.splits * (a.n_chunks > 0 ? a.n_chunks : 1);
     const bool wide = !a.O && lse_wide(a);
     if (!wk::fits_launch(items + kXcds, wide ? kLseWaves * 64 : kModel[plan.layout].qw * kModel[plan.layout].kg * 64)) return WK_ERR_UNSUPPORTED;
@@ -1796,9 +1800,7 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
         a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
         const long long items1 = (long long)H * a.n_qtiles;
         a.splits = O ? choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, usable_bytes) : 1;
-        a.part_o = reinterpret_cast<float *>(workspace);
-        a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
-                                              wk::align_up((size_t)a.splits * H * N_q * WK_D * sizeof(float), 256));
+        if (a.splits > 1) partials_in(a, workspace);
         const long long items = items1 * a.splits;
         if (!wk::fits_launch(items + kXcds, kF32Threads)) return WK_ERR_UNSUPPORTED;
         a.per_xcd = (int)((items + kXcds - 1) / kXcds);
