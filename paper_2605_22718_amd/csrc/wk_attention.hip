@@ -2064,12 +2064,6 @@ extern "C" int32_t wk_internal_attention_plan(int32_t H, int32_t N_q, int32_t N_
     return (int32_t)plan.layout * 100 + plan.splits;
 }
 
-// the workgroups that the two-range form of a frame-masked call takes, and the form and workgroups that the call takes (+ 100: two ranges)
-extern "C" int32_t wk_internal_frame_mask_layout(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T) {
-    double us = 0;
-    return N_q / frame_T + 1 <= kMaxSub ? (int32_t)table_layout(frame_table(N_q, N_kv, denoise_row0, frame_T), H, us) : -1;
-}
-
 extern "C" int32_t wk_internal_frame_mask_plan(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T) {
     if (N_q / frame_T + 1 > kMaxSub) return -1;
     const FramePlan p = plan_frames(H, N_q, N_kv, denoise_row0, frame_T);

@@ -16,9 +16,10 @@
     } while (0)
 
 // Not part of the interface: the tests pin with these that a shape takes the path it is there for.  How bf16 attention would
-// be launched (0: 256 queries per workgroup, 1: 128 in pairs of tiles, 2: 128); head ranges of the similarity GEMM.
+// be launched (0: 256 queries per workgroup, 1: 128 in pairs of tiles, 2: 128), under a frame mask (+ 100: as two key ranges, else as windows
+// with a gap; -1: more frames than the table of launches holds); head ranges of the similarity GEMM.
 extern "C" int32_t wk_internal_attention_plan(int32_t H, int32_t N_q, int32_t N_kv, size_t workspace_bytes);   // layout * 100 + key ranges
-extern "C" int32_t wk_internal_frame_mask_layout(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T);
+extern "C" int32_t wk_internal_frame_mask_plan(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T);
 extern "C" int32_t wk_internal_gemm_head_ranges(const wk_compress_desc *desc);
 
 namespace wk {

@@ -7,8 +7,8 @@ import torch
 
 import oracle
 import paper_2605_22718_amd as wk
-from wkt import (ATT_MAX_ABS_F32, K128, K128_PAIR, K256, assert_attention_close_bf16, attention_errors, attention_plan, dev,
-                 frame_mask_layout)
+from wkt import (ATT_MAX_ABS_F32, K128, K128_PAIR, K256, TWO_RANGES, assert_attention_close_bf16, attention_errors, attention_plan, dev,
+                 frame_mask_plan)
 
 pytestmark = pytest.mark.gpu
 
@@ -206,19 +206,24 @@ def test_large_grids_in_place(n_native, lens, ids):
     _check_rows(Q, *(torch.cat([p[i] for p in window], 1) for i in range(2)), O, lse)
 
 
-# the frame mask's table of launches in 128-query workgroups (small grids) and in 256-query ones: frames that end
-# inside a query tile, a key range behind the chunk that is empty, one key, and an odd count of tiles
-@pytest.mark.parametrize("H,T,row0,n_after,n_dev,layout", [(2, 250, 0, 0, None, K128_PAIR), (2, 129, 64, 1, None, K128_PAIR), (3, 249, 130, 191, None, K128_PAIR),
-                                                           (64, 130, 130, 191, None, K256), (48, 300, 0, 0, None, K256), (48, 300, 70, 1, None, K256),
-                                                           (48, 300, 70, 300, 70 + 900, K256), (64, 130, 130, 300, 130 + 390 + 1, K256)])
-def test_frame_mask_layouts(H, T, row0, n_after, n_dev, layout):
-    N_q, d = 3 * T, dev()
-    assert frame_mask_layout(H, N_q, row0 + N_q + n_after, row0, T) == layout
+# the frame mask's tables of launches, windows with a gap and two key ranges, each in 128-query workgroups (small grids) and in 256-query
+# ones: frames that end inside a query tile; behind the chunk an odd count of tiles, one key, no key, by the host's length and by the device's
+@pytest.mark.parametrize("H,T,F,row0,n_after,n_dev,plan", [
+    (2, 250, 3, 0, 0, None, K128_PAIR), (2, 129, 3, 64, 1, None, K128_PAIR), (3, 249, 3, 130, 191, None, K128_PAIR), (48, 300, 3, 0, 0, None, K128_PAIR),
+    (48, 300, 3, 70, 1, None, K128_PAIR), (48, 300, 3, 70, 300, 70 + 900, K128_PAIR), (64, 130, 3, 130, 191, None, K256),
+    (64, 130, 3, 130, 300, 130 + 390 + 1, K256),
+    (39, 21, 7, 847, 0, None, TWO_RANGES + K128_PAIR), (44, 22, 6, 918, 1, None, TWO_RANGES + K128_PAIR), (6, 162, 3, 324, 567, None, TWO_RANGES + K128_PAIR),
+    (6, 162, 3, 324, 567, 324 + 486, TWO_RANGES + K128_PAIR), (6, 162, 3, 324, 567, 324 + 486 + 1, TWO_RANGES + K128_PAIR),
+    (44, 129, 6, 685, 0, None, TWO_RANGES + K256), (57, 129, 5, 862, 1, None, TWO_RANGES + K256), (47, 132, 3, 483, 648, None, TWO_RANGES + K256),
+    (47, 132, 3, 483, 648, 483 + 396, TWO_RANGES + K256), (47, 132, 3, 483, 648, 483 + 396 + 1, TWO_RANGES + K256)])
+def test_frame_mask_layouts(H, T, F, row0, n_after, n_dev, plan):
+    N_q, d = F * T, dev()
+    assert frame_mask_plan(H, N_q, row0 + N_q + n_after, row0, T) == plan
     Q, K, V = _inputs(H, N_q, row0 + N_q + n_after, seed=T + H)
     O, lse = torch.empty_like(Q, device=d), torch.empty(Q.shape[:2], device=d)
     ws = torch.empty(wk.wk_attention_block_causal_workspace_bytes(H, N_q), dtype=torch.uint8, device=d)
     wk.wk_attention_block_causal(Q.to(d), K.to(d), V.to(d), O, row0, T, ws, lse=lse, n_kv_dev=_device_int(n_dev))
-    rows = np.arange(N_q, dtype=np.int32) if H < 10 else np.unique([0, T - 1, T, 2 * T - 1, 2 * T, 255, 256, N_q - 1]).astype(np.int32)
+    rows = np.arange(N_q, dtype=np.int32) if H < 10 else np.unique([r for r in (0, T - 1, T, 2 * T - 1, 2 * T, 255, 256, N_q - 1) if r < N_q]).astype(np.int32)
     ref, ref_lse = oracle.attention_block_causal(Q, K, V, row0, T, N_kv=n_dev, rows=rows, want_lse=True)
     sel = torch.as_tensor(rows, dtype=torch.long)
     assert_attention_close_bf16(O.cpu()[:, sel], ref, lse.cpu()[:, sel], ref_lse)

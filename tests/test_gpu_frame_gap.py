@@ -1,7 +1,6 @@
 """The frame mask as windows that leave rows out (k_attn_bf16<.., GAP>): the tile with the first row behind the gap wherever it can
 fall -- in front of the hand-scheduled loop, at each step of it, behind it --, at both ends of a tile, and windows that end in front of, at
 and inside it.  Against the oracle, with the bounds of bf16 attention."""
-import ctypes
 import importlib.util
 import os
 
@@ -11,16 +10,9 @@ import torch
 
 import oracle
 import paper_2605_22718_amd as wk
-from wkt import K128_PAIR, K256, assert_attention_close_bf16, dev
+from wkt import K128_PAIR, K256, TWO_RANGES, assert_attention_close_bf16, dev, frame_mask_plan
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_22718_amd", "csrc")
-TWO_RANGES = 100
-
-
-def frame_mask_plan(H, N_q, N_kv, row0, frame_T):
-    f = wk.lib().wk_internal_frame_mask_plan
-    f.argtypes, f.restype = [ctypes.c_int32] * 5, ctypes.c_int32
-    return f(H, N_q, N_kv, row0, frame_T)
 
 
 def test_gap_loops_are_what_their_generator_writes():

@@ -29,9 +29,13 @@ def attention_plan(H, N_q, N_kv, workspace_bytes=0):
     return divmod(f(H, N_q, N_kv, workspace_bytes), 100)
 
 
-def frame_mask_layout(H, N_q, N_kv, row0, frame_T):
+TWO_RANGES = 100   # + a layout: two key ranges and a merge, else windows with a gap
+
+
+def frame_mask_plan(H, N_q, N_kv, row0, frame_T):
+    """How the library launches a frame-masked bf16 call."""
     import paper_2605_22718_amd as wk
-    f = wk.lib().wk_internal_frame_mask_layout
+    f = wk.lib().wk_internal_frame_mask_plan
     f.argtypes, f.restype = [ctypes.c_int32] * 5, ctypes.c_int32
     return f(H, N_q, N_kv, row0, frame_T)
 
