@@ -1,5 +1,5 @@
-"""Anchor rows of K stored by the similarity GEMM's norm pass: whole rows at their places, nothing behind them, the same scores and selections
-as the chunks give one at a time (whose anchors are copied beside the selection)."""
+"""Anchor rows of K stored by the similarity GEMM's norm pass: whole rows at their places, nothing behind them, the scores that the chunks
+give one at a time (whose anchors are copied beside the selection), and the selection that belongs to them."""
 import pytest
 import torch
 
@@ -35,7 +35,11 @@ def test_rows_scores_and_selections(B, H, T, F, head_mode):
     for src, got in zip((K, V), out):
         assert torch.equal(got[:B * H * n_out].view(B, H, n_out, 128), torch.gather(src, 2, rows))
         assert (got[B * H * n_out:] == 7.0).all()
-    for b in (0, B - 1):
-        _, _, one = call(K[b:b + 1].contiguous(), V[b:b + 1].contiguous(), 0)
-        # other head ranges: fp32 partial sums in another order
-        assert (scores[b] - one[0]).abs().max().item() <= 1e-6 if one.numel() else True
+    # the lowest scores, the lower index where they tie, in ascending order
+    kept = torch.sort(scores, dim=-1, stable=True).indices[..., :n_out - T].sort(dim=-1).values
+    assert torch.equal(idx[..., T:], (kept + T).to(torch.int32))
+    if F > 1:
+        for b in (0, B - 1):
+            _, _, one = call(K[b:b + 1].contiguous(), V[b:b + 1].contiguous(), 0)
+            # other head ranges: fp32 partial sums in another order
+            assert (scores[b] - one[0]).abs().max().item() <= 1e-6
