@@ -1,6 +1,6 @@
 """The frame mask as windows that leave rows out (k_attn_bf16<.., GAP>): the tile with the first row behind the gap wherever it can
-fall -- in front of the hand-scheduled loop, at each step of it, behind it --, at both ends of a tile, and windows that end in front of, at
-and inside it.  Against the oracle, with the bounds of bf16 attention."""
+fall -- in front of the hand-scheduled loop, at each step of it, behind it --, at both ends of a tile, and windows that the device ends where
+the gap does (no window may end earlier) or behind it.  Against the oracle, with the bounds of bf16 attention."""
 import importlib.util
 import os
 
