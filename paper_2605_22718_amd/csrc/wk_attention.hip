@@ -917,7 +917,7 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
             unsigned koff = (unsigned)(t0 + 4) * kTileBytes, voff = (unsigned)(t0 + 4 - KG) * kTileBytes;
             // the tile with the first row behind the gap, and the steps up to the one that requests its K tile
             const unsigned gap_tile = gap_from / kTileBytes * kTileBytes;
-            const int to_gap = (((int)(gap_from / kTileBytes) - t0 - 4) >> (KG - 1)) + 2;
+            int gap_steps = (((int)(gap_from / kTileBytes) - t0 - 4) >> (KG - 1)) + 2;
             if constexpr (GAP) {
                 if (koff > gap_tile) koff += gap_bytes;
                 if (voff > gap_tile) voff += gap_bytes;
@@ -927,7 +927,6 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
             const bf16x8 q0 = qb[0], q1 = qb[1], q2 = qb[2], q3 = qb[3], q4 = qb[4], q5 = qb[5], q6 = qb[6], q7 = qb[7];
             f32x16 o0 = o[0], o1 = o[1], o2 = o[2], o3 = o[3], sa0 = s_a[0], sa1 = s_a[1];
             const unsigned ks0 = k_src[0], ks1 = k_src[NB - 1], vs0 = v_src[0], vs1 = v_src[NB - 1];
-int gap_steps = to_gap;
 #define WK_ATTN_LOOP_OUT "+{v[0:15]}"(o0), "+{v[16:31]}"(o1), "+{v[32:47]}"(o2), "+{v[48:63]}"(o3), "+{v[64:79]}"(sa0), \
                   "+{v[80:95]}"(sa1), "+{v240}"(m_run), "+{v241}"(l_run[0]), "+{v242}"(l_run[1]), "+{v243}"(mt), "+{s44}"(g_left)
 #define WK_ATTN_LOOP_IN "{v[128:131]}"(q0), "{v[132:135]}"(q1), "{v[136:139]}"(q2), "{v[140:143]}"(q3), "{v[144:147]}"(q4), \

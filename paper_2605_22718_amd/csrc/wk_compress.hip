@@ -43,14 +43,14 @@ __device__ inline double head_split_sum(double x) {
     return x;
 }
 
-// |key first_row + i|^2, i < n_rows, over the heads of group g; src is [batch][H][rows_per_head][128].  The first n_first of them
+// |key i|^2, i < n_rows, over the heads of group g; src is [batch][H][rows_per_head][128].  The first n_first of them
 // go to out[(b*G+g)*n_first + i], the others to rest[(b*G+g)*(n_rows-n_first) + i - n_first]: anchors and candidates of a
 // similarity GEMM lie side by side and take one launch (four chunks of 40 heads x 4,680 tokens: 40 us as two, 37 as one).
 // STORE: the anchors' rows go to K_out as they pass, instead of being read once more beside the selection.
 template <int DT, int HS, bool STORE>
 __global__ __launch_bounds__(256) void k_rows_normsq(const char *__restrict__ src, CompressDims p, int rows_per_head,
-                                                     int first_row, int n_rows, int n_first, double *__restrict__ out,
-                                                     double *__restrict__ rest, char *__restrict__ K_out) {
+                                                     int n_rows, int n_first, double *__restrict__ out, double *__restrict__ rest,
+                                                     char *__restrict__ K_out) {
     const int i = blockIdx.x * (kRowsPerBlock / HS) + threadIdx.x / (kRowLanes * HS);
     const int hq = (threadIdx.x / kRowLanes) % HS;
     const int sub = threadIdx.x % kRowLanes;
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void k_rows_normsq(const char *__restrict__ sr
     if (i >= n_rows) return;
     const size_t row_bytes = WK_D * wk::esize(DT);
     const size_t head_bytes = (size_t)rows_per_head * row_bytes;
-    const char *base = src + ((size_t)b * p.H * rows_per_head + first_row + i) * row_bytes;
+    const char *base = src + ((size_t)b * p.H * rows_per_head + i) * row_bytes;
     double acc = 0.0;
     for (int hh0 = hq; hh0 < p.hg; hh0 += HS * kHeadBatch) {
         float v[kHeadBatch][8];
@@ -1159,7 +1159,7 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
         auto norms = [&](const char *src, int rows_per_head, int n_rows, int n_first, double *out) {
             const dim3 grid((n_rows + rows_pb - 1) / rows_pb, p.G, d->batch);
             auto launch = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, src, p, rows_per_head, 0, n_rows, n_first, out, nsq_cand, Ko);
+                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, src, p, rows_per_head, n_rows, n_first, out, nsq_cand, Ko);
             };
             if constexpr (DT == WK_BF16) {
                 if (k_anchors_stored) return split ? launch(k_rows_normsq<DT, 4, true>) : launch(k_rows_normsq<DT, 1, true>);
