@@ -1246,9 +1246,10 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
 // the reference moves up (by a power of two, which changes no rounding).  A weight far above the others is thus exact, as it is
 // with a maximum that moves; against 64 bits the error is 0.9 of k_lse_bf16's where keys stand out, and the same (to the bit) where
 // no tile's sum grows that far.  Every K fragment read from LDS feeds two products.
-// 120 chunks of 1,560 keys, 40 heads x 4,680 queries: 15.8 M cycles at 1.78 GHz, 8.9 ms (matrix pipe busy 56 %), where k_lse_bf16
-// takes 18.4 M at 1.92 GHz, 9.6 ms; this layout with the maxima 18.5 M, 9.4 ms.  Depths of the reads ahead and the place of the
-// vector work change nothing (0.3 %) as long as it leaves no gap: without it beside a step's first three products 18.0 M.
+// 120 chunks of 1,560 keys, 40 heads x 4,680 queries, both in turn on one box: 15.7 M cycles at 1.73 GHz, 8.99 ms (matrix pipe busy
+// 57 %, vector pipe 71 %), k_lse_bf16 18.4 M at 1.79 GHz, 10.27 ms; this layout with the maxima 18.5 M.  Depths of the reads ahead and
+// the place of the vector work change nothing (0.3 %) as long as it leaves no gap: without it beside a step's first three products 18.0 M.
+// Nothing lies in scratch: three registers of query numbers that did wrote 265 MB a launch beside its 90 MB of results.
 // ------------------------------------------------------------------------------------------
 #define WK_LSE_LOOP_CLOBBERS \
     "v64", "v65", "v66", "v67", "v68", "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", \
@@ -1267,9 +1268,9 @@ __global__ __launch_bounds__(kLseWaves * 64, 2) void k_lse_wide_bf16(AttnArgs a)
     if (!work_item(a, c, h, qt, sp)) return;
     const Window win = window_of(a, c);
     const int n_kv = win.n_kv;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 31, g = lane >> 5;
+    int lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int q0 = qt * 256 + wave * 64;   // the wave's first query; a lane has q0 + col and q0 + 32 + col
     float *const out = win.lse + (size_t)h * a.q_rows + a.q_off;
     if (n_kv == 0) {
@@ -1428,6 +1429,9 @@ __global__ __launch_bounds__(kLseWaves * 64, 2) void k_lse_wide_bf16(AttnArgs a)
         s_a[0][0] = s00; s_a[0][1] = s01; s_a[1][0] = s10; s_a[1][1] = s11;
         qb[0][0] = q00; qb[0][1] = q01; qb[0][2] = q02; qb[0][3] = q03; qb[0][4] = q04; qb[0][5] = q05; qb[0][6] = q06; qb[0][7] = q07;
         qb[1][0] = q10; qb[1][1] = q11; qb[1][2] = q12; qb[1][3] = q13; qb[1][4] = q14; qb[1][5] = q15; qb[1][6] = q16; qb[1][7] = q17;
+        // (known anew, so that nothing made of them waits in scratch while the loop has the registers)
+        asm("" : "+v"(lane));
+        col = lane & 31, g = lane >> 5;
         mask_tail(s_a);   // the last tile: the only one that can be partial
     }
     if (n_steps & 1) swap_parity();
@@ -1710,9 +1714,11 @@ wk_status allow_large_lds() {
     return WK_OK;
 }
 
-// k_lse_wide_bf16 where windows are long enough for its loop to matter and its four waves have queries, by the bound that the
-// host knows: 4 chunks of 1,560 keys x 40 heads x 256 queries 32.0 -> 29.2 us, 60 of 880 x 12 x 2,640 501 -> 466, 135 of 680 x 26 x 1,780 1,267 ->
-// 1,184; but 1 of 601 x 8 x 877 15.6 -> 16.6, 60 of 256 x 12 x 2,640 163 -> 176, 117 of 597 x 8 x 143 43.7 -> 47.5.
+// k_lse_wide_bf16 where windows are long enough for its loop to matter and its four waves have queries: 8 chunks of 1,560 keys x 40
+// heads x 256 queries 55.2 -> 48.1 us, 24 of 640 x 8 x 877 36.9 -> 33.9, one of 641 x 16 x 1,000 15.8 -> 14.8; but one of 601 x 8 x 877 15.6 -> 16.6,
+// 117 of 597 x 8 x 143 43.7 -> 47.5.  A store's lengths lie on the device, and the host goes by its bound, max_tok: chunks that are much
+// shorter gain nothing (60 of 256 keys x 12 x 2,640 154 -> 148 us, 24 x 8 x 877 18.0 -> 18.0), and lose up to 4 % where they are few
+// (8 of 256 x 40 x 256 13.6 -> 14.1); one long chunk in eight outweighs that (51.4 -> 43.8).
 bool lse_wide(const AttnArgs &a) { return (a.n_chunks > 0 ? a.max_tok : a.N_kv) > 10 * kKeys && a.N_q > 192; }
 
 template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP = false>

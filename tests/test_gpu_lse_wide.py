@@ -1,7 +1,11 @@
 """The log-sum-exp alone over windows long enough for its own workgroup layout (64 queries a wave, every score against a reference
 that seldom moves): every count of left-over tiles, rows and queries, and scores far above the first tile's."""
+import glob
 import importlib.util
 import os
+import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -23,6 +27,22 @@ def test_loop_is_what_its_generator_writes():
     # two steps of 32 matrix instructions, the first LEAD once more in front of the loop, what either last step keeps back behind it
     assert sum(ln.startswith("v_mfma") for ln in lines) == 2 * 32 + gen.LEAD + 2 * gen.BACK
     assert sum(ln == "s_barrier" for ln in lines) == 2
+    # a trip leaves for code behind the loop where a sum has grown or the loop ends, and branches nowhere else
+    trip = lines[lines.index("L_trip_%=:"):lines.index("s_cbranch_scc0 L_trip_%=")]
+    assert [re.sub(r"\d.*", "", ln) for ln in trip if "branch" in ln] == ["s_cbranch_scc"] * 5
+    assert all(ln.startswith(("s_cbranch_scc1 L_grown", "s_cbranch_scc1 L_odd")) for ln in trip if "branch" in ln)
+
+
+def test_no_register_waits_in_scratch(tmp_path):
+    tools = "/opt/rocm/llvm/bin"
+    if not os.path.exists(os.path.join(tools, "llvm-readelf")):
+        pytest.skip("no llvm-readelf")
+    shutil.copy(os.path.join(os.path.dirname(CSRC), "libwk.so"), tmp_path)
+    subprocess.run([os.path.join(tools, "llvm-objdump"), "--offloading", "libwk.so"], cwd=tmp_path, check=True, capture_output=True)
+    notes = "".join(subprocess.run([os.path.join(tools, "llvm-readelf"), "--notes", f], check=True, capture_output=True, text=True).stdout
+                    for f in glob.glob(str(tmp_path / "*gfx950*")))
+    kernels = [k for k in notes.split(".args:") if "k_lse_wide_bf16" in k]
+    assert len(kernels) == 1 and re.search(r"\.private_segment_fixed_size: *0\b", kernels[0])
 
 
 def _inputs(H, N_q, N_kv, seed):
