@@ -1655,7 +1655,11 @@ SubTable frame_gap_table(int N_q, int N_kv, int row0, int frame_T) {
 // end two, write their partial results and merge them.  12 heads x 3 frames of 880 queries on 10,560 keys: 252 workgroups of 128
 // queries 160 us; two ranges, 504 workgroups and a merge, 175 us.  17 x 3 x 558 on 4,464 keys 92 -> 69 us, 48 x 3 x 300 on
 // 900 58 -> 36, 2 x 3 x 250 on 750 19.7 -> 16.7.  Two ranges where the frames alone leave compute units idle, as splits of the keys:
-// 5 heads x 2 x 993 on 8,440 keys 75 us, with a gap 103.
+// 5 heads x 2 x 993 on 8,440 keys 75 us, with a gap 103; 40 x 3 x 1,560 on 28,080 keys 2,292 and 2,372.
+// Over 1,500 drawn shapes (2 to 64 heads, 1 to 7 frames of 16 to 1,560 queries, both forms in both workgroup sizes timed) the choice is 10 % faster
+// than two ranges alone and 0.8 % slower than the best, on average; it is more than 2 % slower than two ranges alone on 17, by 12 % at most:
+// the model takes a last, partly filled round for a whole one, also where workgroups of unequal length fill it (8 x 2 x 1,231 on 9,848 keys:
+// 122 us, two ranges 109; and 40 x 3 x 1,560 on 14,040: two ranges 1,167, windows with a gap in 256-query workgroups 1,118).
 struct FramePlan { SubTable table; Layout layout; bool merge; };
 
 FramePlan plan_frames(int H, int N_q, int N_kv, int row0, int frame_T) {

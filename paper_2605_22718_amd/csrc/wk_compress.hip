@@ -172,8 +172,8 @@ typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte v
 // scores).  The four waves' sums meet through LDS in a fixed order, and one workgroup writes one partial sum per
 // (head, feature); k_anchor_mean_fold adds the partials in fp64.  The separate norm pass and its buffer are gone.
 // K_out (anchors that belong to the chunk): the rows are stored with it as they pass, instead of being read once more by the
-// compaction.  64 chunks of 40 heads x 4,680 tokens: 253 -> 441 us here, selection, anchors of V and compaction 1,428 -> 1,160, the whole
-// call 2,101 -> 2,040 (reads and stores of 256 bytes a head at 4.6 TB/s; past the caches the same).
+// compaction.  64 chunks of 40 heads x 4,680 tokens, half of the candidates kept: 253 -> 443 us here, selection, anchors of V and compaction
+// 1,428 -> 1,137, the whole call 2,106 -> 2,017 (reads and stores of 256 bytes a head at 4.6 TB/s; past the caches the same).
 constexpr int kFuseWaves = 4;
 
 template <int DT, int IT>
@@ -631,11 +631,11 @@ __device__ inline double key_score(uint64_t key) {   // the score of an order ke
 constexpr int kSelThreads = 1024;
 
 // Anchor rows are stored whatever the scores say, so they are copied while one workgroup per list selects and the other compute
-// units would be idle: workgroups behind the lists' take `units` pieces of 32 bytes a thread per (chunk, head), of K and V or of V
-// alone.  24 heads x 3,039 tokens with a list each: selection and compaction 9.0 + 6.4 us, now 10.3 + 4.5, the whole call 27.4 -> 25.4;
-// four chunks of 40 x 4,680 299 -> 290.
+// units would be idle: workgroups behind the lists' take `units` pieces of 32 bytes a thread per (chunk, head), of V and, where no pass
+// before has stored them, of K.  Against the compaction copying them too: 24 heads x 3,039 tokens with a list each, 27.3 -> 25.7 us (selection
+// and compaction 9.0 + 6.4, now 9.7 + 4.0); one chunk of 40 x 4,680, half of the candidates kept, 61.3 -> 54.7, four, a quarter kept, 144.1 -> 140.3.
 struct AnchorCopy {
-    const char *K, *V;   // K null: already there (k_anchor_norm_mean)
+    const char *K, *V;   // K null: already there (k_anchor_norm_mean, k_rows_normsq)
     char *K_out, *V_out;
     int lists, row_bytes;
     unsigned units;
@@ -951,9 +951,10 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
     }
 }
 
-// K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of rows first_row and up (behind the anchors), copied verbatim.  STREAM: past the caches, for batches that
-// they cannot hold anyway (kStreamBytes): 64 chunks of 40 heads x 4,680 tokens, whole call 2,159 -> 2,087 us.  Smaller
-// ones find K's rows in the Infinity Cache: four chunks take 298 us, streaming 303; one of 24 x 3,039 28.7 and 30.2.
+// K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of rows first_row and up (behind the anchors), copied verbatim.  STREAM: past the
+// caches, for batches that they cannot hold anyway (kStreamBytes).  With the anchors' rows copied elsewhere little depends on it: 64 chunks of
+// 40 heads x 4,680 tokens take 2,017 us streaming and 2,019 through the caches, one of 12 x 2,640 25.1 and 23.9, one of 24 x 3,039 25.9 and 25.7, one of
+// 40 x 4,680 52.3 and 54.7 (the compaction of all rows: 64 chunks 2,087 and 2,159, four, which find K in the Infinity Cache, 303 and 298).
 constexpr long long kStreamBytes = 512ll << 20;   // of K: twice the Infinity Cache
 
 template <int DT, bool STREAM>
@@ -1131,8 +1132,9 @@ wk_status launch_norm_mean(const FusePlan &f, const char *A, const CompressDims 
 }
 
 // More anchor rows of K than this are stored by the similarity GEMM's norm pass; fewer are copied while the selection's one
-// workgroup per list keeps the chip waiting anyway.  40 heads x 4,680 tokens: one chunk (16 MB) 98.1 us as copies, 100.2 stored, two 173.0 and
-// 170.3, four 315.9 and 309.7, eight 638 and 610; 8 chunks of 12 x 2,640 (22 MB) 87.8 and 87.1, 2 of 24 x 3,039 (12 MB) 58.8 and 60.0.
+// workgroup per list keeps the chip waiting anyway.  40 heads x 4,680 tokens, half of the candidates kept: one chunk (16 MB) 98.1 us as
+// copies, 100.1 stored, two 176.6 and 173.5, four 318.7 and 313.3 (a quarter kept 297.9 and 290.3), eight 645 and 612; 8 chunks of 12 x 2,640
+// (22 MB) 88.9 and 88.4, 2 of 24 x 3,039 (12 MB) 60.2 and 61.3.
 constexpr long long kNormStoreBytes = 20'000'000;
 
 template <int DT>
