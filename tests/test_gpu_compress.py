@@ -368,3 +368,36 @@ def test_two_million_heads_of_anchors(T, batch):
     wk.wk_compress_chunk(desc, K.view(torch.bfloat16), V.view(torch.bfloat16), None, idx, *(x.view(torch.bfloat16) for x in out), ws)
     assert torch.equal(idx, torch.arange(T, dtype=torch.int32, device=d).expand(batch, 1, T))
     assert torch.equal(out[0], K) and torch.equal(out[1], V)
+
+
+# The anchor mean of the one-pass kernel, to the bit: a wave adds its run of tokens in fp32, the four waves' sums meet in fp64, the partial sums
+# are rounded to fp32 and added in fp64.  Integer keys, so that the norms are exact; candidates with a single 1 score one element of
+# the mean each.  (Another order moves scores by about 2e-10, and with it selections that are closer than that.)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_one_pass_anchor_mean_keeps_its_order_of_summation(dtype):
+    H, T, F, B, d = 2, 100, 3, 300, dev()
+    run = -(-T * B // 4096)   # tokens a wave: 8
+    K = torch.zeros((B, H, F * T, 128))
+    K[:, :, :T] = torch.randint(-9, 10, (B, H, T, 128), generator=torch.Generator().manual_seed(3)).float()
+    for j in range(2 * T):
+        K[:, j // 128, T + j, j % 128] = 1
+    desc = wk.make_compress_desc(H, T, F, wk.WK_BF16 if dtype == torch.bfloat16 else wk.WK_F32, 0.5, batch=B, ratio_kind=wk.WK_RATIO_NONANCHOR)
+    n_out, _ = wk.wk_keep_count(0.5, wk.WK_RATIO_NONANCHOR, wk.WK_ANCHOR_FIRST_FRAME, F, T)
+    Kd = K.to(d, dtype)
+    out = [torch.empty((B, H, n_out, 128), dtype=dtype, device=d) for _ in range(2)]
+    ws = torch.empty(wk.wk_compress_workspace_bytes(desc), dtype=torch.uint8, device=d)
+    wk.wk_compress_chunk(desc, Kd, Kd, None, None, *out, ws)
+    scores = ws[:B * 2 * T * 8].view(torch.float64).view(B, 2 * T).cpu().numpy()
+    for b in (0, 1, B - 1):
+        a = K[b, :, :T].transpose(0, 1).reshape(T, H * 128).numpy().astype(np.float64)
+        rn = (1.0 / np.sqrt((a * a).sum(1))).astype(np.float32).astype(np.float64)
+        total = np.zeros(H * 128)
+        for s0 in range(0, T, 4 * run):
+            part = np.zeros(H * 128)
+            for w0 in range(s0, s0 + 4 * run, run):
+                acc = np.zeros(H * 128, np.float32)
+                for i in range(w0, min(T, w0 + run)):
+                    acc = (a[i] * rn[i] + acc).astype(np.float32)
+                part += acc
+            total += part.astype(np.float32)
+        assert np.array_equal(scores[b], (total / T).astype(np.float32)[:2 * T].astype(np.float64))
