@@ -1138,6 +1138,20 @@ wk_status launch_norm_mean(const FusePlan &f, const char *A, const CompressDims 
 // (22 MB) 88.9 and 88.4, 2 of 24 x 3,039 (12 MB) 60.2 and 61.3.
 constexpr long long kNormStoreBytes = 20'000'000;
 
+// Where anchor rows are copied beside the selection: always where the norm pass has stored K's, or where they are all that is kept (no
+// compaction follows: 16 heads x 305 tokens x 12 chunks, fp32, 31 -> 27 us); else where the selection leaves room for them, in calls with little to copy
+// or with few lists.  More lists and more bytes only move them from one launch that is bound by HBM to another: 64 lists of 800 with
+// 52 MB of anchor rows 136 -> 143 us, 840 of 816 with 176 MB 461 -> 469; 27 MB of 432 lists of 498 79 -> 77.  Few lists: four of 3,120, 64 MB,
+// 144 -> 141, sixteen, 256 MB, 508 -> 495; but not rows of 512 bytes past the caches: eight of 3,120, fp32, 256 MB, 518 -> 560.
+constexpr long long kBesideBytes = 36'000'000;   // of K's anchor rows
+constexpr int kBesideLists = 16;
+
+bool copies_beside_selection(const wk_compress_desc *d, const CompressDims &p, bool k_stored, bool stream) {
+    if (p.first_cand == 0) return false;   // external anchors are not stored
+    if (k_stored || p.n_cand == 0 || (long long)d->batch * p.H * p.T * (long long)(WK_D * wk::esize(d->dtype)) <= kBesideBytes) return true;
+    return d->batch * p.G <= kBesideLists && !(stream && d->dtype == WK_F32);
+}
+
 template <int DT>
 wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsLayout &ws, const void *K,
                      const void *V, const void *K_anchor, int32_t *kept_idx, void *K_out, void *V_out,
@@ -1233,14 +1247,12 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
     int first_row = p.first_cand;   // of the compaction
     AnchorCopy copy{k_anchors_stored ? nullptr : Kc, Vc, Ko, Vo, d->batch * p.G, (int)(WK_D * wk::esize(DT)), 0, stream};
     auto select = [&](auto kernel, int threads) {
-        long long blocks = copy.lists;
-        if (p.first_cand > 0) {
-            const long long vectors = (long long)p.T * copy.row_bytes / 16;
-            copy.units = (unsigned)((vectors + 2 * threads - 1) / (2 * threads));
-            const long long copies = (long long)d->batch * p.H * (copy.K ? 2 : 1) * copy.units;
-            if (wk::fits_launch(blocks + copies, threads)) blocks += copies;
-            else first_row = 0;   // the compaction copies the anchors too
-        }
+        const long long vectors = (long long)p.T * copy.row_bytes / 16;
+        copy.units = (unsigned)((vectors + 2 * threads - 1) / (2 * threads));
+        const long long copies = (long long)d->batch * p.H * (copy.K ? 2 : 1) * copy.units;
+        const bool beside = copies_beside_selection(d, p, k_anchors_stored, stream) && wk::fits_launch(copy.lists + copies, threads);
+        if (!beside) first_row = 0;   // the compaction copies the anchors (external ones are none of the chunk's rows)
+        const long long blocks = copy.lists + (beside ? copies : 0);
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, st, scores, p, kept, copy);
     };
     const int threads = select_threads(p);

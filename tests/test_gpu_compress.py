@@ -355,6 +355,34 @@ def test_anchors_are_stored_whole(dtype, head_mode, T, F, rho):
         assert (got[B * H * n_out:] == 7.0).all()
 
 
+# anchors that the compaction copies (many lists, or fp32 rows past the caches, with more than 36 MB of anchor rows), and calls on the
+# other side of each bound
+@pytest.mark.parametrize("dtype,head_mode,B,H,T,F", [
+    (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 64, 24, 91, 2), (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 64, 24, 92, 2),
+    (torch.bfloat16, wk.WK_HEADS_SHARED, 16, 37, 601, 2), (torch.bfloat16, wk.WK_HEADS_SHARED, 17, 37, 601, 2),
+    (torch.float32, wk.WK_HEADS_SHARED, 3, 40, 3001, 2), (torch.float32, wk.WK_HEADS_SHARED, 3, 40, 3001, 3)])
+def test_anchors_copied_by_the_compaction(dtype, head_mode, B, H, T, F):
+    d = dev()
+    g = torch.Generator(device=d).manual_seed(T)
+    K, V = (torch.randn((B, H, F * T, 128), generator=g, device=d).to(dtype) for _ in range(2))
+    desc = wk.make_compress_desc(H, T, F, wk.WK_BF16 if dtype == torch.bfloat16 else wk.WK_F32, 0.25, batch=B, head_mode=head_mode,
+                                 ratio_kind=wk.WK_RATIO_NONANCHOR)
+    n_out, _ = wk.wk_keep_count(0.25, wk.WK_RATIO_NONANCHOR, wk.WK_ANCHOR_FIRST_FRAME, F, T)
+    G = H if head_mode == wk.WK_HEADS_INDEPENDENT else 1
+    idx = torch.full((B, G, n_out), -1, dtype=torch.int32, device=d)
+    out = [torch.full((B * H * n_out + 64, 128), 7.0, dtype=dtype, device=d) for _ in range(2)]
+    ws = torch.empty(wk.wk_compress_workspace_bytes(desc), dtype=torch.uint8, device=d)
+    wk.wk_compress_chunk(desc, K, V, None, idx, *(x[:B * H * n_out].view(B, H, n_out, 128) for x in out), ws)
+    scores = ws[:B * G * (F - 1) * T * 8].view(torch.float64).view(B, G, -1)
+    kept = torch.sort(scores, dim=-1, stable=True).indices[..., :n_out - T].sort(dim=-1).values + T
+    want = torch.cat((torch.arange(T, device=d).expand(B, G, T), kept), -1)
+    assert torch.equal(idx.long(), want)
+    rows = want.expand(B, H, n_out).unsqueeze(-1).expand(B, H, n_out, 128)
+    for src, got in zip((K, V), out):
+        assert torch.equal(got[:B * H * n_out].view(B, H, n_out, 128), torch.gather(src, 2, rows))
+        assert (got[B * H * n_out:] == 7.0).all()
+
+
 # so many small chunks that a copy workgroup for each head's anchors would give the selection's launch 2^32 threads
 @pytest.mark.parametrize("T,batch", [(1, 32768), (2, 32767)])
 def test_two_million_heads_of_anchors(T, batch):
