@@ -1142,14 +1142,18 @@ constexpr long long kNormStoreBytes = 20'000'000;
 // compaction follows: 16 heads x 305 tokens x 12 chunks, fp32, 31 -> 27 us); else where the selection leaves room for them, in calls with little to copy
 // or with few lists.  More lists and more bytes only move them from one launch that is bound by HBM to another: 64 lists of 800 with
 // 52 MB of anchor rows 136 -> 143 us, 840 of 816 with 176 MB 461 -> 469; 27 MB of 432 lists of 498 79 -> 77.  Few lists: four of 3,120, 64 MB,
-// 144 -> 141, sixteen, 256 MB, 508 -> 495; but not rows of 512 bytes past the caches: eight of 3,120, fp32, 256 MB, 518 -> 560.
+// 144 -> 141, sixteen, 256 MB, 508 -> 495; but not rows of 512 bytes past the caches: eight of 3,120, fp32, 256 MB, 518 -> 560.  Nor where the selection's
+// workgroups of 1,024 threads fill the chip by themselves: 225 lists of 651, 12 MB, 53.5 -> 54.9, 228 of 660, 26 MB, 80.5 -> 83.3.
 constexpr long long kBesideBytes = 36'000'000;   // of K's anchor rows
-constexpr int kBesideLists = 16;
+constexpr int kBesideLists = 16, kFillingLists = 192;
 
 bool copies_beside_selection(const wk_compress_desc *d, const CompressDims &p, bool k_stored, bool stream) {
     if (p.first_cand == 0) return false;   // external anchors are not stored
-    if (k_stored || p.n_cand == 0 || (long long)d->batch * p.H * p.T * (long long)(WK_D * wk::esize(d->dtype)) <= kBesideBytes) return true;
-    return d->batch * p.G <= kBesideLists && !(stream && d->dtype == WK_F32);
+    if (k_stored || p.n_cand == 0) return true;
+    const int lists = d->batch * p.G;
+    if ((long long)d->batch * p.H * p.T * (long long)(WK_D * wk::esize(d->dtype)) <= kBesideBytes)
+        return lists <= kFillingLists || select_threads(p) < kSelThreads;
+    return lists <= kBesideLists && !(stream && d->dtype == WK_F32);
 }
 
 template <int DT>

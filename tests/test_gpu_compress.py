@@ -355,10 +355,12 @@ def test_anchors_are_stored_whole(dtype, head_mode, T, F, rho):
         assert (got[B * H * n_out:] == 7.0).all()
 
 
-# anchors that the compaction copies (many lists, or fp32 rows past the caches, with more than 36 MB of anchor rows), and calls on the
-# other side of each bound
+# anchors that the compaction copies (more than 36 MB of anchor rows with many lists or in fp32 rows past the caches; more than 192 lists of
+# more than 512), and calls on the other side of each bound
 @pytest.mark.parametrize("dtype,head_mode,B,H,T,F", [
     (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 64, 24, 91, 2), (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 64, 24, 92, 2),
+    (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 193, 1, 513, 2), (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 193, 1, 512, 2),
+    (torch.bfloat16, wk.WK_HEADS_INDEPENDENT, 96, 2, 513, 2),
     (torch.bfloat16, wk.WK_HEADS_SHARED, 16, 37, 601, 2), (torch.bfloat16, wk.WK_HEADS_SHARED, 17, 37, 601, 2),
     (torch.float32, wk.WK_HEADS_SHARED, 3, 40, 3001, 2), (torch.float32, wk.WK_HEADS_SHARED, 3, 40, 3001, 3)])
 def test_anchors_copied_by_the_compaction(dtype, head_mode, B, H, T, F):
