@@ -296,7 +296,7 @@ wk_status wk_attention_in_place(const void *Q, const void *K_native, const void 
 
 /* First half of query-based retrieval (Sec. 4.2, App. C): the log-sum-exp of the current queries'
  * scaled logits against the stored keys of every chunk of the store, all chunks in one launch.
- * The result is the `lse` input of wk_score_chunks_query.  Only K_ptr, n_tok, M, H, d and dtype
+ * The result is the `lse` input of wk_score_chunks_query.  Only K_ptr, n_tok, max_tok, M, H, d and dtype
  * of the store are used; the key tables may describe whole compacted chunks or, for a cheaper
  * index, the anchor-frame keys of each chunk alone.
  *
