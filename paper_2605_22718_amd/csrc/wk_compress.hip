@@ -8,6 +8,7 @@
 // candidates that accumulates both k_j . m and |k_j|^2.  Partial sums over a lane's 8 elements
 // are fp32 (bf16 products are exact in fp32), everything across lanes and heads is fp64, so the
 // scores agree with an fp64 evaluation of the double sum to ~1e-9 absolute.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -19,6 +20,8 @@ using wk::kRowLanes;
 using wk::load_row8;
 
 constexpr int kRowsPerBlock = 16;  // 256 threads
+
+typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
 
 struct CompressDims {
     int H, T, n_tok;    // heads, anchors per chunk, rows per head in K
@@ -162,8 +165,6 @@ __global__ __launch_bounds__(WK_D) void k_anchor_mean_finish(const double *__res
     m[bh * WK_D + threadIdx.x] = (float)(s / (double)p.T);
 }
 
-typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
-
 // Anchor norms and the normalised anchor mean in ONE pass over the anchor rows, for head-shared lists (a token's
 // norm runs over all heads, so a wave takes whole tokens): each of the workgroup's four waves walks
 // tok_per_wave anchor tokens; per token it requests the token's rows of all heads at once (head h goes to
@@ -302,55 +303,120 @@ __global__ __launch_bounds__(WK_D) void k_anchor_mean_fold(const float *__restri
 }
 
 // scores[(b*G+g)*n_cand + j] = (k_j . m) / |k_j|
-template <int DT, int HS>
-__global__ __launch_bounds__(256) void k_score_factored(const char *__restrict__ K, CompressDims p,
-                                                        const float *__restrict__ m,
-                                                        double *__restrict__ scores) {
-    const int j = blockIdx.x * (kRowsPerBlock / HS) + threadIdx.x / (kRowLanes * HS);
-    const int hq = (threadIdx.x / kRowLanes) % HS;
-    const int sub = threadIdx.x % kRowLanes;
-    const int g = blockIdx.y, b = blockIdx.z;
-    if (j >= p.n_cand) return;
+//
+// Bound by HBM: the candidates' rows are read once, by 16 lanes each.  A row's products with the mean's 128 features of its head, which
+// are 512 bytes beside the row's 256 in bf16, so rows share them: see the two forms.
+
+// a lane's share of a row, as it was loaded: the 8 elements from 8*sub on
+template <int DT>
+struct RowPart {
+    uvec4 w[DT == WK_BF16 ? 1 : 2];
+    template <bool STREAM>   // past the caches
+    __device__ inline void load(const char *row, int sub) {
+        constexpr int n = DT == WK_BF16 ? 1 : 2;
+        const uvec4 *src = reinterpret_cast<const uvec4 *>(row) + n * sub;
+#pragma unroll
+        for (int i = 0; i < n; ++i) w[i] = STREAM ? __builtin_nontemporal_load(src + i) : src[i];
+    }
+    __device__ inline float at(int e) const {   // (e is a constant where this is unrolled)
+        if constexpr (DT == WK_BF16) return __uint_as_float(e & 1 ? w[0][e / 2] & 0xffff0000u : w[0][e / 2] << 16);
+        else return __uint_as_float(w[e / 4][e & 3]);
+    }
+};
+
+template <int DT>
+__device__ inline void add_products(const RowPart<DT> &row, float4 m0, float4 m1, double &dot, double &norm) {
+    const float mm[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+    float dp = 0.f, ns = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        dp = fmaf(row.at(e), mm[e], dp);
+        ns = fmaf(row.at(e), row.at(e), ns);
+    }
+    dot += (double)dp;
+    norm += (double)ns;
+}
+
+__device__ inline double score_of(double dot, double norm) {
+    return (norm < 1e-60 ? 0.0 : dot / sqrt(norm)) + 0.0;   // -0.0 -> +0.0
+}
+
+// Lists over many heads: a wave per token, its four 16-lane groups taking every fourth head, and the mean of kMeanHeads heads at a time
+// in LDS for the workgroup's eight tokens.  Fetched by every token, the mean kept the L1 and L2 as busy as HBM: 64 chunks of 40 heads x 3,120
+// candidates 428 us = 4.8 TB/s, now 311 = 6.6 TB/s (the whole call 2,021 -> 1,937; with four waves a workgroup 1 % more).
+constexpr int kScoreWaves = 8, kMeanHeads = 64;
+
+template <int DT, bool STREAM>
+__global__ __launch_bounds__(kScoreWaves * 64) void k_score_tokens(const char *__restrict__ K, CompressDims p,
+                                                                   const float *__restrict__ m, double *__restrict__ scores) {
+    extern __shared__ __attribute__((aligned(16))) float mean_lds[];   // [min(H, kMeanHeads)][128]
+    constexpr int kBatch = 5;   // rows requested at a time by a lane group (ten: 3 % more for the whole call of 64 chunks)
+    const int wave = threadIdx.x >> 6, hq = (threadIdx.x >> 4) & 3, sub = threadIdx.x & 15;
+    const int j = blockIdx.x * kScoreWaves + wave, b = blockIdx.z;
     const size_t row_bytes = WK_D * wk::esize(DT);
     const size_t head_bytes = (size_t)p.n_tok * row_bytes;
-    const char *base = K + ((size_t)b * p.H * p.n_tok + p.first_cand + j) * row_bytes;
-    const float *mb = m + (size_t)b * p.H * WK_D + 8 * sub;
+    const char *base = K + ((size_t)b * p.H * p.n_tok + p.first_cand + min(j, p.n_cand - 1)) * row_bytes;
     double dacc = 0.0, nacc = 0.0;
-    for (int hh0 = hq; hh0 < p.hg; hh0 += HS * kHeadBatch) {
-        float v[kHeadBatch][8];
+    for (int h0 = 0; h0 < p.H; h0 += kMeanHeads) {
+        const int h1 = min(p.H, h0 + kMeanHeads);
+        for (int hh0 = h0; hh0 < h1; hh0 += 4 * kBatch) {
+            RowPart<DT> v[kBatch];
 #pragma unroll
-        for (int u = 0; u < kHeadBatch; ++u) {
-            const int hh = hh0 + u * HS;
-            if (hh < p.hg) {
-                load_row8<DT>(base + (size_t)(p.G == 1 ? hh : g) * head_bytes, sub, v[u]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[u][e] = 0.f;
+            for (int u = 0; u < kBatch; ++u) {
+                const int hh = hh0 + 4 * u + hq;
+                if (hh < h1) v[u].template load<STREAM>(base + (size_t)hh * head_bytes, sub);
             }
-        }
+            if (hh0 == h0) {   // behind the first rows' requests
+                if (h0 > 0) __syncthreads();   // the heads before have been read
+                const float4 *src = reinterpret_cast<const float4 *>(m + ((size_t)b * p.H + h0) * WK_D);
+                float4 *dst = reinterpret_cast<float4 *>(mean_lds);
+                for (int i = threadIdx.x; i < (h1 - h0) * (WK_D / 4); i += kScoreWaves * 64) dst[i] = src[i];
+                __syncthreads();
+            }
 #pragma unroll
-        for (int u = 0; u < kHeadBatch; ++u) {
-            const int hh = hh0 + u * HS;
-            if (hh < p.hg) {
-                const float4 *mp = reinterpret_cast<const float4 *>(mb + (size_t)(p.G == 1 ? hh : g) * WK_D);
-                const float4 m0 = mp[0], m1 = mp[1];
-                const float mm[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
-                float dp = 0.f, ns = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    dp = fmaf(v[u][e], mm[e], dp);
-                    ns = fmaf(v[u][e], v[u][e], ns);
+            for (int u = 0; u < kBatch; ++u) {
+                const int hh = hh0 + 4 * u + hq;
+                if (hh < h1) {
+                    const float4 *mp = reinterpret_cast<const float4 *>(mean_lds + (hh - h0) * WK_D + 8 * sub);
+                    add_products(v[u], mp[0], mp[1], dacc, nacc);
                 }
-                dacc += (double)dp;
-                nacc += (double)ns;
             }
         }
     }
-    dacc = head_split_sum<HS>(dacc);
-    nacc = head_split_sum<HS>(nacc);
-    if (sub == 0 && hq == 0) {
-        double s = nacc < 1e-60 ? 0.0 : dacc / sqrt(nacc);
-        scores[((size_t)b * p.G + g) * p.n_cand + j] = s + 0.0;  // -0.0 -> +0.0
+    dacc = head_split_sum<4>(dacc);
+    nacc = head_split_sum<4>(nacc);
+    if ((threadIdx.x & 63) == 0 && j < p.n_cand) scores[(size_t)b * p.n_cand + j] = score_of(dacc, nacc);
+}
+
+// Lists over one head (or two or three): 16 lanes per token.  Past the caches (STREAM) they take ROWS = 4 tokens of the head with the
+// mean they fetch once: 40 chunks of 40 heads x 2,000 candidates with a list each 210 -> 150 us; where a launch is short, more
+// workgroups count for more (10 chunks of 8 heads x 1,000, whole call, 31.4 us with four tokens, 30.1 with one; before 30.6).
+template <int DT, int ROWS, bool STREAM>
+__global__ __launch_bounds__(256) void k_score_rows(const char *__restrict__ K, CompressDims p, const float *__restrict__ m,
+                                                    double *__restrict__ scores) {
+    const int j0 = blockIdx.x * (kRowsPerBlock * ROWS) + threadIdx.x / kRowLanes, sub = threadIdx.x % kRowLanes;
+    const int g = blockIdx.y, b = blockIdx.z;
+    const size_t row_bytes = WK_D * wk::esize(DT);
+    double dacc[ROWS], nacc[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) dacc[u] = nacc[u] = 0.0;
+    for (int hh = 0; hh < p.hg; ++hh) {
+        const size_t bh = (size_t)b * p.H + (p.G == 1 ? hh : g);
+        const char *base = K + (bh * p.n_tok + p.first_cand) * row_bytes;
+        RowPart<DT> v[ROWS];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+            v[u].template load<STREAM>(base + (size_t)min(j0 + u * kRowsPerBlock, p.n_cand - 1) * row_bytes, sub);
+        const float4 *mp = reinterpret_cast<const float4 *>(m + bh * WK_D + 8 * sub);
+        const float4 m0 = mp[0], m1 = mp[1];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) add_products(v[u], m0, m1, dacc[u], nacc[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        const int j = j0 + u * kRowsPerBlock;
+        const double d = wk::row_group_sum(dacc[u]), n = wk::row_group_sum(nacc[u]);
+        if (sub == 0 && j < p.n_cand) scores[((size_t)b * p.G + g) * p.n_cand + j] = score_of(d, n);
     }
 }
 
@@ -1242,9 +1308,15 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
                 hipLaunchKernelGGL(k_anchor_mean_finish, dim3(p.H, d->batch), dim3(WK_D), 0, st, mean_partial, p, mean);
                 WK_LAUNCH_CHECK();
             }
-            dim3 g3((p.n_cand + rows_pb - 1) / rows_pb, p.G, d->batch);
-            if (split) hipLaunchKernelGGL((k_score_factored<DT, 4>), g3, dim3(256), 0, st, Kc, p, mean, scores);
-            else hipLaunchKernelGGL((k_score_factored<DT, 1>), g3, dim3(256), 0, st, Kc, p, mean, scores);
+            const size_t mean_bytes = (size_t)std::min(p.H, kMeanHeads) * WK_D * sizeof(float);
+            const dim3 g_tokens((p.n_cand + kScoreWaves - 1) / kScoreWaves, 1, d->batch);
+            auto tokens = [&](auto kernel) { hipLaunchKernelGGL(kernel, g_tokens, dim3(kScoreWaves * 64), mean_bytes, st, Kc, p, mean, scores); };
+            auto rows = [&](auto kernel, int each) {
+                const int per = kRowsPerBlock * each;
+                hipLaunchKernelGGL(kernel, dim3((p.n_cand + per - 1) / per, p.G, d->batch), dim3(256), 0, st, Kc, p, mean, scores);
+            };
+            if (split) stream ? tokens(k_score_tokens<DT, true>) : tokens(k_score_tokens<DT, false>);
+            else stream ? rows(k_score_rows<DT, 4, true>, 4) : rows(k_score_rows<DT, 1, false>, 1);
             WK_LAUNCH_CHECK();
         }
     }
