@@ -1018,41 +1018,38 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
     }
 }
 
-// K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of rows first_row and up (behind the anchors), copied verbatim.  STREAM: past the
-// caches, for batches that they cannot hold anyway (kStreamBytes).  With the anchors' rows copied elsewhere little depends on it: 64 chunks of
-// 40 heads x 4,680 tokens take 2,017 us streaming and 2,019 through the caches, one of 12 x 2,640 25.1 and 23.9, one of 24 x 3,039 25.9 and 25.7, one of
-// 40 x 4,680 52.3 and 54.7 (the compaction of all rows: 64 chunks 2,087 and 2,159, four, which find K in the Infinity Cache, 303 and 298).
+// K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of rows first_row and up (behind the anchors), copied verbatim, K by the first `tiles`
+// workgroups of a head and V by as many behind them: a launch that sweeps one array at a time comes closer to the rate of a plain copy.
+// 64 chunks of 40 heads x 4,680 tokens, half of the candidates kept: 800 us with a row of K and one of V per lane group, 704 with one row (5.8 TB/s),
+// two heads' rows 717.  STREAM: past the caches, for batches that they cannot hold anyway (kStreamBytes).  With the anchors' rows copied
+// elsewhere little depends on it: 64 chunks of 40 heads x 4,680 tokens take 2,017 us streaming and 2,019 through the caches, one of 12 x 2,640 25.1 and 23.9, one of
+// 24 x 3,039 25.9 and 25.7, one of 40 x 4,680 52.3 and 54.7 (the compaction of all rows: 64 chunks 2,087 and 2,159, four, which find K in the Infinity Cache, 303
+// and 298).
 constexpr long long kStreamBytes = 512ll << 20;   // of K: twice the Infinity Cache
 
 template <int DT, bool STREAM>
 __global__ __launch_bounds__(256) void k_compact(const char *__restrict__ K, const char *__restrict__ V,
-                                                 CompressDims p, int first_row, const int32_t *__restrict__ kept_idx,
+                                                 CompressDims p, int first_row, unsigned tiles, const int32_t *__restrict__ kept_idx,
                                                  char *__restrict__ K_out, char *__restrict__ V_out) {
-    const int r = first_row + blockIdx.x * kRowsPerBlock + threadIdx.x / kRowLanes;
+    const bool is_v = blockIdx.x >= tiles;
+    const int r = first_row + (is_v ? blockIdx.x - tiles : blockIdx.x) * kRowsPerBlock + threadIdx.x / kRowLanes;
     const int sub = threadIdx.x % kRowLanes;
     const int h = blockIdx.y, b = blockIdx.z;
     if (r >= p.n_out) return;
     const int g = p.G == 1 ? 0 : h;
-    int src = kept_idx[((size_t)b * p.G + g) * p.n_out + r];
-    src = src < 0 ? 0 : (src >= p.n_tok ? p.n_tok - 1 : src);  // never read outside the chunk
+    int row = kept_idx[((size_t)b * p.G + g) * p.n_out + r];
+    row = row < 0 ? 0 : (row >= p.n_tok ? p.n_tok - 1 : row);  // never read outside the chunk
     constexpr size_t row_bytes = WK_D * (DT == WK_BF16 ? 2 : 4);
     constexpr int vec_per_lane = row_bytes / (kRowLanes * 16);  // 1 (bf16) or 2 (fp32)
-    const size_t in_off = (((size_t)b * p.H + h) * p.n_tok + src) * row_bytes;
-    const size_t out_off = (((size_t)b * p.H + h) * p.n_out + r) * row_bytes;
+    const uvec4 *src = reinterpret_cast<const uvec4 *>((is_v ? V : K) + (((size_t)b * p.H + h) * p.n_tok + row) * row_bytes) + sub;
+    uvec4 *dst = reinterpret_cast<uvec4 *>((is_v ? V_out : K_out) + (((size_t)b * p.H + h) * p.n_out + r) * row_bytes) + sub;
+    uvec4 v[vec_per_lane];
+#pragma unroll
+    for (int t = 0; t < vec_per_lane; ++t) v[t] = STREAM ? __builtin_nontemporal_load(src + t * kRowLanes) : src[t * kRowLanes];
 #pragma unroll
     for (int t = 0; t < vec_per_lane; ++t) {
-        const int c = sub + t * kRowLanes;
-        const uvec4 *ks = reinterpret_cast<const uvec4 *>(K + in_off) + c, *vs = reinterpret_cast<const uvec4 *>(V + in_off) + c;
-        uvec4 *ko = reinterpret_cast<uvec4 *>(K_out + out_off) + c, *vo = reinterpret_cast<uvec4 *>(V_out + out_off) + c;
-        if constexpr (STREAM) {
-            const uvec4 kv = __builtin_nontemporal_load(ks), vv = __builtin_nontemporal_load(vs);
-            __builtin_nontemporal_store(kv, ko);
-            __builtin_nontemporal_store(vv, vo);
-        } else {
-            const uvec4 kv = *ks, vv = *vs;
-            *ko = kv;
-            *vo = vv;
-        }
+        if constexpr (STREAM) __builtin_nontemporal_store(v[t], dst + t * kRowLanes);
+        else dst[t * kRowLanes] = v[t];
     }
 }
 
@@ -1340,9 +1337,10 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
     else select(k_select_held<1024, 4>, threads);
     WK_LAUNCH_CHECK();
     if (first_row == p.n_out) return WK_OK;
-    const dim3 g5((p.n_out - first_row + kRowsPerBlock - 1) / kRowsPerBlock, p.H, d->batch);
-    if (stream) hipLaunchKernelGGL((k_compact<DT, true>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, kept, Ko, Vo);
-    else hipLaunchKernelGGL((k_compact<DT, false>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, kept, Ko, Vo);
+    const unsigned tiles = (unsigned)((p.n_out - first_row + kRowsPerBlock - 1) / kRowsPerBlock);
+    const dim3 g5(2 * tiles, p.H, d->batch);
+    if (stream) hipLaunchKernelGGL((k_compact<DT, true>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, tiles, kept, Ko, Vo);
+    else hipLaunchKernelGGL((k_compact<DT, false>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, tiles, kept, Ko, Vo);
     WK_LAUNCH_CHECK();
     return WK_OK;
 }
