@@ -1021,11 +1021,14 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
 // K_out/V_out[b][h][r] = K/V[b][h][kept_idx[b][g(h)][r]] of rows first_row and up (behind the anchors), copied verbatim, K by the first `tiles`
 // workgroups of a head and V by as many behind them: a launch that sweeps one array at a time comes closer to the rate of a plain copy.
 // 64 chunks of 40 heads x 4,680 tokens, half of the candidates kept: 800 us with a row of K and one of V per lane group, 704 with one row (5.8 TB/s),
-// two heads' rows 717.  STREAM: past the caches, for batches that they cannot hold anyway (kStreamBytes).  With the anchors' rows copied
-// elsewhere little depends on it: 64 chunks of 40 heads x 4,680 tokens take 2,017 us streaming and 2,019 through the caches, one of 12 x 2,640 25.1 and 23.9, one of
-// 24 x 3,039 25.9 and 25.7, one of 40 x 4,680 52.3 and 54.7 (the compaction of all rows: 64 chunks 2,087 and 2,159, four, which find K in the Infinity Cache, 303
-// and 298).
-constexpr long long kStreamBytes = 512ll << 20;   // of K: twice the Infinity Cache
+// two heads' rows 717.
+//
+// Past the caches (STREAM) go the candidates' rows in the score pass and the copies of calls whose K has more than kStreamBytes: rows that are stored
+// once would push out K, which the passes behind them read.  Whole calls through the caches and streaming: 4 chunks of 40 x 4,680 tokens
+// (183 MB) 159 and 143 us, 30 of 12 x 2,640 (232 MB) 223 and 198, 2 of 40 x 4,680 (91 MB) 86 and 80, 6 of 12 x 2,640 (46 MB) 48.9 and 49.8, 51 of 3 x 1,200 (45 MB)
+// 49.0 and 50.0.  fp32 with a list per head: 10 chunks of 12 x 2,640 (155 MB) 123 and 122, 5 (77 MB) 61 and 68; shared lists: 8 of
+// 24 x 3,039 (285 MB) 236 and 202, 3 of 12 x 2,640 (46 MB) 45 and 48.
+constexpr long long kStreamBytes = 64ll << 20, kStreamBytesF32 = 144ll << 20;
 
 template <int DT, bool STREAM>
 __global__ __launch_bounds__(256) void k_compact(const char *__restrict__ K, const char *__restrict__ V,
@@ -1230,7 +1233,7 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
     const char *A = reinterpret_cast<const char *>(d->anchor_mode == WK_ANCHOR_EXTERNAL ? K_anchor : K);
     const char *Kc = reinterpret_cast<const char *>(K), *Vc = reinterpret_cast<const char *>(V);
     char *Ko = reinterpret_cast<char *>(K_out), *Vo = reinterpret_cast<char *>(V_out);
-    const bool stream = (long long)d->batch * p.H * p.n_tok * (long long)(WK_D * wk::esize(DT)) > kStreamBytes;
+    const bool stream = (long long)d->batch * p.H * p.n_tok * (long long)(WK_D * wk::esize(DT)) > (DT == WK_BF16 ? kStreamBytes : kStreamBytesF32);
     bool k_anchors_stored = false;
     if (p.n_cand > 0) {  // scores are always produced: callers may read them from the workspace
         // a token's vector spans hg heads: with four or more, a wave per token (heads dealt to its four
