@@ -2,27 +2,31 @@
 // K/V rows are placed behind the native sliding-window rows, byte for byte.
 //
 // In the head-major layout every (head, chunk) pair is one contiguous byte range, so the gather
-// is a set of H x (1 + R) straight copies.  One launch covers K and V.  A work unit is 32 KB of
+// is a set of H x (1 + R) straight copies.  One launch covers K and V.  A work unit is 24 or 32 KB of
 // one head's K or V window; a workgroup walks units blockIdx.x, blockIdx.x + gridDim.x, ...: with
 // the default grid that is one unit each, with a capped grid (a prefetch that runs beside other
 // kernels and is bound by the host link anyway) a few workgroups stream the whole window.  The
 // source of each 16-byte vector is found by binary search over the retrieved chunks' prefix
 // offsets, built per workgroup in LDS from the device-resident ids (the ids never visit the
-// host); 8 vectors per lane in flight cover the latency of HBM and of reads from a pinned-host
+// host); 3 to 8 vectors per lane in flight cover the latency of HBM and of reads from a pinned-host
 // store over the host link.  Loads and stores are nontemporal (the data is touched once here), rows
 // are 16 or 32 vectors so all index arithmetic is shifts on 32-bit values, and a unit that lies in
-// one segment -- the usual case -- looks its segment up once: together these bring the kernel from
-// 3.2 TB/s to the rate of a plain device copy (5.5 TB/s read + written at the LingBot shape).  Small gathers are bound by
+// one segment -- the usual case -- looks its segment up once: together with units of the right size these bring the kernel from
+// 3.2 TB/s to 5.9 TB/s read + written (8 chunks of 40 heads x 2,340 tokens; the best plain device copy 6.4).  Small gathers are bound by
 // the chain of look-ups before the first copy: units cover the retrieved rows only when the native ones are in place, unit
 // numbers are 32-bit (4 chunks of 12 heads x 1,320 tokens: 20 -> 15 us).
 #include "wk_internal.h"
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kVecPerThread = 8;
-constexpr int kVecPerBlock = kThreads * kVecPerThread;  // 16-byte vectors per work unit
 constexpr int kMaxR = 1024;
+
+// Work units: 256 threads with six vectors each where the copy is short, 512 with three beyond kLargeCopy bytes, the launch in order then
+// sweeping the window closer to in sequence.  32 KB as 256 x 8, 24 KB as 256 x 6 and as 512 x 3: 8 chunks of 40 heads x 2,340 tokens (383 MB)
+// 144, 142 and 130 us, 16 of 12 x 1,320 (130 MB) 54.9, 50.6 and 49.8, 3 of 40 x 700 (43 MB) 17.2, 14.7 and 18.7, 4 of 12 x 1,320 13.1, 13.0
+// and 15.7 (512 x 2: 136, 51.4, 19.4, 15.4; 256 x 4: 133, 51.1, 19.3, 17.1; 256 x 1: 169, 66, 22, 17).  A capped grid has 256 x 8: what a few
+// workgroups keep in flight over the host link.
+constexpr long long kLargeCopy = 128'000'000;
 
 typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
 
@@ -50,8 +54,9 @@ struct GatherArgs {
 // base address of its K block and V block, its length and the first window row after it
 // U: the type of unit numbers, 32 bits except for a capped grid over 2^31 units or more (heads without end and next to no
 // rows; the windows of anything else would not fit the device).  A 64-bit division takes longer than a unit's look-ups.
-template <typename U>
-__global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
+template <typename U, int THREADS, int VECS>
+__global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
+    constexpr unsigned kUnit = THREADS * VECS;   // 16-byte vectors
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int cap = a.R_max + 1;
     const char **seg_k = reinterpret_cast<const char **>(lds);
@@ -63,7 +68,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
 
     int n = a.n_ids ? *a.n_ids : a.R_max;
     n = n < 0 ? 0 : (n > a.R_max ? a.R_max : n);
-    for (int t = tid; t < n; t += kThreads) {
+    for (int t = tid; t < n; t += THREADS) {
         const int id = a.ids[t];   // (ids behind the count are never read)
         int len = 0;
         const char *k = nullptr, *v = nullptr;
@@ -114,21 +119,21 @@ __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
 
     for (U u = blockIdx.x; u < units; u += gridDim.x) {
         const unsigned hz = (unsigned)(u / (U)a.units_per_head), unit = (unsigned)(u - (U)hz * (U)a.units_per_head);
-        const unsigned v0 = first_vec + unit * kVecPerBlock;
+        const unsigned v0 = first_vec + unit * kUnit;
         if (v0 >= total_vec) continue;
         const int h = (int)(hz % (unsigned)a.H);
         const bool is_v = hz >= (unsigned)a.H;
         const char *const *seg_src = is_v ? seg_v : seg_k;
         uvec4 *win = reinterpret_cast<uvec4 *>((is_v ? a.V_win : a.K_win) + (size_t)h * a.win_capacity * row_bytes);
         // the unit's rows usually lie in one segment: look that up once
-        const unsigned v_last = min(v0 + kVecPerBlock, total_vec) - 1;
+        const unsigned v_last = min(v0 + kUnit, total_vec) - 1;
         const int s_first = segment_of((int)(v0 >> row_shift), 0, nseg - 1);
         const int s_last = segment_of((int)(v_last >> row_shift), s_first, nseg - 1);
-        uvec4 buf[kVecPerThread];
-        bool have[kVecPerThread];
+        uvec4 buf[VECS];
+        bool have[VECS];
 #pragma unroll
-        for (int i = 0; i < kVecPerThread; ++i) {
-            const unsigned v = v0 + tid + i * kThreads;
+        for (int i = 0; i < VECS; ++i) {
+            const unsigned v = v0 + tid + i * THREADS;
             have[i] = false;
             if (v < total_vec) {
                 const int row = (int)(v >> row_shift);
@@ -144,8 +149,8 @@ __global__ __launch_bounds__(kThreads) void k_gather(GatherArgs a) {
             }
         }
 #pragma unroll
-        for (int i = 0; i < kVecPerThread; ++i) {
-            const unsigned v = v0 + tid + i * kThreads;
+        for (int i = 0; i < VECS; ++i) {
+            const unsigned v = v0 + tid + i * THREADS;
             if (have[i]) __builtin_nontemporal_store(buf[i], win + v);
         }
     }
@@ -181,17 +186,22 @@ wk_status wk::gather_launch(const wk_store_desc *store, const int32_t *ids, cons
     a.vec_per_row = (int)(WK_D * wk::esize(store->dtype) / 16);
     a.first_row = K_native ? 0 : n_native;
     const long long cap_vec = (long long)(n_native - a.first_row + (int64_t)R_max * store->max_tok) * a.vec_per_row;
-    long long per_head = (cap_vec + kVecPerBlock - 1) / kVecPerBlock;
-    if (per_head == 0) per_head = 1;  // nothing to copy: one workgroup still reports the (zero) length
-    a.units_per_head = (int)per_head;
-    const long long units = per_head * store->H * 2;
-    const long long grid = max_workgroups > 0 && units > max_workgroups ? max_workgroups : units;
-    if (grid > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
     const size_t lds_bytes = (size_t)(R_max + 1) * (2 * sizeof(char *) + 2 * sizeof(int));
-    if (units <= 0x7fffffffLL)   // (a unit number plus a grid stays below 2^32)
-        hipLaunchKernelGGL(k_gather<uint32_t>, dim3((unsigned)grid), dim3(kThreads), lds_bytes, stream, a);
-    else
-        hipLaunchKernelGGL(k_gather<uint64_t>, dim3((unsigned)grid), dim3(kThreads), lds_bytes, stream, a);
+    wk_status st = WK_OK;
+    auto launch = [&](auto narrow, auto wide, int threads, int vecs) {
+        long long per_head = (cap_vec + threads * vecs - 1) / (threads * vecs);
+        if (per_head == 0) per_head = 1;  // nothing to copy: one workgroup still reports the (zero) length
+        a.units_per_head = (int)per_head;
+        const long long units = per_head * store->H * 2;
+        const long long grid = max_workgroups > 0 && units > max_workgroups ? max_workgroups : units;
+        if (grid > 0x7fffffffLL) st = WK_ERR_UNSUPPORTED;
+        else   // (a unit number plus a grid stays below 2^32)
+            hipLaunchKernelGGL(units <= 0x7fffffffLL ? narrow : wide, dim3((unsigned)grid), dim3(threads), lds_bytes, stream, a);
+    };
+    if (max_workgroups > 0) launch(k_gather<uint32_t, 256, 8>, k_gather<uint64_t, 256, 8>, 256, 8);
+    else if (cap_vec * store->H * 32 > kLargeCopy) launch(k_gather<uint32_t, 512, 3>, k_gather<uint32_t, 512, 3>, 512, 3);
+    else launch(k_gather<uint32_t, 256, 6>, k_gather<uint32_t, 256, 6>, 256, 6);
+    if (st != WK_OK) return st;
     WK_LAUNCH_CHECK();
     return WK_OK;
 }
@@ -205,6 +215,8 @@ extern "C" wk_status wk_gather_window(const wk_store_desc *store, const int32_t 
 }
 
 namespace {
+
+constexpr int kThreads = 256, kVecPerThread = 8, kVecPerBlock = kThreads * kVecPerThread;
 
 // Straight copy with ordinary (cached) 16-byte loads and stores, one vector per lane and pass: the
 // access pattern of the tile loads in the attention kernels, with a byte count known exactly.
