@@ -171,34 +171,110 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32: v_mfma_f32_32x32x2_f32, 128 queries per workgroup, 32-key tiles in pairs.
+// fp32: every operand as the sum of two fp16 numbers, multiplied on v_mfma_f32_32x32x16_f16.
 //
-// Bound by the matrix pipe: 128 products of 64 cycles per tile and wave, all else must run beside them.  Eight waves, two
-// per SIMD: waves 0..3 take the even tiles, waves 4..7 the odd ones for the same queries, and their (O, max, sum) meet in
-// LDS at the end.  The next pair of tiles goes from global memory straight into the other half of the LDS while a pair is
-// multiplied.  A pair takes 7.9 us on an otherwise idle chip, where the products alone would take 6.8 us at 2.4 GHz.
-// 4 heads x 880 queries x 2,640 keys: 58 us in 9 key ranges; 40 x 1,560 x 4,680: 1,410 us (106 TFLOP/s in 2.03 rounds of
-// workgroups).  (Four waves of one workgroup per compute unit, one per SIMD because of 268 registers, with the tiles staged
-// through registers between two barriers, took 87 us, in 14 key ranges, and 2,180 us.)
+// x = x1 + x2 with x1 = fp16(x), x2 = fp16(x - x1) is off by at most 2^-24 of x, and a product of two such sums is taken without x2*y2, which is
+// below 2^-24 of it: three matrix instructions of 32 cycles do what eight fp32 ones of 64 do, and their sums are rounded less often.  On N(0, 1)
+// inputs results are 2.0e-7 to 3.6e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.
+// fp16's range is met by powers of two: one per query, one for the keys and one per feature of the values, from the first tile's
+// largest numbers, which leaves a factor of 32 for those that follow.  A workgroup that meets larger ones, infinities,
+// or values that are 2^-11 smaller than their feature's in the first tile, begins again from its first tile, with
+// v_mfma_f32_32x32x2_f32 on the numbers themselves.
 //
-// Tiles are row-major, 32 chunks of 16 bytes per row, chunk c of K row k at slot c ^ (k & 15), of V row k at
-// slot c ^ (8 * (k >> 2 & 1)): the 16 lanes of a K read then hit 16 different bank groups, the two key rows of a V read
-// different halves of the banks.
+// Four waves of 32 queries per workgroup, 32-key tiles, KG tiles at a time by as many groups of waves; KG == 1 leaves room for two
+// workgroups on a compute unit, whose phases then overlap by themselves.  KG == 2: the groups' (O, max, sum) meet in
+// LDS at the end, for small grids, whose key ranges would otherwise be many and their partial results with them.
+// Tiles come to LDS as they are (global_load_lds), a step ahead.  The threads split each once for all waves, beside the matrix
+// instructions of the phase before the one that reads it, and leave the parts in the order in which those are read:
+//   K part p: [chunk of 8 features][key], V part p: [keys of a k slot group][feature] x 8 keys, 16 bytes each.
+// Even features of V come first: a thread holds two adjacent ones and stores them apart.
+//
+// Bound by the matrix and the vector pipe together: a tile is 48 products (1,536 cycles) and about 300 vector instructions a wave, of which
+// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 39 us (with its merge), 8 x 1,560 x 4,680 293 -> 130, 40 x 1,560 x 4,680 1,411 -> 589 (254 TFLOP/s), 1 x 128 x
+// 30,000 248 -> 104, 6 x 250 x 100 25.0 -> 17.8.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
+// instead of beside the products: the same, as long as the compiler waited for the loads to LDS in front of every read of LDS, see load_to_lds.)
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 4;                           // across the queries
-constexpr int kF32Threads = 2 * kF32Waves * 64;
 constexpr int kF32Keys = 32;
-constexpr int kF32Tile = kF32Keys * 512;               // bytes of one K or V tile
-constexpr int kF32Stage = 4 * kF32Tile;                // [tile of the pair][K, V]
-constexpr int kF32Lds = 2 * kF32Stage;
+constexpr int kF32Part = kF32Keys * 256;               // bytes of one part of a K or V tile
+constexpr int kF32V = 2 * kF32Part;                    // K parts, V parts, K and V as they came
+constexpr int kF32RawK = 4 * kF32Part;
+constexpr int kF32RawV = kF32RawK + kF32Keys * 512;
+constexpr int kF32Group = kF32RawV + kF32Keys * 512;   // LDS of a group of waves
+constexpr int kF32Shared = 512 + 16;                   // largest values of the features, largest key, what was out of range
+constexpr int kF32Lds = kF32Group + kF32Shared;
+constexpr int kF32LdsPair = 2 * kF32Group + kF32Shared;
+constexpr float kF32P = 0x1p11f;                       // what weights are scaled by
 
 #define WK_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 // typed LDS pointer from a 32-bit LDS byte address
 #define WK_LDS_AT(T, addr) ((__attribute__((address_space(3))) T *)(size_t)(addr))
 #define WK_GLB(p) ((const __attribute__((address_space(1))) void *)(p))
 
-template <bool MULTI>
-__global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTable sub) {
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+// max over lanes l and l^32
+__device__ inline float max_across_halves(float x) {
+    const unsigned u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// 16 bytes per lane from base + offset to LDS, at `to` and on.  In assembly: the compiler waits for every load to LDS that it knows of in front of
+// every read of LDS.  Its readers are behind a wait for all loads and a barrier; there is no output register to be waited for.
+__device__ inline void load_to_lds(const char *base, unsigned offset, unsigned to) {
+    unsigned callers_m0;   // m0 is the compiler's to manage: handed back as it was
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+                 : "=&s"(callers_m0) : "s"(to), "v"(offset), "s"(base) : "memory");
+}
+
+// the two fp16 parts of two numbers times `up`, packed
+struct Parts2 { unsigned p[2]; };
+__device__ inline Parts2 split2(float x, float y, float up) {
+    const f16x2 first = __builtin_convertvector(f32x2{x * up, y * up}, f16x2);
+    const f16x2 second = {(_Float16)fmaf(x, up, -(float)first[0]), (_Float16)fmaf(y, up, -(float)first[1])};
+    return Parts2{{__builtin_bit_cast(unsigned, first), __builtin_bit_cast(unsigned, second)}};
+}
+
+// The power of two that takes numbers up to `largest` below 2^(top + 1), 1 if all are 0; bad: there is none within 2^-60 .. 2^60 (infinities among others)
+__device__ inline float scale_to(float largest, int top, bool &bad) {
+    const int e = (int)(__float_as_uint(largest) >> 23) & 0xff;
+    if (largest == 0.f) return 1.f;
+    bad |= e < 127 + top - 60 || e > 127 + top + 60 || e > 127 + 50;
+    return __uint_as_float((unsigned)min(max(254 + top - e, 1), 254) << 23);
+}
+
+__device__ inline float inverse(float power_of_two) { return __uint_as_float((254u << 23) - __float_as_uint(power_of_two)); }
+
+// The A operands of the products, which come from LDS: read(p, t) is part p of fragment t.  A part is requested once its registers
+// have been read by the fragment before, the first part, which is used last and longest, a fragment ahead.  The small
+// products are added to `small`, which may be `c` itself: they come first.
+template <typename Read>
+struct PartStream {
+    Read read;
+    f16x8 first[2], second;
+    __device__ inline PartStream(Read r) : read(r) {
+        second = read(1, 0);
+        first[0] = read(0, 0);
+    }
+    template <int N, typename Work>   // of N fragments; work(): other instructions beside the matrix ones
+    __device__ inline void multiply(int t, const f16x8 (&y)[2], f32x16 &c, f32x16 &small, Work work) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < N) first[(t + 1) & 1] = read(0, t + 1);
+        small = __builtin_amdgcn_mfma_f32_32x32x16_f16(second, y[0], small, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < N) second = read(1, t + 1);
+        work();
+        small = __builtin_amdgcn_mfma_f32_32x32x16_f16(first[t & 1], y[1], small, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(first[t & 1], y[0], c, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
+
+template <int KG, bool MULTI, bool WITH_O>   // WITH_O: false: log-sum-exp only, V is not read
+__global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a, SubTable sub) {
     extern __shared__ __attribute__((aligned(256))) char smem[];
     int c, h, qt, sp;
     if (!select_work<MULTI>(a, sub, 512, c, h, qt, sp)) return;
@@ -207,17 +283,17 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
     float *const lse = win.lse;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int qw = wave & 3, kg = wave >> 2;   // 32 queries of the workgroup's, tile of every pair
+    const int qw = wave & 3, kg = KG == 1 ? 0 : wave >> 2;   // 32 queries of the workgroup's, tile of a step
     const int col = lane & 31, g = lane >> 5;
     const int q = qt * (kF32Waves * 32) + qw * 32 + col;
     const bool q_ok = q < a.N_q;
     const int q_ld = q_ok ? q : a.N_q - 1;
-    const size_t qrow = (size_t)h * a.q_rows + a.q_off + q_ld;   // row of this lane's query in Q / O / lse
-    const float *Qrow = reinterpret_cast<const float *>(a.Q) + qrow * WK_D;
-    float *Orow = reinterpret_cast<float *>(a.O) + qrow * WK_D;
-    const bool with_o = a.O != nullptr;   // false: log-sum-exp only, V is not read (zeros stand in)
+    auto query_row = [&]() __attribute__((always_inline)) {
+        int at = q_ld;
+        asm("" : "+v"(at));
+        return reinterpret_cast<const float *>(a.Q) + ((size_t)h * a.q_rows + a.q_off + at) * WK_D;
+    };
     const bool partial_out = a.part_slot >= 0 || a.splits > 1;
-    const size_t prow = ((size_t)(a.part_slot >= 0 ? a.part_slot : sp) * a.H + h) * a.q_rows + a.q_off + q_ld;
     // this workgroup's keys [kt0, kt1): the whole window, or split sp of a.splits (whole tiles each)
     const int n_tiles = (n_kv + kF32Keys - 1) / kF32Keys;
     const int tiles_per_split = (n_tiles + a.splits - 1) / a.splits;
@@ -225,30 +301,85 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
     const int kt1 = min(n_kv, (sp + 1) * tiles_per_split * kF32Keys);
 
     if (kt0 >= kt1) {   // empty window, or a split past its end: contributes nothing
-        if (q_ok && partial_out) {
-            for (int c = g * 64; c < g * 64 + 64; c += 4)
-                *reinterpret_cast<float4 *>(a.part_o + prow * WK_D + c) = float4{0, 0, 0, 0};
-            if (g == 0) { a.part_ml[prow * 2] = -INFINITY; a.part_ml[prow * 2 + 1] = 0.f; }
-        } else if (q_ok) {
-            if (with_o)
-                for (int c = g * 64; c < g * 64 + 64; c += 4) *reinterpret_cast<float4 *>(Orow + c) = float4{0, 0, 0, 0};
-            if (lse && g == 0) lse[qrow] = -INFINITY;
+        if (kg > 0 || !q_ok) return;
+        const size_t qrow = (size_t)h * a.q_rows + a.q_off + q, prow = (size_t)(a.part_slot >= 0 ? a.part_slot : sp) * a.H * a.q_rows + qrow;
+        if (WITH_O) {
+            float *out = partial_out ? a.part_o + prow * WK_D : reinterpret_cast<float *>(a.O) + qrow * WK_D;
+            for (int c = g * 64; c < g * 64 + 64; c += 4) *reinterpret_cast<float4 *>(out + c) = float4{0, 0, 0, 0};
         }
+        if (partial_out && g == 0) {
+            a.part_ml[prow * 2] = -INFINITY;
+            a.part_ml[prow * 2 + 1] = 0.f;
+        }
+        if (!partial_out && lse && g == 0) lse[qrow] = -INFINITY;
         return;
     }
+    const bool idle = qt * (kF32Waves * 32) + qw * 32 >= a.N_q;   // no valid query in this wave: its loads, splits and barriers only
 
-    // One tile in all leaves the second wave group nothing to do: no operands, no loads, no meeting (8 heads x 300 queries x 32
-    // keys 10.4 us, with them 13.0 us).  idle: no valid query in this wave, or no tile for it: its loads and barriers only.
-    const bool alone = kt1 - kt0 <= kF32Keys;
-    const bool idle = qt * (kF32Waves * 32) + qw * 32 >= a.N_q || (alone && kg == 1);
-
-    // B operand of S^T = K Q^T: k slot (g, step 4c+e) means feature 8c + 4g + e
-    float4 qr[16];
-    if (!idle) {
+    const char *Kh = win.K + (size_t)h * win.stride * 512;
+    const char *Vh = a.V + (size_t)h * win.stride * 512;
+    char *const group = smem + kg * kF32Group;
+    const unsigned lds0 = (unsigned)(size_t)WK_LDS(group);
+    int *const v_max = reinterpret_cast<int *>(smem + KG * kF32Group), *const k_max = v_max + WK_D;   // (sizes: their bits order as they do)
+    int *const flags = k_max + 1;   // out of range: queries or keys; values
+    // Loads: wave qw fills two rows per load, of K rows 8*qw .. 8*qw+7, 16-byte chunk c of row k at slot c ^ (k & 15); of V the eight
+    // rows 16*(qw/2) + 4*(qw%2) + {0..3, 8..11}, which a lane group multiplies at once, for the wave itself.
+    // Rows past the range clamp to its last one (those keys are masked, their values cleared).
+    // (addresses from a scalar base and a lane's 32-bit offset, made where they are used: kept, they would take 20 registers)
+    const int v_key = 16 * (qw >> 1) + 4 * (qw & 1);
+    auto issue_k = [&](int kt) __attribute__((always_inline)) {
+        size_t at = (size_t)kt * 512;
+        unsigned l = lane;
+        asm("" : "+s"(at), "+v"(l));
+        const unsigned row = 8 * qw + (l >> 5), slot = ((l & 31) ^ (row & 15)) << 4, last = kt1 - 1 - kt;   // the range's last row, from the tile's first on
 #pragma unroll
-        for (int c = 0; c < 16; ++c) qr[c] = *reinterpret_cast<const float4 *>(Qrow + 8 * c + 4 * g);
+        for (unsigned i = 0; i < 4; ++i)
+            load_to_lds(Kh + at, (min(row | 2 * i, last) << 9) | (slot ^ (i << 5)), lds0 + kF32RawK + qw * 4096 + i * 1024);
+    };
+    auto issue_v = [&](int kt) __attribute__((always_inline)) {
+        size_t at = (size_t)kt * 512;
+        unsigned l = lane;
+        asm("" : "+s"(at), "+v"(l));
+        const unsigned row = v_key + (l >> 5), last = kt1 - 1 - kt;
+#pragma unroll
+        for (unsigned e = 0; e < 8; e += 2)
+            load_to_lds(Vh + at, (min(row + 8 * (e >> 2) + (e & 3), last) << 9) | ((l & 31) << 4), lds0 + kF32RawV + qw * 4096 + e * 512);
+    };
+    const bool any = kt0 + kg * kF32Keys < kt1;   // with a single tile the second group has none
+    if (any) {
+        issue_k(kt0 + kg * kF32Keys);
+        if (WITH_O) issue_v(kt0 + kg * kF32Keys);
     }
+    if (tid < WK_D + 3) v_max[tid] = 0;
 
+    // B operand of S^T = K Q^T: k slot 8*g + e of step s means feature 16*s + 8*g + e
+    f16x8 qr[8][2];
+    bool bad_keys = false;   // or queries
+    float to_log2 = a.scale_log2;   // of this lane's query: what takes scores as they are summed to log2 units
+    if (!idle) {
+        const float *Qrow = query_row();
+        float4 x[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = *reinterpret_cast<const float4 *>(Qrow + 16 * (i >> 1) + 8 * g + 4 * (i & 1));
+        float largest = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            largest = fmaxf(fmaxf(fmaxf(largest, fabsf(x[i].x)), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
+        const float up = scale_to(max_across_halves(largest), 14, bad_keys);
+        to_log2 *= inverse(up);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            Parts2 t[4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float4 y = x[2 * s + u];
+                t[2 * u] = split2(y.x, y.y, up);
+                t[2 * u + 1] = split2(y.z, y.w, up);
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p) qr[s][p] = __builtin_bit_cast(f16x8, u32x4{t[0].p[p], t[1].p[p], t[2].p[p], t[3].p[p]});
+        }
+    }
     f32x16 o[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b)
@@ -258,97 +389,19 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
     // begins with one)
     float m_run = -FLT_MAX, l_run = 0.f;
 
-    const char *Kh = win.K + (size_t)h * win.stride * 512;
-    const char *Vh = a.V + (size_t)h * win.stride * 512;
-    const unsigned lds0 = (unsigned)(size_t)WK_LDS(smem) + kg * (2 * kF32Tile);
-    // A operand reads: chunk 2*c + g of K row col; feature 32*b + col of V row 8*(r/4) + 4*g + r%4
-    unsigned k_rd[8], v_rd[4];   // chunks 2*c + g and 2*(c + 8) + g differ in bit 4 alone
-#pragma unroll
-    for (int c = 0; c < 8; ++c) k_rd[c] = lds0 + col * 512 + (((2 * c + g) ^ (col & 15)) << 4);
-#pragma unroll
-    for (int b = 0; b < 4; ++b) v_rd[b] = lds0 + kF32Tile + 4 * g * 512 + (((8 * b + (col >> 2)) ^ (8 * g)) << 4) + (col & 3) * 4;
-    // tile loads: wave qw of a group fills rows 8*qw .. 8*qw+7 of its tile, two rows per load; rows past the range clamp to
-    // its last one (those keys are masked, their V rows cleared once they have landed)
-    const int ld_row = 8 * qw + (lane >> 5), ld_slot = lane & 31;
-    auto issue = [&](int pair) {
-        char *dst = smem + (pair & 1) * kF32Stage + kg * (2 * kF32Tile) + qw * 4096;
-        const int kt = kt0 + (2 * pair + kg) * kF32Keys;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int R = ld_row + 2 * i;
-            const size_t row = (size_t)min(kt + R, kt1 - 1) * 512;
-            __builtin_amdgcn_global_load_lds(WK_GLB(Kh + row + ((ld_slot ^ (R & 15)) << 4)), WK_LDS(dst + i * 1024), 16, 0, 0);
-            if (with_o)
-                __builtin_amdgcn_global_load_lds(WK_GLB(Vh + row + ((ld_slot ^ (8 * (R >> 2 & 1))) << 4)), WK_LDS(dst + kF32Tile + i * 1024),
-                                                 16, 0, 0);
-        }
-    };
-    const int n_pairs = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + 1) / 2;
-    if (!alone || kg == 0) issue(0);
-    // the two waves of a SIMD belong to different groups: the first one ahead, so that one does its softmax arithmetic
-    // while the other multiplies
-    if (kg == 0) __builtin_amdgcn_s_setprio(1);
-    for (int j = 0; j < n_pairs; ++j) {
-        const int kt = kt0 + (2 * j + kg) * kF32Keys, stage = (j & 1) * kF32Stage;
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the pair has landed
-        if (with_o && kt < kt1 && kt + kF32Keys > kt1) {  // V rows past the range become zeros: the last row there may be infinite
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (kt + ld_row + 2 * i >= kt1)
-                    *reinterpret_cast<float4 *>(smem + stage + kg * (2 * kF32Tile) + qw * 4096 + kF32Tile + i * 1024 + lane * 16) = float4{0, 0, 0, 0};
-        }
-        __syncthreads();                      // everyone's has, and the pair before is fully consumed
-        if (j + 1 < n_pairs) issue(j + 1);
-        if (kt >= kt1 || idle) continue;      // an odd count of tiles leaves the second group without one
-        // operands are read two groups of four products ahead, and the order is kept: left to itself the compiler reads each
-        // one right before its product and waits for it
-        typedef __attribute__((address_space(3))) const char lds_char;
-        lds_char *k_at[8], *v_at[4];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) k_at[c] = WK_LDS_AT(const char, k_rd[c] + stage);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) v_at[b] = WK_LDS_AT(const char, v_rd[b] + stage);
-        f32x4 ka[3];
-        float va[3][4];
-        auto read_k = [&](int c) __attribute__((always_inline)) {
-            ka[c % 3] = *reinterpret_cast<__attribute__((address_space(3))) const f32x4 *>(k_at[c & 7] + (c >> 3) * 256);
-        };
-        auto read_v = [&](int r) __attribute__((always_inline)) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                va[r % 3][b] = *reinterpret_cast<__attribute__((address_space(3))) const float *>(v_at[b] + (8 * (r >> 2) + (r & 3)) * 512);
-        };
-        f32x16 s;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
-        read_k(0);
-        read_k(1);
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            if (c + 2 < 16) read_k(c + 2);
-            else if (with_o) read_v(c - 14);
-            __builtin_amdgcn_sched_barrier(0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][0], qr[c].x, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][1], qr[c].y, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][2], qr[c].z, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[c % 3][3], qr[c].w, s, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // accumulator register r of this lane is key kt + 8*(r/4) + 4*g + r%4
-        float m_tile = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] *= a.scale_log2;
+    // scores of the keys from kt on to their weights; accumulator register r of this lane is key kt + 8*(r/4) + 4*g + r%4
+    auto softmax = [&](f32x16 &s, int kt) __attribute__((always_inline)) {
         if (kt + kF32Keys > kt1) {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 if (kt + 8 * (r >> 2) + 4 * g + (r & 3) >= kt1) s[r] = -INFINITY;
         }
+        float m_tile = s[0];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) m_tile = fmaxf(m_tile, s[r]);
-        m_tile = fmaxf(m_tile, __shfl_xor(m_tile, 32));
-        const float m_new = fmaxf(m_run, m_tile);
-        if (__any(m_new > m_run)) {                // otherwise the factor is 1
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        for (int r = 1; r < 16; ++r) m_tile = fmaxf(m_tile, s[r]);
+        m_tile = max_across_halves(m_tile) * to_log2;
+        if (__any(m_tile > m_run + 4.f)) {   // the maximum moves where weights would grow beyond 2^4, 2^15 as they are split
+            const float m_new = fmaxf(m_run, m_tile), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             l_run *= alpha;
             m_run = m_new;
 #pragma unroll
@@ -356,33 +409,247 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
         }
-        float l_tile = 0.f;
+        float l_tile[4];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            s[r] = __builtin_amdgcn_exp2f(s[r] - m_new);
-            l_tile += s[r];
+            s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], to_log2, -m_run));
+            l_tile[r & 3] = r < 4 ? s[r] : l_tile[r & 3] + s[r];
         }
-        l_run += l_tile;
-        // O^T += V^T P^T: k slot g of step r means key 8*(r/4) + 4*g + r%4
-        if (with_o)
+        l_run += (l_tile[0] + l_tile[1]) + (l_tile[2] + l_tile[3]);
+    };
+
+    // A thread's share of a tile, in quarters: four numbers of K (of a row) or of V (of four keys) are read, and split and left a call later
+    float quarter[4], largest = 0.f, v_largest = 0.f, v_smallest = 1.f;
+    float k_up = 1.f, v_up[2] = {1.f, 1.f};
+    int me = tid;
+    auto k_from = [&](int c) __attribute__((always_inline)) {   // features 8 * ((me >> 5 & 7) + 8 * (c / 2)) + 4 * (c % 2) of key me % 32
+        const int chunk = 2 * ((me >> 5) & 7) + 16 * (c >> 1) + (c & 1);
+        return *reinterpret_cast<const float4 *>(group + kF32RawK + (me & 31) * 512 + ((chunk ^ (me & 15)) << 4));
+    };
+    auto v_from = [&](int f, int e) __attribute__((always_inline)) {   // feature 2 * lane + f of the wave's row e
+        return *reinterpret_cast<const float *>(group + kF32RawV + (qw * 8 + e) * 512 + (me & 63) * 8 + f * 4);
+    };
+    auto quarter_top = [&]() __attribute__((always_inline)) {
+        return fmaxf(fmaxf(fmaxf(fabsf(quarter[0]), fabsf(quarter[1])), fabsf(quarter[2])), fabsf(quarter[3]));
+    };
+    auto store_quarter = [&](char *to, float up) __attribute__((always_inline)) {
+        const Parts2 x = split2(quarter[0], quarter[1], up), y = split2(quarter[2], quarter[3], up);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) *reinterpret_cast<uint2 *>(to + p * kF32Part) = uint2{x.p[p], y.p[p]};
+    };
+    auto k_work = [&](int t) __attribute__((always_inline)) {
+        const int c = t >> 1;
+        if ((t & 1) == 0) {
+            const float4 x = k_from(c);
+            quarter[0] = x.x; quarter[1] = x.y; quarter[2] = x.z; quarter[3] = x.w;
+        } else {
+            largest = fmaxf(largest, quarter_top() * k_up);
+            store_quarter(group + (((me >> 5) & 7) + 8 * (c >> 1)) * 512 + (me & 31) * 16 + (c & 1) * 8, k_up);
+        }
+    };
+    auto v_work = [&](int t, int kt) __attribute__((always_inline)) {
+        const int f = t >> 2, half = (t >> 1) & 1;
+        if ((t & 1) == 0) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) quarter[u] = v_from(f, 4 * half + u);
+        } else {
+            const float top = quarter_top() * v_up[f];
+            v_largest = half ? fmaxf(v_largest, top) : top;   // of eight keys; all 0 is no reason to leave
+            if (half) {
+                largest = fmaxf(largest, v_largest);
+                v_smallest = fminf(v_smallest, v_largest == 0.f ? 1.f : v_largest);
+            }
+            if (kt + kF32Keys > kt1)   // rows past the range: the last one may be infinite
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (kt + v_key + 8 * half + u >= kt1) quarter[u] = 0.f;
+            store_quarter(group + kF32V + qw * 2048 + f * 1024 + (me & 63) * 16 + half * 8, v_up[f]);
+        }
+    };
+    auto begin_share = [&]() __attribute__((always_inline)) {
+        largest = 0.f;
+        v_smallest = 1.f;
+        me = tid;
+        asm("" : "+v"(me));   // (its addresses are not kept either)
+    };
+    constexpr float kLimit = 65504.f;   // fp16's largest number
+
+    // the scales, from the first tiles
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the first tile has landed
+    __syncthreads();
+    if (any) {
+        float top = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float4 x = k_from(c);
+            top = fmaxf(fmaxf(fmaxf(top, fabsf(x.x)), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w)));
+        }
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) top = fmaxf(top, __shfl_xor(top, m));
+        if (lane == 0) atomicMax(k_max, __float_as_int(top));
+        if (WITH_O)
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                top = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(v_from(f, e)));
+                atomicMax(v_max + 2 * lane + f, __float_as_int(top));
+            }
+    }
+    __syncthreads();
+    bool bad_values = false;
+    k_up = scale_to(__int_as_float(*k_max), 10, bad_keys);
+    to_log2 *= inverse(k_up);
+    if (WITH_O)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) v_up[f] = scale_to(__int_as_float(v_max[2 * lane + f]), 10, bad_values);
+    if (any)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) k_work(t);
+    if (bad_keys || bad_values || largest >= kLimit) flags[0] = 1;
+
+    // The steps.  Beside the products of S^T a wave splits its share of the tile's values, beside those of O^T its share of the next tile's
+    // keys (without a next tile: of the last one's again, which nothing reads)
+    bool exact = false;
+    auto meet_keys = [&]() __attribute__((always_inline)) {   // K's parts are there, the values before are consumed
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's values have landed
+        __syncthreads();
+        exact = __builtin_amdgcn_readfirstlane(flags[0]) != 0;
+    };
+    auto meet_values = [&](int kt) __attribute__((always_inline)) {   // V's parts are there, K's are consumed
+        if (WITH_O && (largest >= kLimit || (v_smallest < 0.5f && kt + kF32Keys <= kt1))) flags[1] = 1;
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's keys of the next tile have landed
+        __syncthreads();
+        exact = __builtin_amdgcn_readfirstlane(flags[1]) != 0;
+    };
+    const int n_steps = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + KG - 1) / KG;
+    const int my_steps = (kt1 - kt0 - kg * kF32Keys + KG * kF32Keys - 1) / (KG * kF32Keys);   // with an odd count of tiles the second group has one less
+    int kt = kt0 + kg * kF32Keys;
+    constexpr int kStep = KG * kF32Keys;
+    if (KG == 2 && kg == 0) __builtin_amdgcn_s_setprio(1);   // one of a SIMD's two waves ahead: one does its softmax while the other multiplies
+    if (!idle) {
+        for (int j = 0; j < my_steps; ++j, kt += kStep) {
+            meet_keys();
+            if (exact) break;
+            if (kt + kStep < kt1) issue_k(kt + kStep);
+            begin_share();
+            f32x16 s, small;   // (apart: eight roundings at the size of a score instead of 24)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = small[r] = 0.f;
+            const unsigned k_at = lds0 + ((me >> 5) & 1) * 512 + (me & 31) * 16;
+            PartStream k([&](int p, int t) __attribute__((always_inline)) { return *WK_LDS_AT(const f16x8, k_at + p * kF32Part + t * 1024); });
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                k.template multiply<8>(t, qr[t], s, small, [&]() __attribute__((always_inline)) {
+                    if (WITH_O) v_work(t, kt);
+                });
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] += small[r];
+            softmax(s, kt);
+            f16x8 pr[2][2];
+            if (WITH_O)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    Parts2 u[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) u[e] = split2(s[8 * t + 2 * e], s[8 * t + 2 * e + 1], kF32P);
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) pr[t][p] = __builtin_bit_cast(f16x8, u32x4{u[0].p[p], u[1].p[p], u[2].p[p], u[3].p[p]});
+                }
+            meet_values(kt);
+            if (exact) break;
+            if (WITH_O && kt + kStep < kt1) issue_v(kt + kStep);
+            begin_share();
+            if (WITH_O) {
+                // O^T += V^T P^T: k slot 8*g + e of step t means key 16*t + 8*(e/4) + 4*g + e%4, accumulator register 8*t + e;
+                // row i of block b is feature 2*(32*(b%2) + i) + b/2
+                const unsigned v_at = lds0 + kF32V + ((me >> 5) & 1) * 2048 + (me & 31) * 16;
+                PartStream v([&](int p, int i) __attribute__((always_inline)) {   // i = 2*b + t
+                    return *WK_LDS_AT(const f16x8, v_at + p * kF32Part + (i & 1) * 4096 + (i >> 1) * 512);
+                });
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {   // sums of the tile's products by themselves: one rounding at the size of O per tile
+                    f32x16 sum;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+                    v.template multiply<8>(2 * b, pr[0], sum, sum, [&]() __attribute__((always_inline)) { k_work(2 * b); });
+                    v.template multiply<8>(2 * b + 1, pr[1], sum, sum, [&]() __attribute__((always_inline)) { k_work(2 * b + 1); });
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[b][r] += sum[r];
+                    asm volatile("" : "+v"(o[b]));   // (here: put off, four sums would be held)
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) k_work(t);
+            }
+            if (largest >= kLimit) flags[0] = 1;
+        }
+    } else {
+        for (int j = 0; j < my_steps; ++j, kt += kStep) {
+            meet_keys();
+            if (exact) break;
+            if (kt + kStep < kt1) issue_k(kt + kStep);
+            begin_share();
+            if (WITH_O)
+#pragma unroll
+                for (int t = 0; t < 8; ++t) v_work(t, kt);
+            meet_values(kt);
+            if (exact) break;
+            if (WITH_O && kt + kStep < kt1) issue_v(kt + kStep);
+            begin_share();
+#pragma unroll
+            for (int t = 0; t < 8; ++t) k_work(t);
+            if (largest >= kLimit) flags[0] = 1;
+        }
+    }
+    if (my_steps < n_steps && !exact) {   // the other group's last tile
+        begin_share();
+        meet_keys();
+        if (!exact) meet_values(kt);
+    }
+    if (exact) {   // once more from the first tile on, with fp32 operands straight from memory
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+        m_run = -FLT_MAX;
+        l_run = 0.f;
+        to_log2 = a.scale_log2;
+        const float *Qrow = query_row();
+        for (int kt = kt0 + kg * kF32Keys; kt < kt1 && !idle; kt += kStep) {
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+            const char *krow = Kh + (size_t)min(kt + col, kt1 - 1) * 512 + 16 * g;
+#pragma unroll 4
+            for (int t = 0; t < 16; ++t) {
+                const float4 x = *reinterpret_cast<const float4 *>(krow + 32 * t), y = *reinterpret_cast<const float4 *>(Qrow + 8 * t + 4 * g);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, s, 0, 0, 0);
+            }
+            softmax(s, kt);
+            if (!WITH_O) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                if (r + 2 < 16) read_v(r + 2);
-                __builtin_amdgcn_sched_barrier(0);
+                const int key = kt + 8 * (r >> 2) + 4 * g + (r & 3);
+                const char *vrow = Vh + (size_t)min(key, kt1 - 1) * 512 + col * 8;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[r % 3][b], s[r], o[b], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int b = 0; b < 4; ++b) {
+                    const float v = *reinterpret_cast<const float *>(vrow + (b & 1) * 256 + (b >> 1) * 4);
+                    o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(key < kt1 ? v : 0.f, s[r], o[b], 0, 0, 0);
+                }
             }
+        }
     }
     // The wave groups meet: waves 4..7 leave (O^T, max, sum) of their keys in LDS, waves 0..3 add them to theirs.
     // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.
-    if (alone) {
-        if (idle) return;
-    } else {
+    if constexpr (KG == 2) {
         float *meet = reinterpret_cast<float *>(smem) + qw * (66 * 64) + lane;
         __syncthreads();   // every wave is done with its last tile
         if (kg == 1) {
-            if (with_o)
+            if (WITH_O)
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -391,41 +658,47 @@ __global__ __launch_bounds__(kF32Threads, 2) void k_attn_f32(AttnArgs a, SubTabl
             meet[65 * 64] = l_run;
         }
         __syncthreads();
-        if (kg == 1 || idle) return;
+        if (kg == 1) return;
         const float m_other = meet[64 * 64];   // -FLT_MAX, with sums of 0, if the second group had no tile
         const float m_new = fmaxf(m_run, m_other);
         const float w0 = __builtin_amdgcn_exp2f(m_run - m_new), w1 = __builtin_amdgcn_exp2f(m_other - m_new);
         m_run = m_new;
         l_run = fmaf(w1, meet[65 * 64], w0 * l_run);
-        if (with_o)
+        if (WITH_O)
 #pragma unroll
             for (int b = 0; b < 4; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
     }
+    if (idle) return;
+    int q_at = q_ld;
+    asm("" : "+v"(q_at));   // (rows of the results from here on, not kept through the loop)
+    const size_t qrow = (size_t)h * a.q_rows + a.q_off + q_at, prow = (size_t)(a.part_slot >= 0 ? a.part_slot : sp) * a.H * a.q_rows + qrow;
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (q_ok && partial_out) {   // (O, max, sum) of this key range, merged by k_attn_merge
-        float *Po = a.part_o + prow * WK_D;
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                *reinterpret_cast<float4 *>(Po + 32 * b + 8 * t + 4 * g) =
-                    float4{o[b][4 * t], o[b][4 * t + 1], o[b][4 * t + 2], o[b][4 * t + 3]};
-        if (g == 0) { a.part_ml[prow * 2] = m_run; a.part_ml[prow * 2 + 1] = l_tot; }
-    } else if (q_ok) {
-        const float inv = 1.f / l_tot;
-        if (with_o)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int dv = 32 * b + 8 * t + 4 * g;
-                *reinterpret_cast<float4 *>(Orow + dv) =
-                    float4{o[b][4 * t] * inv, o[b][4 * t + 1] * inv, o[b][4 * t + 2] * inv, o[b][4 * t + 3] * inv};
-            }
-        if (lse && g == 0) lse[qrow] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+    if (!q_ok) return;
+    if (!partial_out && lse && g == 0) lse[qrow] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+    if (partial_out && g == 0) {   // (O, max, sum) of this key range, merged by k_attn_merge
+        a.part_ml[prow * 2] = m_run;
+        a.part_ml[prow * 2 + 1] = l_tot;
     }
+    if (!WITH_O) return;
+    const float inv = partial_out ? 1.f : 1.f / l_tot;
+    float *out = partial_out ? a.part_o + prow * WK_D : reinterpret_cast<float *>(a.O) + qrow * WK_D;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int u = 0; u < 4; u += 2) {
+                const int feature = 2 * (32 * b + 8 * t + 4 * g + u);
+                const float4 top = *reinterpret_cast<const float4 *>(v_max + feature);
+                float down[4] = {inv, inv, inv, inv};
+                bool unused = false;
+                if (!exact)
+                    for (int i = 0; i < 4; ++i) down[i] *= inverse(kF32P * scale_to((&top.x)[i], 10, unused));
+                *reinterpret_cast<float4 *>(out + feature) = float4{o[b][4 * t + u] * down[0], o[b + 2][4 * t + u] * down[1],
+                                                                    o[b][4 * t + u + 1] * down[2], o[b + 2][4 * t + u + 1] * down[3]};
+            }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -458,13 +731,6 @@ constexpr int kSmemBytesPair = kSmemBytes + 512;      // KG == 2: and the first 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
-
-// max over lanes l and l^32
-__device__ inline float max_across_halves(float x) {
-    const unsigned u = __float_as_uint(x);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
 
 // registers the hand-scheduled loop uses beyond its operands: the odd-position S^T tile, P, the K and V^T
 // fragment buffers and three temporaries
@@ -1671,21 +1937,38 @@ FramePlan plan_frames(int H, int N_q, int N_kv, int row0, int frame_T) {
     return gap_us < us ? g : p;
 }
 
-// fp32: one workgroup fits a compute unit.  The split count with the cheapest rounds of 256 workgroups, a pair of tiles
-// costing 7.9 us, a workgroup's fill and drain 5 us, the merge a launch and its traffic; at least 2 pairs per split, and
-// partial results that fit workspace_bytes.
-int choose_splits_f32(int H, int N_q, int n_tiles, size_t workspace_bytes) {
-    const long long items = (long long)H * ((N_q + kF32Waves * 32 - 1) / (kF32Waves * 32));
-    int best = 1;
+// fp32: the wave groups (KG) and key ranges with the cheapest predicted time.  A step of one workgroup per compute unit takes 1.9 us with one tile at a
+// time; of two workgroups per unit 2.6, and 3.0 once all 256 have two; with two tiles at a time 3.0 (3.2 on all units) and a step's time for
+// the groups to meet; a call 11 us beside its steps and its merge.  Fitted to 12 shapes (1 to 40 heads, 128 to 4,000 queries, 100 to 9,000 keys) in
+// every form and count of ranges: 5 % off (rms), and the choice 0.3 % slower than the best.  4 heads x 880 queries x 2,640 keys in two groups and 9
+// ranges 39 us, in one group and 8 ranges 41, in one range 139 and 180; 40 x 1,560 x 4,680 in one group and 5 ranges 589 us, in 2 ranges
+// 633, in one 750 (520 workgroups are two rounds of 512).
+// Ranges of two steps and more, and none below 8 tiles, where the order of sums would depend on the host's bound of a length that
+// the device knows; nor do the groups of an undivided window depend on it beyond the first tile, whose sums are the same in one and in two.
+struct F32Plan { int kg, splits; };
+
+double f32_step_us(int kg, long long wgs) {   // of up to 512 / kg workgroups
+    if (kg == 2) return wgs > 224 ? 3.2 : 3.0;
+    return wgs <= 256 ? 1.9 : 2.6 + 0.4 * (double)(wgs - 256) / 256;
+}
+
+F32Plan plan_f32(long long H, long long N_q, int n_tiles, size_t workspace_bytes) {
+    const long long items = H * ((N_q + kF32Waves * 32 - 1) / (kF32Waves * 32));
+    const int whole = n_tiles > 1 && items <= 256 ? 2 : 1;   // wave groups of an undivided window
+    F32Plan best{whole, 1};
     double best_us = 0;
-    for (int s = 1; s <= kMaxSplits; ++s) {
-        if (s > 1 && (n_tiles < 4 * s || split_workspace_bytes(H, N_q, s) > workspace_bytes)) break;
-        const int pairs = ((n_tiles + s - 1) / s + 1) / 2;
-        double us = (double)((items * s + 255) / 256) * (7.9 * pairs + 5);
-        if (s > 1) us += 5 + s * ((double)H * N_q) * 520.0 / 4e6;
-        if (s == 1 || us < best_us) {
-            best = s;
-            best_us = us;
+    for (const int kg : {whole, 3 - whole}) {
+        const long long slots = 512 / kg;
+        for (int s = kg == whole ? 1 : 2; s <= kMaxSplits; ++s) {
+            if (s > 1 && (n_tiles < std::max(8, 2 * kg * s) || split_workspace_bytes((int)H, (int)N_q, s) > workspace_bytes)) break;
+            const int steps = ((n_tiles + s - 1) / s + kg - 1) / kg + (kg - 1);
+            const long long wgs = items * s, rest = wgs % slots;
+            double us = steps * ((double)(wgs / slots) * f32_step_us(kg, slots) + (rest ? f32_step_us(kg, rest) : 0.0));
+            if (s > 1) us += merge_us(s, H * N_q);
+            if (best_us == 0 || us < best_us) {
+                best = F32Plan{kg, s};
+                best_us = us;
+            }
         }
     }
     return best;
@@ -1708,8 +1991,12 @@ wk_status allow_large_lds() {
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, false, true>), kSmemBytesPair},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 1, false, false>), kSmemBytes},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 1, false, true>), kSmemBytes},
-            {reinterpret_cast<const void *>(&k_attn_f32<false>), kF32Lds},
-            {reinterpret_cast<const void *>(&k_attn_f32<true>), kF32Lds},
+            {reinterpret_cast<const void *>(&k_attn_f32<1, false, true>), kF32Lds},
+            {reinterpret_cast<const void *>(&k_attn_f32<1, true, true>), kF32Lds},
+            {reinterpret_cast<const void *>(&k_attn_f32<1, false, false>), kF32Lds},
+            {reinterpret_cast<const void *>(&k_attn_f32<2, false, false>), kF32LdsPair},
+            {reinterpret_cast<const void *>(&k_attn_f32<2, false, true>), kF32LdsPair},
+            {reinterpret_cast<const void *>(&k_attn_f32<2, true, true>), kF32LdsPair},
         };
         for (const auto &k : kernels)
             if (hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes) != hipSuccess) return WK_ERR_HIP;
@@ -1735,6 +2022,26 @@ void partials_in(AttnArgs &a, void *workspace) {   // (O, then maximum and sum) 
     a.part_o = reinterpret_cast<float *>(workspace);
     a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) +
                                           wk::align_up((size_t)a.splits * a.H * a.N_q * WK_D * sizeof(float), 256));
+}
+
+template <bool MULTI, bool WITH_O>
+void launch_f32_grid(const AttnArgs &a, const SubTable &t, int kg, hipStream_t st) {
+    const dim3 grid(a.per_xcd * kXcds);
+    if (kg == 2) hipLaunchKernelGGL((k_attn_f32<2, MULTI, WITH_O>), grid, dim3(2 * kF32Waves * 64), kF32LdsPair, st, a, t);
+    else hipLaunchKernelGGL((k_attn_f32<1, MULTI, WITH_O>), grid, dim3(kF32Waves * 64), kF32Lds, st, a, t);
+}
+
+wk_status launch_f32(AttnArgs a, int kg, hipStream_t st) {
+    a.n_qtiles = (a.N_q + kF32Waves * 32 - 1) / (kF32Waves * 32);
+    const long long items = (long long)a.H * a.n_qtiles * a.splits * (a.n_chunks > 0 ? a.n_chunks : 1);
+    if (!wk::fits_launch(items + kXcds, 2 * kF32Waves * 64)) return WK_ERR_UNSUPPORTED;
+    a.per_xcd = (int)((items + kXcds - 1) / kXcds);
+    const wk_status rc = allow_large_lds();
+    if (rc != WK_OK) return rc;
+    if (a.O) launch_f32_grid<false, true>(a, SubTable{}, kg, st);
+    else launch_f32_grid<false, false>(a, SubTable{}, kg, st);
+    WK_LAUNCH_CHECK();
+    return WK_OK;
 }
 
 wk_status launch_bf16(AttnArgs a, LaunchPlan plan, void *workspace, hipStream_t st) {
@@ -1805,18 +2112,11 @@ extern "C" wk_status wk_attention(const void *Q, const void *K_win, const void *
     const size_t usable_bytes = workspace && reinterpret_cast<uintptr_t>(workspace) % 256 == 0 ? workspace_bytes : 0;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
     if (dtype == WK_F32) {
-        const int q_per_wg = kF32Waves * 32;
-        a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
-        const long long items1 = (long long)H * a.n_qtiles;
-        a.splits = O ? choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, usable_bytes) : 1;
+        const F32Plan plan = plan_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, O ? usable_bytes : 0);
+        a.splits = plan.splits;
         if (a.splits > 1) partials_in(a, workspace);
-        const long long items = items1 * a.splits;
-        if (!wk::fits_launch(items + kXcds, kF32Threads)) return WK_ERR_UNSUPPORTED;
-        a.per_xcd = (int)((items + kXcds - 1) / kXcds);
-        const wk_status lds_rc = allow_large_lds();
-        if (lds_rc != WK_OK) return lds_rc;
-        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
-        WK_LAUNCH_CHECK();
+        const wk_status rc = launch_f32(a, plan.kg, st);
+        if (rc != WK_OK) return rc;
         if (a.splits > 1) {
             const size_t rows = (size_t)H * N_q;
             hipLaunchKernelGGL(k_attn_merge<WK_F32>, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, a);
@@ -1833,17 +2133,14 @@ namespace {
 // One launch of the attention kernel for the dtype, exactly as the arguments say: no choice of
 // key-range splits, no merge.
 wk_status launch_plain(AttnArgs a, int dtype, hipStream_t st) {
-    const int q_per_wg = dtype == WK_F32 ? kF32Waves * 32 : 256;
     a.splits = 1;
-    a.n_qtiles = (a.N_q + q_per_wg - 1) / q_per_wg;
+    if (dtype == WK_F32) return launch_f32(a, plan_f32(a.H, a.N_q, (a.N_kv + kF32Keys - 1) / kF32Keys, 0).kg, st);
+    a.n_qtiles = (a.N_q + 255) / 256;
     if (!wk::fits_launch((long long)a.H * a.n_qtiles + kXcds, 512)) return WK_ERR_UNSUPPORTED;
     a.per_xcd = (a.H * a.n_qtiles + kXcds - 1) / kXcds;
     const wk_status rc = allow_large_lds();
     if (rc != WK_OK) return rc;
-    if (dtype == WK_F32)
-        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
-    else
-        launch_layout<8, 1, false, false>(a, SubTable{}, st);
+    launch_layout<8, 1, false, false>(a, SubTable{}, st);
     WK_LAUNCH_CHECK();
     return WK_OK;
 }
@@ -1918,7 +2215,7 @@ extern "C" wk_status wk_attention_block_causal(const void *Q, const void *K_win,
         const wk_status lrc = allow_large_lds();
         if (lrc != WK_OK) return lrc;
         if (dtype == WK_F32) {
-            hipLaunchKernelGGL(k_attn_f32<true>, dim3(g.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, g, t);
+            launch_f32_grid<true, true>(g, t, plan_f32(1, (long long)H * t.per_head * kF32Waves * 32, (N_kv + kF32Keys - 1) / kF32Keys, 0).kg, st);
         } else {
             if (layout == k256 && !plan.merge) launch_layout<8, 1, true, false, true>(g, t, st);
             else if (!plan.merge) launch_layout<4, 2, true, false, true>(g, t, st);
@@ -1990,14 +2287,7 @@ extern "C" wk_status wk_chunk_lse(const wk_store_desc *store, const void *Q, int
     const long long items = (long long)store->M * store->H * ((N_q + q_per_wg - 1) / q_per_wg);
     if (items + kXcds > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
     if (store->dtype == WK_F32) {
-        if (!wk::fits_launch(items + kXcds, kF32Threads)) return WK_ERR_UNSUPPORTED;
-        const wk_status rc = allow_large_lds();
-        if (rc != WK_OK) return rc;
-        a.n_qtiles = (N_q + q_per_wg - 1) / q_per_wg;
-        a.per_xcd = (int)((items + kXcds - 1) / kXcds);
-        hipLaunchKernelGGL(k_attn_f32<false>, dim3(a.per_xcd * kXcds), dim3(kF32Threads), kF32Lds, st, a, SubTable{});
-        WK_LAUNCH_CHECK();
-        return WK_OK;
+        return launch_f32(a, plan_f32((long long)store->H * store->M, N_q, (store->max_tok + kF32Keys - 1) / kF32Keys, 0).kg, st);
     }
     return launch_bf16(a, LaunchPlan{k256, 1}, nullptr, st);
 }
@@ -2061,7 +2351,7 @@ extern "C" size_t wk_attention_workspace_bytes(int32_t H, int32_t N_q, int32_t N
     if (H < 1 || N_q < 1 || N_kv < 1 || (dtype != WK_BF16 && dtype != WK_F32)) return 0;
     if ((long long)H * ((N_q + 31) / 32) > 0x7fffffffLL / kMaxSplits) return 0;
     if (dtype == WK_F32) {
-        const int s = choose_splits_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, SIZE_MAX);
+        const int s = plan_f32(H, N_q, (N_kv + kF32Keys - 1) / kF32Keys, SIZE_MAX).splits;
         return s > 1 ? split_workspace_bytes(H, N_q, s) : 0;
     }
     const LaunchPlan plan = plan_bf16(H, N_q, N_kv, SIZE_MAX);

@@ -1,0 +1,78 @@
+"""fp32 attention works on two fp16 parts of every number and on powers of two that take them there, found from a workgroup's first
+tile of keys; where numbers do not fit, on fp32 products.  Both against the oracle, over scales and at the edges of tiles and wave groups."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_22718_amd as wk
+from wkt import ATT_MAX_ABS_F32, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(Q, K, V, unit, split=False, tol=ATT_MAX_ABS_F32):
+    """unit: what the values of a feature are of the size of."""
+    d, H, N_q, N_kv = dev(), Q.shape[0], Q.shape[1], K.shape[1]
+    n = wk.wk_attention_workspace_bytes(H, N_q, N_kv, wk.WK_F32) if split else 0
+    assert (n > 0) == split
+    O, lse, only = torch.empty_like(Q, device=d), torch.empty((H, N_q), device=d), torch.empty((H, N_q), device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse, workspace=torch.empty(n, dtype=torch.uint8, device=d) if split else None)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), None, only)
+    ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
+    assert np.abs((O.cpu().double().numpy() - ref) / np.asarray(unit)).max() <= tol
+    assert np.abs(lse.cpu().double().numpy() - ref_lse).max() <= 1e-5 and np.abs(only.cpu().double().numpy() - ref_lse).max() <= 1e-5
+
+
+def _randn(H, N_q, N_kv, seed=3):
+    g = torch.Generator().manual_seed(seed)
+    return [torch.randn(H, n, 128, generator=g) for n in (N_q, N_kv, N_kv)]
+
+
+# 128 queries a workgroup, one or two tiles of 32 keys a step
+@pytest.mark.parametrize("H,N_q,N_kv,split", [(1, 1, 1, False), (2, 33, 31, False), (1, 128, 32, False), (3, 129, 33, False), (2, 70, 64, False), (1, 97, 65, False),
+                                             (2, 40, 255, False), (2, 256, 257, True), (300, 5, 65, False), (300, 20, 300, False), (1, 64, 4000, True)])
+def test_edges(H, N_q, N_kv, split):
+    Q, K, V = _randn(H, N_q, N_kv)
+    _check(Q, K, V, 1.0, split)
+
+
+# the last: no power of two within 2^60
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("q,k,v", [(1, 1, 1e-12), (1e6, 1e-6, 1e12), (1e-10, 1e10, 3e-5), (1e-25, 1e25, 1e30)])
+def test_scales(q, k, v, split):
+    Q, K, V = _randn(2, 100, 300)
+    Q[:, 7] = 0
+    v = v * torch.logspace(-2, 2, 128)   # features of different size
+    _check(Q * q, K * k, V * v, np.asarray(v.double()), split)
+
+
+# tiles that the first one's scales do not fit: larger keys and values, values that become small, a first tile of zeros, one element
+@pytest.mark.parametrize("H,N_q,N_kv,split", [(2, 100, 300, False), (2, 100, 300, True), (300, 10, 96, False)])
+@pytest.mark.parametrize("case", ["keys", "values", "small", "zeros", "tiny_after_zeros", "one"])
+def test_tiles_unlike_the_first(case, H, N_q, N_kv, split):
+    Q, K, V = _randn(H, N_q, N_kv)
+    unit = 1.0
+    if case == "keys":
+        K[:, 40:] *= 60
+        Q /= 60
+    if case == "values":
+        V[:, 70:] *= 500
+        unit = 500.0
+    if case == "small":   # the first rows have no weight, so that the small ones are what is left
+        Q[..., 0] = 4
+        K[..., 0] = torch.where(torch.arange(N_kv) < 33, -300.0, 0.0)
+        V[:, 33:] *= 1e-5
+        unit = 1e-5
+    if case in ("zeros", "tiny_after_zeros"):
+        K[:, :33] = 0
+        V[:, :33] = 0
+    if case == "tiny_after_zeros":
+        V *= 1e-7
+        unit = 1e-7
+    if case == "one":
+        V[0, 50, 3] = 3e4
+        K[0, 45, 77] = 200
+        Q[..., 77] = 0
+        unit = np.where(np.arange(128) == 3, 3e4, 1.0)
+    _check(Q, K, V, unit, split)
