@@ -3,10 +3,11 @@
 // One launch, fp64 throughout.  M is a few hundred for minute-long rollouts, a few thousand at most, so the step is bound
 // by latency: launch, pose loads, one chain of trigonometry, two reductions, ranks.  Ranks are all-pairs counts of the
 // (D, id) pairs that precede a candidate (broadcast reads from LDS), which gives the Top-k already ordered, with
-// ties to the lower chunk id, and no sort.  They are what grows with M*M, so each workgroup ranks 64 candidates only
-// -- a lane per candidate, each wave counting over its share of the others -- and works out all M distances for
+// ties to the lower chunk id, and no sort.  They are what grows with M*M, so each workgroup ranks 16 candidates only
+// -- a lane per candidate, each row of 16 lanes counting over its share of the others -- and works out all M distances for
 // itself: that costs less than a second launch would.  One workgroup ranking everything with a thread per candidate took
-// 7.4 / 47 / 662 us at M = 60 / 1,000 / 4,096; this takes 3.7 / 8.8 / 25 us.
+// 7.4 / 47 / 662 us at M = 60 / 1,000 / 4,096; workgroups of 64 candidates (and reductions by shuffles) 3.8 / 9.1 / 24.8; this takes
+// 3.3 / 5.8 / 15.3 us, of which the trigonometry of 1,000 distances on one compute unit is about 2.
 #include <cmath>
 #include <type_traits>
 
@@ -69,7 +70,40 @@ __device__ inline double normalise(double v, int mode, double mx, double mn, dou
     return sum > 0.0 ? v / (sum / (double)M) : 0.0;
 }
 
-constexpr int kRankPerBlock = 64;   // candidates a workgroup ranks
+// max or min over a row of 16 lanes, in all of them: rotations inside the vector pipe, where shuffles go through the LDS
+template <int OP>
+__device__ inline double row_reduce(double x) {
+    auto rotated = [](double v, auto by) {
+        const long long b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x120 + decltype(by)::value, 0xf, 0xf, false);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x120 + decltype(by)::value, 0xf, 0xf, false);
+        return __longlong_as_double((long long)(unsigned)lo | (long long)hi << 32);
+    };
+    x = combine<OP>(x, rotated(x, std::integral_constant<int, 8>{}));
+    x = combine<OP>(x, rotated(x, std::integral_constant<int, 4>{}));
+    x = combine<OP>(x, rotated(x, std::integral_constant<int, 2>{}));
+    return combine<OP>(x, rotated(x, std::integral_constant<int, 1>{}));
+}
+
+// the same for max and min, whose order is free: rows of 16 lanes first, and every thread over the rows
+template <int OP, int WAVES>
+__device__ inline void block_extreme(double &x, double &y, double2 *scratch /*[4 * WAVES]*/) {
+    x = row_reduce<OP>(x);
+    y = row_reduce<OP>(y);
+    __syncthreads();   // scratch may still be read from the reduction before
+    if ((threadIdx.x & 15) == 0) scratch[threadIdx.x >> 4] = double2{x, y};
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < WAVES / 4; ++r) {
+        const double2 v = scratch[16 * r + (threadIdx.x & 15)];
+        x = r ? combine<OP>(x, v.x) : v.x;
+        y = r ? combine<OP>(y, v.y) : v.y;
+    }
+    x = row_reduce<OP>(x);
+    y = row_reduce<OP>(y);
+}
+
+constexpr int kRankPerBlock = 16;   // candidates a workgroup ranks
 
 // workgroups of WAVES waves, up to PER_THREAD candidates per thread: WAVES * 64 * PER_THREAD >= M
 template <int WAVES, int PER_THREAD>
@@ -78,8 +112,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_score_chunks(const float *__rest
                                                              double *__restrict__ dist_out,
                                                              int32_t *__restrict__ n_found) {
     constexpr int THREADS = WAVES * 64;
-    __shared__ double D[THREADS * PER_THREAD];
-    __shared__ double2 scratch[WAVES];
+    __shared__ __attribute__((aligned(16))) double D[THREADS * PER_THREAD];
+    __shared__ double2 scratch[4 * WAVES];
     __shared__ int part[WAVES][kRankPerBlock];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int found = R < M ? R : M;
@@ -112,35 +146,35 @@ __global__ __launch_bounds__(WAVES * 64) void k_score_chunks(const float *__rest
             r_max = fmax(r_max, dr[e]); r_min = fmin(r_min, dr[e]); r_sum += dr[e];
         }
     }
-    if (norm_mode != WK_NORM_MEAN) block_reduce<RED_MAX, WAVES>(t_max, r_max, scratch);
-    if (norm_mode == WK_NORM_MINMAX) block_reduce<RED_MIN, WAVES>(t_min, r_min, scratch);
+    if (norm_mode != WK_NORM_MEAN) block_extreme<RED_MAX, WAVES>(t_max, r_max, scratch);
+    if (norm_mode == WK_NORM_MINMAX) block_extreme<RED_MIN, WAVES>(t_min, r_min, scratch);
     if (norm_mode == WK_NORM_MEAN) block_reduce<RED_SUM, WAVES>(t_sum, r_sum, scratch);
 #pragma unroll
     for (int e = 0; e < PER_THREAD; ++e) {
         const int i = tid + e * THREADS;
-        if (i < M)
-            D[i] = normalise(dt[e], norm_mode, t_max, t_min, t_sum, M) +
-                   normalise(dr[e], norm_mode, r_max, r_min, r_sum, M);
+        D[i] = i < M ? normalise(dt[e], norm_mode, t_max, t_min, t_sum, M) + normalise(dr[e], norm_mode, r_max, r_min, r_sum, M)
+                     : INFINITY;   // behind all others
     }
     __syncthreads();
-    const int i = blockIdx.x * kRankPerBlock + lane;   // this lane's candidate, in every wave
+    // a lane's candidate, in every row of 16 lanes; the rows share the others, two at a time
+    const int i = blockIdx.x * kRankPerBlock + (lane & 15), row = tid >> 4;
     const double di = i < M ? D[i] : INFINITY;
-    const int per = (M + WAVES - 1) / WAVES, j1 = min(M, (wave + 1) * per);
     int rank = 0;
     // (unrolled: the reads of several distances are in flight at once, where one read per trip took 140 cycles)
-#pragma unroll 8
-    for (int j = wave * per; j < j1; ++j) {
-        const double dj = D[j];
-        rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
+#pragma unroll 4
+    for (int j = 2 * row; j < M; j += 2 * (THREADS / 16)) {
+        const double2 dj = *reinterpret_cast<const double2 *>(D + j);
+        rank += (dj.x < di || (dj.x == di && j < i)) ? 1 : 0;
+        rank += (dj.y < di || (dj.y == di && j + 1 < i)) ? 1 : 0;
     }
-    if constexpr (WAVES > 1) {
-        part[wave][lane] = rank;
-        __syncthreads();
-        if (wave != 0) return;
-        rank = 0;
+    rank += __shfl_xor(rank, 16);
+    rank += __shfl_xor(rank, 32);
+    if (lane < 16) part[wave][lane] = rank;
+    __syncthreads();
+    if (tid >= 16) return;
+    rank = 0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) rank += part[w][lane];
-    }
+    for (int w = 0; w < WAVES; ++w) rank += part[w][lane];
     if (i < M && rank < found) {
         ids_out[rank] = i;
         if (dist_out) dist_out[rank] = di;
@@ -162,8 +196,8 @@ extern "C" wk_status wk_score_chunks(const float *poses, int32_t M, const float 
     for (int c = 0; c < 5; ++c) cur.v[c] = cur_pose[c];
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
     const dim3 grid(M > 0 ? (M + kRankPerBlock - 1) / kRankPerBlock : 1);
-    // sixteen waves share the ranking's all-pairs count best (M = 256: 5.0 us, with four waves 7.1 us); up to 128
-    // candidates four waves are enough and meet at the barriers sooner
+    // sixteen waves share the distances and the ranking's all-pairs count best (M = 256: 3.8 us); up to 128 candidates four waves are
+    // enough and meet at the barriers sooner (M = 128: 3.5 us)
     auto launch = [&](auto waves, auto per_thread) {
         constexpr int W = decltype(waves)::value, P = decltype(per_thread)::value;
         hipLaunchKernelGGL((k_score_chunks<W, P>), grid, dim3(W * 64), 0, st, poses, (int)M, cur, (int)norm_mode, (int)R,

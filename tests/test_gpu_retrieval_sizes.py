@@ -29,3 +29,22 @@ def test_exact_ties_across_workgroups(M, norm_mode):
     np.testing.assert_allclose(dist, o_all[ids], rtol=0, atol=1e-7)   # as the bar of the other retrieval tests
     assert np.all(np.diff(dist) >= 0)
     assert np.all(np.diff(ids)[np.diff(dist) == 0] > 0)
+
+
+# 16 candidates a workgroup, a row of 16 lanes for every pair of the others: one candidate, partial rows and workgroups, odd counts
+@pytest.mark.parametrize("M", [1, 2, 3, 15, 16, 17, 31, 33, 255, 1009, 2049])
+@pytest.mark.parametrize("norm_mode", [wk.WK_NORM_MAX, wk.WK_NORM_MINMAX, wk.WK_NORM_MEAN])
+def test_top_of_any_count(M, norm_mode):
+    rng = np.random.default_rng(7 * M)
+    poses, cur = rng.normal(0, 2, (M, 5)).astype(np.float32), rng.normal(0, 2, 5).astype(np.float32)
+    R, d = min(M, 12) + 2, dev()
+    ids = torch.full((R,), -7, dtype=torch.int32, device=d)
+    dist = torch.full((R,), -7.0, dtype=torch.float64, device=d)
+    nf = torch.full((1,), -7, dtype=torch.int32, device=d)
+    wk.wk_score_chunks(torch.from_numpy(poses).to(d), M, cur, norm_mode, R, ids, dist, nf)
+    o_ids, o_dist, _ = oracle.score_chunks(poses, cur, R, norm_mode)
+    n = int(nf.item())
+    assert n == min(R, M)
+    np.testing.assert_array_equal(ids.cpu().numpy()[:n], o_ids[:n])
+    np.testing.assert_allclose(dist.cpu().numpy()[:n], o_dist[:n], rtol=1e-12, atol=1e-14)   # fp64 throughout
+    assert (ids.cpu().numpy()[n:] == -1).all() and np.isinf(dist.cpu().numpy()[n:]).all()
