@@ -183,6 +183,10 @@ def _dev(t, name, dtype=None):
 
 
 def _stream():
+    """Handle of the current stream of the current device.  By the number alone: building the Stream object that carries it takes 2.8 us
+    of a call's 8, the number 0.3."""
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
