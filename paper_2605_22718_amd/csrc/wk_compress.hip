@@ -733,16 +733,40 @@ __device__ inline void copy_anchors(const AnchorCopy &c, const CompressDims &p) 
     }
 }
 
+// Inclusive prefix sums over the wave, in the vector pipe (shuffles go through the LDS): shifts inside rows of 16 lanes, then the rows' last
+// lanes to the rows behind them.
+__device__ inline int wave_prefix(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15, rows 1 and 3
+    return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31, rows 2 and 3
+}
+
+// the lowest and the highest key over a row of 16 lanes, in all of them
+__device__ inline void row_range(uint64_t &lo, uint64_t &hi) {
+    auto rotated = [](uint64_t v, auto by) {
+        constexpr int kRor = 0x120 + decltype(by)::value;
+        const unsigned a = __builtin_amdgcn_mov_dpp((int)v, kRor, 0xf, 0xf, false), b = __builtin_amdgcn_mov_dpp((int)(v >> 32), kRor, 0xf, 0xf, false);
+        return (uint64_t)b << 32 | a;
+    };
+    auto step = [&](auto by) {
+        const uint64_t a = rotated(lo, by), b = rotated(hi, by);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    };
+    step(std::integral_constant<int, 8>{});
+    step(std::integral_constant<int, 4>{});
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 1>{});
+}
+
 // exclusive scan of one int per thread over the block; total = sum over the block
 template <int THREADS>
 __device__ inline int block_excl_scan(int v, int *wsum /*[THREADS/64]*/, int &total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
+    const int x = wave_prefix(v);
     __syncthreads();  // wsum may still be read from the previous scan
     if (lane == 63) wsum[w] = x;
     __syncthreads();
@@ -863,6 +887,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select(const double *__restrict
 // counts give the places.  A list of 3,120 candidates: 9.5 us, with the byte-wise passes and ordered block scans of k_select
 // 12.6 us; 24 lists of 2,026: 8.3 and 9.8 us.  (Counting, for every key, the keys before it -- 64 keys per
 // workgroup, comparing all pairs -- takes 12 and 22 us: 64-bit comparisons are slow.)
+// The range of the keys and the prefix sums stay in the vector pipe: by shuffles, which go through the LDS one behind the other, whole calls with 24
+// lists of 2,026, one of 1,760 and sixteen of 600 candidates took 25.8, 21.6 and 27.2 us, now 24.0, 20.0 and 25.3.
 // The workgroup is the smallest that holds the list: barriers of sixteen waves and the work on keys that are not there
 // made short lists slower than k_select does (whole calls with 1 list of 128, 2 of 400 and 12 of 936 candidates 18.5, 21.9 and 31.6 us;
 // k_select 16.8, 19.4 and 30.2; now 15.6, 18.7 and 30.1).
@@ -875,10 +901,11 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
     constexpr int kWaves = THREADS / 64, kList = 64, kWords = EACH * kWaves;
     constexpr int kBits = 31 - __builtin_clz(THREADS);   // of a bucket number
     __shared__ int hist[THREADS];
-    __shared__ uint64_t w_lo[kWaves], w_hi[kWaves], list_key[kList], words[kWords];
+    __shared__ uint64_t r_lo[4 * kWaves], r_hi[4 * kWaves], list_key[kList], words[kWords];   // (of rows of 16 lanes)
     __shared__ int list_j[kList], wsum[kWaves];
     __shared__ int s_bucket, s_below, s_count, s_listed;
-    const int list = blockIdx.x, n = p.n_cand, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int list = blockIdx.x, n = p.n_cand, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double *s = scores + (size_t)list * n;
     int32_t *out = kept_idx + (size_t)list * p.n_out;
     for (int i = tid; i < p.first_cand; i += THREADS) out[i] = i;  // anchor tokens, kept in full
@@ -903,24 +930,21 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
                 lo = key[u] < lo ? key[u] : lo;
                 hi = key[u] > hi ? key[u] : hi;
             }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const uint64_t a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
-            lo = a < lo ? a : lo;
-            hi = b > hi ? b : hi;
-        }
+        row_range(lo, hi);
         hist[tid] = 0;
-        if (lane == 0) {
-            w_lo[wave] = lo;
-            w_hi[wave] = hi;
+        if ((lane & 15) == 0) {
+            r_lo[tid >> 4] = lo;
+            r_hi[tid >> 4] = hi;
         }
         if (tid == 0) s_listed = 0;
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            lo = w_lo[w] < lo ? w_lo[w] : lo;
-            hi = w_hi[w] > hi ? w_hi[w] : hi;
+        for (int w = 0; w < kWaves / 4; ++w) {
+            const uint64_t a = r_lo[16 * w + (lane & 15)], b = r_hi[16 * w + (lane & 15)];
+            lo = a < lo ? a : lo;
+            hi = b > hi ? b : hi;
         }
+        row_range(lo, hi);
         if (lo == hi) {   // equal scores: the lowest indices are kept
             int base = 0;
 #pragma unroll
@@ -947,16 +971,11 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
         }
         __syncthreads();
         const int count = hist[tid];
-        int incl = count;   // inclusive prefix sums of the buckets, first one >= k
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(incl, o);
-            if (lane >= o) incl += y;
-        }
+        int incl = wave_prefix(count);   // inclusive prefix sums of the buckets, first one >= k
         if (lane == 63) wsum[wave] = incl;
         __syncthreads();
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) incl += w < wave ? wsum[w] : 0;
+        const int before = wave_prefix(lane < kWaves ? wsum[lane] : 0);   // (of the waves, a lane each)
+        if (wave > 0) incl += __builtin_amdgcn_readlane(before, wave - 1);
         if (incl >= k && incl - count < k) {   // exactly one bucket satisfies this
             s_bucket = tid;
             s_below = incl - count;
@@ -1004,16 +1023,10 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
     }
     __syncthreads();
     // kept tokens before each 64 candidates: a lane per word
-    int incl = lane < kWords ? __popcll(words[lane]) : 0;
-    const int ones = incl;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
+    const int ones = lane < kWords ? __popcll(words[lane]) : 0, incl = wave_prefix(ones);
 #pragma unroll
     for (int u = 0; u < EACH; ++u) {
-        const int w = wave + u * kWaves, pos = __shfl(incl - ones, w) + __popcll(words[w] & ((1ull << lane) - 1));
+        const int w = wave + u * kWaves, pos = __builtin_amdgcn_readlane(incl - ones, w) + __popcll(words[w] & ((1ull << lane) - 1));
         if (kept[u]) out[p.first_cand + pos] = p.first_cand + tid + u * THREADS;
     }
 }
