@@ -190,8 +190,8 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 // Even features of V come first: a thread holds two adjacent ones and stores them apart.
 //
 // Bound by the matrix and the vector pipe together: a tile is 48 products (1,536 cycles) and about 300 vector instructions a wave, of which
-// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 38 us (with its merge), 8 x 1,560 x 4,680 293 -> 127, 40 x 1,560 x 4,680 1,411 -> 554 (270 TFLOP/s), 1 x 128 x
-// 30,000 248 -> 98, 6 x 250 x 100 25.0 -> 17.1.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
+// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 36.4 us (with its merge), 8 x 1,560 x 4,680 293 -> 126, 40 x 1,560 x 4,680 1,411 -> 555 (269 TFLOP/s), 1 x 128 x
+// 30,000 248 -> 97, 6 x 250 x 100 25.0 -> 16.1.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
 // instead of beside the products: the same, as long as the compiler waited for the loads to LDS in front of every read of LDS, see load_to_lds.)
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 4;                           // across the queries
@@ -220,6 +220,14 @@ __device__ inline float max_across_halves(float x) {
     const unsigned u = __float_as_uint(x);
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// max over a row of 16 lanes
+__device__ inline float row_max(float x) {
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false)));   // row_ror:8, 4, 2, 1
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, false)));
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x122, 0xf, 0xf, false)));
+    return fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x121, 0xf, 0xf, false)));
 }
 
 // 16 bytes per lane from base + offset to LDS, at `to` and on.  In assembly: the compiler waits for every load to LDS that it knows of in front of
@@ -345,6 +353,22 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         for (unsigned e = 0; e < 8; e += 2)
             load_to_lds(Vh + at, (min(row + 8 * (e >> 2) + (e & 3), last) << 9) | ((l & 31) << 4), lds0 + kF32RawV + qw * 4096 + e * 512);
     };
+    // Queries come through LDS, the first and the second 64 features one after the other, in the wave's share of the parts' place: rows of 512 bytes, one
+    // per lane, keep the L1 busy three times as long.  16-byte chunk c of row r at slot c ^ (r & 15).
+    char *const q_lds = group + qw * (4 * kF32Part / kF32Waves);
+    auto issue_q = [&](unsigned half) __attribute__((always_inline)) {
+        unsigned l = lane;
+        asm("" : "+v"(l));
+        const int q0 = qt * (kF32Waves * 32) + qw * 32;
+        const unsigned last = a.N_q - 1 - q0;
+        const char *base = a.Q + ((size_t)h * a.q_rows + a.q_off + q0) * 512;
+#pragma unroll
+        for (unsigned i = 0; i < 8; ++i) {
+            const unsigned row = 4 * i + (l >> 4);
+            load_to_lds(base, (min(row, last) << 9) | (half << 8) | (((l & 15) ^ (row & 15)) << 4), lds0 + qw * (4 * kF32Part / kF32Waves) + i * 1024);
+        }
+    };
+    if (!idle) issue_q(0);
     const bool any = kt0 + kg * kF32Keys < kt1;   // with a single tile the second group has none
     if (any) {
         issue_k(kt0 + kg * kF32Keys);
@@ -357,10 +381,21 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     bool bad_keys = false;   // or queries
     float to_log2 = a.scale_log2;   // of this lane's query: what takes scores as they are summed to log2 units
     if (!idle) {
-        const float *Qrow = query_row();
         float4 x[16];
+        auto read_q = [&](int half) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = *reinterpret_cast<const float4 *>(Qrow + 16 * (i >> 1) + 8 * g + 4 * (i & 1));
+            for (int i = 0; i < 8; ++i)
+                x[8 * half + i] = *reinterpret_cast<const float4 *>(q_lds + col * 256 + (((4 * (i >> 1) + 2 * g + (i & 1)) ^ (col & 15)) << 4));
+        };
+        if (any) __builtin_amdgcn_s_waitcnt(WITH_O ? 0x0F78 : 0x0F74);   // all but the keys' and values' loads, four each
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        asm volatile("" ::: "memory");
+        read_q(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // before the place is written again
+        issue_q(1);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        asm volatile("" ::: "memory");
+        read_q(1);
         float largest = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
@@ -484,9 +519,8 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
             const float4 x = k_from(c);
             top = fmaxf(fmaxf(fmaxf(top, fabsf(x.x)), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w)));
         }
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) top = fmaxf(top, __shfl_xor(top, m));
-        if (lane == 0) atomicMax(k_max, __float_as_int(top));
+        top = row_max(top);
+        if ((lane & 15) == 0) atomicMax(k_max, __float_as_int(top));
         if (WITH_O)
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
@@ -665,35 +699,48 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
     }
+    if (KG == 1) __syncthreads();   // every wave is done with its last tile, and its share of the LDS free
     if (idle) return;
     int q_at = q_ld;
     asm("" : "+v"(q_at));   // (rows of the results from here on, not kept through the loop)
     const size_t qrow = (size_t)h * a.q_rows + a.q_off + q_at, prow = (size_t)(a.part_slot >= 0 ? a.part_slot : sp) * a.H * a.q_rows + qrow;
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (!q_ok) return;
-    if (!partial_out && lse && g == 0) lse[qrow] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
-    if (partial_out && g == 0) {   // (O, max, sum) of this key range, merged by k_attn_merge
+    if (q_ok && !partial_out && lse && g == 0) lse[qrow] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
+    if (q_ok && partial_out && g == 0) {   // (O, max, sum) of this key range, merged by k_attn_merge
         a.part_ml[prow * 2] = m_run;
         a.part_ml[prow * 2 + 1] = l_tot;
     }
     if (!WITH_O) return;
+    // O leaves through the wave's own LDS, so that a store has two whole rows, not 16 bytes of 32 (with the queries' way: 4 heads x 880
+    // queries x 2,640 keys in 9 ranges 38.0 -> 36.4 us): chunk c of row r at slot
+    // c ^ (r & 15)
+    char *const o_lds = smem + qw * (KG == 2 ? 66 * 64 * 4 : 32 * 512);
     const float inv = partial_out ? 1.f : 1.f / l_tot;
-    float *out = partial_out ? a.part_o + prow * WK_D : reinterpret_cast<float *>(a.O) + qrow * WK_D;
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int u = 0; u < 4; u += 2) {
-                const int feature = 2 * (32 * b + 8 * t + 4 * g + u);
-                const float4 top = *reinterpret_cast<const float4 *>(v_max + feature);
+                const int chunk = 16 * b + 4 * t + 2 * g + u / 2;
+                const float4 top = *reinterpret_cast<const float4 *>(v_max + 4 * chunk);
                 float down[4] = {inv, inv, inv, inv};
                 bool unused = false;
                 if (!exact)
                     for (int i = 0; i < 4; ++i) down[i] *= inverse(kF32P * scale_to((&top.x)[i], 10, unused));
-                *reinterpret_cast<float4 *>(out + feature) = float4{o[b][4 * t + u] * down[0], o[b + 2][4 * t + u] * down[1],
-                                                                    o[b][4 * t + u + 1] * down[2], o[b + 2][4 * t + u + 1] * down[3]};
+                *reinterpret_cast<float4 *>(o_lds + col * 512 + ((chunk ^ (col & 15)) << 4)) =
+                    float4{o[b][4 * t + u] * down[0], o[b + 2][4 * t + u] * down[1], o[b][4 * t + u + 1] * down[2], o[b + 2][4 * t + u + 1] * down[3]};
             }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const int q0 = qt * (kF32Waves * 32) + qw * 32, rows = min(32, a.N_q - q0);
+    const size_t row0 = (size_t)h * a.q_rows + a.q_off + q0;
+    char *const out = partial_out ? reinterpret_cast<char *>(a.part_o) + ((size_t)(a.part_slot >= 0 ? a.part_slot : sp) * a.H * a.q_rows + row0) * 512
+                                  : a.O + row0 * 512;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = 2 * i + (lane >> 5), chunk = lane & 31;
+        if (row < rows) *reinterpret_cast<float4 *>(out + (size_t)row * 512 + chunk * 16) = *reinterpret_cast<const float4 *>(o_lds + row * 512 + ((chunk ^ (row & 15)) << 4));
+    }
 }
 
 // ------------------------------------------------------------------------------------------
