@@ -177,9 +177,9 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 // below 2^-24 of it: three matrix instructions of 32 cycles do what eight fp32 ones of 64 do, and their sums are rounded less often.  On N(0, 1)
 // inputs results are 2.0e-7 to 5.3e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.
 // fp16's range is met by powers of two: one per query, one for the keys and one per feature of the values, from the first tile's
-// largest numbers, which leaves a factor of 32 for those that follow.  A workgroup that meets larger ones, infinities,
-// or values that are 2^-11 smaller than their feature's in the first tile, begins again from its first tile, with
-// v_mfma_f32_32x32x2_f32 on the numbers themselves.
+// largest numbers, which leaves a factor of 32 for those that follow.  A workgroup that has met larger ones, infinities,
+// or values that are 2^-11 smaller than their feature's in the first tile, does its work once more, with v_mfma_f32_32x32x2_f32 on the
+// numbers themselves.
 //
 // Four waves of 32 queries per workgroup, 32-key tiles, KG tiles at a time by as many groups of waves; KG == 1 leaves room for two
 // workgroups on a compute unit, whose phases then overlap by themselves.  KG == 2: the groups' (O, max, sum) meet in
@@ -201,7 +201,7 @@ constexpr int kF32V = 2 * kF32Part;                    // K parts, V parts, K an
 constexpr int kF32RawK = 4 * kF32Part;
 constexpr int kF32RawV = kF32RawK + kF32Keys * 512;
 constexpr int kF32Group = kF32RawV + kF32Keys * 512;   // LDS of a group of waves
-constexpr int kF32Shared = 512 + 16;                   // largest values of the features, largest key, what was out of range
+constexpr int kF32Shared = 512 + 16;                   // largest values of the features, largest key, whether anything was out of range
 constexpr int kF32Lds = kF32Group + kF32Shared;
 constexpr int kF32LdsPair = 2 * kF32Group + kF32Shared;
 constexpr float kF32P = 0x1p11f;                       // what weights are scaled by
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     char *const group = smem + kg * kF32Group;
     const unsigned lds0 = (unsigned)(size_t)WK_LDS(group);
     int *const v_max = reinterpret_cast<int *>(smem + KG * kF32Group), *const k_max = v_max + WK_D;   // (sizes: their bits order as they do)
-    int *const flags = k_max + 1;   // out of range: queries or keys; values
+    int *const out_of_range = k_max + 1;
     // Loads: wave qw fills two rows per load, of K rows 8*qw .. 8*qw+7, 16-byte chunk c of row k at slot c ^ (k & 15); of V the eight
     // rows 16*(qw/2) + 4*(qw%2) + {0..3, 8..11}, which a lane group multiplies at once, for the wave itself.
     // Rows past the range clamp to its last one (those keys are masked, their values cleared).
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         issue_k(kt0 + kg * kF32Keys);
         if (WITH_O) issue_v(kt0 + kg * kF32Keys);
     }
-    if (tid < WK_D + 3) v_max[tid] = 0;
+    if (tid < WK_D + 2) v_max[tid] = 0;
 
     // B operand of S^T = K Q^T: k slot 8*g + e of step s means feature 16*s + 8*g + e
     f16x8 qr[8][2];
@@ -540,21 +540,18 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     if (any)
 #pragma unroll
         for (int t = 0; t < 8; ++t) k_work(t);
-    if (bad_keys || bad_values || largest >= kLimit) flags[0] = 1;
+    if (bad_keys || bad_values || largest >= kLimit) *out_of_range = 1;
 
     // The steps.  Beside the products of S^T a wave splits its share of the tile's values, beside those of O^T its share of the next tile's
     // keys (without a next tile: of the last one's again, which nothing reads)
-    bool exact = false;
     auto meet_keys = [&]() __attribute__((always_inline)) {   // K's parts are there, the values before are consumed
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's values have landed
         __syncthreads();
-        exact = __builtin_amdgcn_readfirstlane(flags[0]) != 0;
     };
     auto meet_values = [&](int kt) __attribute__((always_inline)) {   // V's parts are there, K's are consumed
-        if (WITH_O && (largest >= kLimit || (v_smallest < 0.5f && kt + kF32Keys <= kt1))) flags[1] = 1;
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's keys of the next tile have landed
+        if (WITH_O && (largest >= kLimit || (v_smallest < 0.5f && kt + kF32Keys <= kt1))) *out_of_range = 1;
+        __builtin_amdgcn_s_waitcnt(WITH_O ? 0x0F74 : 0x0F70);   // this wave's keys of the next tile have landed; its values, four loads, are behind them
         __syncthreads();
-        exact = __builtin_amdgcn_readfirstlane(flags[1]) != 0;
     };
     const int n_steps = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + KG - 1) / KG;
     const int my_steps = (kt1 - kt0 - kg * kF32Keys + KG * kF32Keys - 1) / (KG * kF32Keys);   // with an odd count of tiles the second group has one less
@@ -564,7 +561,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     if (!idle) {
         for (int j = 0; j < my_steps; ++j, kt += kStep) {
             meet_keys();
-            if (exact) break;
             if (kt + kStep < kt1) issue_k(kt + kStep);
             begin_share();
             f32x16 s, small;   // (apart: eight roundings at the size of a score instead of 24)
@@ -579,6 +575,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
                 });
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] += small[r];
+            if (WITH_O && kt + kStep < kt1) issue_v(kt + kStep);   // (the wave's own rows: no other reads them)
             softmax(s, kt);
             f16x8 pr[2][2];
             if (WITH_O)
@@ -591,8 +588,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
                     for (int p = 0; p < 2; ++p) pr[t][p] = __builtin_bit_cast(f16x8, u32x4{u[0].p[p], u[1].p[p], u[2].p[p], u[3].p[p]});
                 }
             meet_values(kt);
-            if (exact) break;
-            if (WITH_O && kt + kStep < kt1) issue_v(kt + kStep);
             begin_share();
             if (WITH_O) {
                 // O^T += V^T P^T: k slot 8*g + e of step t means key 16*t + 8*(e/4) + 4*g + e%4, accumulator register 8*t + e;
@@ -611,31 +606,34 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
                 for (int t = 0; t < 8; ++t) k_work(t);
             }
-            if (largest >= kLimit) flags[0] = 1;
+            if (largest >= kLimit) *out_of_range = 1;
         }
     } else {
         for (int j = 0; j < my_steps; ++j, kt += kStep) {
             meet_keys();
-            if (exact) break;
             if (kt + kStep < kt1) issue_k(kt + kStep);
             begin_share();
             if (WITH_O)
 #pragma unroll
                 for (int t = 0; t < 8; ++t) v_work(t, kt);
-            meet_values(kt);
-            if (exact) break;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // before the place is written again
             if (WITH_O && kt + kStep < kt1) issue_v(kt + kStep);
+            meet_values(kt);
             begin_share();
 #pragma unroll
             for (int t = 0; t < 8; ++t) k_work(t);
-            if (largest >= kLimit) flags[0] = 1;
+            if (largest >= kLimit) *out_of_range = 1;
         }
     }
-    if (my_steps < n_steps && !exact) {   // the other group's last tile
+    if (my_steps < n_steps) {   // the other group's last tile
         begin_share();
         meet_keys();
-        if (!exact) meet_values(kt);
+        meet_values(kt);
     }
+    __syncthreads();   // every wave is done with its last tile, and its share of the LDS free
+    // (looked at here only: behind every barrier, and with the values requested behind the second one, 4 heads x 880 queries x 2,640 keys in one
+    // range took 129 us, now 125)
+    const bool exact = __builtin_amdgcn_readfirstlane(*out_of_range) != 0;
     if (exact) {   // once more from the first tile on, with fp32 operands straight from memory
 #pragma unroll
         for (int b = 0; b < 4; ++b)
@@ -676,7 +674,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.
     if constexpr (KG == 2) {
         float *meet = reinterpret_cast<float *>(smem) + qw * (66 * 64) + lane;
-        __syncthreads();   // every wave is done with its last tile
         if (kg == 1) {
             if (WITH_O)
 #pragma unroll
@@ -699,7 +696,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[b][r] = fmaf(w1, meet[(16 * b + r) * 64], w0 * o[b][r]);
     }
-    if (KG == 1) __syncthreads();   // every wave is done with its last tile, and its share of the LDS free
     if (idle) return;
     int q_at = q_ld;
     asm("" : "+v"(q_at));   // (rows of the results from here on, not kept through the loop)
