@@ -217,3 +217,28 @@ def test_chunk_lse_and_masses_at_the_lingbot_index_size_sampled():
     np.testing.assert_allclose(all_mass, expect, rtol=1e-9)
     assert abs(all_mass.sum() - 1.0) < 1e-9 and int(nf.item()) == cfg.R
     np.testing.assert_array_equal(ids.cpu().numpy(), np.lexsort((np.arange(M), -expect))[: cfg.R])
+
+
+# eight chunks at a time, 256 rows a workgroup: counts around them, chunks that some or all rows do not see
+@pytest.mark.parametrize("M", [1, 7, 8, 9, 17])
+@pytest.mark.parametrize("n_rows", [1, 255, 257, 300000])
+def test_masses_at_the_edges_of_batches(M, n_rows):
+    rng = np.random.default_rng(M * 1000 + n_rows % 997)
+    lse = rng.normal(3, 2, (M, n_rows)).astype(np.float32)
+    lse[:, ::5] = -np.inf if n_rows > 1 else lse[:, ::5]   # rows that see no key
+    lse[M // 2, ::3] = -np.inf
+    R, d = min(M, 3), dev()
+    ids, nf = torch.empty(R, dtype=torch.int32, device=d), torch.empty(1, dtype=torch.int32, device=d)
+    mass = torch.empty(R, dtype=torch.float64, device=d)
+    ws = torch.empty(wk.wk_score_chunks_query_workspace_bytes(M, n_rows), dtype=torch.uint8, device=d)
+    wk.wk_score_chunks_query(torch.from_numpy(lse).to(d), M, n_rows, R, ids, mass, nf, ws)
+    got = ws[:8 * M].view(torch.float64).cpu().numpy()
+    x = lse.astype(np.float64)
+    top = x.max(0)
+    seen = np.isfinite(top)
+    w = np.exp(x[:, seen] - (top[seen] + np.log(np.exp(x[:, seen] - top[seen]).sum(0))))
+    want = w.sum(1) / n_rows
+    np.testing.assert_allclose(got, want, rtol=1e-12, atol=1e-15)   # fp64 sums of up to 300,000 terms: 3e5 * 2^-53 at most, 1e-14 in fact
+    order = np.argsort(-got, kind="stable")[:R]
+    np.testing.assert_array_equal(ids.cpu().numpy(), order)
+    np.testing.assert_array_equal(mass.cpu().numpy(), got[order])
