@@ -792,7 +792,7 @@ struct Segment { const char *K; const char *V; int len; int pad; };
 using wk::uniform_ptr;
 
 // QW: waves across the queries; KG: wave groups, which take alternate tiles
-template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP = false>
+template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP = false, bool TRIPS = !IN_PLACE>
 __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTable sub) {
     static_assert((QW == 8 && KG == 1) || (QW == 4 && (KG == 1 || KG == 2)), "one tile, or a pair of tiles, per step");
     constexpr int NB = 16 / (QW * KG); // 1 KB blocks of a tile that a wave loads
@@ -1207,18 +1207,12 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
         end_step();
     };
     int j = 0;
-    if constexpr (!IN_PLACE && QW * KG == 8) {
-        // Steady state: whole trips round the ring whose look-ahead loads all lie inside the window run in a
-        // hand-scheduled loop (written by gen_attn_loop.py, which documents its schedule and register map).  It is
-        // the four (KG == 2: two) `step`s below instruction for instruction in what it computes -- same ring protocol,
-        // same arithmetic in the same order, bit-identical results -- so the steps behind it stay in C++: the last whole
-        // trips, whose loads are clamped to the window, the left-over steps and the last, possibly partial tile.  Its
-        // operands are pinned to the registers its text names.
-        int G = (n_kv / kKeys - 4 - t0) / 4;
-        const int G_steps = n_steps / (4 / KG);
-        G = G < G_steps ? G : G_steps;
-        if (G > 0) {
-            unsigned koff = (unsigned)(t0 + 4) * kTileBytes, voff = (unsigned)(t0 + 4 - KG) * kTileBytes;
+    // Whole trips round the ring in a hand-scheduled loop (written by gen_attn_loop.py, which documents its schedule and register map), whose
+    // look-ahead loads must all lie in full tiles of one array: K tiles from k_base + koff on, V tiles from v_base + voff on.  It is
+    // the four (KG == 2: two) `step`s below instruction for instruction in what it computes -- same ring protocol,
+    // same arithmetic in the same order, bit-identical results.  Its operands are pinned to the registers its text names.
+    auto trips = [&](int G, const char *k_base, const char *v_base, unsigned koff, unsigned voff) __attribute__((always_inline)) {
+        if constexpr (QW * KG == 8) {
             // the tile with the first row behind the gap, and the steps up to the one that requests its K tile
             const unsigned gap_tile = gap_from / kTileBytes * kTileBytes;
             int gap_steps = (((int)(gap_from / kTileBytes) - t0 - 4) >> (KG - 1)) + 2;
@@ -1237,7 +1231,7 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
                   "{v[148:151]}"(q5), "{v[152:155]}"(q6), "{v[156:159]}"(q7), "{v224}"(k_rd[0]), "{v225}"(k_rd[1]), \
                   "{v226}"(k_rd[2]), "{v227}"(k_rd[3]), "{v228}"(k_rd[4]), "{v229}"(k_rd[5]), "{v230}"(k_rd[6]), "{v231}"(k_rd[7]), \
                   "{v232}"(v_rd[0]), "{v233}"(v_rd[1]), "{v234}"(v_rd[2]), "{v235}"(v_rd[3]), "{v236}"(ks0), "{v237}"(ks1), \
-                  "{v238}"(vs0), "{v239}"(vs1), "{s[36:37]}"(Kh), "{s[38:39]}"(Vh), "{s40}"(koff), "{s41}"(voff), \
+                  "{v238}"(vs0), "{v239}"(vs1), "{s[36:37]}"(k_base), "{s[38:39]}"(v_base), "{s40}"(koff), "{s41}"(voff), \
                   "{s42}"(dst), "{s43}"(c_log2)
             if constexpr (GAP && KG == 1) {
                 asm volatile(
@@ -1261,11 +1255,36 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
                     : WK_ATTN_LOOP_OUT : WK_ATTN_LOOP_IN : WK_ATTN_LOOP_CLOBBERS, "s45", "vcc", "memory");
             }
             o[0] = o0; o[1] = o1; o[2] = o2; o[3] = o3; s_a[0] = sa0; s_a[1] = sa1;
-            j = G * (4 / KG);
+            j += G * (4 / KG);
         }
+    };
+    if constexpr (TRIPS && !IN_PLACE && QW * KG == 8) {
+        // the steps behind these stay in C++: the last whole trips, whose loads are clamped to the window, the left-over steps and the
+        // last, possibly partial tile
+        const int G = min((n_kv / kKeys - 4 - t0) / 4, n_steps / (4 / KG));
+        if (G > 0) trips(G, Kh, Vh, (unsigned)(t0 + 4) * kTileBytes, (unsigned)(t0 + 4 - KG) * kTileBytes);
     }
+    // IN_PLACE: the trips whose tiles -- from the ones whose S^T comes next to the last one requested -- are full and of the cursor's segment, and
+    // leave the cursor in it.  The steps across a segment's boundary stay in C++.
+    auto trips_in_segment = [&]() __attribute__((always_inline)) {
+        if constexpr (IN_PLACE && TRIPS && QW * KG == 8) {
+            constexpr unsigned kAhead = KG == 1 ? 0x404040u : 0x4040u;   // tiles j+1 to j+3, KG == 2: 2j+2 and 2j+3
+            if ((valid_line & (KG == 1 ? 0xffffffu : 0xffffu)) != kAhead) return;
+            if (cur_row < KG * kKeys || v_line[0].base != cur_v || v_line[0].row + kKeys != cur_row) return;
+            if (KG == 2 && (v_line[1].base != cur_v || v_line[1].row + 2 * kKeys != cur_row)) return;
+            const int G = min((cur_len - cur_row - 1) / kKeys / 4, (n_steps - j) / (4 / KG));
+            if (G <= 0) return;
+            trips(G, cur_k, cur_v, (unsigned)cur_row * 256u, (unsigned)(cur_row - KG * kKeys) * 256u);
+            cur_row += 4 * G * kKeys;
+            v_line[0] = TileRef{cur_v, cur_row - kKeys, cur_len};
+            v_line[1] = TileRef{cur_v, cur_row - 2 * kKeys, cur_len};
+            valid_line = 0x40404040u;
+        }
+    };
     if constexpr (KG == 1) {
         for (; j + 4 <= n_steps; j += 4) {
+            trips_in_segment();
+            if (IN_PLACE && TRIPS && j + 4 > n_steps) break;
             step(j, 0, s_a, s_b, l_run[0]);
             step(j + 1, 1, s_b, s_a, l_run[1]);
             step(j + 2, 2, s_a, s_b, l_run[0]);
@@ -1273,6 +1292,8 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
         }
     } else {
         for (; j + 2 <= n_steps; j += 2) {
+            trips_in_segment();
+            if (IN_PLACE && TRIPS && j + 2 > n_steps) break;
             step(j, 0, s_a, s_b, l_run[0]);
             step(j + 1, 2, s_b, s_a, l_run[0]);
         }
@@ -2023,10 +2044,12 @@ wk_status allow_large_lds() {
             {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, true, false>), kSmemBytes},
             {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, true, false, true>), kSmemBytes},
             {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, false, true>), kSmemBytes},
+            {reinterpret_cast<const void *>(&k_attn_bf16<8, 1, false, true, false, true>), kSmemBytes},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, false, false>), kSmemBytesPair},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, true, false>), kSmemBytesPair},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, true, false, true>), kSmemBytesPair},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, false, true>), kSmemBytesPair},
+            {reinterpret_cast<const void *>(&k_attn_bf16<4, 2, false, true, false, true>), kSmemBytesPair},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 1, false, false>), kSmemBytes},
             {reinterpret_cast<const void *>(&k_attn_bf16<4, 1, false, true>), kSmemBytes},
             {reinterpret_cast<const void *>(&k_attn_f32<1, false, true>), kF32Lds},
@@ -2050,9 +2073,20 @@ wk_status allow_large_lds() {
 // (8 of 256 x 40 x 256 13.6 -> 14.1); one long chunk in eight outweighs that (51.4 -> 43.8).
 bool lse_wide(const AttnArgs &a) { return (a.n_chunks > 0 ? a.max_tok : a.N_kv) > 10 * kKeys && a.N_q > 192; }
 
-template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP = false>
+// In place: whether most tiles lie deep enough in their segments for the hand-scheduled loop, which begins once the tiles ahead are of one segment and
+// ends before they leave it: about eight tiles of a segment stay outside, in steps that its registers make 4 % slower.
+// Without it and with it, by the share of tiles inside: 0.19 (12 heads x 2,640 queries, 12 chunks of 640 keys) 130 and 135 us, 0.38 (of 800) 161 and 164, 0.46 (of
+// 900) 180 and 181, 0.55 (of 1,100) 214 and 215, 0.61 (of 1,300) 253 and 252, 0.54 (40 x 2,000, 6 of 900 and 2,000 native) 345 and 343, 0.56 (8 x 900, 8 of 1,200)
+// 142 and 135, 0.71 (4 x 300, 3,000 native, 2 of 200) 53 and 49, 0.78 (16 x 3,333, 6,101 native, 7 of 1,747) 470 and 458, 40 x 4,680, 9,360 native, 8 of 2,340
+// 2,311 and 2,247.
+bool trips_in_place(long long n_native, long long R, long long max_tok) {
+    const long long native = (n_native + kKeys - 1) / kKeys, chunk = (max_tok + kKeys - 1) / kKeys;
+    return 100 * (std::max(native - 8, 0ll) + R * std::max(chunk - 8, 0ll)) >= 55 * (native + R * chunk);
+}
+
+template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP = false, bool TRIPS = !IN_PLACE>
 void launch_layout(const AttnArgs &a, const SubTable &t, hipStream_t st) {
-    hipLaunchKernelGGL((k_attn_bf16<QW, KG, MULTI, IN_PLACE, GAP>), dim3(a.per_xcd * kXcds), dim3(QW * KG * 64),
+    hipLaunchKernelGGL((k_attn_bf16<QW, KG, MULTI, IN_PLACE, GAP, TRIPS>), dim3(a.per_xcd * kXcds), dim3(QW * KG * 64),
                        KG == 1 ? kSmemBytes : kSmemBytesPair, st, a, t);
 }
 
@@ -2378,8 +2412,10 @@ extern "C" wk_status wk_attention_in_place(const void *Q, const void *K_native, 
     const wk_status rc = allow_large_lds();
     if (rc != WK_OK) return rc;
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-    if (plan.layout == k256) launch_layout<8, 1, false, true>(a, SubTable{}, st);
-    else if (plan.layout == k128Pair) launch_layout<4, 2, false, true>(a, SubTable{}, st);
+    const bool trips = trips_in_place(n_native, a.R_max, store->max_tok);
+    if (plan.layout == k256) trips ? launch_layout<8, 1, false, true, false, true>(a, SubTable{}, st) : launch_layout<8, 1, false, true>(a, SubTable{}, st);
+    else if (plan.layout == k128Pair)
+        trips ? launch_layout<4, 2, false, true, false, true>(a, SubTable{}, st) : launch_layout<4, 2, false, true>(a, SubTable{}, st);
     else launch_layout<4, 1, false, true>(a, SubTable{}, st);
     WK_LAUNCH_CHECK();
     return WK_OK;
