@@ -634,6 +634,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     // (looked at here only: behind every barrier, and with the values requested behind the second one, 4 heads x 880 queries x 2,640 keys in one
     // range took 129 us, now 125)
     const bool exact = __builtin_amdgcn_readfirstlane(*out_of_range) != 0;
+    // 4 heads x 880 queries x 2,640 keys, two of them at -inf: 97 us; the kernel that had fp32 products only took 65 for any keys, this one 39 for others
     if (exact) {   // once more from the first tile on, with fp32 operands straight from memory
 #pragma unroll
         for (int b = 0; b < 4; ++b)
@@ -642,31 +643,54 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         m_run = -FLT_MAX;
         l_run = 0.f;
         to_log2 = a.scale_log2;
-        const float *Qrow = query_row();
-        for (int kt = kt0 + kg * kF32Keys; kt < kt1 && !idle; kt += kStep) {
+        float4 y[16];
+        if (!idle) {
+            const float *Qrow = query_row();
+#pragma unroll
+            for (int t = 0; t < 16; ++t) y[t] = *reinterpret_cast<const float4 *>(Qrow + 8 * t + 4 * g);
+        }
+        for (int kt = kt0 + kg * kF32Keys; kt < kt1 && !idle; kt += kStep) {   // (eight pieces of a key row and 32 values in flight)
             f32x16 s;
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = 0.f;
             const char *krow = Kh + (size_t)min(kt + col, kt1 - 1) * 512 + 16 * g;
-#pragma unroll 4
-            for (int t = 0; t < 16; ++t) {
-                const float4 x = *reinterpret_cast<const float4 *>(krow + 32 * t), y = *reinterpret_cast<const float4 *>(Qrow + 8 * t + 4 * g);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, s, 0, 0, 0);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                float4 x[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) x[t] = *reinterpret_cast<const float4 *>(krow + 32 * (8 * half + t));
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const float4 q4 = y[8 * half + t];
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].x, q4.x, s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].y, q4.y, s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].z, q4.z, s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].w, q4.w, s, 0, 0, 0);
+                }
             }
+            float v[2][16];   // [r / 4 even or odd][r % 4, block]: asked for four rows ahead, the first ones before the weights are there
+            auto read_values = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int key = kt + 8 * t + 4 * g + i;
+                    const char *vrow = Vh + (size_t)min(key, kt1 - 1) * 512 + col * 8;
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        const float x = *reinterpret_cast<const float *>(vrow + (b & 1) * 256 + (b >> 1) * 4);
+                        v[t & 1][4 * i + b] = key < kt1 ? x : 0.f;
+                    }
+                }
+            };
+            if (WITH_O) read_values(0);
             softmax(s, kt);
             if (!WITH_O) continue;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = kt + 8 * (r >> 2) + 4 * g + (r & 3);
-                const char *vrow = Vh + (size_t)min(key, kt1 - 1) * 512 + col * 8;
+            for (int t = 0; t < 4; ++t) {
+                if (t + 1 < 4) read_values(t + 1);
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const float v = *reinterpret_cast<const float *>(vrow + (b & 1) * 256 + (b >> 1) * 4);
-                    o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(key < kt1 ? v : 0.f, s[r], o[b], 0, 0, 0);
-                }
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[t & 1][4 * i + b], s[4 * t + i], o[b], 0, 0, 0);
             }
         }
     }
