@@ -223,7 +223,10 @@ wk_status wk_gather_window(const wk_store_desc *store, const int32_t *ids, const
 /* Attention of the denoising chunk's queries over the assembled window (Sec. 4.2, Sec. 4.3):
  * O = softmax(Q K^T * scale) V per head, every window key visible to every query.
  * bf16: matrix-core products with fp32 accumulation, probabilities rounded to bf16 before the
- * P*V product, one rounding of O to bf16 at the end.  fp32: fp32 throughout.
+ * P*V product, one rounding of O to bf16 at the end.  fp32: matrix-core products of numbers that are split into two scaled fp16
+ * parts each (within 2^-23 of a number, 2^-21 of a product), fp32 accumulation and softmax.  Where magnitudes in a workgroup's keys, queries
+ * or values lie so far apart that the parts would lose more than fp32 rounding does, or are infinite, it
+ * works on fp32 products instead, which takes two to four times as long.
  *
  *   Q          device, [H][N_q][d]
  *   K_win,V_win device, [H][kv_row_stride][d]; the first N_kv rows of each head are attended

@@ -173,13 +173,20 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 // ------------------------------------------------------------------------------------------
 // fp32: every operand as the sum of two fp16 numbers, multiplied on v_mfma_f32_32x32x16_f16.
 //
-// x = x1 + x2 with x1 = fp16(x), x2 = fp16(x - x1) is off by at most 2^-24 of x, and a product of two such sums is taken without x2*y2, which is
-// below 2^-24 of it: three matrix instructions of 32 cycles do what eight fp32 ones of 64 do, and their sums are rounded less often.  On N(0, 1)
-// inputs results are 2.0e-7 to 5.3e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.
+// x = x1 + x2 with x1 = fp16(x), x2 = fp16(x - x1) is off by at most 2^-23 of x, and a product of two such sums is taken without x2*y2, which is
+// at most 2^-22 of it: three matrix instructions of 32 cycles do what eight fp32 ones of 64 do, and their sums are rounded less often.  On N(0, 1)
+// inputs results are 2.0e-7 to 5.3e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.  (A logit that is one product alone, where
+// roundings do not average, may be off by 2^-21 of itself; 2^-24 with fp32 instructions.)
 // fp16's range is met by powers of two: one per query, one for the keys and one per feature of the values, from the first tile's
-// largest numbers, which leaves a factor of 32 for those that follow.  A workgroup that has met larger ones, infinities,
-// or values that are 2^-11 smaller than their feature's in the first tile, does its work once more, with v_mfma_f32_32x32x2_f32 on the
-// numbers themselves.
+// largest numbers, which leaves a factor of 32 for those that follow.  Where scaled numbers are below 1/4 the second part's step, 2^-24, is what
+// is left, so a workgroup keeps its result only if that is small beside it, all with the numbers that it has met (kLogitLoss and on):
+//   logits      2^-25 * (sum of the query's sizes in key steps + 128 * the largest key in query steps) within 2^-20, which is fp32's rounding of a logit of 8
+//   by query    the largest |O| of the features within 2^-20 of half a step of every value, and at least 2^-12 (many keys: 2^-19 a key) of the largest
+//               value: weights, which are below 2^-36 of the largest in their last step, then lose no more than fp32 sums do
+//   by feature  the same over four queries, at 2^-18 and 2^-14, for features that have four adjacent keys whose values are 2^-11 of the first tile's (not all 0)
+// Otherwise, and with numbers beyond the factor of 32 or infinities, it does its work once more, with v_mfma_f32_32x32x2_f32 on the
+// numbers themselves.  tests/test_attention_f32_parts_bounds.py has this arithmetic for the CPU.  (Without the conditions one key at -1e9, a stand-in for
+// -inf, in a window's first tile took the others' logits with it: O was off by 9e-3, at -1e12 by 0.8.)
 //
 // Four waves of 32 queries per workgroup, 32-key tiles, KG tiles at a time by as many groups of waves; KG == 1 leaves room for two
 // workgroups on a compute unit, whose phases then overlap by themselves.  KG == 2: the groups' (O, max, sum) meet in
@@ -201,7 +208,7 @@ constexpr int kF32V = 2 * kF32Part;                    // K parts, V parts, K an
 constexpr int kF32RawK = 4 * kF32Part;
 constexpr int kF32RawV = kF32RawK + kF32Keys * 512;
 constexpr int kF32Group = kF32RawV + kF32Keys * 512;   // LDS of a group of waves
-constexpr int kF32Shared = 512 + 16;                   // largest values of the features, largest key, whether anything was out of range
+constexpr int kF32Shared = 3 * 512 + 16;               // for all groups: see `shared` in the kernel
 constexpr int kF32Lds = kF32Group + kF32Shared;
 constexpr int kF32LdsPair = 2 * kF32Group + kF32Shared;
 constexpr float kF32P = 0x1p11f;                       // what weights are scaled by
@@ -220,6 +227,12 @@ __device__ inline float max_across_halves(float x) {
     const unsigned u = __float_as_uint(x);
     const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// max over four adjacent lanes
+__device__ inline float quad_max(float x) {
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, false)));   // quad_perm [1, 0, 3, 2], [2, 3, 0, 1]
+    return fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4e, 0xf, 0xf, false)));
 }
 
 // max over a row of 16 lanes
@@ -295,7 +308,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     const int col = lane & 31, g = lane >> 5;
     const int q = qt * (kF32Waves * 32) + qw * 32 + col;
     const bool q_ok = q < a.N_q;
-    const int q_ld = q_ok ? q : a.N_q - 1;
+    const int q_ld = q_ok ? q : max(2 * a.N_q - 2 - q, 0);   // behind the last query the ones before it, so that a wave has few queries twice
     auto query_row = [&]() __attribute__((always_inline)) {
         int at = q_ld;
         asm("" : "+v"(at));
@@ -328,8 +341,11 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     const char *Vh = a.V + (size_t)h * win.stride * 512;
     char *const group = smem + kg * kF32Group;
     const unsigned lds0 = (unsigned)(size_t)WK_LDS(group);
-    int *const v_max = reinterpret_cast<int *>(smem + KG * kF32Group), *const k_max = v_max + WK_D;   // (sizes: their bits order as they do)
-    int *const out_of_range = k_max + 1;
+    // shared: the first tiles' largest value of every feature, what takes its sums back, the largest of all its values as they are split; the first tiles' largest
+    // key, the largest of all as they are split, whether the parts do not hold what they have to (sizes as int: their bits order as they do)
+    int *const v_max = reinterpret_cast<int *>(smem + KG * kF32Group);
+    float *const v_down = reinterpret_cast<float *>(v_max + WK_D);
+    int *const v_seen = v_max + 2 * WK_D, *const k_max = v_max + 3 * WK_D, *const k_seen = k_max + 1, *const out_of_range = k_max + 2, *const mixed = k_max + 3;
     // Loads: wave qw fills two rows per load, of K rows 8*qw .. 8*qw+7, 16-byte chunk c of row k at slot c ^ (k & 15); of V the eight
     // rows 16*(qw/2) + 4*(qw%2) + {0..3, 8..11}, which a lane group multiplies at once, for the wave itself.
     // Rows past the range clamp to its last one (those keys are masked, their values cleared).
@@ -359,13 +375,13 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     auto issue_q = [&](unsigned half) __attribute__((always_inline)) {
         unsigned l = lane;
         asm("" : "+v"(l));
-        const int q0 = qt * (kF32Waves * 32) + qw * 32;
-        const unsigned last = a.N_q - 1 - q0;
-        const char *base = a.Q + ((size_t)h * a.q_rows + a.q_off + q0) * 512;
+        const int q0 = qt * (kF32Waves * 32) + qw * 32, first = max(q0 - 32, 0), last = a.N_q - 1 - first;   // (rows from `first` on)
+        const char *base = a.Q + ((size_t)h * a.q_rows + a.q_off + first) * 512;
 #pragma unroll
         for (unsigned i = 0; i < 8; ++i) {
             const unsigned row = 4 * i + (l >> 4);
-            load_to_lds(base, (min(row, last) << 9) | (half << 8) | (((l & 15) ^ (row & 15)) << 4), lds0 + qw * (4 * kF32Part / kF32Waves) + i * 1024);
+            const int at = q0 - first + (int)row;
+            load_to_lds(base, ((unsigned)max(min(at, 2 * last - at), 0) << 9) | (half << 8) | (((l & 15) ^ (row & 15)) << 4), lds0 + qw * (4 * kF32Part / kF32Waves) + i * 1024);
         }
     };
     if (!idle) issue_q(0);
@@ -374,11 +390,12 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         issue_k(kt0 + kg * kF32Keys);
         if (WITH_O) issue_v(kt0 + kg * kF32Keys);
     }
-    if (tid < WK_D + 2) v_max[tid] = 0;
+    for (int i = tid; i < kF32Shared / 4; i += KG * kF32Waves * 64) v_max[i] = 0;
 
     // B operand of S^T = K Q^T: k slot 8*g + e of step s means feature 16*s + 8*g + e
     f16x8 qr[8][2];
     bool bad_keys = false;   // or queries
+    float q_sum = 0.f;       // of the sizes of this lane's query's numbers, as they are split
     float to_log2 = a.scale_log2;   // of this lane's query: what takes scores as they are summed to log2 units
     if (!idle) {
         float4 x[16];
@@ -398,9 +415,13 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         read_q(1);
         float largest = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
+        for (int i = 0; i < 16; ++i) {
             largest = fmaxf(fmaxf(fmaxf(largest, fabsf(x[i].x)), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
-        const float up = scale_to(max_across_halves(largest), 14, bad_keys);
+            q_sum += (fabsf(x[i].x) + fabsf(x[i].y)) + (fabsf(x[i].z) + fabsf(x[i].w));
+        }
+        largest = max_across_halves(largest);
+        const float up = largest == 0.f ? 0x1p40f : scale_to(largest, 14, bad_keys);   // (zeros have all the range)
+        q_sum = (q_sum + __shfl_xor(q_sum, 32)) * up;
         to_log2 *= inverse(up);
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
@@ -454,7 +475,8 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     };
 
     // A thread's share of a tile, in quarters: four numbers of K (of a row) or of V (of four keys) are read, and split and left a call later
-    float quarter[4], largest = 0.f, v_largest = 0.f, v_smallest = 1.f;
+    float quarter[4], k_largest = 0.f, v_largest[2] = {0.f, 0.f};   // (of all tiles)
+    unsigned v_least[2] = {~0u, ~0u};   // the smallest of the four keys' largest, as bits less 1, so that it is none that is all zeros
     float k_up = 1.f, v_up[2] = {1.f, 1.f};
     int me = tid;
     auto k_from = [&](int c) __attribute__((always_inline)) {   // features 8 * ((me >> 5 & 7) + 8 * (c / 2)) + 4 * (c % 2) of key me % 32
@@ -478,7 +500,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
             const float4 x = k_from(c);
             quarter[0] = x.x; quarter[1] = x.y; quarter[2] = x.z; quarter[3] = x.w;
         } else {
-            largest = fmaxf(largest, quarter_top() * k_up);
+            k_largest = fmaxf(k_largest, quarter_top());
             store_quarter(group + (((me >> 5) & 7) + 8 * (c >> 1)) * 512 + (me & 31) * 16 + (c & 1) * 8, k_up);
         }
     };
@@ -488,26 +510,22 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
             for (int u = 0; u < 4; ++u) quarter[u] = v_from(f, 4 * half + u);
         } else {
-            const float top = quarter_top() * v_up[f];
-            v_largest = half ? fmaxf(v_largest, top) : top;   // of eight keys; all 0 is no reason to leave
-            if (half) {
-                largest = fmaxf(largest, v_largest);
-                v_smallest = fminf(v_smallest, v_largest == 0.f ? 1.f : v_largest);
-            }
             if (kt + kF32Keys > kt1)   // rows past the range: the last one may be infinite
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (kt + v_key + 8 * half + u >= kt1) quarter[u] = 0.f;
+            const float top = quarter_top();
+            v_largest[f] = fmaxf(v_largest[f], top);
+            v_least[f] = min(v_least[f], __float_as_uint(top) - 1);
             store_quarter(group + kF32V + qw * 2048 + f * 1024 + (me & 63) * 16 + half * 8, v_up[f]);
         }
     };
     auto begin_share = [&]() __attribute__((always_inline)) {
-        largest = 0.f;
-        v_smallest = 1.f;
         me = tid;
         asm("" : "+v"(me));   // (its addresses are not kept either)
     };
     constexpr float kLimit = 65504.f;   // fp16's largest number
+    constexpr float kLogitLoss = 0x1p-20f;   // of a logit in log2 units
 
     // the scales, from the first tiles
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the first tile has landed
@@ -536,11 +554,14 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     to_log2 *= inverse(k_up);
     if (WITH_O)
 #pragma unroll
-        for (int f = 0; f < 2; ++f) v_up[f] = scale_to(__int_as_float(v_max[2 * lane + f]), 10, bad_values);
+        for (int f = 0; f < 2; ++f) {
+            v_up[f] = scale_to(__int_as_float(v_max[2 * lane + f]), 10, bad_values);
+            if (wave == 0) v_down[2 * lane + f] = inverse(kF32P * v_up[f]);
+        }
     if (any)
 #pragma unroll
         for (int t = 0; t < 8; ++t) k_work(t);
-    if (bad_keys || bad_values || largest >= kLimit) *out_of_range = 1;
+    if (bad_keys || bad_values || to_log2 * q_sum * 0x1p-25f > kLogitLoss) *out_of_range = 1;
 
     // The steps.  Beside the products of S^T a wave splits its share of the tile's values, beside those of O^T its share of the next tile's
     // keys (without a next tile: of the last one's again, which nothing reads)
@@ -548,8 +569,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's values have landed
         __syncthreads();
     };
-    auto meet_values = [&](int kt) __attribute__((always_inline)) {   // V's parts are there, K's are consumed
-        if (WITH_O && (largest >= kLimit || (v_smallest < 0.5f && kt + kF32Keys <= kt1))) *out_of_range = 1;
+    auto meet_values = [&]() __attribute__((always_inline)) {   // V's parts are there, K's are consumed
         __builtin_amdgcn_s_waitcnt(WITH_O ? 0x0F74 : 0x0F70);   // this wave's keys of the next tile have landed; its values, four loads, are behind them
         __syncthreads();
     };
@@ -587,7 +607,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
                     for (int p = 0; p < 2; ++p) pr[t][p] = __builtin_bit_cast(f16x8, u32x4{u[0].p[p], u[1].p[p], u[2].p[p], u[3].p[p]});
                 }
-            meet_values(kt);
+            meet_values();
             begin_share();
             if (WITH_O) {
                 // O^T += V^T P^T: k slot 8*g + e of step t means key 16*t + 8*(e/4) + 4*g + e%4, accumulator register 8*t + e;
@@ -606,7 +626,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
                 for (int t = 0; t < 8; ++t) k_work(t);
             }
-            if (largest >= kLimit) *out_of_range = 1;
         }
     } else {
         for (int j = 0; j < my_steps; ++j, kt += kStep) {
@@ -618,19 +637,68 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
                 for (int t = 0; t < 8; ++t) v_work(t, kt);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // before the place is written again
             if (WITH_O && kt + kStep < kt1) issue_v(kt + kStep);
-            meet_values(kt);
+            meet_values();
             begin_share();
 #pragma unroll
             for (int t = 0; t < 8; ++t) k_work(t);
-            if (largest >= kLimit) *out_of_range = 1;
         }
     }
     if (my_steps < n_steps) {   // the other group's last tile
         begin_share();
         meet_keys();
-        meet_values(kt);
+        meet_values();
     }
+    // What was met, and whether the parts lose too much by it, see above.
+    k_largest = row_max(k_largest) * k_up;
+    if ((lane & 15) == 0) atomicMax(k_seen, __float_as_int(k_largest));
+    bool lost = k_largest >= kLimit;
+    if (WITH_O)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            v_largest[f] *= v_up[f];
+            atomicMax(v_seen + 2 * lane + f, __float_as_int(v_largest[f]));
+            lost |= v_largest[f] >= kLimit;
+            if (v_least[f] != ~0u && __uint_as_float(v_least[f] + 1) * v_up[f] < 0.5f) v_max[2 * lane + f] = *mixed = -1;   // (no longer needed as it was)
+        }
     __syncthreads();   // every wave is done with its last tile, and its share of the LDS free
+    lost |= !idle && to_log2 * __int_as_float(*k_seen) * 0x1p-18f > kLogitLoss;
+    if (WITH_O && my_steps > 0 && !idle) {
+        const float l_tot = l_run + __shfl_xor(l_run, 32);
+        float of_values = 0.f, of_weights = 0.f;   // the features' largest, of a lane's two at first
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const float seen = __int_as_float(v_seen[2 * lane + f]), down = v_down[2 * lane + f];
+            of_weights = fmaxf(of_weights, seen * down);
+            of_values = fmaxf(of_values, seen > 0.f ? down : 0.f);
+        }
+        of_weights = row_max(of_weights);
+        of_values = row_max(of_values);
+        of_weights = max_across_halves(fmaxf(of_weights, __shfl_xor(of_weights, 16)));
+        of_values = max_across_halves(fmaxf(of_values, __shfl_xor(of_values, 16)));
+        const float least = fmaxf(of_weights * kF32P * fmaxf(0x1p-12f, (float)(my_steps * kF32Keys) * 0x1p-19f), of_values * 64.f * l_tot);
+        const bool by_feature = __builtin_amdgcn_readfirstlane(*mixed) != 0;
+        float row = 0.f;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < 4; u += 2) {   // the registers of a 16-byte chunk's features, as they are stored below
+                    const int chunk = 16 * b + 4 * t + 2 * g + u / 2;
+                    const float4 down = *reinterpret_cast<const float4 *>(v_down + 4 * chunk);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int blk = b + 2 * (i & 1), r = 4 * t + u + (i >> 1);
+                        if (by_feature && v_max[4 * chunk + i] < 0)
+                            lost |= quad_max(fabsf(o[blk][r])) < fmaxf(__int_as_float(v_seen[4 * chunk + i]) * (kF32P * 0x1p-14f), 16.f * l_tot);
+                        o[blk][r] *= (&down.x)[i];
+                        row = fmaxf(row, fabsf(o[blk][r]));
+                    }
+                }
+        lost |= max_across_halves(row) < least;
+    }
+    if (lost) *out_of_range = 1;
+    __syncthreads();
     // (looked at here only: behind every barrier, and with the values requested behind the second one, 4 heads x 880 queries x 2,640 keys in one
     // range took 129 us, now 125)
     const bool exact = __builtin_amdgcn_readfirstlane(*out_of_range) != 0;
@@ -743,13 +811,8 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
             for (int u = 0; u < 4; u += 2) {
                 const int chunk = 16 * b + 4 * t + 2 * g + u / 2;
-                const float4 top = *reinterpret_cast<const float4 *>(v_max + 4 * chunk);
-                float down[4] = {inv, inv, inv, inv};
-                bool unused = false;
-                if (!exact)
-                    for (int i = 0; i < 4; ++i) down[i] *= inverse(kF32P * scale_to((&top.x)[i], 10, unused));
                 *reinterpret_cast<float4 *>(o_lds + col * 512 + ((chunk ^ (col & 15)) << 4)) =
-                    float4{o[b][4 * t + u] * down[0], o[b + 2][4 * t + u] * down[1], o[b][4 * t + u + 1] * down[2], o[b + 2][4 * t + u + 1] * down[3]};
+                    float4{o[b][4 * t + u] * inv, o[b + 2][4 * t + u] * inv, o[b][4 * t + u + 1] * inv, o[b + 2][4 * t + u + 1] * inv};
             }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const int q0 = qt * (kF32Waves * 32) + qw * 32, rows = min(32, a.N_q - q0);

@@ -76,3 +76,79 @@ def test_tiles_unlike_the_first(case, H, N_q, N_kv, split):
         Q[..., 77] = 0
         unit = np.where(np.arange(128) == 3, 3e4, 1.0)
     _check(Q, K, V, unit, split)
+
+
+# One number that sets a power of two for others which it has nothing to do with, and weights or values that are small beside it: the parts alone
+# lose them, more with every power of ten.  (20 and 52 keys: one partial tile, and one behind the first; 300: two wave groups, key ranges)
+def _unlike(case, x, Q, K, V, at):
+    """-> the size of the outputs"""
+    at %= K.shape[1]
+    first = slice(0, 32 if K.shape[1] > 32 else 10)
+    if case == "masked_key":
+        Q[..., 0], K[..., 0] = 1, 0
+        K[:, at, 0] = -x
+    if case == "query_channel":
+        Q[..., 7], K[..., 7] = x, 0
+    if case == "key_channel":
+        Q[..., 7], K[..., 7] = 0, x
+    if case == "zeros_then_small":
+        K[:, :at] = 0
+        K /= x
+        Q *= x
+    if case in ("large_value", "large_values", "one_feature"):   # without weight: e^-53
+        Q[..., 0], K[..., 0] = 1, 0
+        K[:, at if case != "large_values" else first, 0] = -600
+    if case == "large_value":
+        V[:, at] = x
+    if case == "large_values":
+        V[:, first] *= x
+    unit = np.ones(128)
+    if case == "one_feature":
+        unit[9] = 1e-4
+        V[..., 9] *= 1e-4
+        V[:, at, 9] = x * 1e-4
+    if case == "sink":   # a key without values that takes all but 1 / x of the weight
+        Q[..., 0], K[..., 0] = 16, 0
+        K[:, at], V[:, at] = 0, 0
+        K[:, at, 0] = float(np.float16(np.log(x) / np.sqrt(2)))   # (a logit of one product, exact in parts)
+        unit = unit * np.abs(oracle.attention(Q, K, V)).max() / 4
+    return unit
+
+
+@pytest.mark.parametrize("H,N_q,N_kv,split", [(2, 64, 20, False), (3, 33, 52, False), (2, 100, 300, False), (2, 100, 300, True), (300, 10, 96, False)])
+@pytest.mark.parametrize("at", [5, 45, 290])
+@pytest.mark.parametrize("case,x", [(c, x) for c, xs in (
+    ("masked_key", (1e3, 1e4, 1e6, 1e9, 1e12, 1e15)), ("query_channel", (1e4, 1e6, 1e9, 1e12)), ("key_channel", (1e4, 1e9, 1e12)),
+    ("zeros_then_small", (1e3, 1e6)), ("large_value", (1e3, 1e6, 1e9, 1e12)), ("large_values", (1e3, 1e6, 1e9)), ("one_feature", (1e3, 1e6)),
+    ("sink", (1e2, 1e5, 1e9, 1e13))) for x in xs])
+def test_numbers_that_others_are_small_beside(case, x, at, H, N_q, N_kv, split):
+    Q, K, V = _randn(H, N_q, N_kv)
+    unit = _unlike(case, x, Q, K, V, at)
+    _check(Q, K, V, unit, split)
+
+
+@pytest.mark.parametrize("case,x", [("masked_key", 1e6), ("masked_key", 1e12), ("query_channel", 1e9), ("large_value", 1e9)])
+@pytest.mark.parametrize("T,F,row0,N_kv", [(100, 2, 0, 300), (40, 3, 70, 190)])
+def test_numbers_that_others_are_small_beside_under_the_frame_mask(case, x, T, F, row0, N_kv):
+    d = dev()
+    Q, K, V = _randn(2, T * F, N_kv)
+    unit = _unlike(case, x, Q, K, V, row0 + 5)
+    O, lse = torch.empty_like(Q, device=d), torch.empty((2, T * F), device=d)
+    ws = torch.empty(wk.wk_attention_block_causal_workspace_bytes(2, T * F), dtype=torch.uint8, device=d)
+    wk.wk_attention_block_causal(Q.to(d), K.to(d), V.to(d), O, row0, T, ws, lse=lse)
+    ref, ref_lse = oracle.attention_block_causal(Q, K, V, row0, T, want_lse=True)
+    assert np.abs((O.cpu().double().numpy() - ref) / unit).max() <= ATT_MAX_ABS_F32
+    assert np.abs(lse.cpu().double().numpy() - ref_lse).max() <= 1e-5
+
+
+@pytest.mark.parametrize("case,x", [("masked_key", 1e6), ("masked_key", 1e12), ("query_channel", 1e9), ("zeros_then_small", 1e6)])
+def test_numbers_that_others_are_small_beside_in_stored_chunks(case, x):
+    d = dev()
+    Q, K, V = _randn(3, 70, 240)
+    _unlike(case, x, Q, K, V, 45)
+    Ks = [k.contiguous() for k in K.split([100, 52, 88], 1)]
+    store = wk.Store([k.to(d) for k in Ks], [k.to(d) for k in Ks])
+    out = torch.empty((3, 3, 70), device=d)
+    wk.wk_chunk_lse(store.desc, Q.to(d), out)
+    for k, got in zip(Ks, out.cpu().double().numpy()):
+        assert np.abs(got - oracle.attention(Q, k, k, want_lse=True)[1]).max() <= 1e-5
