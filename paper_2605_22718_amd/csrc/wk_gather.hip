@@ -156,7 +156,30 @@ __global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
     }
 }
 
+// One workgroup per unit, as far as a cap on workgroups and a launch's 2^32 threads allow: behind them workgroups take further units.
+struct GatherPlan {
+    int threads, vecs;
+    long long units_per_head, units, grid;
+};
+
+GatherPlan plan_gather(long long cap_vec, long long H, int max_workgroups) {   // cap_vec: 16-byte vectors to copy of a head's K, at most
+    GatherPlan p{256, 6, 0, 0, 0};
+    if (max_workgroups > 0) p.vecs = 8;
+    else if ((double)cap_vec * (double)H * 32 > (double)kLargeCopy) p = GatherPlan{512, 3, 0, 0, 0};
+    const long long unit = p.threads * p.vecs;
+    p.units_per_head = cap_vec > 0 ? (cap_vec + unit - 1) / unit : 1;   // nothing to copy: one workgroup still reports the (zero) length
+    p.units = p.units_per_head * H * 2;
+    p.grid = max_workgroups > 0 && p.units > max_workgroups ? max_workgroups : p.units;
+    if (!wk::fits_launch(p.grid, p.threads)) p.grid = UINT32_MAX / p.threads;
+    return p;
+}
+
 }  // namespace
+
+extern "C" int64_t wk_internal_gather_threads(int32_t H, int64_t rows, int32_t dtype, int32_t max_workgroups) {
+    const GatherPlan p = plan_gather(rows * (int64_t)(WK_D * wk::esize(dtype) / 16), H, max_workgroups);
+    return p.grid * p.threads;
+}
 
 wk_status wk::gather_launch(const wk_store_desc *store, const int32_t *ids, const int32_t *n_ids, int32_t R_max,
                             const void *K_native, const void *V_native, int32_t n_native, void *K_win,
@@ -187,21 +210,14 @@ wk_status wk::gather_launch(const wk_store_desc *store, const int32_t *ids, cons
     a.first_row = K_native ? 0 : n_native;
     const long long cap_vec = (long long)(n_native - a.first_row + (int64_t)R_max * store->max_tok) * a.vec_per_row;
     const size_t lds_bytes = (size_t)(R_max + 1) * (2 * sizeof(char *) + 2 * sizeof(int));
-    wk_status st = WK_OK;
-    auto launch = [&](auto narrow, auto wide, int threads, int vecs) {
-        long long per_head = (cap_vec + threads * vecs - 1) / (threads * vecs);
-        if (per_head == 0) per_head = 1;  // nothing to copy: one workgroup still reports the (zero) length
-        a.units_per_head = (int)per_head;
-        const long long units = per_head * store->H * 2;
-        const long long grid = max_workgroups > 0 && units > max_workgroups ? max_workgroups : units;
-        if (grid > 0x7fffffffLL) st = WK_ERR_UNSUPPORTED;
-        else   // (a unit number plus a grid stays below 2^32)
-            hipLaunchKernelGGL(units <= 0x7fffffffLL ? narrow : wide, dim3((unsigned)grid), dim3(threads), lds_bytes, stream, a);
-    };
-    if (max_workgroups > 0) launch(k_gather<uint32_t, 256, 8>, k_gather<uint64_t, 256, 8>, 256, 8);
-    else if (cap_vec * store->H * 32 > kLargeCopy) launch(k_gather<uint32_t, 512, 3>, k_gather<uint32_t, 512, 3>, 512, 3);
-    else launch(k_gather<uint32_t, 256, 6>, k_gather<uint32_t, 256, 6>, 256, 6);
-    if (st != WK_OK) return st;
+    const GatherPlan p = plan_gather(cap_vec, store->H, max_workgroups);
+    if (max_workgroups == 0 && p.units > 0x7fffffffLL) return WK_ERR_UNSUPPORTED;
+    a.units_per_head = (int)p.units_per_head;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)p.grid), dim3(p.threads), lds_bytes, stream, a); };
+    // (32-bit unit numbers: one plus a grid stays below 2^32)
+    if (max_workgroups > 0) p.units <= 0x7fffffffLL ? launch(k_gather<uint32_t, 256, 8>) : launch(k_gather<uint64_t, 256, 8>);
+    else if (p.threads == 512) launch(k_gather<uint32_t, 512, 3>);
+    else launch(k_gather<uint32_t, 256, 6>);
     WK_LAUNCH_CHECK();
     return WK_OK;
 }

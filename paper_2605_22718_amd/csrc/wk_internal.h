@@ -17,10 +17,12 @@
 
 // Not part of the interface: the tests pin with these that a shape takes the path it is there for.  How bf16 attention would
 // be launched (0: 256 queries per workgroup, 1: 128 in pairs of tiles, 2: 128), under a frame mask (+ 100: as two key ranges, else as windows
-// with a gap; -1: more frames than the table of launches holds); head ranges of the similarity GEMM.
+// with a gap; -1: more frames than the table of launches holds); head ranges of the similarity GEMM; threads that assemble a window of which
+// `rows` a head are copied.
 extern "C" int32_t wk_internal_attention_plan(int32_t H, int32_t N_q, int32_t N_kv, size_t workspace_bytes);   // layout * 100 + key ranges
 extern "C" int32_t wk_internal_frame_mask_plan(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T);
 extern "C" int32_t wk_internal_gemm_head_ranges(const wk_compress_desc *desc);
+extern "C" int64_t wk_internal_gather_threads(int32_t H, int64_t rows, int32_t dtype, int32_t max_workgroups);
 
 namespace wk {
 
@@ -42,7 +44,7 @@ inline void mark_device(std::atomic<uint64_t> &flags, int dev) {
     if (dev >= 0 && dev <= 63) flags.fetch_or(uint64_t(1) << dev, std::memory_order_release);
 }
 
-// wk_gather_window with a cap on the number of workgroups (0 = one per 32 KB work unit)
+// wk_gather_window with a cap on the number of workgroups (0 = one per work unit)
 wk_status gather_launch(const wk_store_desc *store, const int32_t *ids, const int32_t *n_ids, int32_t R_max,
                         const void *K_native, const void *V_native, int32_t n_native, void *K_win, void *V_win,
                         int32_t win_capacity, int32_t *n_win, int32_t max_workgroups, hipStream_t stream);

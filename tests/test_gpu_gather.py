@@ -169,3 +169,16 @@ def test_id_list_no_longer_than_its_count():
     wk.wk_gather_window(store.desc, torch.tensor([2, 1], dtype=torch.int32, device=d), torch.tensor([2], dtype=torch.int32, device=d), 4,
                         None, None, 0, Kw, Vw, 4 * 70, n_win)
     assert int(n_win.item()) == 90 and torch.equal(bits(Kw[:, :90].cpu()), bits(torch.cat([ks[2], ks[1]], 1)))
+
+
+def test_more_units_than_a_launch_has_workgroups_of_512():
+    """A row each of 2^22 + 1 heads: 2^23 + 2 work units, where 2^23 workgroups of 512 threads are a launch's limit."""
+    d, H = dev(), 2 ** 22 + 1
+    g = torch.Generator(device=d).manual_seed(1)
+    K, V = [torch.randint(-2 ** 61, 2 ** 61, (H, 1, 32), generator=g, device=d).view(torch.bfloat16) for _ in range(2)]
+    store = wk.Store([K], [V])
+    Kw, Vw = [torch.zeros((H, 1, 128), dtype=torch.bfloat16, device=d) for _ in range(2)]
+    n_win = torch.empty(1, dtype=torch.int32, device=d)
+    wk.wk_gather_window(store.desc, torch.zeros(1, dtype=torch.int32, device=d), None, 1, None, None, 0, Kw, Vw, 1, n_win)
+    assert int(n_win) == 1
+    assert torch.equal(bits(Kw), bits(K)) and torch.equal(bits(Vw), bits(V))
