@@ -1043,6 +1043,9 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
 // 24 x 3,039 (285 MB) 236 and 202, 3 of 12 x 2,640 (46 MB) 45 and 48.
 constexpr long long kStreamBytes = 64ll << 20, kStreamBytesF32 = 144ll << 20;
 
+// K's and V's workgroups of `tiles` tiles in one launch as long as it has threads for both
+int compact_launches(long long tiles) { return wk::fits_launch(2 * tiles, 256) ? 1 : 2; }
+
 template <int DT, bool STREAM>
 __global__ __launch_bounds__(256) void k_compact(const char *__restrict__ K, const char *__restrict__ V,
                                                  CompressDims p, int first_row, unsigned tiles, const int32_t *__restrict__ kept_idx,
@@ -1354,9 +1357,17 @@ wk_status launch_all(const wk_compress_desc *d, const CompressDims &p, const WsL
     WK_LAUNCH_CHECK();
     if (first_row == p.n_out) return WK_OK;
     const unsigned tiles = (unsigned)((p.n_out - first_row + kRowsPerBlock - 1) / kRowsPerBlock);
-    const dim3 g5(2 * tiles, p.H, d->batch);
-    if (stream) hipLaunchKernelGGL((k_compact<DT, true>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, tiles, kept, Ko, Vo);
-    else hipLaunchKernelGGL((k_compact<DT, false>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, tiles, kept, Ko, Vo);
+    auto compact = [&](unsigned workgroups, unsigned k_tiles) {
+        const dim3 g5(workgroups, p.H, d->batch);
+        if (stream) hipLaunchKernelGGL((k_compact<DT, true>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, k_tiles, kept, Ko, Vo);
+        else hipLaunchKernelGGL((k_compact<DT, false>), g5, dim3(256), 0, st, Kc, Vc, p, first_row, k_tiles, kept, Ko, Vo);
+    };
+    if (compact_launches(tiles) == 1) {
+        compact(2 * tiles, tiles);
+    } else {   // K, then V
+        compact(tiles, tiles);
+        compact(tiles, 0);
+    }
     WK_LAUNCH_CHECK();
     return WK_OK;
 }
@@ -1450,6 +1461,8 @@ wk_status scratch_of_current_device(char **out) {
 }  // namespace
 
 extern "C" size_t wk_compress_scratch_bytes(void) { return WK_COMPRESS_SCRATCH_BYTES; }
+
+extern "C" int32_t wk_internal_compact_launches(int64_t rows) { return compact_launches((rows + kRowsPerBlock - 1) / kRowsPerBlock); }
 
 extern "C" int32_t wk_internal_gemm_head_ranges(const wk_compress_desc *desc) {
     CompressDims p;

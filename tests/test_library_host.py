@@ -398,3 +398,11 @@ def test_gather_never_launches_more_threads_than_a_launch_has(H, rows, dtype, ca
     f.argtypes, f.restype = [C.c_int32, C.c_int64, C.c_int32, C.c_int32], C.c_int64
     got = f(H, rows, dtype, cap)
     assert got == threads if threads else 2 ** 31 < got < 2 ** 32
+
+
+# rows of one head: 16 threads each for K and for V
+@pytest.mark.parametrize("rows,launches", [(1, 1), (4680, 1), (2 ** 27 - 16, 1), (2 ** 27 - 15, 2), (2 ** 28 - 16, 2)])
+def test_compaction_never_launches_more_threads_than_a_launch_has(rows, launches):
+    f = wk.lib().wk_internal_compact_launches
+    f.argtypes, f.restype = [C.c_int64], C.c_int32
+    assert f(rows) == launches and -(-rows // 16) * 256 * (2 if launches == 1 else 1) < 2 ** 32
