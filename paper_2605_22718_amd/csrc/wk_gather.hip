@@ -24,8 +24,11 @@ constexpr int kMaxR = 1024;
 // Work units: 256 threads with six vectors each where the copy is short, 512 with three beyond kLargeCopy bytes, the launch in order then
 // sweeping the window closer to in sequence.  32 KB as 256 x 8, 24 KB as 256 x 6 and as 512 x 3: 8 chunks of 40 heads x 2,340 tokens (383 MB)
 // 144, 142 and 130 us, 16 of 12 x 1,320 (130 MB) 54.9, 50.6 and 49.8, 3 of 40 x 700 (43 MB) 17.2, 14.7 and 18.7, 4 of 12 x 1,320 13.1, 13.0
-// and 15.7 (512 x 2: 136, 51.4, 19.4, 15.4; 256 x 4: 133, 51.1, 19.3, 17.1; 256 x 1: 169, 66, 22, 17).  A capped grid has 256 x 8: what a few
-// workgroups keep in flight over the host link.
+// and 15.7 (512 x 2: 136, 51.4, 19.4, 15.4; 256 x 4: 133, 51.1, 19.3, 17.1; 256 x 1: 169, 66, 22, 17).  Between them either may be ahead: 256 x 6 and
+// 512 x 3 take 27.1 and 25.5 us for 8 of 12 x 1,320 (65 MB), 32.2 and 32.2 for 10 (81 MB), 35.3 and 36.5 for 12 (97 MB), 41.5 and 38.0 for 5 of 40 x 1,040 (107 MB);
+// above, 512 x 3 is: 50.3 and 47.4 for 7 of 16 x 2,340 (134 MB), 69.7 and 64.8 for 4 of 40 x 2,340 (192 MB).  A capped grid has 256 x 8: what a few
+// workgroups keep in flight over the host link.  Heads of less than a unit leave most of 512 threads idle (one row of 2^22 heads 17.6 ms, in
+// 256 threads 9.9).
 constexpr long long kLargeCopy = 128'000'000;
 
 typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
@@ -165,7 +168,7 @@ struct GatherPlan {
 GatherPlan plan_gather(long long cap_vec, long long H, int max_workgroups) {   // cap_vec: 16-byte vectors to copy of a head's K, at most
     GatherPlan p{256, 6, 0, 0, 0};
     if (max_workgroups > 0) p.vecs = 8;
-    else if ((double)cap_vec * (double)H * 32 > (double)kLargeCopy) p = GatherPlan{512, 3, 0, 0, 0};
+    else if (cap_vec >= 512 * 3 && (double)cap_vec * (double)H * 32 > (double)kLargeCopy) p = GatherPlan{512, 3, 0, 0, 0};
     const long long unit = p.threads * p.vecs;
     p.units_per_head = cap_vec > 0 ? (cap_vec + unit - 1) / unit : 1;   // nothing to copy: one workgroup still reports the (zero) length
     p.units = p.units_per_head * H * 2;

@@ -390,8 +390,9 @@ def test_the_hand_scheduled_attention_loop_is_what_its_generator_writes():
 # heads x rows (of 256 or 512 bytes): a launch has fewer than 2^32 threads, whatever the copy; what fits has a workgroup per unit of 24 or, capped, 32 KB
 @pytest.mark.parametrize("H,rows,dtype,cap,threads", [
     (1, 0, wk.WK_BF16, 0, 2 * 256), (12, 5280, wk.WK_BF16, 0, 12 * 2 * 55 * 256), (40, 18720, wk.WK_BF16, 0, 40 * 2 * 195 * 512),
-    (40, 9360, wk.WK_F32, 0, 40 * 2 * 195 * 512), (12, 5280, wk.WK_BF16, 64, 64 * 256), (2 ** 22 - 1, 1, wk.WK_BF16, 0, (2 ** 23 - 2) * 512),
-    (2 ** 22, 1, wk.WK_BF16, 0, None), (2 ** 22 + 1, 1, wk.WK_BF16, 0, None), (2 ** 23 + 5, 1, wk.WK_F32, 0, None), (2 ** 30 - 1, 1, wk.WK_BF16, 0, None),
+    (40, 9360, wk.WK_F32, 0, 40 * 2 * 195 * 512), (12, 5280, wk.WK_BF16, 64, 64 * 256), (2 ** 22 + 1, 1, wk.WK_BF16, 0, (2 ** 23 + 2) * 256),
+    (2 ** 22 - 1, 96, wk.WK_BF16, 0, (2 ** 23 - 2) * 512), (2 ** 22, 96, wk.WK_BF16, 0, None), (2 ** 22 + 1, 48, wk.WK_F32, 0, None),
+    (2 ** 20, 96, wk.WK_BF16, 0, 2 ** 21 * 512), (2 ** 20, 95, wk.WK_BF16, 0, 2 ** 21 * 256), (2 ** 23 + 5, 1, wk.WK_F32, 0, None), (2 ** 30 - 1, 1, wk.WK_BF16, 0, None),
     (2 ** 30, 3, wk.WK_BF16, 2 ** 31 - 1, None)])
 def test_gather_never_launches_more_threads_than_a_launch_has(H, rows, dtype, cap, threads):
     f = wk.lib().wk_internal_gather_threads
