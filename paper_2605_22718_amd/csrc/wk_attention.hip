@@ -185,7 +185,7 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 //               value: weights, which are below 2^-36 of the largest in their last step, then lose no more than fp32 sums do
 //   by feature  the same over four queries, at 2^-18 and 2^-14, for features that have four adjacent keys whose values are 2^-11 of the first tile's (not all 0)
 // Otherwise, and with numbers beyond the factor of 32 or infinities, it does its work once more, with v_mfma_f32_32x32x2_f32 on the
-// numbers themselves.  tests/test_attention_f32_parts_bounds.py has this arithmetic for the CPU.  (Without the conditions one key at -1e9, a stand-in for
+// numbers themselves (before its first step, if its first tile is enough to know).  tests/test_attention_f32_parts_bounds.py has this arithmetic for the CPU.  (Without the conditions one key at -1e9, a stand-in for
 // -inf, in a window's first tile took the others' logits with it: O was off by 9e-3, at -1e12 by 0.8.)
 //
 // Four waves of 32 queries per workgroup, 32-key tiles, KG tiles at a time by as many groups of waves; KG == 1 leaves room for two
@@ -351,23 +351,23 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     // Rows past the range clamp to its last one (those keys are masked, their values cleared).
     // (addresses from a scalar base and a lane's 32-bit offset, made where they are used: kept, they would take 20 registers)
     const int v_key = 16 * (qw >> 1) + 4 * (qw & 1);
-    auto issue_k = [&](int kt) __attribute__((always_inline)) {
+    auto issue_k = [&](int kt, unsigned place = kF32RawK) __attribute__((always_inline)) {
         size_t at = (size_t)kt * 512;
         unsigned l = lane;
         asm("" : "+s"(at), "+v"(l));
         const unsigned row = 8 * qw + (l >> 5), slot = ((l & 31) ^ (row & 15)) << 4, last = kt1 - 1 - kt;   // the range's last row, from the tile's first on
 #pragma unroll
         for (unsigned i = 0; i < 4; ++i)
-            load_to_lds(Kh + at, (min(row | 2 * i, last) << 9) | (slot ^ (i << 5)), lds0 + kF32RawK + qw * 4096 + i * 1024);
+            load_to_lds(Kh + at, (min(row | 2 * i, last) << 9) | (slot ^ (i << 5)), lds0 + place + qw * 4096 + i * 1024);
     };
-    auto issue_v = [&](int kt) __attribute__((always_inline)) {
+    auto issue_v = [&](int kt, unsigned place = kF32RawV) __attribute__((always_inline)) {
         size_t at = (size_t)kt * 512;
         unsigned l = lane;
         asm("" : "+s"(at), "+v"(l));
         const unsigned row = v_key + (l >> 5), last = kt1 - 1 - kt;
 #pragma unroll
         for (unsigned e = 0; e < 8; e += 2)
-            load_to_lds(Vh + at, (min(row + 8 * (e >> 2) + (e & 3), last) << 9) | ((l & 31) << 4), lds0 + kF32RawV + qw * 4096 + e * 512);
+            load_to_lds(Vh + at, (min(row + 8 * (e >> 2) + (e & 3), last) << 9) | ((l & 31) << 4), lds0 + place + qw * 4096 + e * 512);
     };
     // Queries come through LDS, the first and the second 64 features one after the other, in the wave's share of the parts' place: rows of 512 bytes, one
     // per lane, keep the L1 busy three times as long.  16-byte chunk c of row r at slot c ^ (r & 15).
@@ -573,8 +573,10 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         __builtin_amdgcn_s_waitcnt(WITH_O ? 0x0F74 : 0x0F70);   // this wave's keys of the next tile have landed; its values, four loads, are behind them
         __syncthreads();
     };
-    const int n_steps = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + KG - 1) / KG;
-    const int my_steps = (kt1 - kt0 - kg * kF32Keys + KG * kF32Keys - 1) / (KG * kF32Keys);   // with an odd count of tiles the second group has one less
+    __syncthreads();
+    const bool steps = __builtin_amdgcn_readfirstlane(*out_of_range) == 0;   // (not behind a first tile that leads to fp32 products as it is)
+    const int n_steps = steps ? ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + KG - 1) / KG : 0;
+    const int my_steps = steps ? (kt1 - kt0 - kg * kF32Keys + KG * kF32Keys - 1) / (KG * kF32Keys) : 0;   // with an odd count of tiles the second group has one less
     int kt = kt0 + kg * kF32Keys;
     constexpr int kStep = KG * kF32Keys;
     if (KG == 2 && kg == 0) __builtin_amdgcn_s_setprio(1);   // one of a SIMD's two waves ahead: one does its softmax while the other multiplies
@@ -702,8 +704,11 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     // (looked at here only: behind every barrier, and with the values requested behind the second one, 4 heads x 880 queries x 2,640 keys in one
     // range took 129 us, now 125)
     const bool exact = __builtin_amdgcn_readfirstlane(*out_of_range) != 0;
-    // 4 heads x 880 queries x 2,640 keys, two of them at -inf: 97 us; the kernel that had fp32 products only took 65 for any keys, this one 39 for others
-    if (exact) {   // once more from the first tile on, with fp32 operands straight from memory
+    // Once more from the first tile on, with fp32 operands: tiles as they come, in the raw tiles' place and in the parts' in turn.  Bound by the products, 128 of 64 cycles a tile.  With
+    // a key at -inf in the first tile, which is known before any step, 4 heads x 880 queries x 2,640 keys take 72 us, 8 x 1,560 x 4,680 221, 1 x 128 x 30,000 254 (operands
+    // straight from memory and behind all the steps: 96, 388, 380; the kernel of fp32 products alone, for any keys, 64, 295, 252); found out at the end
+    // only, by the values' spread, 95, 425 and 340.
+    if (exact) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -717,50 +722,67 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
             for (int t = 0; t < 16; ++t) y[t] = *reinterpret_cast<const float4 *>(Qrow + 8 * t + 4 * g);
         }
-        for (int kt = kt0 + kg * kF32Keys; kt < kt1 && !idle; kt += kStep) {   // (eight pieces of a key row and 32 values in flight)
+        const int all_steps = ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + KG - 1) / KG;
+        int kt = kt0 + kg * kF32Keys;
+        if (kt < kt1) {
+            issue_k(kt);
+            if (WITH_O) issue_v(kt);
+        }
+        for (int j = 0; j < all_steps; ++j, kt += kStep) {
+            const unsigned place = j & 1 ? 0u : kF32RawK, next = kF32RawK - place;
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's share has landed
+            asm volatile("" ::: "memory");
+            if (WITH_O && kt < kt1 && kt + kF32Keys > kt1) {   // values past the range become zeros: the last row there may be infinite
+#pragma unroll
+                for (int e = 0; e < 8; e += 2)
+                    if (kt + v_key + 8 * (e >> 2) + (e & 3) + (lane >> 5) >= kt1)
+                        *reinterpret_cast<float4 *>(group + place + kF32Keys * 512 + qw * 4096 + e * 512 + lane * 16) = float4{0, 0, 0, 0};
+            }
+            __syncthreads();   // everyone's has, and the tile before is consumed
+            if (kt + kStep < kt1) {
+                issue_k(kt + kStep, next);
+                if (WITH_O) issue_v(kt + kStep, next + kF32Keys * 512);
+            }
+            if (kt >= kt1 || idle) continue;
+            // operands are read two groups of four products ahead, and the order is kept
+            unsigned at = lds0 + place;
+            asm("" : "+s"(at));
+            f32x4 ka[3];
+            f32x2 va[3][2];   // of features 64 * b + 2 * col and one more, of which the second's block is b + 2
+            auto read_k = [&](int t) __attribute__((always_inline)) { ka[t % 3] = *WK_LDS_AT(const f32x4, at + col * 512 + (((2 * t + g) ^ (col & 15)) << 4)); };
+            auto read_v = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    va[r % 3][b] = *WK_LDS_AT(const f32x2, at + kF32Keys * 512 + ((2 * (r >> 3) + g) * 8 + 4 * ((r >> 2) & 1) + (r & 3)) * 512 + b * 256 + col * 8);
+            };
             f32x16 s;
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = 0.f;
-            const char *krow = Kh + (size_t)min(kt + col, kt1 - 1) * 512 + 16 * g;
+            read_k(0);
+            read_k(1);
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                float4 x[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) x[t] = *reinterpret_cast<const float4 *>(krow + 32 * (8 * half + t));
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const float4 q4 = y[8 * half + t];
-                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].x, q4.x, s, 0, 0, 0);
-                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].y, q4.y, s, 0, 0, 0);
-                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].z, q4.z, s, 0, 0, 0);
-                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(x[t].w, q4.w, s, 0, 0, 0);
-                }
+            for (int t = 0; t < 16; ++t) {
+                if (t + 2 < 16) read_k(t + 2);
+                else if (WITH_O) read_v(t - 14);
+                __builtin_amdgcn_sched_barrier(0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[t % 3][0], y[t].x, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[t % 3][1], y[t].y, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[t % 3][2], y[t].z, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[t % 3][3], y[t].w, s, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            float v[2][16];   // [r / 4 even or odd][r % 4, block]: asked for four rows ahead, the first ones before the weights are there
-            auto read_values = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int key = kt + 8 * t + 4 * g + i;
-                    const char *vrow = Vh + (size_t)min(key, kt1 - 1) * 512 + col * 8;
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const float x = *reinterpret_cast<const float *>(vrow + (b & 1) * 256 + (b >> 1) * 4);
-                        v[t & 1][4 * i + b] = key < kt1 ? x : 0.f;
-                    }
-                }
-            };
-            if (WITH_O) read_values(0);
             softmax(s, kt);
             if (!WITH_O) continue;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (t + 1 < 4) read_values(t + 1);
+            for (int r = 0; r < 16; ++r) {
+                if (r + 2 < 16) read_v(r + 2);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[t & 1][4 * i + b], s[4 * t + i], o[b], 0, 0, 0);
+                for (int b = 0; b < 4; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[r % 3][b & 1][b >> 1], s[r], o[b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __syncthreads();   // the last tiles are consumed
     }
     // The wave groups meet: waves 4..7 leave (O^T, max, sum) of their keys in LDS, waves 0..3 add them to theirs.
     // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.

@@ -152,3 +152,12 @@ def test_numbers_that_others_are_small_beside_in_stored_chunks(case, x):
     wk.wk_chunk_lse(store.desc, Q.to(d), out)
     for k, got in zip(Ks, out.cpu().double().numpy()):
         assert np.abs(got - oracle.attention(Q, k, k, want_lse=True)[1]).max() <= 1e-5
+
+
+# the walk on fp32 products: whole and partial tiles, odd counts of them, known from the first tile (5) or from the last one
+@pytest.mark.parametrize("H,N_q", [(2, 130), (300, 20)])
+@pytest.mark.parametrize("N_kv", [32, 33, 64, 65, 97, 128, 161, 290])
+@pytest.mark.parametrize("at", [5, -1])
+def test_edges_of_fp32_products(H, N_q, N_kv, at):
+    Q, K, V = _randn(H, N_q, N_kv)
+    _check(Q, K, V, _unlike("masked_key" if at > 0 else "large_value", 1e9, Q, K, V, at))
