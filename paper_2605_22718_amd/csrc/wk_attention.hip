@@ -2546,6 +2546,8 @@ extern "C" int32_t wk_internal_attention_plan(int32_t H, int32_t N_q, int32_t N_
     return (int32_t)plan.layout * 100 + plan.splits;
 }
 
+extern "C" int32_t wk_internal_in_place_trips(int32_t n_native, int32_t R_max, int32_t max_tok) { return trips_in_place(n_native, R_max, max_tok) ? 1 : 0; }
+
 extern "C" int32_t wk_internal_frame_mask_plan(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T) {
     if (N_q / frame_T + 1 > kMaxSub) return -1;
     const FramePlan p = plan_frames(H, N_q, N_kv, denoise_row0, frame_T);

@@ -1041,6 +1041,9 @@ __global__ __launch_bounds__(THREADS) void k_select_held(const double *__restric
 // (183 MB) 159 and 143 us, 30 of 12 x 2,640 (232 MB) 223 and 198, 2 of 40 x 4,680 (91 MB) 86 and 80, 6 of 12 x 2,640 (46 MB) 48.9 and 49.8, 51 of 3 x 1,200 (45 MB)
 // 49.0 and 50.0.  fp32 with a list per head: 10 chunks of 12 x 2,640 (155 MB) 123 and 122, 5 (77 MB) 61 and 68; shared lists: 8 of
 // 24 x 3,039 (285 MB) 236 and 202, 3 of 12 x 2,640 (46 MB) 45 and 48.
+// Near the line it depends on where the inputs are.  2 of 40 x 4,680 (96 MB), half of the chunk kept: the same inputs again and again 65 and 71, three sets in turn
+// 73 and 71, not in the caches 93 and 78, just written 66 and 68 (with a window of what was stored assembled behind the call 105 and 111); 16 of 12 x 2,640
+// (130 MB) 87 and 89, 98 and 89, 121 and 99, 89 and 86 (106 and 102).
 constexpr long long kStreamBytes = 64ll << 20, kStreamBytesF32 = 144ll << 20;
 
 // K's and V's workgroups of `tiles` tiles in one launch as long as it has threads for both

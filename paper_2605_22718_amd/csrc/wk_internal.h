@@ -17,10 +17,12 @@
 
 // Not part of the interface: the tests pin with these that a shape takes the path it is there for.  How bf16 attention would
 // be launched (0: 256 queries per workgroup, 1: 128 in pairs of tiles, 2: 128), under a frame mask (+ 100: as two key ranges, else as windows
-// with a gap; -1: more frames than the table of launches holds); head ranges of the similarity GEMM; threads that assemble a window of which
+// with a gap; -1: more frames than the table of launches holds); whether attention in place takes the hand-scheduled loop inside segments;
+// head ranges of the similarity GEMM; threads that assemble a window of which
 // `rows` a head are copied; launches of the compaction that writes `rows` a head.
 extern "C" int32_t wk_internal_attention_plan(int32_t H, int32_t N_q, int32_t N_kv, size_t workspace_bytes);   // layout * 100 + key ranges
 extern "C" int32_t wk_internal_frame_mask_plan(int32_t H, int32_t N_q, int32_t N_kv, int32_t denoise_row0, int32_t frame_T);
+extern "C" int32_t wk_internal_in_place_trips(int32_t n_native, int32_t R_max, int32_t max_tok);
 extern "C" int32_t wk_internal_gemm_head_ranges(const wk_compress_desc *desc);
 extern "C" int32_t wk_internal_compact_launches(int64_t rows);
 extern "C" int64_t wk_internal_gather_threads(int32_t H, int64_t rows, int32_t dtype, int32_t max_workgroups);

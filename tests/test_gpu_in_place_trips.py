@@ -6,17 +6,20 @@ import torch
 
 import oracle
 import paper_2605_22718_amd as wk
-from wkt import assert_attention_close_bf16, dev
+from wkt import K128_PAIR, K256, assert_attention_close_bf16, attention_plan, dev
 
 pytestmark = pytest.mark.gpu
 
 
-# H = 130: workgroups of 256 queries, H = 2: of 128, tiles in pairs
-@pytest.mark.parametrize("H", [2, 130])
-@pytest.mark.parametrize("n_native,lens", [(64 * 30, []), (64 * 29 + 1, [64]), (64 * 40, [63, 130]), (0, [64 * 24, 64 * 23 + 63, 64 * 25 + 1]), (64 * 9, [64 * 26]),
+# workgroups of 256 queries, and of 128 with tiles in pairs, in less than a round and in more; 9 tiles of native rows beside 26 of a chunk are
+# just short of the share that takes the loop, 10 have it
+@pytest.mark.parametrize("H,layout", [(2, K128_PAIR), (100, K256), (130, K128_PAIR)])
+@pytest.mark.parametrize("n_native,lens", [(64 * 30, []), (64 * 29 + 1, [64]), (64 * 40, [63, 130]), (0, [64 * 24, 64 * 23 + 63, 64 * 25 + 1]), (64 * 9, [64 * 26]), (64 * 10, [64 * 26]),
                                            (64 * 21 - 1, [64 * 22, 1, 64 * 21, 700]), (100, [64 * 27 - 1, 64 * 13, 64 * 12, 64 * 11 + 5])])
-def test_against_oracle(H, n_native, lens):
+def test_against_oracle(H, layout, n_native, lens):
     N_q, d = 270, dev()
+    assert attention_plan(H, N_q, n_native + len(lens) * max(lens, default=0))[0] == layout
+    assert wk.lib().wk_internal_in_place_trips(n_native, len(lens), max(lens, default=1)) == (n_native != 64 * 9)
     g = torch.Generator().manual_seed(n_native + len(lens))
     rn = lambda n: torch.randn(H, n, 128, generator=g).to(torch.bfloat16)
     Q, Kn, Vn = rn(N_q), rn(n_native), rn(n_native)
