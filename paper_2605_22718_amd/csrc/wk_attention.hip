@@ -178,15 +178,18 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 // inputs results are 2.0e-7 to 5.3e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.  (A logit that is one product alone, where
 // roundings do not average, may be off by 2^-21 of itself; 2^-24 with fp32 instructions.)
 // fp16's range is met by powers of two: one per query, one for the keys and one per feature of the values, from the first tile's
-// largest numbers, which leaves a factor of 32 for those that follow.  Where scaled numbers are below 1/4 the second part's step, 2^-24, is what
-// is left, so a workgroup keeps its result only if that is small beside it, all with the numbers that it has met (kLogitLoss and on):
-//   logits      2^-25 * (sum of the query's sizes in key steps + 128 * the largest key in query steps) within 2^-20, which is fp32's rounding of a logit of 8
-//   by query    the largest |O| of the features within 2^-20 of half a step of every value, and at least 2^-12 (many keys: 2^-19 a key) of the largest
-//               value: weights, which are below 2^-36 of the largest in their last step, then lose no more than fp32 sums do
-//   by feature  the same over four queries, at 2^-18 and 2^-14, for features that have four adjacent keys whose values are 2^-11 of the first tile's (not all 0)
-// Otherwise, and with numbers beyond the factor of 32 or infinities, it does its work once more, with v_mfma_f32_32x32x2_f32 on the
-// numbers themselves (before its first step, if its first tile is enough to know).  tests/test_attention_f32_parts_bounds.py has this arithmetic for the CPU.  (Without the conditions one key at -1e9, a stand-in for
-// -inf, in a window's first tile took the others' logits with it: O was off by 9e-3, at -1e12 by 0.8.)
+// largest numbers, which leaves a factor of 32 for those that follow.  Scaled numbers below 1/4 are off by half of the second part's step, 2^-25,
+// whatever their size, so a workgroup keeps its result only if that is small beside it:
+//   logits      what takes them from their sums to log2 units is within 2^-15.  Half a step of each of 128 numbers of a key, times a query's (below 2^15), then
+//               makes 2^-18 of a logit at most and about a twentieth of that as such errors fall; half steps of a query's as much, twice with the largest keys.
+//   by query    the largest |O| of the features is 2^20 times half a step of every value, and at least 2^-12 (beyond 128 keys: 2^-19 a key) of the largest
+//               value: weights, whose half steps are 2^-36 of the largest one, then lose no more than fp32 sums do.
+//   by feature  the same over four queries, with 2^18 and 2^-14, for features that have four adjacent keys whose values are below 2^-11 of the
+//               first tile's (fewer, at the end: 2^-20) and not all 0.
+// Otherwise, and with numbers beyond the factor of 32 or infinities, it does its work once more with v_mfma_f32_32x32x2_f32 on the
+// numbers themselves, before any step if the first tile is enough to know.  tests/test_attention_f32_parts_bounds.py has this arithmetic for the CPU: what is kept is
+// as good as plain fp32.  (Without the conditions one key at -1e9, a stand-in for -inf, in a window's first tile took the others' logits with it: O was
+// off by 9e-3, at -1e12 by 0.8.)
 //
 // Four waves of 32 queries per workgroup, 32-key tiles, KG tiles at a time by as many groups of waves; KG == 1 leaves room for two
 // workgroups on a compute unit, whose phases then overlap by themselves.  KG == 2: the groups' (O, max, sum) meet in
@@ -197,8 +200,8 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 // Even features of V come first: a thread holds two adjacent ones and stores them apart.
 //
 // Bound by the matrix and the vector pipe together: a tile is 48 products (1,536 cycles) and about 300 vector instructions a wave, of which
-// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 36.4 us (with its merge), 8 x 1,560 x 4,680 293 -> 126, 40 x 1,560 x 4,680 1,411 -> 555 (269 TFLOP/s), 1 x 128 x
-// 30,000 248 -> 97, 6 x 250 x 100 25.0 -> 16.1.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
+// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 34.8 us (with its merge), 8 x 1,560 x 4,680 293 -> 120, 40 x 1,560 x 4,680 1,411 -> 540 (277 TFLOP/s), 1 x 128 x
+// 30,000 248 -> 93, 6 x 250 x 100 25.0 -> 14.5.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
 // instead of beside the products: the same, as long as the compiler waited for the loads to LDS in front of every read of LDS, see load_to_lds.)
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 4;                           // across the queries
@@ -212,6 +215,7 @@ constexpr int kF32Shared = 3 * 512 + 16;               // for all groups: see `s
 constexpr int kF32Lds = kF32Group + kF32Shared;
 constexpr int kF32LdsPair = 2 * kF32Group + kF32Shared;
 constexpr float kF32P = 0x1p11f;                       // what weights are scaled by
+constexpr float kF32Zeros = 0x1p5f;                    // what keys and values are scaled by behind a first tile of zeros
 
 #define WK_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 // typed LDS pointer from a 32-bit LDS byte address
@@ -233,6 +237,12 @@ __device__ inline float max_across_halves(float x) {
 __device__ inline float quad_max(float x) {
     x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, false)));   // quad_perm [1, 0, 3, 2], [2, 3, 0, 1]
     return fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4e, 0xf, 0xf, false)));
+}
+
+__device__ inline float sum_across_halves(float x) {
+    const unsigned u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // max over a row of 16 lanes
@@ -259,10 +269,10 @@ __device__ inline Parts2 split2(float x, float y, float up) {
     return Parts2{{__builtin_bit_cast(unsigned, first), __builtin_bit_cast(unsigned, second)}};
 }
 
-// The power of two that takes numbers up to `largest` below 2^(top + 1), 1 if all are 0; bad: there is none within 2^-60 .. 2^60 (infinities among others)
-__device__ inline float scale_to(float largest, int top, bool &bad) {
+// The power of two that takes numbers up to `largest` below 2^(top + 1), of_zeros if all are 0; bad: there is none within 2^-60 .. 2^60 (infinities among others)
+__device__ inline float scale_to(float largest, int top, float of_zeros, bool &bad) {
     const int e = (int)(__float_as_uint(largest) >> 23) & 0xff;
-    if (largest == 0.f) return 1.f;
+    if (largest == 0.f) return of_zeros;
     bad |= e < 127 + top - 60 || e > 127 + top + 60 || e > 127 + 50;
     return __uint_as_float((unsigned)min(max(254 + top - e, 1), 254) << 23);
 }
@@ -342,10 +352,10 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     char *const group = smem + kg * kF32Group;
     const unsigned lds0 = (unsigned)(size_t)WK_LDS(group);
     // shared: the first tiles' largest value of every feature, what takes its sums back, the largest of all its values as they are split; the first tiles' largest
-    // key, the largest of all as they are split, whether the parts do not hold what they have to (sizes as int: their bits order as they do)
+    // key, whether the parts do not hold what they have to, whether a feature's values are of unlike size (sizes as int: their bits order as they do)
     int *const v_max = reinterpret_cast<int *>(smem + KG * kF32Group);
     float *const v_down = reinterpret_cast<float *>(v_max + WK_D);
-    int *const v_seen = v_max + 2 * WK_D, *const k_max = v_max + 3 * WK_D, *const k_seen = k_max + 1, *const out_of_range = k_max + 2, *const mixed = k_max + 3;
+    int *const v_seen = v_max + 2 * WK_D, *const k_max = v_max + 3 * WK_D, *const out_of_range = k_max + 1, *const mixed = k_max + 2;
     // Loads: wave qw fills two rows per load, of K rows 8*qw .. 8*qw+7, 16-byte chunk c of row k at slot c ^ (k & 15); of V the eight
     // rows 16*(qw/2) + 4*(qw%2) + {0..3, 8..11}, which a lane group multiplies at once, for the wave itself.
     // Rows past the range clamp to its last one (those keys are masked, their values cleared).
@@ -395,7 +405,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     // B operand of S^T = K Q^T: k slot 8*g + e of step s means feature 16*s + 8*g + e
     f16x8 qr[8][2];
     bool bad_keys = false;   // or queries
-    float q_sum = 0.f;       // of the sizes of this lane's query's numbers, as they are split
     float to_log2 = a.scale_log2;   // of this lane's query: what takes scores as they are summed to log2 units
     if (!idle) {
         float4 x[16];
@@ -415,13 +424,9 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         read_q(1);
         float largest = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < 16; ++i)
             largest = fmaxf(fmaxf(fmaxf(largest, fabsf(x[i].x)), fabsf(x[i].y)), fmaxf(fabsf(x[i].z), fabsf(x[i].w)));
-            q_sum += (fabsf(x[i].x) + fabsf(x[i].y)) + (fabsf(x[i].z) + fabsf(x[i].w));
-        }
-        largest = max_across_halves(largest);
-        const float up = largest == 0.f ? 0x1p40f : scale_to(largest, 14, bad_keys);   // (zeros have all the range)
-        q_sum = (q_sum + __shfl_xor(q_sum, 32)) * up;
+        const float up = scale_to(max_across_halves(largest), 14, 0x1p40f, bad_keys);   // (zeros have all the range)
         to_log2 *= inverse(up);
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
@@ -514,8 +519,9 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (kt + v_key + 8 * half + u >= kt1) quarter[u] = 0.f;
-            const float top = quarter_top();
+            float top = quarter_top();
             v_largest[f] = fmaxf(v_largest[f], top);
+            if (kt + v_key + 8 * half + 4 > kt1) top *= 0x1p9f;   // (less than four keys: now and then all small in some feature)
             v_least[f] = min(v_least[f], __float_as_uint(top) - 1);
             store_quarter(group + kF32V + qw * 2048 + f * 1024 + (me & 63) * 16 + half * 8, v_up[f]);
         }
@@ -525,7 +531,6 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         asm("" : "+v"(me));   // (its addresses are not kept either)
     };
     constexpr float kLimit = 65504.f;   // fp16's largest number
-    constexpr float kLogitLoss = 0x1p-20f;   // of a logit in log2 units
 
     // the scales, from the first tiles
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of the first tile has landed
@@ -550,18 +555,18 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     }
     __syncthreads();
     bool bad_values = false;
-    k_up = scale_to(__int_as_float(*k_max), 10, bad_keys);
+    k_up = scale_to(__int_as_float(*k_max), 10, kF32Zeros, bad_keys);
     to_log2 *= inverse(k_up);
     if (WITH_O)
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
-            v_up[f] = scale_to(__int_as_float(v_max[2 * lane + f]), 10, bad_values);
+            v_up[f] = scale_to(__int_as_float(v_max[2 * lane + f]), 10, kF32Zeros, bad_values);
             if (wave == 0) v_down[2 * lane + f] = inverse(kF32P * v_up[f]);
         }
     if (any)
 #pragma unroll
         for (int t = 0; t < 8; ++t) k_work(t);
-    if (bad_keys || bad_values || to_log2 * q_sum * 0x1p-25f > kLogitLoss) *out_of_range = 1;
+    if (bad_keys || bad_values || (!idle && to_log2 > 0x1p-15f)) *out_of_range = 1;
 
     // The steps.  Beside the products of S^T a wave splits its share of the tile's values, beside those of O^T its share of the next tile's
     // keys (without a next tile: of the last one's again, which nothing reads)
@@ -573,7 +578,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         __builtin_amdgcn_s_waitcnt(WITH_O ? 0x0F74 : 0x0F70);   // this wave's keys of the next tile have landed; its values, four loads, are behind them
         __syncthreads();
     };
-    __syncthreads();
+    meet_keys();
     const bool steps = __builtin_amdgcn_readfirstlane(*out_of_range) == 0;   // (not behind a first tile that leads to fp32 products as it is)
     const int n_steps = steps ? ((kt1 - kt0 + kF32Keys - 1) / kF32Keys + KG - 1) / KG : 0;
     const int my_steps = steps ? (kt1 - kt0 - kg * kF32Keys + KG * kF32Keys - 1) / (KG * kF32Keys) : 0;   // with an odd count of tiles the second group has one less
@@ -582,7 +587,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     if (KG == 2 && kg == 0) __builtin_amdgcn_s_setprio(1);   // one of a SIMD's two waves ahead: one does its softmax while the other multiplies
     if (!idle) {
         for (int j = 0; j < my_steps; ++j, kt += kStep) {
-            meet_keys();
+            if (j > 0) meet_keys();
             if (kt + kStep < kt1) issue_k(kt + kStep);
             begin_share();
             f32x16 s, small;   // (apart: eight roundings at the size of a score instead of 24)
@@ -631,7 +636,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         }
     } else {
         for (int j = 0; j < my_steps; ++j, kt += kStep) {
-            meet_keys();
+            if (j > 0) meet_keys();
             if (kt + kStep < kt1) issue_k(kt + kStep);
             begin_share();
             if (WITH_O)
@@ -647,13 +652,11 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
     }
     if (my_steps < n_steps) {   // the other group's last tile
         begin_share();
-        meet_keys();
+        if (my_steps > 0) meet_keys();
         meet_values();
     }
     // What was met, and whether the parts lose too much by it, see above.
-    k_largest = row_max(k_largest) * k_up;
-    if ((lane & 15) == 0) atomicMax(k_seen, __float_as_int(k_largest));
-    bool lost = k_largest >= kLimit;
+    bool lost = k_largest * k_up >= kLimit;
     if (WITH_O)
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
@@ -662,10 +665,10 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
             lost |= v_largest[f] >= kLimit;
             if (v_least[f] != ~0u && __uint_as_float(v_least[f] + 1) * v_up[f] < 0.5f) v_max[2 * lane + f] = *mixed = -1;   // (no longer needed as it was)
         }
+    if (!WITH_O && lost) *out_of_range = 1;
     __syncthreads();   // every wave is done with its last tile, and its share of the LDS free
-    lost |= !idle && to_log2 * __int_as_float(*k_seen) * 0x1p-18f > kLogitLoss;
     if (WITH_O && my_steps > 0 && !idle) {
-        const float l_tot = l_run + __shfl_xor(l_run, 32);
+        const float l_tot = sum_across_halves(l_run);
         float of_values = 0.f, of_weights = 0.f;   // the features' largest, of a lane's two at first
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
@@ -678,36 +681,47 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
         of_weights = max_across_halves(fmaxf(of_weights, __shfl_xor(of_weights, 16)));
         of_values = max_across_halves(fmaxf(of_values, __shfl_xor(of_values, 16)));
         const float least = fmaxf(of_weights * kF32P * fmaxf(0x1p-12f, (float)(my_steps * kF32Keys) * 0x1p-19f), of_values * 64.f * l_tot);
-        const bool by_feature = __builtin_amdgcn_readfirstlane(*mixed) != 0;
+        // by 16-byte chunks of features, as they are stored below: read(chunk), then use(its feature i, that one's register: block and number)
+        auto each = [&](auto read, auto use) __attribute__((always_inline)) {
+#pragma unroll
+            for (int n = 0; n < 16; ++n) {
+                const int b = n >> 3, t = (n >> 1) & 3, u = 2 * (n & 1), chunk = 16 * b + 4 * t + 2 * g + u / 2;
+                read(chunk);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) use(i, b + 2 * (i & 1), 4 * t + u + (i >> 1));
+            }
+        };
+        if (__builtin_amdgcn_readfirstlane(*mixed) != 0) {
+            int4 of_unlike_size;
+            float4 seen;
+            each([&](int chunk) __attribute__((always_inline)) {
+                of_unlike_size = *reinterpret_cast<const int4 *>(v_max + 4 * chunk);
+                seen = *reinterpret_cast<const float4 *>(v_seen + 4 * chunk);
+            }, [&](int i, int b, int r) __attribute__((always_inline)) {
+                const float at_least = fmaxf((&seen.x)[i] * (kF32P * 0x1p-14f), 16.f * l_tot);
+                lost |= quad_max(fabsf(o[b][r])) < ((&of_unlike_size.x)[i] < 0 ? at_least : 0.f);
+            });
+        }
+        float4 down;
         float row = 0.f;
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int u = 0; u < 4; u += 2) {   // the registers of a 16-byte chunk's features, as they are stored below
-                    const int chunk = 16 * b + 4 * t + 2 * g + u / 2;
-                    const float4 down = *reinterpret_cast<const float4 *>(v_down + 4 * chunk);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int blk = b + 2 * (i & 1), r = 4 * t + u + (i >> 1);
-                        if (by_feature && v_max[4 * chunk + i] < 0)
-                            lost |= quad_max(fabsf(o[blk][r])) < fmaxf(__int_as_float(v_seen[4 * chunk + i]) * (kF32P * 0x1p-14f), 16.f * l_tot);
-                        o[blk][r] *= (&down.x)[i];
-                        row = fmaxf(row, fabsf(o[blk][r]));
-                    }
-                }
+        each([&](int chunk) __attribute__((always_inline)) { down = *reinterpret_cast<const float4 *>(v_down + 4 * chunk); },
+             [&](int i, int b, int r) __attribute__((always_inline)) {
+                 o[b][r] *= (&down.x)[i];
+                 row = fmaxf(row, fabsf(o[b][r]));
+             });
         lost |= max_across_halves(row) < least;
     }
-    if (lost) *out_of_range = 1;
-    __syncthreads();
+    if constexpr (WITH_O) {
+        if (lost) *out_of_range = 1;
+        __syncthreads();
+    }
     // (looked at here only: behind every barrier, and with the values requested behind the second one, 4 heads x 880 queries x 2,640 keys in one
     // range took 129 us, now 125)
     const bool exact = __builtin_amdgcn_readfirstlane(*out_of_range) != 0;
     // Once more from the first tile on, with fp32 operands: tiles as they come, in the raw tiles' place and in the parts' in turn.  Bound by the products, 128 of 64 cycles a tile.  With
-    // a key at -inf in the first tile, which is known before any step, 4 heads x 880 queries x 2,640 keys take 72 us, 8 x 1,560 x 4,680 221, 1 x 128 x 30,000 254 (operands
+    // a key at -inf in the first tile, which is known before any step, 4 heads x 880 queries x 2,640 keys take 72 us, 8 x 1,560 x 4,680 216, 1 x 128 x 30,000 254 (operands
     // straight from memory and behind all the steps: 96, 388, 380; the kernel of fp32 products alone, for any keys, 64, 295, 252); found out at the end
-    // only, by the values' spread, 95, 425 and 340.
+    // only, by the values' spread, 93, 418 and 338.
     if (exact) {
 #pragma unroll
         for (int b = 0; b < 4; ++b)

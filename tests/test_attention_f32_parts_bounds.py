@@ -8,7 +8,7 @@ SCALE_LOG2 = np.log2(np.e) / np.sqrt(128)
 P = 2.0 ** 11   # what weights are scaled by
 
 
-def _power(largest, top, of_zero=1.0):
+def _power(largest, top, of_zero=32.0):
     """The power of two that takes `largest` to [2^top, 2^(top + 1))."""
     e = np.frexp(np.where(largest == 0, 1, largest))[1] - 1
     return np.where(largest == 0, of_zero, np.exp2(top - e))
@@ -40,14 +40,15 @@ def parts_attention(Q, K, V):
         lse = m + np.log2(l)
     k_seen, v_seen = np.abs(K * k_up).max(), np.abs(V * v_up).max(0)
     kept = k_seen < 65504 and v_seen.max() < 65504
-    # logits: a part's smallest step is 2^-24, half of it per number, whatever the other operand's numbers add up to
-    kept &= (to_log2 * (np.abs(Q * q_up).sum(1, keepdims=True) * 2.0 ** -25 + k_seen * 2.0 ** -18) <= 2.0 ** -20).all()
+    # logits: half a step, 2^-25, of each of 128 numbers of a key times the query's, which are below 2^15, and the other way round, below 2^16
+    kept &= (to_log2 <= 2.0 ** -15).all()
     # values and weights: every query over the features,
     N, down = len(K), np.where(v_seen == 0, 0, 1 / (P * v_up))
     least = np.maximum((v_seen * down).max() * P * max(2.0 ** -12, N * 2.0 ** -19), (64 * l * down).max(1))
     kept &= (np.abs(o * down).max(1) >= least).all()
-    # and over four queries every feature that has four adjacent keys with values of less than 2^-11 of the first tile's, not all 0
+    # and over four queries every feature that has four adjacent keys with values of less than 2^-11 of the first tile's (fewer: 2^-20), not all 0
     quads = np.abs(np.pad(V * v_up, ((0, -N % 4), (0, 0)))).reshape(-1, 4, 128).max(1)
+    quads[N // 4:] *= 2.0 ** 9
     mixed = ((quads > 0) & (quads < 0.5)).any(0)
     kept &= (np.abs(o).reshape(-1, 4, 128).max(1) >= np.maximum(v_seen * P * 2.0 ** -14, 16 * l).reshape(-1, 4, 128).max(1))[:, mixed].all()
     return o / (P * v_up) / l, lse, kept
