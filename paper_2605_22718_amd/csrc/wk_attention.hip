@@ -175,7 +175,7 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 //
 // x = x1 + x2 with x1 = fp16(x), x2 = fp16(x - x1) is off by at most 2^-23 of x, and a product of two such sums is taken without x2*y2, which is
 // at most 2^-22 of it: three matrix instructions of 32 cycles do what eight fp32 ones of 64 do, and their sums are rounded less often.  On N(0, 1)
-// inputs results are 2.0e-7 to 5.3e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.  (A logit that is one product alone, where
+// inputs results are 2.0e-7 to 3.6e-7 from fp64 (2-norm), with fp32 instructions they were 3.8e-7 to 7.1e-7.  (A logit that is one product alone, where
 // roundings do not average, may be off by 2^-21 of itself; 2^-24 with fp32 instructions.)
 // fp16's range is met by powers of two: one per query, one for the keys and one per feature of the values, from the first tile's
 // largest numbers, which leaves a factor of 32 for those that follow.  Scaled numbers below 1/4 are off by half of the second part's step, 2^-25,
@@ -200,8 +200,8 @@ __device__ inline bool select_work(AttnArgs &a, const SubTable &t, size_t row_by
 // Even features of V come first: a thread holds two adjacent ones and stores them apart.
 //
 // Bound by the matrix and the vector pipe together: a tile is 48 products (1,536 cycles) and about 300 vector instructions a wave, of which
-// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 34.8 us (with its merge), 8 x 1,560 x 4,680 293 -> 120, 40 x 1,560 x 4,680 1,411 -> 540 (277 TFLOP/s), 1 x 128 x
-// 30,000 248 -> 93, 6 x 250 x 100 25.0 -> 14.5.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
+// a third hides.  4 heads x 880 queries x 2,640 keys 64.5 -> 35.4 us (with its merge), 8 x 1,560 x 4,680 293 -> 126, 40 x 1,560 x 4,680 1,411 -> 565 (265 TFLOP/s), 1 x 128 x
+// 30,000 248 -> 98, 6 x 250 x 100 25.0 -> 14.9.  (Three bf16 parts and six products: 50, 202, 897 us; its splitting in a phase of its own
 // instead of beside the products: the same, as long as the compiler waited for the loads to LDS in front of every read of LDS, see load_to_lds.)
 // ------------------------------------------------------------------------------------------
 constexpr int kF32Waves = 4;                           // across the queries
@@ -623,11 +623,16 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
                 PartStream v([&](int p, int i) __attribute__((always_inline)) {   // i = 2*b + t
                     return *WK_LDS_AT(const f16x8, v_at + p * kF32Part + (i & 1) * 4096 + (i >> 1) * 512);
                 });
-                // (Sums of a tile by themselves, added to O once, would be off by 2.0e-7 to 3.6e-7 only, for 4 % of the time.)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    v.template multiply<8>(2 * b, pr[0], o[b], o[b], [&]() __attribute__((always_inline)) { k_work(2 * b); });
-                    v.template multiply<8>(2 * b + 1, pr[1], o[b], o[b], [&]() __attribute__((always_inline)) { k_work(2 * b + 1); });
+                for (int b = 0; b < 4; ++b) {   // sums of the tile's products by themselves: one rounding at the size of O per tile, not six, for 4 % of the time
+                    f32x16 sum;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+                    v.template multiply<8>(2 * b, pr[0], sum, sum, [&]() __attribute__((always_inline)) { k_work(2 * b); });
+                    v.template multiply<8>(2 * b + 1, pr[1], sum, sum, [&]() __attribute__((always_inline)) { k_work(2 * b + 1); });
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[b][r] += sum[r];
+                    asm volatile("" : "+v"(o[b]));   // (here: put off, four sums would be held)
                 }
             } else {
 #pragma unroll

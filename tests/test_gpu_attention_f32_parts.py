@@ -161,3 +161,16 @@ def test_numbers_that_others_are_small_beside_in_stored_chunks(case, x):
 def test_edges_of_fp32_products(H, N_q, N_kv, at):
     Q, K, V = _randn(H, N_q, N_kv)
     _check(Q, K, V, _unlike("masked_key" if at > 0 else "large_value", 1e9, Q, K, V, at))
+
+
+# Roundings at the size of O where nothing cancels: one a tile, of which the 75 of a wave group add up to 2^-24 sqrt(75 / 3) * 0.42 (the rms of a rounding
+# over that of a number) = 1.3e-7, less what the two groups average; parts and weights make less than 1e-7 of it.  (One a product: 2.4 times as much.)
+@pytest.mark.parametrize("H,N_q,N_kv", [(2, 64, 4800)])
+def test_sums_of_many_tiles(H, N_q, N_kv):
+    d = dev()
+    Q, K, V = _randn(H, N_q, N_kv)
+    Q, V = Q * 0.01, V.abs()
+    O = torch.empty_like(Q, device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O)
+    ref = oracle.attention(Q, K, V)
+    assert np.linalg.norm(O.cpu().double().numpy() - ref) <= 1.6e-7 * np.linalg.norm(ref)
