@@ -734,7 +734,7 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
             for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
         m_run = -FLT_MAX;
         l_run = 0.f;
-        to_log2 = a.scale_log2;
+        to_log2 = 1.f;   // (rounded before the maximum is taken: a fused product would differ from it by 2^-24 of itself, beyond 2^31 by more than exp2 can hold)
         float4 y[16];
         if (!idle) {
             const float *Qrow = query_row();
@@ -790,6 +790,8 @@ __global__ __launch_bounds__(KG * kF32Waves * 64, 2) void k_attn_f32(AttnArgs a,
                 s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[t % 3][3], y[t].w, s, 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] *= a.scale_log2;
             softmax(s, kt);
             if (!WITH_O) continue;
 #pragma unroll

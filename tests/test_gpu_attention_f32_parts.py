@@ -174,3 +174,21 @@ def test_sums_of_many_tiles(H, N_q, N_kv):
     wk.wk_attention(Q.to(d), K.to(d), V.to(d), O)
     ref = oracle.attention(Q, K, V)
     assert np.linalg.norm(O.cpu().double().numpy() - ref) <= 1.6e-7 * np.linalg.norm(ref)
+
+
+# every key at -x, whose logit has no room for anything else: even weights, whatever the size
+@pytest.mark.parametrize("H,N_q,N_kv,split", [(2, 5, 1, False), (2, 64, 40, False), (300, 3, 70, False), (2, 100, 300, True)])
+@pytest.mark.parametrize("x", [1e3, 1e6, 1e9, 1e10, 1e11, 1e13, 1e15])
+def test_windows_far_below_0(H, N_q, N_kv, split, x):
+    d = dev()
+    Q, K, V = _randn(H, N_q, N_kv)
+    Q[..., 0] = 1
+    K[:] = 0
+    K[..., 0] = -x
+    n = wk.wk_attention_workspace_bytes(H, N_q, N_kv, wk.WK_F32) if split else 0
+    assert (n > 0) == split
+    O, lse = torch.empty_like(Q, device=d), torch.empty((H, N_q), device=d)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse, workspace=torch.empty(n, dtype=torch.uint8, device=d) if split else None)
+    ref, ref_lse = oracle.attention(Q, K, V, want_lse=True)
+    assert np.abs(O.cpu().double().numpy() - ref).max() <= ATT_MAX_ABS_F32
+    assert np.abs(lse.cpu().double().numpy() / ref_lse - 1).max() <= 5e-7   # (parts 2^-21, a few roundings)
