@@ -11,7 +11,7 @@ its LDS read addresses) -- the same ring protocol, the same arithmetic in the sa
 and without a running maximum:
 
   * probabilities are relative to a reference, the first tile's maximum, that moves only when a lane's row sum has reached 2^24 at the
-    beginning of a trip: up by the power of two that brings the sum below 1.  Their size does not matter to bf16 or to the fp32 sums, so results
+    beginning of a trip: up by the power of two that brings the sum below 1, but by 2^63 at most.  Their size does not matter to bf16 or to the fp32 sums, so results
     are those of a running maximum up to rounding, and bit-identical where that does not move either.  Looking for the tiles' maxima was 23 of a
     step's 113 vector instructions.  What grows beyond fp32 within a trip leaves infinities or NaN in the sums, which the kernel looks for at the
     end (and then does its work once more in the compiled steps, with the running maximum);
@@ -214,9 +214,11 @@ def step(E, pos, kg, kreads=None, gap=False):
         E.emit(f"v_cmp_ngt_f32_e32 vcc, {GROWN}, v{T0}")   # (true of NaN)
         E.emit("s_cbranch_vccnz L_grown_%=")
         E.emit("L_weighed_%=:")
-        # (the exponent of an infinity and of NaN reads as 0)
+        # (the exponent of an infinity and of NaN reads as 0.  63 at most: v_exp gives 0 below -126, which would leave out all keys so far, and the reference
+        # plus e, rounded, is up to e further away than e)
         E.behind += ["L_grown_%=:", "s_nop 7", "s_nop 7", f"v_frexp_exp_i32_f32_e32 v{T0}, v{T0}", f"v_mov_b32_e32 v{T1}, v{T0}", "s_nop 1",
-                     f"v_permlane32_swap_b32_e32 v{T0}, v{T1}", "s_nop 0", f"v_max3_i32 v{T0}, v{T0}, v{T1}, 0", f"v_cvt_f32_i32_e32 v{T0}, v{T0}",
+                     f"v_permlane32_swap_b32_e32 v{T0}, v{T1}", "s_nop 0", f"v_max3_i32 v{T0}, v{T0}, v{T1}, 0", f"v_min_i32_e32 v{T0}, 63, v{T0}",
+                     f"v_cvt_f32_i32_e32 v{T0}, v{T0}",
                      f"v_add_f32_e32 v{T0}, v{M}, v{T0}", f"v_sub_f32_e32 v{T1}, v{M}, v{T0}", f"v_exp_f32_e32 v{T1}, v{T1}", f"v_mov_b32_e32 v{M}, v{T0}",
                      "s_nop 1"]
         E.behind += [f"v_mul_f32_e32 v{L[t]}, v{L[t]}, v{T1}" for t in range(2)]

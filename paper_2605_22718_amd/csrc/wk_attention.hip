@@ -1354,7 +1354,7 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
     // Whole trips round the ring in a hand-scheduled loop (written by gen_attn_loop.py, which documents its schedule and register map), whose
     // look-ahead loads must all lie in full tiles of one array: K tiles from k_base + koff on, V tiles from v_base + voff on.  It is
     // the four (KG == 2: two) `step`s below in what it computes -- same ring protocol, same arithmetic in the same order -- except
-    // that the maximum does not run: the reference goes up by a power of two when a row sum has reached 2^24.  Its operands
+    // that the maximum does not run: the reference goes up by a power of two, 2^63 at most, when a row sum has reached 2^24.  Its operands
     // are pinned to the registers its text names.  Without the maximum, and with its vector work dealt over 22 of a step's 32 products, 40 heads x
     // 4,680 queries x 28,080 keys 2,256 -> 2,155 us, 12 x 2,640 x 10,560 156.8 -> 151.9, 12 x 2,640 x 211,200 3,044 -> 2,933.
     auto trips = [&](int G, const char *k_base, const char *v_base, unsigned koff, unsigned voff) __attribute__((always_inline)) {
@@ -1407,11 +1407,12 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
             o[0] = o0; o[1] = o1; o[2] = o2; o[3] = o3; s_a[0] = sa0; s_a[1] = sa1;
             mt = tile_max(s_a);
             tripped = true;
-            // row sums that have grown are brought below 1 here too, so that the reference is near the maximum where it is compared with others
+            // row sums that have grown are brought below 1 here too (from 2^63 at most, as in the loop: exp2 gives 0 below -126), so that the reference is near the
+            // maximum where it is compared with others
             if (__any(l_run[0] + l_run[1] >= 0x1p24f)) {
                 const auto e = __builtin_amdgcn_permlane32_swap(__builtin_amdgcn_frexp_expf(l_run[0] + l_run[1]),
                                                                 __builtin_amdgcn_frexp_expf(l_run[0] + l_run[1]), false, false);
-                const float m_new = m_run + (float)max(max((int)e[0], (int)e[1]), 0), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                const float m_new = m_run + (float)min(max(max((int)e[0], (int)e[1]), 0), 63), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
                 m_run = m_new;
                 l_run[0] *= alpha;
                 l_run[1] *= alpha;

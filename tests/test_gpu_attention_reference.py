@@ -89,3 +89,65 @@ def test_in_place(H, layout, kind):
                              torch.zeros(1, dtype=torch.int32, device=d), None, 1, O, lse)
     rows = np.array([0, 31, 128, 255, 256, 269], np.int32)
     _check(O, lse, rows, lambda v: oracle.attention(Q, K, v, rows=rows, want_lse=True), V)
+
+
+# A run of 64 keys whose row sums lie at the end of fp32's range without leaving it: from 2^125 to 2^127 over the first tile's maximum (and at
+# 2^65 and beyond the range), with nothing behind it but keys of no weight, or keys that have weight once the run is gone.
+LEVELS = [60.0, 120.5, 121.0, 121.5, 122.0, 122.5, 124.5]
+
+
+def _run_inputs(level, behind, H, N_q, N_kv, at):
+    g = torch.Generator().manual_seed(N_q + N_kv)
+    Q, K, V = (torch.randn(H, n, 128, generator=g) for n in (N_q, N_kv, N_kv))
+    K *= 0.1   # (a run's sums are 2^5 of its level, row for row)
+    Q[..., 0] = 8
+    K[..., 0] = 0
+    K[:, at + 64:, 0] = 100.0 if behind else 0.0
+    K[:, at:at + 64, 0] = level
+    K[..., 0] /= 8 * 128 ** -0.5 * np.log2(np.e)
+    return [x.to(torch.bfloat16) for x in (Q, K, V * 2.0 ** -10)]   # (outputs stay within fp32 while they are summed)
+
+
+@pytest.mark.parametrize("behind", [False, True])
+@pytest.mark.parametrize("level", LEVELS)
+@pytest.mark.parametrize("H,N_q,N_kv,plan", [(2, 129, 2111, (K128_PAIR, 1)), (40, 1100, 900, (K256, 1)), (40, 1100, 2100, (K256, 1)), (40, 512, 5200, (K256, 3)),
+                                             (2, 300, 3000, (K128_PAIR, 8))])
+def test_sums_at_the_end_of_the_range(H, N_q, N_kv, plan, level, behind):
+    d = dev()
+    n = wk.wk_attention_workspace_bytes(H, N_q, N_kv, wk.WK_BF16) if plan[1] > 1 else 0
+    assert attention_plan(H, N_q, N_kv, n) == plan
+    Q, K, V = _run_inputs(level, behind, H, N_q, N_kv, 5 * N_kv // 9 // 64 * 64)
+    O, lse = _out(Q)
+    wk.wk_attention(Q.to(d), K.to(d), V.to(d), O, lse, workspace=torch.empty(n, dtype=torch.uint8, device=d) if n else None)
+    rows = np.unique([r % N_q for r in (0, 31, 64, 127, 128, 200, -1)]).astype(np.int32)
+    _check(O, lse, rows, lambda v: oracle.attention(Q, K, v, rows=rows, want_lse=True), V)
+
+
+@pytest.mark.parametrize("behind", [False, True])
+@pytest.mark.parametrize("level", LEVELS)
+@pytest.mark.parametrize("H,T,F,row0,n_after,plan", [(30, 130, 2, 320, 510, K128_PAIR), (64, 129, 3, 319, 500, K256)])
+def test_sums_at_the_end_of_the_range_frame_mask(H, T, F, row0, n_after, plan, level, behind):
+    N_q, N_kv, d = F * T, row0 + F * T + n_after, dev()
+    assert frame_mask_plan(H, N_q, N_kv, row0, T) == plan
+    Q, K, V = _run_inputs(level, behind, H, N_q, N_kv, row0 + F * T)
+    O, lse = _out(Q)
+    ws = torch.empty(wk.wk_attention_block_causal_workspace_bytes(H, N_q), dtype=torch.uint8, device=d)
+    wk.wk_attention_block_causal(Q.to(d), K.to(d), V.to(d), O, row0, T, ws, lse=lse)
+    rows = np.unique([f * T + r for f in range(F) for r in (0, T // 2, T - 1)]).astype(np.int32)
+    _check(O, lse, rows, lambda v: oracle.attention_block_causal(Q, K, v, row0, T, rows=rows, want_lse=True), V)
+
+
+@pytest.mark.parametrize("behind", [False, True])
+@pytest.mark.parametrize("level", LEVELS)
+@pytest.mark.parametrize("H,layout", [(2, K128_PAIR), (100, K256)])
+@pytest.mark.parametrize("at", [64 * 6, 64 * 19])   # in either segment
+def test_sums_at_the_end_of_the_range_in_place(at, H, layout, level, behind):
+    N_q, n_native, n, d = 270, 64 * 14, 64 * 22 - 1, dev()
+    assert attention_plan(H, N_q, n_native + n)[0] == layout and wk.lib().wk_internal_in_place_trips(n_native, 1, n)
+    Q, K, V = _run_inputs(level, behind, H, N_q, n_native + n, at)
+    store = wk.Store([K[:, n_native:].contiguous().to(d)], [V[:, n_native:].contiguous().to(d)])
+    O, lse = _out(Q)
+    wk.wk_attention_in_place(Q.to(d), K[:, :n_native].contiguous().to(d), V[:, :n_native].contiguous().to(d), n_native, store.desc,
+                             torch.zeros(1, dtype=torch.int32, device=d), None, 1, O, lse)
+    rows = np.array([0, 31, 128, 255, 256, 269], np.int32)
+    _check(O, lse, rows, lambda v: oracle.attention(Q, K, v, rows=rows, want_lse=True), V)
