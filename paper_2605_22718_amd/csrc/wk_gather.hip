@@ -13,7 +13,7 @@
 // one segment -- the usual case -- looks its segment up once: together with units of the right size these bring the kernel from
 // 3.2 TB/s to 5.9 TB/s read + written (8 chunks of 40 heads x 2,340 tokens; the best plain device copy 6.4).  Small gathers are bound by
 // the chain of look-ups before the first copy: units cover the retrieved rows only when the native ones are in place, unit
-// numbers are 32-bit (4 chunks of 12 heads x 1,320 tokens: 20 -> 15 us), segments are in lanes (-> 11.3; 2 of 4 heads x 440, fp32, 5.3 -> 3.8).
+// numbers are 32-bit (4 chunks of 12 heads x 1,320 tokens: 20 -> 15 us), segments are in lanes (11.9 -> 11.3; 2 of 4 heads x 440, fp32, 5.2 -> 3.7, in smaller units 3.4).
 #include <type_traits>
 
 #include "wk_internal.h"
@@ -31,10 +31,12 @@ constexpr int kMaxR = 1024;
 // workgroups keep in flight over the host link.  Heads of less than a unit leave most of 512 threads idle (one row of 2^22 heads 17.6 ms, in
 // 256 threads 9.9).
 constexpr long long kLargeCopy = 128'000'000;
-// Up to this many units of 256 x 6 are copied as 256 x 2: two latencies behind one another instead of six.  2 chunks of 4 heads x 440 rows, fp32 (3.6 MB, 152 units),
-// 3.74 -> 3.24 us, in a step whose store is not in the caches 59.2 -> 57.3; 5 of 2 x 64 3.50 -> 2.70; 4 of 8 x 300 (208 units) 4.17 and 4.09, but from pinned memory 91.0 and
-// 96.0 (one of 12 x 500, 144 units, 59.1 and 61.3, one of 4 x 100 11.3 and 8.0).
-constexpr long long kFewUnits = 160;
+// Copies of few units of 256 x 6 are made as 256 x 4 or 256 x 2: four or two latencies behind one another instead of six.  The bounds lie where pinned memory, which
+// prefers few requests at a time, would lose more than a hundredth or two by it.  256 x 6, x 4 and x 2, from HBM in a graph / past the caches / from pinned memory: 16 units
+// (4 heads x 100 rows) 3.2, 2.9, 2.6 / - / 10.9, 8.8, 7.6 us; 24 (4 x 280) 3.3, 3.0, 2.7 / 5.1, 4.1, 3.1 (4 x 200) / 14.4, 14.2, 14.6; 40 (4 x 440) 3.3, 3.0, 2.7 / 5.2, 4.2, 3.2 / 20.0, 19.9, 20.5;
+// 152 (2 chunks of 4 x 440, fp32) 3.7, 3.4, 3.2 / 5.8, 4.9, 4.1 / 67.7, 68.8, 70.6; 336 (12 x 1,320) 6.8, 5.7, 5.1 / 7.4, 5.5, - / 148.6, 149.9, 178.6; 352 (16 x 1,000) 6.9, 5.8, - / - /
+// 150.2, 151.7, -; but 456 (2 of 12 x 880) 8.0, 6.7, - / 7.9, 6.9, - / 196.8, 202.0, -, 672 (2 of 12 x 1,320) 9.4, 7.8, - / 9.4, 8.3, - / 296.7, 336.6, -.
+constexpr long long kFewUnits = 360, kFewestUnits = 24;
 
 typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
 typedef const __attribute__((address_space(1))) uvec4 *gvec4;     // in global memory, which a pointer put together from its halves does not tell
@@ -219,14 +221,15 @@ __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs
 struct GatherPlan {
     int threads, vecs;
     long long units_per_head, units, grid;
-    bool paced() const { return units >= 256 && units <= 2048; }   // (256 threads with up to 64 registers: eight workgroups a compute unit)
+    bool paced() const { return vecs == 6 && units >= 256 && units <= 2048; }   // (256 threads with up to 64 registers: eight workgroups a compute unit)
 };
 
 GatherPlan plan_gather(long long cap_vec, long long H, int max_workgroups) {   // cap_vec: 16-byte vectors to copy of a head's K, at most
     GatherPlan p{256, 6, 0, 0, 0};
     if (max_workgroups > 0) p.vecs = 8;
     else if (cap_vec >= 512 * 3 && (double)cap_vec * (double)H * 32 > (double)kLargeCopy) p = GatherPlan{512, 3, 0, 0, 0};
-    if (p.vecs == 6 && (cap_vec + 256 * 6 - 1) / (256 * 6) * H * 2 <= kFewUnits) p.vecs = 2;
+    const long long units = (cap_vec + 256 * 6 - 1) / (256 * 6) * H * 2;
+    if (p.vecs == 6 && units <= kFewUnits) p.vecs = units <= kFewestUnits ? 2 : 4;
     const long long unit = p.threads * p.vecs;
     p.units_per_head = cap_vec > 0 ? (cap_vec + unit - 1) / unit : 1;   // nothing to copy: one workgroup still reports the (zero) length
     p.units = p.units_per_head * H * 2;
@@ -281,6 +284,7 @@ wk_status wk::gather_launch(const wk_store_desc *store, const int32_t *ids, cons
         if (max_workgroups > 0) p.units <= 0x7fffffffLL ? launch(k_gather<uint32_t, 256, 8, L, false>) : launch(k_gather<uint64_t, 256, 8, L, false>);
         else if (p.threads == 512) launch(k_gather<uint32_t, 512, 3, L, false>);
         else if (p.vecs == 2) launch(k_gather<uint32_t, 256, 2, L, false>);
+        else if (p.vecs == 4) launch(k_gather<uint32_t, 256, 4, L, false>);
         else if (p.paced()) launch(k_gather<uint32_t, 256, 6, L, true>);
         else launch(k_gather<uint32_t, 256, 6, L, false>);
     };

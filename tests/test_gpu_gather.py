@@ -1,4 +1,6 @@
 """GPU parity of wk_gather_window against the oracle: byte-exact window assembly (Sec. 4.2)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -210,3 +212,27 @@ def test_segments_in_lanes_and_in_lds(R, n_ids, n_native, native, dtype):
     wk.wk_gather_window(store.desc, ids.to(d), torch.tensor([n_ids], dtype=torch.int32, device=d), R, Kn if native else None, Vn if native else None,
                         n_native, Kw, Vw, cap, n_win)
     assert n_win.item() == n and torch.equal(Kw, want[0]) and torch.equal(Vw, want[1])
+
+
+# copies of few work units are made in smaller ones: heads of one unit of 96 rows, either side of the two bounds, and 24 KB in 256 threads behind them
+@pytest.mark.parametrize("H,pieces", [(1, 3), (12, 3), (13, 2), (180, 2), (181, 1)])
+@pytest.mark.parametrize("native", [True, False])
+def test_smaller_units_for_few(H, pieces, native):
+    f = wk.lib().wk_internal_gather_threads
+    f.argtypes, f.restype = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32], ctypes.c_int64
+    assert f(H, 96, wk.WK_BF16, 0) == 2 * H * pieces * 256
+    n_native, lens, d = 7, [44 if native else 48, 37, 5], dev()   # 95 or 96 rows to copy at most: one unit of 24 KB
+    g = torch.Generator().manual_seed(H)
+    ks, vs = ([torch.randn((H, n, 128), generator=g).to(torch.bfloat16).to(d) for n in lens] for _ in range(2))
+    store = wk.Store(ks, vs)
+    Kn, Vn = (torch.randn((H, n_native, 128), generator=g).to(torch.bfloat16).to(d) for _ in range(2))
+    cap = n_native + 2 * store.max_tok
+    Kw, Vw = (torch.full((H, cap, 128), 7.0, dtype=torch.bfloat16, device=d) for _ in range(2))
+    n_win = torch.zeros(1, dtype=torch.int32, device=d)
+    wk.wk_gather_window(store.desc, torch.tensor([1, 0], dtype=torch.int32, device=d), None, 2, Kn if native else None, Vn if native else None,
+                        n_native, Kw, Vw, cap, n_win)
+    n = n_native + lens[1] + lens[0]
+    assert n_win.item() == n
+    for w, nat, chunks in ((Kw, Kn, ks), (Vw, Vn, vs)):
+        assert torch.equal(w[:, :n_native], nat if native else torch.full_like(nat, 7.0))
+        assert torch.equal(w[:, n_native:n], torch.cat([chunks[1], chunks[0]], 1)) and (w[:, n:] == 7.0).all()
