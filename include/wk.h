@@ -408,7 +408,7 @@ wk_status wk_prefetch_after(wk_prefetch *p, void *hip_stream);
 /* wk_gather_window (same arguments, same errors) on the copy stream into the window buffers of
  * `slot`: first waits until the consumers recorded by the last wk_prefetch_release of that slot
  * have finished, afterwards marks the slot ready.  max_workgroups > 0 caps the grid (a host-link
- * bound gather needs only a few workgroups in flight; 0 = one workgroup per 32 KB). */
+ * bound gather needs only a few workgroups in flight; 0 = one workgroup per 24 KB, less for small copies). */
 wk_status wk_prefetch_gather(wk_prefetch *p, int32_t slot, const wk_store_desc *store, const int32_t *ids,
                              const int32_t *n_ids, int32_t R_max, const void *K_native,
                              const void *V_native, int32_t n_native, void *K_win, void *V_win,

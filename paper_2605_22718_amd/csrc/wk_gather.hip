@@ -27,8 +27,9 @@ constexpr int kMaxR = 1024;
 // 144, 142 and 130 us, 16 of 12 x 1,320 (130 MB) 54.9, 50.6 and 49.8, 3 of 40 x 700 (43 MB) 17.2, 14.7 and 18.7, 4 of 12 x 1,320 13.1, 13.0
 // and 15.7 (512 x 2: 136, 51.4, 19.4, 15.4; 256 x 4: 133, 51.1, 19.3, 17.1; 256 x 1: 169, 66, 22, 17).  Between them either may be ahead: 256 x 6 and
 // 512 x 3 take 27.1 and 25.5 us for 8 of 12 x 1,320 (65 MB), 32.2 and 32.2 for 10 (81 MB), 35.3 and 36.5 for 12 (97 MB), 41.5 and 38.0 for 5 of 40 x 1,040 (107 MB);
-// above, 512 x 3 is: 50.3 and 47.4 for 7 of 16 x 2,340 (134 MB), 69.7 and 64.8 for 4 of 40 x 2,340 (192 MB).  A capped grid has 256 x 8: what a few
-// workgroups keep in flight over the host link.  Heads of less than a unit leave most of 512 threads idle (one row of 2^22 heads 17.6 ms, in
+// above, 512 x 3 is: 50.3 and 47.4 for 7 of 16 x 2,340 (134 MB), 69.7 and 64.8 for 4 of 40 x 2,340 (192 MB).  A capped grid has 256 x 8,
+// whose loads wait for one another as all do: 4 chunks of 40 x 2,340 from pinned memory 26 GB/s with 8 workgroups, 50 with 16, 60 with 32 and more (with all of a thread's loads
+// under way 59, 60 and 59; 4 of 12 x 1,320 with 256 workgroups 337 us, 362 so).  Heads of less than a unit leave most of 512 threads idle (one row of 2^22 heads 17.6 ms, in
 // 256 threads 9.9).
 constexpr long long kLargeCopy = 128'000'000;
 // Copies of few units of 256 x 6 are made as 256 x 4 or 256 x 2: four or two latencies behind one another instead of six.  The bounds lie where pinned memory, which
