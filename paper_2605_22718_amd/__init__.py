@@ -7,7 +7,8 @@ missing, importing a function raises.
 
 The calls of a denoising step go through wk_binding (binding/wk_binding.cpp), which marshals the usual arguments in native code: 5.6 -> 3.4 us of
 host time for wk_score_chunks, 2.8 of them the launch.  It answers None, and has done nothing, where an argument is not the usual one
-(or it is not built); the functions here then marshal by themselves and raise what is to be raised.
+(or there is none); the functions here then marshal by themselves and raise what is to be raised.  One that does not load, or is of another
+wk.h than the library, raises.
 """
 import ctypes as C
 import math
@@ -15,16 +16,26 @@ import os
 
 import torch
 
+_HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+class _Absent:
+    """Stands for a binding that is not built, or one that does not load: the package is imported to build it, too."""
+
+    def __init__(self, error=None):
+        self._error = error
+
+    def __getattr__(self, name):
+        if self._error is not None:
+            raise ImportError("wk_binding.so does not load: run `python -c 'import __graft_entry__ as g; g.build()'`") from self._error
+        return lambda *args: None
+
+
 try:
     from . import wk_binding as _native
-except ImportError:   # (the package is imported to build it, too)
-    class _Absent:
-        def __getattr__(self, name):
-            return lambda *args: None
+except ImportError as e:
+    _native = _Absent(e if os.path.exists(os.path.join(_HERE, "wk_binding.so")) else None)
 
-    _native = _Absent()
-
-_HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libwk.so")
 
 WK_OK, WK_ERR_INVALID_ARG, WK_ERR_SHAPE, WK_ERR_RATIO, WK_ERR_WORKSPACE, WK_ERR_UNSUPPORTED, WK_ERR_HIP = range(7)
@@ -161,6 +172,10 @@ def lib():
         L.wk_host_device_pointer.argtypes = [vp, C.POINTER(vp)]
         L.wk_status_string.restype = C.c_char_p
         L.wk_status_string.argtypes = [C.c_int]
+        L.wk_internal_interface.restype = C.c_uint64
+        made_for = _native.interface() if hasattr(_native, "interface") else 0   # (0: an older one, which does not say)
+        if made_for not in (None, L.wk_internal_interface()):
+            raise ImportError(f"wk_binding.so is of another include/wk.h than {path}: run `python -c 'import __graft_entry__ as g; g.build()'`")
         for name, struct in _NATIVE.items():
             _native.bind(name, C.cast(getattr(L, name), vp).value, struct)
         _lib = L

@@ -211,13 +211,17 @@ PyObject *bind(PyObject *, PyObject *args) {
     return PyErr_Format(PyExc_KeyError, "%s", name);
 }
 
-PyMethodDef methods[kEntries + 2];
+// interface(): of the wk.h this was compiled with, and so of the signatures that it calls
+PyObject *interface(PyObject *, PyObject *) { return PyLong_FromUnsignedLongLong(WK_INTERFACE); }
+
+PyMethodDef methods[kEntries + 3];
 
 template <int... K>
 void fill(std::integer_sequence<int, K...>) {
     ((methods[K] = PyMethodDef{entries[K].name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(&method<K>)), METH_FASTCALL, nullptr}), ...);
     methods[kEntries] = PyMethodDef{"bind", &bind, METH_VARARGS, nullptr};
-    methods[kEntries + 1] = PyMethodDef{nullptr, nullptr, 0, nullptr};
+    methods[kEntries + 1] = PyMethodDef{"interface", &interface, METH_NOARGS, nullptr};
+    methods[kEntries + 2] = PyMethodDef{nullptr, nullptr, 0, nullptr};
 }
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "wk_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

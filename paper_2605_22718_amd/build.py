@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ for gfx950 into paper_2605_22718_amd/libwk.so."""
+"""Compile the HIP sources under csrc/ for gfx950 into paper_2605_22718_amd/libwk.so, and the package's binding beside it."""
+import hashlib
 import os
 import subprocess
 import sys
@@ -12,11 +13,20 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libwk.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+INTERFACE = os.path.join(ROOT, "include", "wk.h")
+
+
+def interface_flag() -> str:
+    """What the library and the binding were compiled against, in both: the binding calls entry points by address, as its own wk.h declares them."""
+    with open(INTERFACE, "rb") as f:
+        return f"-DWK_INTERFACE=0x{hashlib.sha256(f.read()).hexdigest()[:16]}ull"
+
+
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
     # packed-fp32 instructions are kept out of every kernel of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+    "-I", os.path.join(ROOT, "include"), "-I", CSRC, interface_flag(),
 ]
 
 
@@ -44,13 +54,19 @@ def _compile(src: str) -> str:
 def dependencies():
     """Every file whose change makes the built library stale: sources, their headers and the generated loops they include."""
     return [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".h", ".inc"))] + \
-        [os.path.join(ROOT, "include", "wk.h")]
+        [INTERFACE]
+
+
+def _is_newer(product: str, deps) -> bool:
+    return os.path.exists(product) and all(os.path.getmtime(product) >= os.path.getmtime(d) for d in deps)
 
 
 def build(force: bool = True) -> str:
+    """The library and the binding."""
     srcs = sources()
-    deps = dependencies()
-    if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
+    if force or not _is_newer(BINDING, [BINDING_SRC, INTERFACE]):
+        build_binding()
+    if not force and _is_newer(LIB, dependencies()):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
@@ -68,7 +84,7 @@ def build_binding() -> str:
     import torch
     from torch.utils import cpp_extension as ext
     subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-isystem{d}" for d in ext.include_paths("cuda")),
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", interface_flag(), *(f"-isystem{d}" for d in ext.include_paths("cuda")),
                     "-isystem" + sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), BINDING_SRC, "-o", BINDING,
                     *(f"-L{d}" for d in ext.library_paths("cuda")), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"], check=True)
     return BINDING

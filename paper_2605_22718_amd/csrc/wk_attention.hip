@@ -2644,6 +2644,8 @@ extern "C" int32_t wk_internal_frame_mask_plan(int32_t H, int32_t N_q, int32_t N
     return (int32_t)p.layout + (p.merge ? 100 : 0);
 }
 
+extern "C" uint64_t wk_internal_interface() { return WK_INTERFACE; }   // of the wk.h this was compiled with
+
 extern "C" const char *wk_status_string(wk_status s) {
     switch (s) {
     case WK_OK: return "ok";
