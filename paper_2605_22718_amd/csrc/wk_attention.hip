@@ -923,9 +923,10 @@ using wk::uniform_ptr;
 
 // One pass over a workgroup's keys.  QW: waves across the queries; KG: wave groups, which take alternate tiles; TRIPS: by the hand-scheduled loop
 // where that can run.  It has no running maximum: where scores grow by more than fp32 can hold within a trip, or weights times values
-// do, it leaves infinities or NaN; then nothing is stored, and true returned in every thread.
+// do, it leaves infinities or NaN; then true is returned in every thread, and stored says of each wave whether its results hold and are in place (a pass
+// of that wave's stores nothing).
 template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP, bool TRIPS>
-__device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const SubTable &sub, const int wave) {
+__device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const SubTable &sub, const int wave, bool &stored) {
     static_assert((QW == 8 && KG == 1) || (QW == 4 && (KG == 1 || KG == 2)), "one tile, or a pair of tiles, per step");
     constexpr int NB = 16 / (QW * KG); // 1 KB blocks of a tile that a wave loads
     // s_waitcnt vmcnt(4 * NB) alone: all but the last four tile shares have landed
@@ -1280,11 +1281,9 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
     // Trips of the hand-scheduled loop: the steps behind them stay in C++, which are the last whole trips, whose loads are clamped to the window, the
     // left-over steps and the last, possibly partial tile.  (IN_PLACE: the most there can be; where they run is seen on the way.)
     const int n_trips = IN_PLACE ? n_steps / (4 / KG) : min((n_kv / kKeys - 4 - t0) / 4, n_steps / (4 / KG));
-    // A single trip of a wave group that walks every tile costs more at its end (row sums and outputs looked over, the first tile's maximum found again) than
-    // it gives: 40 heads x 4,680 queries x 600 keys 77.2 us with it, 75.3 without, 40 x 1,000 x 512 20.8 and 20.5; two trips (900 keys) 101.2 and
-    // 101.2.  In pairs of tiles a trip is two steps, and one is still as good as none (5 x 392 x 615 15.20 and 15.17).
-    constexpr int kFewestTrips = KG == 1 && !IN_PLACE ? 2 : 1;
-    const bool may_lose = kTrips && n_trips >= kFewestTrips;   // of the whole workgroup
+    // (One trip is still as good as none: 40 heads x 1,000 queries x 512 keys 19.9 us with it, 20.3 without, x 700 24.0 and 24.2, 40 x 4,680 x 512 69.7 and 70.0, x 600 78.5
+    // and 78.0, x 700 83.3 and 82.9; in pairs of tiles, where it is two steps, 5 x 392 x 615 15.0 and 15.0.)
+    const bool may_lose = kTrips && n_trips > 0;   // of the whole workgroup
     int *const lost = reinterpret_cast<int *>(smem + kRings + 512);
     if (may_lose && tid == 0) *lost = 0;   // (barriers lie between)
     issue_k(0, 0);
@@ -1425,7 +1424,7 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
         }
     };
     if constexpr (kTrips && !IN_PLACE) {
-        if (n_trips >= kFewestTrips) trips(n_trips, Kh, Vh, (unsigned)(t0 + 4) * kTileBytes, (unsigned)(t0 + 4 - KG) * kTileBytes);
+        if (n_trips > 0) trips(n_trips, Kh, Vh, (unsigned)(t0 + 4) * kTileBytes, (unsigned)(t0 + 4 - KG) * kTileBytes);
     }
     // IN_PLACE: the trips whose tiles -- from the ones whose S^T comes next to the last one requested -- are full and of the cursor's segment, and
     // leave the cursor in it.  The steps across a segment's boundary stay in C++.
@@ -1496,23 +1495,29 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
     // the last row again -- has no part in this one)
     if (KG == 1 || kg == 0 || (t1 - t0) % 2 == 0) last_tile(ring_pos(n_steps), s_a, l_run[0]);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // drain the clamped look-ahead loads before the LDS is released
+    bool wave_lost = false;
     if constexpr (kTrips)
         if (tripped) {
-            // infinities and NaN are the largest bit patterns of their sign: signed for the positive ones, unsigned for the negative ones
-            int top = __float_as_int(l_run[0] + l_run[1]);
-            unsigned bottom = __float_as_uint(l_run[0] + l_run[1]);
+            // The bits of the largest magnitude, or of NaN where there is one.  In assembly, and looked at as bits, because the compiler takes no number here
+            // for NaN; and with the wait for O^T's matrix instructions, which it does not put in front of assembly.
+            unsigned top = __float_as_uint(l_run[0] + l_run[1]);
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    top = max(top, __float_as_int(o[b][r]));
-                    bottom = max(bottom, __float_as_uint(o[b][r]));
-                }
-            if (top >= 0x7f800000 || bottom >= 0xff800000u) *lost = 1;
+            for (int b = 0; b < 4; ++b) {
+                const f32x16 &x = o[b];
+                if (b == 0) asm("s_nop 7\n\ts_nop 7\n\tv_maximum3_f32 %0, |%0|, |%1|, |%1|" : "+v"(top) : "v"(x[0]));
+                asm("v_maximum3_f32 %0, %0, |%1|, |%2|\n\tv_maximum3_f32 %0, %0, |%3|, |%4|\n\tv_maximum3_f32 %0, %0, |%5|, |%6|\n\t"
+                    "v_maximum3_f32 %0, %0, |%7|, |%8|\n\tv_maximum3_f32 %0, %0, |%9|, |%10|\n\tv_maximum3_f32 %0, %0, |%11|, |%12|\n\t"
+                    "v_maximum3_f32 %0, %0, |%13|, |%14|\n\tv_maximum3_f32 %0, %0, |%15|, |%16|"
+                    : "+v"(top)
+                    : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]), "v"(x[8]), "v"(x[9]), "v"(x[10]),
+                      "v"(x[11]), "v"(x[12]), "v"(x[13]), "v"(x[14]), "v"(x[15]));
+            }
+            wave_lost = __any((top & 0x7fffffffu) >= 0x7f800000u);
+            if (wave_lost) *lost = 1;
         }
-    if (KG == 2 || may_lose) __syncthreads();   // every wave has read its last tile and its look-ahead loads have landed
-    if (may_lose && __builtin_amdgcn_readfirstlane(*lost) != 0) return true;
     if constexpr (KG == 2) {
+        __syncthreads();   // every wave has read its last tile and its look-ahead loads have landed
+        if (may_lose && __builtin_amdgcn_readfirstlane(*lost) != 0) return true;
         // The wave groups meet: waves 4..7 leave (O^T, max, sum) of their keys in the ring, waves 0..3 add it to theirs.
         // Register r of a wave's lane sits at [qw][r][lane]: consecutive lanes, consecutive banks.
         float *meet = reinterpret_cast<float *>(smem) + qw * (66 * 64) + lane;
@@ -1539,7 +1544,8 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
     }
     const float l_lane = l_run[0] + l_run[1];
     const float l_tot = l_lane + __shfl_xor(l_lane, 32);
-    if (q_ok && !partial_out) {
+    const bool store = q_ok && !wave_lost && !stored;
+    if (store && !partial_out) {
         const size_t qrow = out_row();
         char *Orow = a.O + qrow * 256;
         const float inv = 1.f / l_tot;
@@ -1556,7 +1562,7 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
                 *reinterpret_cast<uint2 *>(Orow + dv * 2) = w;
             }
         if (lse && g == 0) lse[qrow] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
-    } else if (q_ok) {   // partial result of this key range, merged by k_attn_merge
+    } else if (store) {   // partial result of this key range, merged by k_attn_merge
         const size_t prow = part_row();
         float *Po = a.part_o + prow * WK_D;
 #pragma unroll
@@ -1566,6 +1572,14 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
                 *reinterpret_cast<float4 *>(Po + 32 * b + 8 * t + 4 * g) =
                     float4{o[b][4 * t], o[b][4 * t + 1], o[b][4 * t + 2], o[b][4 * t + 3]};
         if (g == 0) { a.part_ml[prow * 2] = m_run; a.part_ml[prow * 2 + 1] = l_tot; }
+    }
+    // Waves that walk every tile meet behind their stores: the older wave of each SIMD is done hundreds of cycles before the younger one, and in front of its
+    // stores that was lost to every workgroup (40 heads x 4,680 queries x 900 keys 102.6 -> 101.0 us, x 1,000 108.3 -> 106.7, of a kernel with a running maximum and no such
+    // meeting 101.9 and 107.2)
+    if (KG == 1 && may_lose) {
+        stored = !wave_lost;
+        __syncthreads();   // every wave has read its last tile and its look-ahead loads have landed
+        return __builtin_amdgcn_readfirstlane(*lost) != 0;
     }
     return false;
 }
@@ -1577,13 +1591,14 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
 template <int QW, int KG, bool MULTI, bool IN_PLACE, bool GAP = false, bool TRIPS = !IN_PLACE>
 __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTable sub) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (!attend<QW, KG, MULTI, IN_PLACE, GAP, TRIPS>(a, sub, wave)) return;
+    bool stored = false;
+    if (!attend<QW, KG, MULTI, IN_PLACE, GAP, TRIPS>(a, sub, wave, stored)) return;
     if constexpr (TRIPS && QW * KG == 8) {
         struct Args { AttnArgs a; SubTable sub; };
         auto args = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(args));
         const Args *const again = (const Args *)args;
-        attend<QW, KG, MULTI, IN_PLACE, GAP, false>(again->a, again->sub, wave);
+        attend<QW, KG, MULTI, IN_PLACE, GAP, false>(again->a, again->sub, wave, stored);
     }
 }
 

@@ -151,3 +151,22 @@ def test_sums_at_the_end_of_the_range_in_place(at, H, layout, level, behind):
                              torch.zeros(1, dtype=torch.int32, device=d), None, 1, O, lse)
     rows = np.array([0, 31, 128, 255, 256, 269], np.int32)
     _check(O, lse, rows, lambda v: oracle.attention(Q, K, v, rows=rows, want_lse=True), V)
+
+
+# Waves of a workgroup part where only some of its queries see the growth: their results are in place when the others' work is done once more.
+@pytest.mark.parametrize("alias", [False, True])   # (the second pass of a wave whose results are in place has lost its queries where they take their place)
+@pytest.mark.parametrize("H,N_q,N_kv,plan", [(40, 1100, 900, (K256, 1)), (40, 512, 5200, (K256, 3)), (2, 300, 3000, (K128_PAIR, 1))])
+def test_growth_for_some_waves(H, N_q, N_kv, plan, alias):
+    d = dev()
+    n = wk.wk_attention_workspace_bytes(H, N_q, N_kv, wk.WK_BF16) if plan[1] > 1 else 0
+    assert attention_plan(H, N_q, N_kv, n) == plan
+    Q, K, V = _inputs("beyond_fp32", H, N_q, N_kv)
+    q = torch.arange(N_q)
+    Q[:, (q < 32) | (q >= 64) & (q < 224), 0] = 0   # of the first workgroup of 256 one wave and a wave's neighbour see it, of the others all
+    O, lse = _out(Q)
+    queries = Q.to(d)
+    if alias and plan[1] == 1:
+        O = queries
+    wk.wk_attention(queries, K.to(d), V.to(d), O, lse, workspace=torch.empty(n, dtype=torch.uint8, device=d) if n else None)
+    rows = np.unique([0, 31, 32, 63, 64, 100, 223, 224, 255, 256, N_q - 1]).astype(np.int32)
+    _check(O, lse, rows, lambda v: oracle.attention(Q, K, v, rows=rows, want_lse=True), V)
