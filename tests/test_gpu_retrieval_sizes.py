@@ -70,3 +70,33 @@ def test_rotation_angles(kind):
     want = (angle / angle.max())[ids.cpu().numpy()]
     # a handful of roundings of 2^-53 and the division's; sines and cosines beside their zeros are as good as pi/2 in two parts is, 2^-106 of up to 2^20 of them
     np.testing.assert_allclose(dist.cpu().numpy(), want.astype(np.float64), rtol=2e-15, atol=1e-25)
+
+
+# The angle's error is that of an arctangent of rounded sines and cosines: what numpy's functions give in fp64, and a tenth.  Beside a quarter turn two tenths: there sine,
+# cosine and their sum under the root have their full weight, and are off by 0.30 to 0.31 units in the last place (rms over a quadrant) where numpy's are off by
+# 0.29, each of them three roundings deep.
+@pytest.mark.parametrize("kind", ["any", "wide", "right", "small"])
+def test_rotation_precision(kind):
+    M, d = 4096, dev()
+    yaw, pitch = {"any": (np.pi, np.pi / 6), "wide": (30.0, 0.5), "right": (0.16, 0.1), "small": (0.2, 0.1)}[kind]
+    errors = []
+    for seed in range(24):   # (the largest angle's error is in all of a call)
+        rng = np.random.default_rng(seed)
+        poses = np.zeros((M, 5), np.float32)
+        poses[:, 3] = rng.uniform(-yaw, yaw, M) + (np.pi / 2 if kind == "right" else 0)
+        poses[:, 4] = rng.uniform(-pitch, pitch, M)
+
+        def angles(t):
+            hD, he = (poses[:, c].astype(t) / 2 for c in (3, 4))
+            return 2 * np.arctan2(np.sqrt(np.sin(hD) ** 2 + (np.cos(hD) * np.sin(he)) ** 2), np.abs(np.cos(hD) * np.cos(he)))
+
+        ids = torch.zeros(M, dtype=torch.int32, device=d)
+        dist, nf = torch.zeros(M, dtype=torch.float64, device=d), torch.zeros(1, dtype=torch.int32, device=d)
+        wk.wk_score_chunks(torch.from_numpy(poses).to(d), M, [0.0] * 5, wk.WK_NORM_MAX, M, ids, dist, nf)
+        exact, plain = angles(np.longdouble), angles(np.float64)
+        exact, plain = exact / exact.max(), plain / plain.max()
+        got = np.empty(M)
+        got[ids.cpu().numpy()] = dist.cpu().numpy()
+        errors.append([(x - exact).astype(np.float64) for x in (got, plain)])
+    off, bound = np.sqrt((np.array(errors) ** 2).mean(axis=(0, 2)))
+    assert off <= (1.2 if kind == "right" else 1.1) * bound, (off, bound)
