@@ -28,12 +28,12 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # HBM bytes per wk_attention launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (two runs), each
 # scaled by what the counter reads for the plain calibration copy (0.500 and 1.000), per workload index;
 # see profiles/hbm_traffic_lingbot_pmc.txt for the commands
-MEASURED_ATTENTION_TRAFFIC = {2: (2 * 693240 + 46800) * 1024}
+MEASURED_ATTENTION_TRAFFIC = {2: (2 * 696407 + 46800) * 1024}
 # shader-clock cycles one wk_attention launch on this workload takes (SQ_BUSY_CYCLES over the 32 shader engines in
 # the counter runs of profiles/hbm_traffic_lingbot_pmc.txt): a property of the kernel and the workload, while the
 # clock the chip holds under this load differs from box to box.  The clock reported beside the roofline is this
 # count over the launch time measured here; the peak at that clock is 256 CUs x 4 SIMDs x 1,024 bf16 flop per cycle.
-MEASURED_ATTENTION_CYCLES = {2: 3.592e6}
+MEASURED_ATTENTION_CYCLES = {2: 3.586e6}
 FLOP_PER_CLOCK = 256 * 4 * 1024
 
 

@@ -8,7 +8,7 @@ A trip is two steps; the loop may end behind the first.  A step forms S^T of the
 32-query blocks, then keys 32..63 -- and turns S^T of the current one into the row sums: scale and subtract the reference, exp2,
 round to bf16, add.  Every K fragment read from LDS feeds two matrix instructions.  The vector work of a step is dealt evenly over a window of 32
 matrix instructions that begins three instructions behind the step's first, because the current tile's last products come right
-before: the vector pipe is the busier one and must not idle.  The last four matrix instructions of a step are kept back past
+before: neither pipe is full, and the vector pipe, which is the busier one, must not idle.  The last four matrix instructions of a step are kept back past
 the workgroup barrier, together with the vector work that belongs beside them, and cover the latency of the next step's
 first K reads.  A v_exp result is used six
 instructions later, a row sum is read four behind its last v_dot2c (no hardware wait).

@@ -1221,7 +1221,7 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
     // p = exp2(s*c - m) rounded to bf16; registers 8*t2 .. 8*t2+7 of block b -> k step 2*b + t2.
     // The row sum uses the rounded probabilities, the ones the P V product sees.  Even and odd tiles are summed apart,
     // as the two wave groups of KG == 2 do: the log-sum-exp is then the same in every layout of the launch, as long as the key range
-    // is not split and no row's maximum grows by more than 2^8 behind the first tile (the groups' maxima then part).
+    // is not split, no row's maximum grows by more than 2^8 behind the first tile and no lane's sum reaches 2^24 (what the groups weigh keys against then parts).
     auto probabilities = [&](const f32x16 (&s)[2], bf16x8 (&pb)[4], float &l_sum) __attribute__((always_inline)) {
         const float neg_m = -m_run;
         const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -1611,7 +1611,8 @@ __global__ __launch_bounds__(QW * KG * 64, 2) void k_attn_bf16(AttnArgs a, SubTa
 // others' exp2; the workgroup's waves meet at a barrier only every second tile.  Same tile layout,
 // loads and arithmetic (bf16-rounded probabilities summed by
 // dot2) as the full kernel: the lse values are bit-identical to those wk_attention returns
-// beside O, as long as that call does not split the key range and no row's maximum grows by more than 2^8 behind the first tile.
+// beside O, as long as that call does not split the key range, no row's maximum grows by more than 2^8 behind the first tile and no lane's row sum reaches
+// 2^24 there (which takes 2^16 keys of a lane's that weigh 2^8 each, or growth).
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
     extern __shared__ __attribute__((aligned(256))) char smem[];
@@ -1775,14 +1776,14 @@ __global__ __launch_bounds__(512, 4) void k_lse_bf16(AttnArgs a) {
 // Log-sum-exp only, of longer windows (lse_wide): workgroups of four waves with 64 queries each, two workgroups (two waves
 // per SIMD) on a compute unit, each with its own 64 KB ring of four K tiles.
 //
-// Bound by the vector pipe -- a weight costs an exp2 (16 cycles a wave), a multiply-add and halves of a rounding and of an add --
-// and by power.  So no row maxima are taken (24 of 112 vector instructions per 32 queries and tile): every score is weighed against
+// Bound by neither pipe alone: a tile of 64 queries has 1,024 cycles of matrix and 1,120 of vector instructions (an exp2 of a wave is 8, and a weight costs one, a
+// multiply-add and halves of a rounding and of an add) and takes 1,790; beside full matrix pipes the mix would take 1,340.  So no row maxima are taken (24 of 112 vector instructions per 32 queries and tile): every score is weighed against
 // the first tile's maximum of its row, and only where a lane's sum over a tile reaches 2^8 the tile's weights are added unrounded and
 // the reference moves up (by a power of two, which changes no rounding).  A weight far above the others is thus exact, as it is
 // with a maximum that moves; against 64 bits the error is 0.9 of k_lse_bf16's where keys stand out, and the same (to the bit) where
 // no tile's sum grows that far.  Every K fragment read from LDS feeds two products.
 // 120 chunks of 1,560 keys, 40 heads x 4,680 queries, both in turn on one box: 15.7 M cycles at 1.73 GHz, 8.99 ms (matrix pipe busy
-// 57 %, vector pipe 71 %), k_lse_bf16 18.4 M at 1.79 GHz, 10.27 ms; this layout with the maxima 18.5 M.  Depths of the reads ahead and
+// 57 %, vector pipe 62 %), k_lse_bf16 18.4 M at 1.79 GHz, 10.27 ms; this layout with the maxima 18.5 M.  Depths of the reads ahead and
 // the place of the vector work change nothing (0.3 %) as long as it leaves no gap: without it beside a step's first three products 18.0 M.
 // Nothing lies in scratch: three registers of query numbers that did wrote 265 MB a launch beside its 90 MB of results.
 // ------------------------------------------------------------------------------------------

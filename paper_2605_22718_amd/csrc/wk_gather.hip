@@ -2,7 +2,7 @@
 // K/V rows are placed behind the native sliding-window rows, byte for byte.
 //
 // In the head-major layout every (head, chunk) pair is one contiguous byte range, so the gather
-// is a set of H x (1 + R) straight copies.  One launch covers K and V.  A work unit is 24 or 32 KB of
+// is a set of H x (1 + R) straight copies.  One launch covers K and V.  A work unit is 8 to 32 KB of
 // one head's K or V window; a workgroup walks units blockIdx.x, blockIdx.x + gridDim.x, ...: with
 // the default grid that is one unit each, with a capped grid (a prefetch that runs beside other
 // kernels and is bound by the host link anyway) a few workgroups stream the whole window.  The
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs
 // One workgroup per unit, as far as a cap on workgroups and a launch's 2^32 threads allow: behind them workgroups take further units.
 //
 // A thread's loads wait for one another: asked for together, rows come a little sooner from HBM but later from host memory, and where a store lies only the device
-// knows (2 chunks of 4 heads x 440 rows, fp32, 3.77 us one by one and 3.44 together, 8 of 40 x 2,340 122.3 and 124.6; one of 12 x 1,320 in pinned memory 148 and
+// knows (in units of 256 x 6: 2 chunks of 4 heads x 440 rows, fp32, 3.77 us one by one and 3.44 together, 8 of 40 x 2,340 122.3 and 124.6; one of 12 x 1,320 in pinned memory 148 and
 // 183, two 301 and 339).  Its stores wait where the whole copy is under way at once but more than a workgroup a compute unit: 4 chunks of 12 heads x 1,320 rows 12.7 us
 // without, 11.3 with it, 3 of 40 x 700 16.1 and 14.9, 4 of 24 x 760 14.0 and 12.8; less or more than that they don't: 3.77 and 4.28, 8 of 12 x 1,320 23.9 and 25.9,
 // 8 of 40 x 2,340 122.3 and 125.5.  (With look-ups in LDS and both waiting at all sizes: 5.27, 12.1, 15.5, 13.3, 27.4 and 127.7.)
