@@ -58,6 +58,7 @@ def test_launches_saved(dtype, heads, B, H, T, F):
 
 # either side of the bounds behind which the mean is folded by a launch of its own
 @pytest.mark.parametrize("dtype,heads,B,H,T,F", [
-    (torch.bfloat16, PER_HEAD, 1, 32, 1024, 2), (torch.bfloat16, PER_HEAD, 1, 33, 1024, 2), (torch.bfloat16, SHARED, 1, 4, 1584, 2), (torch.bfloat16, SHARED, 1, 4, 1585, 2)])
+    (torch.bfloat16, PER_HEAD, 1, 32, 1024, 2), (torch.bfloat16, PER_HEAD, 1, 34, 960, 2), (torch.bfloat16, PER_HEAD, 1, 35, 960, 2),
+    (torch.bfloat16, PER_HEAD, 1, 64, 1024, 2), (torch.bfloat16, PER_HEAD, 1, 65, 1024, 2), (torch.bfloat16, SHARED, 1, 4, 1584, 2), (torch.bfloat16, SHARED, 1, 4, 1585, 2)])
 def test_mean_fold_bounds(dtype, heads, B, H, T, F):
     test_against_fp64(dtype, heads, B, H, T, F)
