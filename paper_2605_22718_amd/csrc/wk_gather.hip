@@ -13,7 +13,7 @@
 // one segment -- the usual case -- looks its segment up once: together with units of the right size these bring the kernel from
 // 3.2 TB/s to 5.9 TB/s read + written (8 chunks of 40 heads x 2,340 tokens; the best plain device copy 6.4).  Small gathers are bound by
 // the chain of look-ups before the first copy: units cover the retrieved rows only when the native ones are in place, unit
-// numbers are 32-bit (4 chunks of 12 heads x 1,320 tokens: 20 -> 15 us), segments are in lanes (11.9 -> 11.3; 2 of 4 heads x 440, fp32, 5.2 -> 3.7, in smaller units 3.4).
+// numbers are 32-bit (4 chunks of 12 heads x 1,320 tokens: 20 -> 15 us), segments are in lanes (11.9 -> 11.3; 2 of 4 heads x 440, fp32, 5.2 -> 3.7, in smaller units 3.2).
 #include <type_traits>
 
 #include "wk_internal.h"
@@ -37,6 +37,8 @@ constexpr long long kLargeCopy = 128'000'000;
 // (4 heads x 100 rows) 3.2, 2.9, 2.6 / - / 10.9, 8.8, 7.6 us; 24 (4 x 280) 3.3, 3.0, 2.7 / 5.1, 4.1, 3.1 (4 x 200) / 14.4, 14.2, 14.6; 40 (4 x 440) 3.3, 3.0, 2.7 / 5.2, 4.2, 3.2 / 20.0, 19.9, 20.5;
 // 152 (2 chunks of 4 x 440, fp32) 3.7, 3.4, 3.2 / 5.8, 4.9, 4.1 / 67.7, 68.8, 70.6; 336 (12 x 1,320) 6.8, 5.7, 5.1 / 7.4, 5.5, - / 148.6, 149.9, 178.6; 352 (16 x 1,000) 6.9, 5.8, - / - /
 // 150.2, 151.7, -; but 456 (2 of 12 x 880) 8.0, 6.7, - / 7.9, 6.9, - / 196.8, 202.0, -, 672 (2 of 12 x 1,320) 9.4, 7.8, - / 9.4, 8.3, - / 296.7, 336.6, -.
+// In 256 x 4 the first load tells where the store is, and from HBM the other three come together, two latencies as in 256 x 2: 40 units warm / past the caches / pinned 3.5, 4.2, 19.4 -> 3.4, 3.5, 19.6
+// (256 x 2: 2.9, 3.2, 20.0), 152 5.0, 5.0, 68.3 -> 4.4, 4.2, 68.3 (4.2, 4.1, 70.0), 144 (12 x 500) 4.7, 4.8, 58.9 -> 4.2, 3.8, 58.9 (4.0, 4.0, 60.6), 336 6.2, 5.7, 149.1 -> 5.3, 5.5, 149.3.
 constexpr long long kFewUnits = 360, kFewestUnits = 24;
 
 typedef unsigned int uvec4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the nontemporal builtins accept
@@ -198,10 +200,16 @@ __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs
             }
         }
         uvec4 buf[VECS];
+        bool near = false;   // the store is in HBM, as the first load tells (VECS == 4)
+        const long long asked = VECS == 4 ? clock64() : 0;
 #pragma unroll
         for (int i = 0; i < VECS; ++i) {   // one after the other, see the plan
-            wait();
+            if (!near) wait();
             if (at[i]) buf[i] = __builtin_nontemporal_load(at[i]);   // (streamed once: kept out of the caches' way)
+            if (VECS == 4 && i == 0) {
+                wait();
+                near = __builtin_amdgcn_readfirstlane((int)(clock64() - asked < wk::kNearCycles));
+            }
         }
         if constexpr (!PACED) wait();   // (once: behind a branch the compiler waits for everything in front of each store)
 #pragma unroll
@@ -215,7 +223,7 @@ __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs
 // One workgroup per unit, as far as a cap on workgroups and a launch's 2^32 threads allow: behind them workgroups take further units.
 //
 // A thread's loads wait for one another: asked for together, rows come a little sooner from HBM but later from host memory, and where a store lies only the device
-// knows (in units of 256 x 6: 2 chunks of 4 heads x 440 rows, fp32, 3.77 us one by one and 3.44 together, 8 of 40 x 2,340 122.3 and 124.6; one of 12 x 1,320 in pinned memory 148 and
+// knows (in units of 256 x 6, where a first load that tells does not pay: 2 chunks of 4 heads x 440 rows, fp32, 3.77 us one by one and 3.44 together, 8 of 40 x 2,340 122.3 and 124.6; one of 12 x 1,320 in pinned memory 148 and
 // 183, two 301 and 339).  Its stores wait where the whole copy is under way at once but more than a workgroup a compute unit: 4 chunks of 12 heads x 1,320 rows 12.7 us
 // without, 11.3 with it, 3 of 40 x 700 16.1 and 14.9, 4 of 24 x 760 14.0 and 12.8; less or more than that they don't: 3.77 and 4.28, 8 of 12 x 1,320 23.9 and 25.9,
 // 8 of 40 x 2,340 122.3 and 125.5.  (With look-ups in LDS and both waiting at all sizes: 5.27, 12.1, 15.5, 13.3, 27.4 and 127.7.)

@@ -71,6 +71,9 @@ __device__ inline int wave_prefix(int x) {
     return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31, rows 2 and 3
 }
 
+// A load that comes within so many cycles, about 1.5 us, came from HBM (0.3 to 1 us) and not from host memory (1.1 to 2.6, and then its turn on the link).
+constexpr int kNearCycles = 3500;
+
 // 16 lanes share one 128-element row; each lane owns elements 8*sub .. 8*sub+7.
 constexpr int kRowLanes = 16;
 

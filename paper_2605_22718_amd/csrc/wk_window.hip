@@ -185,7 +185,7 @@ struct FetchArgs {
 //
 // The threads of a block share its entry, head and first vector: scalar work; a thread only steps over the heads that
 // begin inside the block.
-constexpr int kNearCycles = 3500;   // about 1.5 us
+using wk::kNearCycles;
 
 template <typename I>
 struct Fetch {

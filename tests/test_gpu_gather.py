@@ -217,14 +217,15 @@ def test_segments_in_lanes_and_in_lds(R, n_ids, n_native, native, dtype):
 # copies of few work units are made in smaller ones: heads of one unit of 96 rows, either side of the two bounds, and 24 KB in 256 threads behind them
 @pytest.mark.parametrize("H,pieces", [(1, 3), (12, 3), (13, 2), (180, 2), (181, 1)])
 @pytest.mark.parametrize("native", [True, False])
-def test_smaller_units_for_few(H, pieces, native):
+@pytest.mark.parametrize("pinned", [True, False])   # (the first load tells)
+def test_smaller_units_for_few(H, pieces, native, pinned):
     f = wk.lib().wk_internal_gather_threads
     f.argtypes, f.restype = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32], ctypes.c_int64
     assert f(H, 96, wk.WK_BF16, 0) == 2 * H * pieces * 256
     n_native, lens, d = 7, [44 if native else 48, 37, 5], dev()   # 95 or 96 rows to copy at most: one unit of 24 KB
     g = torch.Generator().manual_seed(H)
     ks, vs = ([torch.randn((H, n, 128), generator=g).to(torch.bfloat16).to(d) for n in lens] for _ in range(2))
-    store = wk.Store(ks, vs)
+    store = wk.Store(*([x.cpu().pin_memory() for x in c] for c in (ks, vs))) if pinned else wk.Store(ks, vs)
     Kn, Vn = (torch.randn((H, n_native, 128), generator=g).to(torch.bfloat16).to(d) for _ in range(2))
     cap = n_native + 2 * store.max_tok
     Kw, Vw = (torch.full((H, cap, 128), 7.0, dtype=torch.bfloat16, device=d) for _ in range(2))
