@@ -7,7 +7,7 @@
 // -- a lane per candidate, each row of 16 lanes counting over its share of the others -- and works out all M distances for
 // itself: that costs less than a second launch would.  One workgroup ranking everything with a thread per candidate took
 // 7.4 / 47 / 662 us at M = 60 / 1,000 / 4,096; workgroups of 64 candidates (and reductions by shuffles) 3.8 / 9.1 / 24.8; with trigonometry of the
-// library and the order of ids in every comparison 3.3 / 5.8 / 15.5; this takes 2.9 / 5.0 / 12.1 us, of which an empty launch is about 2.
+// library and the order of ids in every comparison 3.3 / 5.8 / 15.5; this takes 2.9 / 4.9 / 12.0 us, of which an empty launch is about 2.
 #include <cmath>
 #include <type_traits>
 
@@ -23,8 +23,8 @@ struct Pose5 { float v[5]; };
 // quadrant an angle lies in only swaps squares, and of the two values whose squares sum to 1 the smaller one gives the angle, so that nothing is divided.
 // With the library's sincos and atan2 1,000 candidates take 5.8 us, with this 5.1 (4,096: 15.6 and 13.1; four: 3.2 and 3.0).  Polynomials are Chebyshev interpolations in 60 digits of sin, cos and asin; their errors, relative, are
 // below 2e-17.  Distances by rotation alone, over the largest (rms of 48 times 4,096 poses, and the largest error), with the library's functions and with this: yaws all round 5.2e-17 (2.5e-16) and
-// 5.0e-17 (2.2e-16), many times round 5.5e-17 (2.8e-16) and 5.0e-17 (2.3e-16), beside a quarter turn 1.11e-16 (4.6e-16) and 1.02e-16 (4.6e-16), beside a half
-// turn 6.4e-17 (1.9e-16) and 6.6e-17 (2.0e-16), where both are as exact as pi's last place, within 0.1 8.6e-17 and 6.7e-17, within 1e-4 9.3e-17 and 7.2e-17.
+// 5.0e-17 (2.2e-16), many times round 5.5e-17 (2.8e-16) and 5.0e-17 (2.3e-16), beside a quarter turn 1.11e-16 (4.6e-16) and 1.03e-16 (4.2e-16), beside a half
+// turn 6.4e-17 (1.9e-16) and 6.6e-17 (2.0e-16), where both are as exact as pi's last place, within 0.1 8.6e-17 and 6.6e-17, within 1e-4 9.3e-17 and 7.2e-17.
 __device__ inline double horner(const double (&a)[19], double w) {
     double p = a[18];
 #pragma unroll
@@ -84,11 +84,11 @@ __device__ inline double geodesic(double yaw_a, double pitch_a, double yaw_b, do
     sin_cos(0.5 * (yaw_b - yaw_a), sD, cD);
     sin_cos(0.5 * (pitch_b - pitch_a), se, ce);
     const double s = root(fma(sD, sD, cD * cD * (se * se))), c = fabs(cD * ce);
-    const double x = s <= c ? s : c, y = s <= c ? c : s, w = x * x;
-    // Both are rounded, and their squares then sum to 1 but for a rest: it is taken from the smaller one by the weights that leave the least error (x^2 / (x^4 + y^4) of
-    // it by least squares, here close to that, times the slope of asin), as an arctangent of both would.
-    const double beyond = fma(x, x, fma(y, y, -1.0));
-    const double rest = x * w * fma(-beyond, fma(w, 1.95, 0.45), horner(kAsin, w));
+    const double x = s <= c ? s : c, w = x * x;
+    // Both are rounded, and their squares then sum to 1 but for a rest, which is taken from the smaller one as an arctangent of both would: with y the larger one, by
+    // least squares, x^2 / (x^4 + y^4) of it times the slope of asin, for which 2.5 x^2 stands here (1 % more error than with that itself).
+    const double beyond = fma(s, s, fma(c, c, -1.0));
+    const double rest = x * w * fma(-1.25, beyond, horner(kAsin, w));
     // pi, in two parts, less that or nothing: rounded once, what the difference loses goes to the small terms
     const double times = s <= c ? 2.0 : -2.0, from = s <= c ? 0.0 : 3.141592653589793, from_low = s <= c ? 0.0 : 1.2246467991473532e-16;
     const double near = fma(times, x, from);
