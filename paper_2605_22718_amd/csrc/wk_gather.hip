@@ -27,11 +27,12 @@ constexpr int kMaxR = 1024;
 // 144, 142 and 130 us, 16 of 12 x 1,320 (130 MB) 54.9, 50.6 and 49.8, 3 of 40 x 700 (43 MB) 17.2, 14.7 and 18.7, 4 of 12 x 1,320 13.1, 13.0
 // and 15.7 (512 x 2: 136, 51.4, 19.4, 15.4; 256 x 4: 133, 51.1, 19.3, 17.1; 256 x 1: 169, 66, 22, 17).  Between them either may be ahead: 256 x 6 and
 // 512 x 3 take 27.1 and 25.5 us for 8 of 12 x 1,320 (65 MB), 32.2 and 32.2 for 10 (81 MB), 35.3 and 36.5 for 12 (97 MB), 41.5 and 38.0 for 5 of 40 x 1,040 (107 MB);
-// above, 512 x 3 is: 50.3 and 47.4 for 7 of 16 x 2,340 (134 MB), 69.7 and 64.8 for 4 of 40 x 2,340 (192 MB).  A capped grid has 256 x 8,
-// whose loads wait for one another as all do: 4 chunks of 40 x 2,340 from pinned memory 26 GB/s with 8 workgroups, 50 with 16, 60 with 32 and more (with all of a thread's loads
-// under way 59, 60 and 59; 4 of 12 x 1,320 with 256 workgroups 337 us, 362 so).  Heads of less than a unit leave most of 512 threads idle (one row of 2^22 heads 17.6 ms, in
+// above, 512 x 3 is: 50.3 and 47.4 for 7 of 16 x 2,340 (134 MB), 69.7 and 64.8 for 4 of 40 x 2,340 (192 MB).  A capped grid has 256 x 8.  Heads of less than a unit leave most of 512 threads idle (one row of 2^22 heads 17.6 ms, in
 // 256 threads 9.9).
 constexpr long long kLargeCopy = 128'000'000;
+// Capped grids of fewer workgroups than this have all of a thread's loads under way, others one behind the other: 4 chunks of 40 heads x 2,340 rows from pinned memory with 8 workgroups
+// 24.7 -> 56.6 GB/s, with 16 48.0 -> 56.7, but with 24 56.2 -> 54.9, with 256 57.2 -> 55.3 (4 of 12 x 1,320 55.8 -> 51.8); 32 and more reach 57 one behind the other.
+constexpr long long kFewWorkgroups = 24;
 // Copies of few units of 256 x 6 are made as 256 x 4 or 256 x 2: four or two latencies behind one another instead of six.  The bounds lie where pinned memory, which
 // prefers few requests at a time, would lose more than a hundredth or two by it.  256 x 6, x 4 and x 2, from HBM in a graph / past the caches / from pinned memory: 16 units
 // (4 heads x 100 rows) 3.2, 2.9, 2.6 / - / 10.9, 8.8, 7.6 us; 24 (4 x 280) 3.3, 3.0, 2.7 / 5.1, 4.1, 3.1 (4 x 200) / 14.4, 14.2, 14.6; 40 (4 x 440) 3.3, 3.0, 2.7 / 5.2, 4.2, 3.2 / 20.0, 19.9, 20.5;
@@ -92,8 +93,8 @@ __device__ inline Segment segment_at(const GatherArgs &a, int s) {   // s < 1 + 
 // LDS holds, per segment, the base address of its K block and V block, its length and the first window row after it.
 // U: the type of unit numbers, 32 bits except for a capped grid over 2^31 units or more (heads without end and next to no
 // rows; the windows of anything else would not fit the device).  A 64-bit division takes longer than a unit's look-ups.
-// PACED: a thread's stores wait for one another, as its loads do anyway.
-template <typename U, int THREADS, int VECS, bool IN_LANES, bool PACED>
+// PACED: a thread's stores wait for one another, as its loads do but where TOGETHER.
+template <typename U, int THREADS, int VECS, bool IN_LANES, bool PACED, bool TOGETHER = false>
 __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs a) {
     constexpr unsigned kUnit = THREADS * VECS;   // 16-byte vectors
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs
             }
         }
         uvec4 buf[VECS];
-        bool near = false;   // the store is in HBM, as the first load tells (VECS == 4)
+        bool near = TOGETHER;   // VECS == 4: the store is in HBM, as the first load tells
         const long long asked = VECS == 4 ? clock64() : 0;
 #pragma unroll
         for (int i = 0; i < VECS; ++i) {   // one after the other, see the plan
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(THREADS, VECS > 6 ? 6 : 8) void k_gather(GatherArgs
 
 // One workgroup per unit, as far as a cap on workgroups and a launch's 2^32 threads allow: behind them workgroups take further units.
 //
-// A thread's loads wait for one another: asked for together, rows come a little sooner from HBM but later from host memory, and where a store lies only the device
+// A thread's loads wait for one another, but in grids of few units or workgroups (above): asked for together, rows come a little sooner from HBM but later from host memory, and where a store lies only the device
 // knows (in units of 256 x 6, where a first load that tells does not pay: 2 chunks of 4 heads x 440 rows, fp32, 3.77 us one by one and 3.44 together, 8 of 40 x 2,340 122.3 and 124.6; one of 12 x 1,320 in pinned memory 148 and
 // 183, two 301 and 339).  Its stores wait where the whole copy is under way at once but more than a workgroup a compute unit: 4 chunks of 12 heads x 1,320 rows 12.7 us
 // without, 11.3 with it, 3 of 40 x 700 16.1 and 14.9, 4 of 24 x 760 14.0 and 12.8; less or more than that they don't: 3.77 and 4.28, 8 of 12 x 1,320 23.9 and 25.9,
@@ -290,7 +291,9 @@ wk_status wk::gather_launch(const wk_store_desc *store, const int32_t *ids, cons
     // (32-bit unit numbers: one plus a grid stays below 2^32)
     auto launch_by = [&](auto in_lanes) {
         constexpr bool L = decltype(in_lanes)::value;
-        if (max_workgroups > 0) p.units <= 0x7fffffffLL ? launch(k_gather<uint32_t, 256, 8, L, false>) : launch(k_gather<uint64_t, 256, 8, L, false>);
+        if (max_workgroups > 0 && p.grid < kFewWorkgroups)
+            p.units <= 0x7fffffffLL ? launch(k_gather<uint32_t, 256, 8, L, false, true>) : launch(k_gather<uint64_t, 256, 8, L, false, true>);
+        else if (max_workgroups > 0) p.units <= 0x7fffffffLL ? launch(k_gather<uint32_t, 256, 8, L, false>) : launch(k_gather<uint64_t, 256, 8, L, false>);
         else if (p.threads == 512) launch(k_gather<uint32_t, 512, 3, L, false>);
         else if (p.vecs == 2) launch(k_gather<uint32_t, 256, 2, L, false>);
         else if (p.vecs == 4) launch(k_gather<uint32_t, 256, 4, L, false>);

@@ -183,3 +183,34 @@ def test_capped_gather_over_more_units_than_a_grid_can_have():
     finally:
         wk.wk_prefetch_destroy(p)
     assert int(n_win.item()) == 0 and not row.any()
+
+
+# either side of the cap below which a thread's loads are all under way; segments in lanes and in LDS, a store in HBM and in host memory
+@pytest.mark.parametrize("R", [5, 70])
+@pytest.mark.parametrize("max_wg", [1, 23, 24])
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_capped_grids(dtype, pinned, max_wg, R):
+    H, d, n_native = 3, dev(), 37
+    g = torch.Generator().manual_seed(R + max_wg)
+    lens = [1 + (7 * i) % 11 * (23 if i % 5 == 0 else 3) for i in range(R)]
+    ks, vs = ([torch.randn((H, n, 128), generator=g).to(dtype) for n in lens] for _ in range(2))
+    store = wk.Store(*([x.pin_memory() if pinned else x.to(d) for x in c] for c in (ks, vs)))
+    ids = torch.randperm(R, generator=g).to(torch.int32)
+    cap = n_native + R * store.max_tok
+    Kn, Vn = (torch.randn((H, n_native, 128), generator=g).to(dtype) for _ in range(2))
+    Kw, Vw = (torch.full((H, cap, 128), 7.0, dtype=dtype, device=d) for _ in range(2))
+    n_win = torch.zeros(1, dtype=torch.int32, device=d)
+    ids_d, Kn_d, Vn_d = ids.to(d), Kn.to(d), Vn.to(d)
+    p = wk.wk_prefetch_create(1)
+    try:
+        wk.wk_prefetch_after(p)
+        wk.wk_prefetch_gather(p, 0, store.desc, ids_d, None, R, Kn_d, Vn_d, n_native, Kw, Vw, cap, n_win, max_wg)
+        wk.wk_prefetch_acquire(p, 0)
+        torch.cuda.synchronize()
+    finally:
+        wk.wk_prefetch_destroy(p)
+    for w, nat, chunks in ((Kw, Kn, ks), (Vw, Vn, vs)):
+        want = torch.cat([nat] + [chunks[i] for i in ids.tolist()], 1)
+        assert int(n_win.item()) == want.shape[1]
+        assert torch.equal(bits(w[:, :want.shape[1]].cpu()), bits(want)) and (w[:, want.shape[1]:] == 7.0).all()
