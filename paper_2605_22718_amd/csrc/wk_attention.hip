@@ -1499,12 +1499,12 @@ __device__ __attribute__((always_inline)) inline bool attend(AttnArgs a, const S
     if constexpr (kTrips)
         if (tripped) {
             // The bits of the largest magnitude, or of NaN where there is one.  In assembly, and looked at as bits, because the compiler takes no number here
-            // for NaN; and with the wait for O^T's matrix instructions, which it does not put in front of assembly.
+            // for NaN; and behind a wait for O^T's matrix instructions, which it does not put in front of assembly.
             unsigned top = __float_as_uint(l_run[0] + l_run[1]);
+            asm("s_nop 7\n\ts_nop 7" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
                 const f32x16 &x = o[b];
-                if (b == 0) asm("s_nop 7\n\ts_nop 7\n\tv_maximum3_f32 %0, |%0|, |%1|, |%1|" : "+v"(top) : "v"(x[0]));
                 asm("v_maximum3_f32 %0, %0, |%1|, |%2|\n\tv_maximum3_f32 %0, %0, |%3|, |%4|\n\tv_maximum3_f32 %0, %0, |%5|, |%6|\n\t"
                     "v_maximum3_f32 %0, %0, |%7|, |%8|\n\tv_maximum3_f32 %0, %0, |%9|, |%10|\n\tv_maximum3_f32 %0, %0, |%11|, |%12|\n\t"
                     "v_maximum3_f32 %0, %0, |%13|, |%14|\n\tv_maximum3_f32 %0, %0, |%15|, |%16|"
